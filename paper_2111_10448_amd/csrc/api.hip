@@ -35,6 +35,7 @@ struct pstt2_ctx {
   double* Tt = nullptr;  // C x ell column-major (T_m transposed)
   void* ypart = nullptr;
   void* tpart = nullptr;
+  int64_t tpart_bytes = 0;
   int gi = 1, gj_max = 1;
   int* flag = nullptr;     // device: bit 0 non-finite sketch, bit 1 singular LS
   int* piv_dev = nullptr;  // (d + 1) x ell pivots of every split
@@ -226,7 +227,7 @@ struct Piece {
   int64_t count;
 };
 
-// Stream a list of slabs: partial columns one by one, whole columns batched.
+// Stream a list of slabs: partial columns and whole columns, each batched.
 // Pass groups.  Nested scheme: one group (Y_R and T_m).  Independent scheme:
 // group g forms the right sketch of split g + 1 (if g + 1 <= m) and the left
 // sketch of split m + g (if m + g <= d - 1), each with its own factors; the
@@ -288,12 +289,26 @@ pstt2_status run_slabs(pstt2_ctx* c, const std::vector<Piece>& ps) {
     }
   }
   if (!edges.empty()) HIPCK(c, y_settle(c));   // partial columns add into Y
+  // Pieces per launch of the partial-column kernel: all that its argument holds,
+  // fewer (whole 16-piece chunks) where the T partial buffer, free until the
+  // whole columns follow on the stream, is too small for that many workgroups.
+  const int64_t ws_doubles = c->tpart_bytes / (int64_t)sizeof(double);
+  int per = kMaxSeg;
+  while (per > 16 && partial_cols_doubles(R, c->L4, per) > ws_doubles) per -= 16;
   for (int g = 0; g < pass_groups(c); ++g) {
     double *Yd = nullptr, *Td = nullptr;
     const SketchArgs ga = group_args(c, g, &Yd, &Td);
-    for (const Edge& ed : edges) {
-      HIPCK(c, launch_partial_col(c->dtype, ed.x, ed.r0, ed.r1, ed.col, ga, Yd, Td, c->stream));
-      ++c->accum;
+    for (size_t e0 = 0; e0 < edges.size(); e0 += per) {
+      SketchArgs a = ga;
+      a.nseg = (int32_t)std::min<size_t>(per, edges.size() - e0);
+      for (int i = 0; i < a.nseg; ++i) {
+        const Edge& ed = edges[e0 + i];
+        a.seg[i] = Seg{ed.x, ed.col, ed.r1, ed.r0};
+      }
+      bool added = false;
+      const hipError_t e = launch_partial_cols(c->dtype, a, Yd, Td, (double*)c->tpart, ws_doubles, &added, c->stream);
+      if (added) ++c->accum;
+      HIPCK(c, e);
     }
     const pstt2_status st = launch_segs(c, ga, segs, Yd, Td);
     if (st != PSTT2_OK) return st;
@@ -558,8 +573,8 @@ pstt2_status pstt2_create(const pstt2_desc* desc, void* hip_stream, pstt2_ctx** 
   const size_t psz = c->prec == PSTT2_P_F64 ? 8 : 4;
   if ((e = dev_malloc(&c->ypart, psz * c->gj_max * c->ell * c->R)) != hipSuccess) return bail(e, "hipMalloc(ypart)");
   const int64_t trows = omega16_planes(c->prec) ? c->lp : c->ell;   // see SketchArgs::tlp
-  if ((e = dev_malloc(&c->tpart, psz * (c->gi * trows * c->C + kTPartPad))) != hipSuccess)
-    return bail(e, "hipMalloc(tpart)");
+  c->tpart_bytes = (int64_t)psz * (c->gi * trows * c->C + kTPartPad);
+  if ((e = dev_malloc(&c->tpart, c->tpart_bytes)) != hipSuccess) return bail(e, "hipMalloc(tpart)");
   c->L4 = (c->ell + 3) / 4 * 4;
   if ((e = dev_malloc(&c->om_tab, sizeof(double) * c->C * c->L4)) != hipSuccess) return bail(e, "hipMalloc(omega)");
   if ((e = build_omega_table(base_args(c), c->L4, c->om_tab, c->stream)) != hipSuccess)

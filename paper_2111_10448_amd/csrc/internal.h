@@ -175,9 +175,13 @@ hipError_t build_omega_table(const SketchArgs& a, int L4, double* tab, hipStream
 void sketch_geometry(int prec, int ell, int* rows_per_block, int* threads, int* wg_per_cu);
 // Sum the tile partials of one launch into the FP64 accumulators (fixed order).
 hipError_t launch_reduce(int prec, const SketchArgs& a, double* Y, double* Tt, int* flag, hipStream_t s);
-// FP64 contribution of one partial column (rows [r0, r1) of global column gcol).
-hipError_t launch_partial_col(int dtype, const void* x, int64_t r0, int64_t r1, int64_t gcol,
-                              const SketchArgs& a, double* Y, double* Tt, hipStream_t s);
+// FP64 contribution of up to kMaxSeg pieces of columns (seg[e]: first entry,
+// gcol0 the global column, rows [chunk0, ncols) of it) to the sketches Y and Tt;
+// ws holds ws_doubles doubles, at least nseg L4.  *added is set once Y may have
+// changed.  partial_cols_doubles: workspace that lets every workgroup run.
+int64_t partial_cols_doubles(int64_t R, int L4, int pieces);
+hipError_t launch_partial_cols(int dtype, const SketchArgs& a, double* Y, double* Tt, double* ws, int64_t ws_doubles,
+                               bool* added, hipStream_t s);
 
 // Recovery building blocks (recover.hip); all FP64, column-major.
 hipError_t derive_left(const double* Sin, double* Sout, int64_t Rk, int nk1, int ell, const double* omega,

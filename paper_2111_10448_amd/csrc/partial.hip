@@ -1,0 +1,226 @@
+// Partial columns: slab edges that cut a column of the pass's unfolding X_m.
+// Every entry of a piece enters both sketches in FP64, whatever the sketch
+// precision,
+//     Y_R(r, :) += x(r) Omega_m(col, :),   T_m(:, col) += sum_r Psi_m(r, :) x(r).
+#include <algorithm>
+
+#include "drm.h"
+
+namespace pstt2 {
+
+typedef double pc_d4 __attribute__((ext_vector_type(4)));
+
+constexpr int PC_ROWS = 256;        // rows of X_m per workgroup step (64 per wave)
+constexpr int PC_MAXBLK = 1024;     // workgroups per launch at most
+
+// The pieces of a call are the columns of a narrow matrix (zero outside each
+// piece's rows), so 16 of them at a time go through the dual product on FP64
+// matrix cores, as a 16-column chunk does in the streaming kernel: a wave
+// stages its 64 rows x 16 pieces in LDS and
+//     Y(rows, ell) += X(rows, 16 pieces) Omega(piece columns, ell)
+//     T(ell, 16 pieces) = Psi(rows, ell)^T X(rows, pieces).
+// A workgroup owns 256 rows of Y_R and walks every piece of the launch, so Y is
+// read and written once per launch with one writer per entry; T goes to one
+// partial per workgroup, summed in a fixed order by k_partial_t.  Workgroups
+// step over the row blocks when there are more than PC_MAXBLK of them.
+// Latency bound: one launch pair per kMaxSeg pieces, against a single
+// workgroup per piece before (0.42-0.44 ms each at R = 19575, ell = 20 and
+// R = 20592, ell = 16).  A half-precision pass over 3.5e8 entries in 64 slabs
+// with 112 such pieces: 52.7 -> 3.35 ms; an FP64 pass over 1.2e7 entries in 9
+// slabs with per-split factors (3 x 16 pieces): 21.4 -> 0.68 ms.
+// Pieces: seg[e].ptr the first entry, gcol0 the column, rows [chunk0, ncols).
+template <int L4, typename T>
+__global__ __launch_bounds__(256, 2) void k_partial_cols(const SketchArgs A, double* __restrict__ Y,
+                                                         double* __restrict__ tws) {
+  constexpr int ST = 64 + 2;
+  constexpr int NQ = L4 / 16;        // 16-wide tiles of the sketch columns
+  constexpr int NS = (L4 % 16) / 4;  // 4-wide groups
+  constexpr int KT = 16;             // K steps over a wave's rows
+  __shared__ double Xl[4][16 * ST];
+  __shared__ double Tred[4][L4 * 16];
+  __shared__ double Tsum[kMaxSeg / 16][L4 * 16];
+  __shared__ const T* ep[kMaxSeg];
+  __shared__ int64_t e0[kMaxSeg], e1[kMaxSeg], ec[kMaxSeg];
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+  const int l16 = lane & 15, g4 = lane >> 4, l4 = lane & 3, blk = (lane >> 2) & 3;
+  const int ne = A.nseg;
+  const int nch = (ne + 15) / 16;
+  // pieces past the last one: no rows, column 0
+  if (t < kMaxSeg) {
+    const bool in = t < ne;
+    ep[t] = in ? (const T*)A.seg[in ? t : 0].ptr : nullptr;
+    e0[t] = in ? A.seg[in ? t : 0].chunk0 : 0;
+    e1[t] = in ? A.seg[in ? t : 0].ncols : 0;
+    ec[t] = in ? A.seg[in ? t : 0].gcol0 : 0;
+  }
+  for (int i = t; i < nch * L4 * 16; i += 256) (&Tsum[0][0])[i] = 0.0;
+  const int64_t nrb = (A.R + PC_ROWS - 1) / PC_ROWS;
+  for (int64_t rb = blockIdx.x; rb < nrb; rb += gridDim.x) {
+    const int64_t row0w = rb * PC_ROWS + w * 64;
+    double psiq[KT][NQ > 0 ? NQ : 1];
+    double psis[KT][NS > 0 ? NS : 1];
+    {
+      PsiCursor pc;
+      pc.init(A, row0w + g4);
+      double hq[NQ > 0 ? NQ : 1], hs[NS > 0 ? NS : 1];
+#pragma unroll
+      for (int ks = 0; ks < KT; ++ks) {
+        if (ks > 0) pc.advance(A, 4);
+        if (pc.refresh(A)) {
+#pragma unroll
+          for (int q = 0; q < NQ; ++q) hq[q] = psi_hi(A, pc.h, 16 * q + l16);
+#pragma unroll
+          for (int s = 0; s < NS; ++s) hs[s] = psi_hi(A, pc.h, 16 * NQ + 4 * s + l4);
+        }
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) psiq[ks][q] = pc.at(A, 16 * q + l16, hq[q]);
+#pragma unroll
+        for (int s = 0; s < NS; ++s) psis[ks][s] = pc.at(A, 16 * NQ + 4 * s + l4, hs[s]);
+      }
+    }
+    pc_d4 yq[4][NQ > 0 ? NQ : 1];
+    double ys[4][NS > 0 ? NS : 1];
+#pragma unroll
+    for (int mt = 0; mt < 4; ++mt) {
+#pragma unroll
+      for (int q = 0; q < NQ; ++q) yq[mt][q] = pc_d4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int s = 0; s < NS; ++s) ys[mt][s] = 0.0;
+    }
+    for (int ch = 0; ch < nch; ++ch) {
+      __syncthreads();   // the piece table; the last chunk's LDS reads are done
+      const int64_t row = row0w + lane;
+      double v[16];
+#pragma unroll
+      for (int j = 0; j < 16; ++j) {
+        const int e = 16 * ch + j;
+        v[j] = (row >= e0[e] && row < e1[e]) ? (double)ep[e][row - e0[e]] : 0.0;
+      }
+#pragma unroll
+      for (int j = 0; j < 16; ++j) Xl[w][j * ST + lane] = v[j];
+      __syncthreads();
+      const double* xw = Xl[w];
+      pc_d4 tq[NQ > 0 ? NQ : 1];
+      double ts[NS > 0 ? NS : 1];
+#pragma unroll
+      for (int q = 0; q < NQ; ++q) tq[q] = pc_d4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int s = 0; s < NS; ++s) ts[s] = 0.0;
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks) {
+        const int col = 4 * ks + g4;
+        const double* om = A.om_tab + ec[16 * ch + col] * A.L4;
+        double bq[NQ > 0 ? NQ : 1], bs[NS > 0 ? NS : 1];
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) bq[q] = om[16 * q + l16];
+#pragma unroll
+        for (int s = 0; s < NS; ++s) bs[s] = om[16 * NQ + 4 * s + l4];
+#pragma unroll
+        for (int mt = 0; mt < 4; ++mt) {
+          const double a = xw[col * ST + 16 * mt + l16];
+#pragma unroll
+          for (int q = 0; q < NQ; ++q) yq[mt][q] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, bq[q], yq[mt][q], 0, 0, 0);
+#pragma unroll
+          for (int s = 0; s < NS; ++s) ys[mt][s] = __builtin_amdgcn_mfma_f64_4x4x4f64(a, bs[s], ys[mt][s], 0, 0, 0);
+        }
+      }
+#pragma unroll
+      for (int ks = 0; ks < KT; ++ks) {
+        const double b = xw[l16 * ST + 4 * ks + g4];
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) tq[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(psiq[ks][q], b, tq[q], 0, 0, 0);
+#pragma unroll
+        for (int s = 0; s < NS; ++s) ts[s] = __builtin_amdgcn_mfma_f64_4x4x4f64(psis[ks][s], b, ts[s], 0, 0, 0);
+      }
+      double* tr = Tred[w];
+#pragma unroll
+      for (int q = 0; q < NQ; ++q)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) tr[(16 * q + 4 * u + g4) * 16 + l16] = tq[q][u];
+#pragma unroll
+      for (int s = 0; s < NS; ++s) tr[(16 * NQ + 4 * s + g4) * 16 + 4 * blk + l4] = ts[s];
+      __syncthreads();
+      // each thread owns its entries of the running sum
+      for (int i = t; i < L4 * 16; i += 256) Tsum[ch][i] += Tred[0][i] + Tred[1][i] + Tred[2][i] + Tred[3][i];
+    }
+    auto put = [&](int64_t row, int c, double v) {
+      if (row < A.R && c < A.ell) Y[(int64_t)c * A.R + row] += v;
+    };
+#pragma unroll
+    for (int mt = 0; mt < 4; ++mt) {
+#pragma unroll
+      for (int q = 0; q < NQ; ++q)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) put(row0w + 16 * mt + 4 * u + g4, 16 * q + l16, yq[mt][q][u]);
+#pragma unroll
+      for (int s = 0; s < NS; ++s) put(row0w + 16 * mt + 4 * blk + g4, 16 * NQ + 4 * s + l4, ys[mt][s]);
+    }
+  }
+  __syncthreads();
+  // partial [workgroup][piece][a]
+  for (int i = t; i < ne * L4; i += 256) {
+    const int e = i / L4, a = i % L4;
+    tws[((int64_t)blockIdx.x * ne + e) * L4 + a] = Tsum[e / 16][a * 16 + e % 16];
+  }
+}
+
+// T_m(a, col) += the piece's partials, one wavefront per (piece, a): lanes take
+// workgroups lane, lane + 64, ... and a fixed butterfly adds them.  Pieces of one
+// column (a slab's tail and the next one's head) are added in launch order by
+// the first one's wavefront.
+__global__ __launch_bounds__(256) void k_partial_t(const SketchArgs A, const double* __restrict__ tws, int nb, int L4,
+                                                   double* __restrict__ Tt) {
+  const int lane = threadIdx.x & 63;
+  const int o = (int)((blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6);
+  if (o >= A.nseg * A.ell) return;
+  const int e = o / A.ell, a = o % A.ell;
+  const int64_t col = A.seg[e].gcol0;
+  for (int k = 0; k < e; ++k)
+    if (A.seg[k].gcol0 == col) return;   // uniform across the wavefront
+  double s = Tt[(int64_t)a * A.C + col];
+  for (int k = e; k < A.nseg; ++k) {
+    if (A.seg[k].gcol0 != col) continue;
+    double p = 0.0;
+    for (int g = lane; g < nb; g += 64) p += tws[((int64_t)g * A.nseg + k) * L4 + a];
+    for (int off = 32; off > 0; off >>= 1) p += __shfl_xor(p, off);
+    s += p;
+  }
+  if (lane == 0) Tt[(int64_t)a * A.C + col] = s;
+}
+
+template <typename T>
+static void launch_pc(int L4, const SketchArgs& a, int nb, double* Y, double* tws, hipStream_t s) {
+  const dim3 g((unsigned)nb), b(256);
+  switch (L4) {
+    case 4: hipLaunchKernelGGL((k_partial_cols<4, T>), g, b, 0, s, a, Y, tws); break;
+    case 8: hipLaunchKernelGGL((k_partial_cols<8, T>), g, b, 0, s, a, Y, tws); break;
+    case 12: hipLaunchKernelGGL((k_partial_cols<12, T>), g, b, 0, s, a, Y, tws); break;
+    case 16: hipLaunchKernelGGL((k_partial_cols<16, T>), g, b, 0, s, a, Y, tws); break;
+    case 20: hipLaunchKernelGGL((k_partial_cols<20, T>), g, b, 0, s, a, Y, tws); break;
+    case 24: hipLaunchKernelGGL((k_partial_cols<24, T>), g, b, 0, s, a, Y, tws); break;
+    case 28: hipLaunchKernelGGL((k_partial_cols<28, T>), g, b, 0, s, a, Y, tws); break;
+    default: hipLaunchKernelGGL((k_partial_cols<32, T>), g, b, 0, s, a, Y, tws); break;
+  }
+}
+
+int64_t partial_cols_doubles(int64_t R, int L4, int pieces) {
+  return std::min<int64_t>((R + PC_ROWS - 1) / PC_ROWS, PC_MAXBLK) * pieces * L4;
+}
+
+hipError_t launch_partial_cols(int dtype, const SketchArgs& a, double* Y, double* Tt, double* ws, int64_t ws_doubles,
+                               bool* added, hipStream_t s) {
+  if (a.nseg < 1 || a.nseg > kMaxSeg || a.ell < 1 || a.L4 != (a.ell + 3) / 4 * 4) return hipErrorInvalidValue;
+  const int64_t per = (int64_t)a.nseg * a.L4;
+  const int nb = (int)std::min<int64_t>({(a.R + PC_ROWS - 1) / PC_ROWS, (int64_t)PC_MAXBLK, ws_doubles / per});
+  if (nb < 1) return hipErrorInvalidValue;
+  if (fault_take()) return hipErrorLaunchFailure;
+  if (dtype == PSTT2_F64) launch_pc<double>(a.L4, a, nb, Y, ws, s);
+  else launch_pc<float>(a.L4, a, nb, Y, ws, s);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  *added = true;
+  hipLaunchKernelGGL(k_partial_t, dim3((unsigned)((a.nseg * a.ell + 3) / 4)), dim3(256), 0, s, a, ws, nb, a.L4, Tt);
+  return hipGetLastError();
+}
+
+}  // namespace pstt2

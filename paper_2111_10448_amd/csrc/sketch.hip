@@ -24,6 +24,7 @@
 //     Omega rows of a chunk are built cooperatively into LDS two chunks ahead.
 // A separate kernel sums the partials in a fixed order into the FP64 sketches,
 // so results are bitwise reproducible.
+#include "drm.h"
 #include "internal.h"
 
 namespace pstt2 {
@@ -156,87 +157,6 @@ __device__ __forceinline__ typename Eng<PREC>::lds_t drm_to_lds(double v) {
 template <int PREC>
 __device__ __forceinline__ int acc_row(int g4, int v) {
   return PREC == P_F64 ? 4 * v + g4 : 4 * g4 + v;
-}
-
-// Psi_m(row, a) = psi_1(i_1, a) * psi_hi(h, a) for the row i_1 + n_1 h of X_m:
-// psi_hi is the product of the factor entries of modes 2..m (the mixed-radix
-// digits of h), multiplied in increasing mode order.
-__device__ __forceinline__ double psi_hi(const SketchArgs& A, int64_t h, int a) {
-  double v = 1.0;
-  if (h <= 0xffffffffLL) {
-    // 32-bit index arithmetic: a few instructions per division instead of the 64-bit sequence
-    uint32_t r = (uint32_t)h;
-    for (int q = 2; q <= A.m; ++q) {
-      const uint32_t nq = (uint32_t)A.n[q - 1];
-      const uint32_t iq = r % nq;
-      r /= nq;
-      v *= A.fac[A.psi_off[q - 1] + (int64_t)iq * A.ell + a];
-    }
-    return v;
-  }
-  int64_t r = h;
-  for (int q = 2; q <= A.m; ++q) {
-    const int64_t nq = A.n[q - 1];
-    const int64_t iq = r % nq;
-    r /= nq;
-    v *= A.fac[A.psi_off[q - 1] + iq * A.ell + a];
-  }
-  return v;
-}
-
-// Psi_m(row, a) for a global row of X_m (0 outside the matrix / sketch).
-__device__ __forceinline__ double psi_row(const SketchArgs& A, int64_t row, int a) {
-  if (row >= A.R || a >= A.ell) return 0.0;
-  if (A.psi_tab) return A.psi_tab[row * A.L4 + a];
-  const int64_t h = row / A.n[0];
-  const int64_t i1 = row - h * A.n[0];
-  return A.fac[A.psi_off[0] + i1 * A.ell + a] * psi_hi(A, h, a);
-}
-
-// A lane's rows of Psi_m, visited in increasing order by the workgroup
-// prologues: (i_1, h) with row = i_1 + n_1 h is advanced without division, and
-// the caller forms psi_hi again only when h changes (and only inside the
-// matrix, where h's top digit is a valid index).  Values equal psi_row's.
-struct PsiCursor {
-  int64_t row = 0, h = 0, hc = -1;
-  int64_t i1 = 0;
-  __device__ __forceinline__ void init(const SketchArgs& A, int64_t r) {
-    row = r;
-    h = r / A.n[0];
-    i1 = r - h * A.n[0];
-  }
-  __device__ __forceinline__ void advance(const SketchArgs& A, int by) {
-    row += by;
-    i1 += by;
-    while (i1 >= A.n[0]) {
-      i1 -= A.n[0];
-      ++h;
-    }
-  }
-  // true when the caller must recompute its psi_hi values for this row
-  __device__ __forceinline__ bool refresh(const SketchArgs& A) {
-    if (row >= A.R || A.psi_tab || h == hc) return false;
-    hc = h;
-    return true;
-  }
-  __device__ __forceinline__ double at(const SketchArgs& A, int a, double hi) const {
-    if (row >= A.R || a >= A.ell) return 0.0;
-    if (A.psi_tab) return A.psi_tab[row * A.L4 + a];
-    return A.fac[A.psi_off[0] + i1 * A.ell + a] * hi;
-  }
-};
-
-// Omega_m(gcol, c) for a global column of X_m.
-__device__ __forceinline__ double omega_col(const SketchArgs& A, int64_t gcol, int c) {
-  double v = 1.0;
-  int64_t r = gcol;
-  for (int q = A.m + 1; q <= A.d; ++q) {
-    int64_t nq = A.n[q - 1];
-    int64_t iq = r % nq;
-    r /= nq;
-    v *= A.fac[A.omega_off[q - 1] + iq * A.ell + c];
-  }
-  return v;
 }
 
 struct ChunkInfo {
@@ -1502,44 +1422,6 @@ hipError_t launch_sketch(int prec, int lp, const SketchArgs& a, hipStream_t s) {
     case P_BF16X3 * 100 + 32: return launch_t<P_BF16X3, 32>(a, aligned, s);
     default: return hipErrorInvalidValue;
   }
-}
-
-// ---- one partial column (slab edges that cut a column of X_m), FP64 ----
-template <typename T>
-__global__ void k_partial_col(const T* __restrict__ x, int64_t r0, int64_t r1, int64_t gcol, const SketchArgs A,
-                              double* __restrict__ Y, double* __restrict__ Tt) {
-  __shared__ double red[PSTT2_MAX_ELL][8];
-  double om[PSTT2_MAX_ELL];
-  for (int c = 0; c < A.ell; ++c) om[c] = omega_col(A, gcol, c);
-  double t[PSTT2_MAX_ELL];
-  for (int a = 0; a < A.ell; ++a) t[a] = 0.0;
-  for (int64_t r = r0 + threadIdx.x; r < r1; r += blockDim.x) {
-    const double xv = (double)x[r - r0];
-    for (int c = 0; c < A.ell; ++c) Y[(int64_t)c * A.R + r] += xv * om[c];
-    for (int a = 0; a < A.ell; ++a) t[a] += psi_row(A, r, a) * xv;
-  }
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  for (int a = 0; a < A.ell; ++a) {
-    double v = t[a];
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-    if (lane == 0) red[a][w] = v;
-  }
-  __syncthreads();
-  if (threadIdx.x < A.ell) {
-    double s = 0.0;
-    for (int ww = 0; ww < (int)(blockDim.x >> 6); ++ww) s += red[threadIdx.x][ww];
-    Tt[(int64_t)threadIdx.x * A.C + gcol] += s;
-  }
-}
-
-hipError_t launch_partial_col(int dtype, const void* x, int64_t r0, int64_t r1, int64_t gcol, const SketchArgs& a,
-                              double* Y, double* Tt, hipStream_t s) {
-  if (fault_take()) return hipErrorLaunchFailure;
-  if (dtype == PSTT2_F64)
-    hipLaunchKernelGGL(k_partial_col<double>, dim3(1), dim3(512), 0, s, (const double*)x, r0, r1, gcol, a, Y, Tt);
-  else
-    hipLaunchKernelGGL(k_partial_col<float>, dim3(1), dim3(512), 0, s, (const float*)x, r0, r1, gcol, a, Y, Tt);
-  return hipGetLastError();
 }
 
 }  // namespace pstt2
