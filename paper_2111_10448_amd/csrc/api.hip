@@ -1833,6 +1833,11 @@ pstt2_status tt_reconstruct(const tt_cores* cores, void* x_out_dev, pstt2_dtype 
   for (int k = 0; k < cores->d; ++k) N *= cores->n[k];
   if (first < 0 || count < 0 || first + count > N) return fail(nullptr, PSTT2_EINVAL, "range outside the tensor");
   if (!x_out_dev && count > 0) return fail(nullptr, PSTT2_EINVAL, "null output");
+  // returns only after its stream is idle, so it shares tt_error's arena (where
+  // that cannot grow, the stream-ordered allocator serves the exact sizes)
+  Arena* ar = error_arena();
+  if (ar && arena_begin(ar, (hipStream_t)hip_stream) != hipSuccess) ar = nullptr;
+  ArenaScope scope(ar);
   hipError_t e = tt_reconstruct_run(cores, x_out_dev, dtype, first, count, (hipStream_t)hip_stream);
   if (e != hipSuccess) return hfail(nullptr, e, "tt_reconstruct");
   return PSTT2_OK;

@@ -295,7 +295,6 @@ hipError_t svd_last_core(const double* src, int64_t ld, const int* idx, const do
                          hipStream_t s);
 
 // TT evaluation (tt_eval.hip).
-hipError_t tt_interfaces(const tt_cores* c, int split, double** L, double** Rt, double** base, hipStream_t s);
 // Bytes of the static scratch the allocation-free error pass of these cores needs.
 int64_t tt_error_scratch_bytes(const tt_cores* c);
 // The error pass in the static scratch; err_dev receives (relative error,

@@ -20,43 +20,87 @@ static unsigned grid_for(int64_t n, int bs) {
   return (unsigned)std::max<int64_t>(1, std::min<int64_t>((n + bs - 1) / bs, 8192));
 }
 
-// L_k(row + R_{k-1} i, b) = sum_a L_{k-1}(row, a) G_k(a, i, b)
-// One thread per row of L_k: its rp entries of L_{k-1} are read once and kept
-// in registers for all rk outputs (consecutive threads on consecutive rows).
-__global__ void k_left_iface(const double* __restrict__ Lp, int64_t Rp, int rp, const double* __restrict__ G, int nk,
-                             int rk, double* __restrict__ L) {
-  constexpr int MX = PSTT2_MAX_ELL;
-  const int64_t Rk = Rp * nk;
-  for (int64_t rr = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; rr < Rk; rr += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t row = rr % Rp;
-    const int i = (int)(rr / Rp);
-    double lp[MX];
+// One level of both interfaces in one launch (the two chains are independent):
+//   left   L_k(row + R_{k-1} i, b) = sum_a L_{k-1}(row, a) G_k(a, i, b),
+//          workgroups [0, gl): one thread per row of L_k, its rp entries of
+//          L_{k-1} read once and kept in registers for all rk outputs;
+//   right  Rt_k(a, i + n_k col) = sum_b G_k(a, i, b) Rt_{k+1}(b, col), Rt_{k+1}
+//          r_k x C_k, workgroups [gl, gl + gr): one thread per entry.  The last
+//          level is written with ldr >= r rows per column, zero past r (the
+//          streaming kernels read a column's entries as one run of that length).
+// Latency bound (a few microseconds a level at the sizes of a middle split): the
+// chains' levels share launches, and the register slots of the left part are
+// rounded up from the rank, so its loop has no guard per entry.  At R = 20592,
+// r = 8 a left level took 10.8 us with 32 guarded slots, 5 launches for d = 8.
+struct IfaceLevel {
+  const double *Lp, *Gl;
+  double* L;
+  int64_t Rp;
+  int rpl, nl, rkl;
+  unsigned gl;
+  const double *Gr, *Rn;
+  double* Rt;
+  int64_t Ck;
+  int rpr, nr, rkr, ldr;
+  unsigned gr;
+};
+
+template <int RP>
+__global__ __launch_bounds__(256) void k_ifaces(const IfaceLevel A) {
+  if (blockIdx.x < A.gl) {
+    const int64_t Rk = A.Rp * A.nl;
+    const int rp = A.rpl;
+    for (int64_t rr = blockIdx.x * (int64_t)256 + threadIdx.x; rr < Rk; rr += (int64_t)A.gl * 256) {
+      const int i = (int)(rr / A.Rp);
+      const int64_t row = rr - A.Rp * i;
+      double lp[RP];
 #pragma unroll
-    for (int a = 0; a < MX; ++a) lp[a] = a < rp ? Lp[(int64_t)a * Rp + row] : 0.0;
-    for (int b = 0; b < rk; ++b) {
-      const double* g = G + (int64_t)rp * (i + (int64_t)nk * b);
-      double s = 0.0;
+      for (int a = 0; a < RP; ++a) lp[a] = a < rp ? A.Lp[(int64_t)a * A.Rp + row] : 0.0;
+      for (int b = 0; b < A.rkl; ++b) {
+        const double* g = A.Gl + (int64_t)rp * (i + (int64_t)A.nl * b);
+        double s = 0.0;
 #pragma unroll
-      for (int a = 0; a < MX; ++a)
-        if (a < rp) s += lp[a] * g[a];
-      L[rr + Rk * b] = s;
+        for (int a = 0; a < RP; ++a) {
+          const double gv = g[a < rp ? a : 0];   // a finite product with lp = 0 past rp
+          s += lp[a] * (a < rp ? gv : 0.0);
+        }
+        A.L[rr + Rk * b] = s;
+      }
     }
+    return;
+  }
+  const int64_t Cp = A.Ck * A.nr;
+  const int64_t tot = (int64_t)A.ldr * Cp;
+  for (int64_t t = (blockIdx.x - A.gl) * (int64_t)256 + threadIdx.x; t < tot; t += (int64_t)A.gr * 256) {
+    const int64_t cc = t / A.ldr;
+    const int a = (int)(t - cc * A.ldr);
+    const int64_t col = cc / A.nr;
+    const int i = (int)(cc - col * A.nr);
+    double s = 0.0;
+    if (a < A.rpr)
+      for (int b = 0; b < A.rkr; ++b)
+        s += A.Gr[a + (int64_t)A.rpr * (i + (int64_t)A.nr * b)] * A.Rn[b + (int64_t)A.rkr * col];
+    A.Rt[t] = s;
   }
 }
 
-// Rt_k(a, i + n_k col) = sum_b G_k(a, i, b) Rt_{k+1}(b, col); Rt_{k+1} is r_k x C_k.
-__global__ void k_right_iface(const double* __restrict__ G, int rp, int nk, int rk, const double* __restrict__ Rn,
-                              int64_t Ck, double* __restrict__ Rt) {
-  const int64_t Cp = Ck * nk;
-  const int64_t tot = (int64_t)rp * Cp;
+static void launch_ifaces(const IfaceLevel& A, hipStream_t s) {
+  const dim3 g(A.gl + A.gr), b(256);
+  const int rp = A.gl ? A.rpl : 1;
+  if (rp <= 4) hipLaunchKernelGGL(k_ifaces<4>, g, b, 0, s, A);
+  else if (rp <= 8) hipLaunchKernelGGL(k_ifaces<8>, g, b, 0, s, A);
+  else if (rp <= 12) hipLaunchKernelGGL(k_ifaces<12>, g, b, 0, s, A);
+  else if (rp <= 16) hipLaunchKernelGGL(k_ifaces<16>, g, b, 0, s, A);
+  else if (rp <= 24) hipLaunchKernelGGL(k_ifaces<24>, g, b, 0, s, A);
+  else hipLaunchKernelGGL(k_ifaces<32>, g, b, 0, s, A);
+}
+
+// Rt (r x C, column-major) -> Rp (RK x C) with zero rows r..RK-1
+__global__ void k_pad_rt(const double* __restrict__ Rt, int r, int RK, int64_t C, double* __restrict__ Rp) {
+  const int64_t tot = (int64_t)RK * C;
   for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < tot; t += (int64_t)gridDim.x * blockDim.x) {
-    const int a = (int)(t % rp);
-    const int64_t cc = t / rp;
-    const int i = (int)(cc % nk);
-    const int64_t col = cc / nk;
-    double s = 0.0;
-    for (int b = 0; b < rk; ++b) s += G[a + (int64_t)rp * (i + (int64_t)nk * b)] * Rn[b + (int64_t)rk * col];
-    Rt[t] = s;
+    const int k = (int)(t % RK);
+    Rp[t] = k < r ? Rt[(t / RK) * r + k] : 0.0;
   }
 }
 
@@ -78,47 +122,55 @@ static int64_t tt_interfaces_doubles(const tt_cores* c, int split) {
   return tot;
 }
 
-// The interface levels built into ws (tt_interfaces_doubles of them); *Lout
-// (R_split x r_split) and *Rout (r_split x C_split) point into ws or at a core.
-static hipError_t tt_interfaces_in(const tt_cores* c, int split, double* ws, double** Lout, double** Rout,
+// The interface levels built into ws (tt_interfaces_doubles of them): *Lout
+// (R_split x r_split) points into ws or at a core; the right interface goes to
+// Rp with RK >= r_split rows per column, zero past r_split.
+static hipError_t tt_interfaces_in(const tt_cores* c, int split, double* ws, int RK, double* Rp, double** Lout,
                                    hipStream_t s) {
   const int d = c->d;
   double* cur = ws;
-  int64_t Rp = c->n[0];
-  double* L = c->core[0];   // L_1 = G_1 (read only)
-  for (int k = 1; k < split; ++k) {
-    const int nk = (int)c->n[k];
-    double* Ln = cur;
-    cur += Rp * nk * c->r[k + 1];
-    hipLaunchKernelGGL(k_left_iface, dim3(grid_for(Rp * nk, 256)), dim3(256), 0, s, L, Rp, c->r[k], c->core[k], nk,
-                       c->r[k + 1], Ln);
-    L = Ln;
-    Rp *= nk;
-  }
-  int64_t Ck = c->n[d - 1];
+  int64_t rows = c->n[0], Ck = c->n[d - 1];
+  double* L = c->core[0];       // L_1 = G_1 (read only)
   double* R = c->core[d - 1];   // Rt_d = G_d (read only)
-  for (int k = d - 2; k >= split; --k) {
-    const int nk = (int)c->n[k];
-    double* Rn = cur;
-    cur += Ck * nk * c->r[k];
-    hipLaunchKernelGGL(k_right_iface, dim3(grid_for(Ck * nk * c->r[k], 256)), dim3(256), 0, s, c->core[k], c->r[k],
-                       nk, c->r[k + 1], R, Ck, Rn);
-    R = Rn;
-    Ck *= nk;
+  const int nl = split - 1, nr = d - 1 - split;   // levels of each chain
+  for (int j = 0; j < std::max(nl, nr); ++j) {
+    IfaceLevel A = {};
+    if (j < nl) {
+      const int k = j + 1;
+      A.Lp = L;
+      A.Gl = c->core[k];
+      A.L = cur;
+      A.Rp = rows;
+      A.rpl = c->r[k];
+      A.nl = (int)c->n[k];
+      A.rkl = c->r[k + 1];
+      rows *= c->n[k];
+      cur += rows * c->r[k + 1];
+      A.gl = grid_for(rows, 256);
+      L = A.L;
+    }
+    if (j < nr) {
+      const int k = d - 2 - j;
+      const bool last = j == nr - 1;
+      A.Gr = c->core[k];
+      A.Rn = R;
+      A.Ck = Ck;
+      A.rpr = c->r[k];
+      A.nr = (int)c->n[k];
+      A.rkr = c->r[k + 1];
+      A.ldr = last ? RK : c->r[k];
+      Ck *= c->n[k];
+      A.Rt = last ? Rp : cur;
+      if (!last) cur += Ck * c->r[k];
+      A.gr = grid_for(Ck * A.ldr, 256);
+      R = A.Rt;
+    }
+    launch_ifaces(A, s);
   }
+  if (nr == 0)
+    hipLaunchKernelGGL(k_pad_rt, dim3(grid_for(RK * Ck, 256)), dim3(256), 0, s, R, c->r[d - 1], RK, Ck, Rp);
   *Lout = L;
-  *Rout = R;
   return hipGetLastError();
-}
-
-// Interfaces in one stream-ordered workspace allocation: *base is returned for
-// a single ws_free on the same stream.
-hipError_t tt_interfaces(const tt_cores* c, int split, double** Lout, double** Rout, double** base, hipStream_t s) {
-  double* ws = nullptr;
-  hipError_t e = ws_alloc((void**)&ws, sizeof(double) * tt_interfaces_doubles(c, split), s);
-  if (e != hipSuccess) return e;
-  *base = ws;
-  return tt_interfaces_in(c, split, ws, Lout, Rout, s);
 }
 
 // ---- tt_error: one streaming pass over X ----
@@ -258,15 +310,6 @@ __global__ __launch_bounds__(256) void k_sum_parts(const double* __restrict__ pa
   }
 }
 
-// Rt (r x C, column-major) -> Rp (RK x C) with zero rows r..RK-1
-__global__ void k_pad_rt(const double* __restrict__ Rt, int r, int RK, int64_t C, double* __restrict__ Rp) {
-  const int64_t tot = (int64_t)RK * C;
-  for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < tot; t += (int64_t)gridDim.x * blockDim.x) {
-    const int k = (int)(t % RK);
-    Rp[t] = k < r ? Rt[(t / RK) * r + k] : 0.0;
-  }
-}
-
 static int rk_slot(int r) { return r <= 4 ? 4 : r <= 8 ? 8 : r <= 12 ? 12 : r <= 16 ? 16 : r <= 24 ? 24 : 32; }
 
 template <typename T, bool PAIR, bool FN>
@@ -325,10 +368,9 @@ static ErrPlan err_plan(const tt_cores* c) {
 // Every scratch entry is written before it is read: nothing needs clearing.
 static hipError_t err_launch(const tt_cores* c, const ErrPlan& p, const void* x, int dtype, const FnTabs& fn,
                              double* iface, double* part, double* Rp, double* out, bool rel, hipStream_t s) {
-  double *L = nullptr, *Rt = nullptr;
-  hipError_t e = tt_interfaces_in(c, p.split, iface, &L, &Rt, s);
+  double* L = nullptr;
+  hipError_t e = tt_interfaces_in(c, p.split, iface, p.RK, Rp, &L, s);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_pad_rt, dim3(grid_for(p.n_rp, 256)), dim3(256), 0, s, Rt, p.r, p.RK, p.C, Rp);
   if (fn.rec) e = launch_err_p<double, false, true>(nullptr, p.R, p.C, p.r, L, Rp, p.gi, p.gj, part, fn, s);
   else if (dtype == PSTT2_F64) e = launch_err((const double*)x, p.R, p.C, p.r, L, Rp, p.gi, p.gj, part, s);
   else e = launch_err((const float*)x, p.R, p.C, p.r, L, Rp, p.gi, p.gj, part, s);
@@ -429,14 +471,14 @@ hipError_t tt_error_run_gauss(const tt_cores* c, const double* centers_host, int
   if (e != hipSuccess) return e;
   GaussTabs g;
   e = gauss_tables(c->n, d, split, centers_host, nterms, gamma, tabs, &g, s);
-  double *L = nullptr, *Rt = nullptr, *ifb = nullptr;
-  if (e == hipSuccess) e = tt_interfaces(c, split, &L, &Rt, &ifb, s);
+  const int r = c->r[split];
+  const int RK = rk_slot(r);
+  double *L = nullptr, *ifb = nullptr;
+  if (e == hipSuccess) e = ws_alloc((void**)&ifb, sizeof(double) * tt_interfaces_doubles(c, split), s);
   if (e != hipSuccess) {
     ws_free(tabs, s);
     return e;
   }
-  const int r = c->r[split];
-  const int RK = rk_slot(r);
   const int64_t ncmax = gauss_chunk_cols(g, sizeof(double));
   const int64_t nchunk = (C + ncmax - 1) / ncmax;
   const int gi = (int)((R + 511) / 512);
@@ -446,7 +488,7 @@ hipError_t tt_error_run_gauss(const tt_cores* c, const double* centers_host, int
   if (e == hipSuccess) e = ws_alloc((void**)&Rp, sizeof(double) * RK * C, s);
   if (e == hipSuccess) e = ws_alloc((void**)&W, sizeof(double) * R * ncmax, s);
   if (e == hipSuccess) {
-    hipLaunchKernelGGL(k_pad_rt, dim3(grid_for(RK * C, 256)), dim3(256), 0, s, Rt, r, RK, C, Rp);
+    e = tt_interfaces_in(c, split, ifb, RK, Rp, &L, s);
     const bool pair = (R % 2) == 0;
     const FnTabs none{nullptr, nullptr, nullptr};
     int64_t np = 0;   // partial pairs written so far
@@ -473,36 +515,110 @@ hipError_t tt_error_run_gauss(const tt_cores* c, const double* centers_host, int
   return e != hipSuccess ? e : e2;
 }
 
+// Entries [first, first + count) of X~ = L Rt.  A lane keeps V rows of L in
+// registers and walks its workgroup's share of the columns; a column's Rt
+// entries are one wave-uniform run (Rt padded to RK rows).  VEC: the V rows are
+// consecutive and leave as one 16-byte (V = 2 floats: 8-byte) store; needs R,
+// first and count to be multiples of V and an aligned output.  Otherwise they
+// are 64 apart, one scalar store each, still contiguous over the wave.
+// Every entry sums its ranks in increasing order.
+// HBM bound (the output): 4.3 GB of FP32 at R = 64^3, rank 4 slots: one thread
+// per entry, with a 64-bit division and 2 r cached loads each, took 2.25 ms;
+// this takes 0.82 ms (5.2 TB/s).
+template <typename T, int RK, int V, bool VEC>
+__global__ __launch_bounds__(256) void k_reconstruct(T* __restrict__ out, int64_t first, int64_t count, int64_t R,
+                                                     int64_t c0, int64_t ncol, int r, const double* __restrict__ L,
+                                                     const double* __restrict__ Rp, int gi_count, int gj_count) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int gi = blockIdx.x % gi_count, gj = blockIdx.x / gi_count;
+  const int64_t row0 = ((int64_t)gi * 4 + w) * (64 * V) + (VEC ? V * lane : lane);
+  constexpr int ST = VEC ? 1 : 64;
+  double l[V][RK];
+#pragma unroll
+  for (int v = 0; v < V; ++v) {
+    const int64_t row = row0 + ST * v;
+#pragma unroll
+    for (int k = 0; k < RK; ++k) l[v][k] = (row < R && k < r) ? L[(int64_t)k * R + row] : 0.0;
+  }
+  const int64_t cb = c0 + gj * ncol / gj_count, ce = c0 + (gj + 1) * ncol / gj_count;
+#pragma unroll 4
+  for (int64_t col = cb; col < ce; ++col) {
+    const double* rc = Rp + (int64_t)RK * col;
+    double t[V];
+#pragma unroll
+    for (int v = 0; v < V; ++v) t[v] = 0.0;
+#pragma unroll
+    for (int k = 0; k < RK; ++k) {
+      const double rv = rc[k];
+#pragma unroll
+      for (int v = 0; v < V; ++v) t[v] += l[v][k] * rv;
+    }
+    const int64_t f = col * R + row0 - first;
+    if constexpr (VEC) {
+      if (row0 < R && f >= 0 && f < count) {
+        typedef T vec __attribute__((ext_vector_type(V)));
+        vec o;
+#pragma unroll
+        for (int v = 0; v < V; ++v) o[v] = (T)t[v];
+        *(vec*)(out + f) = o;
+      }
+    } else {
+#pragma unroll
+      for (int v = 0; v < V; ++v)
+        if (row0 + ST * v < R && f + ST * v >= 0 && f + ST * v < count) out[f + ST * v] = (T)t[v];
+    }
+  }
+}
+
+template <typename T, int RK>
+static void launch_rec(T* out, int64_t first, int64_t count, int64_t R, int r, const double* L, const double* Rp,
+                       hipStream_t s) {
+  // rows per lane: 16-byte stores, fewer where the rank's register slots leave no room for four
+  constexpr int V = sizeof(T) == 4 && RK <= 16 ? 4 : 2;
+  const bool vec = R % V == 0 && first % V == 0 && count % V == 0 && (uintptr_t)out % (V * sizeof(T)) == 0;
+  const int64_t c0 = first / R, ncol = (first + count + R - 1) / R - c0;
+  const int64_t gi = (R + 256 * V - 1) / (256 * V);
+  // about 4096 workgroups (a lane's V RK loads of L serve its share of the columns)
+  const int64_t gj = std::max<int64_t>(1, std::min<int64_t>(ncol, (4096 + gi - 1) / gi));
+  const dim3 g((unsigned)(gi * gj)), b(256);
+  if (vec)
+    hipLaunchKernelGGL((k_reconstruct<T, RK, V, true>), g, b, 0, s, out, first, count, R, c0, ncol, r, L, Rp, (int)gi,
+                       (int)gj);
+  else
+    hipLaunchKernelGGL((k_reconstruct<T, RK, V, false>), g, b, 0, s, out, first, count, R, c0, ncol, r, L, Rp,
+                       (int)gi, (int)gj);
+}
+
 template <typename T>
-__global__ void k_reconstruct(T* __restrict__ out, int64_t first, int64_t count, int64_t R, int r,
-                              const double* __restrict__ L, const double* __restrict__ Rt) {
-  for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < count; t += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t f = first + t;
-    const int64_t row = f % R, col = f / R;
-    double s = 0.0;
-    for (int b = 0; b < r; ++b) s += L[(int64_t)b * R + row] * Rt[b + (int64_t)r * col];
-    out[t] = (T)s;
+static void launch_rec_r(int RK, T* out, int64_t first, int64_t count, int64_t R, int r, const double* L,
+                         const double* Rp, hipStream_t s) {
+  switch (RK) {
+    case 4: launch_rec<T, 4>(out, first, count, R, r, L, Rp, s); break;
+    case 8: launch_rec<T, 8>(out, first, count, R, r, L, Rp, s); break;
+    case 12: launch_rec<T, 12>(out, first, count, R, r, L, Rp, s); break;
+    case 16: launch_rec<T, 16>(out, first, count, R, r, L, Rp, s); break;
+    case 24: launch_rec<T, 24>(out, first, count, R, r, L, Rp, s); break;
+    default: launch_rec<T, 32>(out, first, count, R, r, L, Rp, s); break;
   }
 }
 
 hipError_t tt_reconstruct_run(const tt_cores* c, void* out, int dtype, int64_t first, int64_t count, hipStream_t s) {
   const int d = c->d;
   const int split = (d + 1) / 2;
-  double *L = nullptr, *Rt = nullptr, *ifb = nullptr;
-  hipError_t e = tt_interfaces(c, split, &L, &Rt, &ifb, s);
-  if (e != hipSuccess) return e;
-  int64_t R = 1;
+  int64_t R = 1, C = 1;
   for (int k = 0; k < split; ++k) R *= c->n[k];
-  const int r = c->r[split];
-  if (count > 0) {
-    if (dtype == PSTT2_F64)
-      hipLaunchKernelGGL(k_reconstruct<double>, dim3(grid_for(count, 256)), dim3(256), 0, s, (double*)out, first,
-                         count, R, r, L, Rt);
-    else
-      hipLaunchKernelGGL(k_reconstruct<float>, dim3(grid_for(count, 256)), dim3(256), 0, s, (float*)out, first,
-                         count, R, r, L, Rt);
+  for (int k = split; k < d; ++k) C *= c->n[k];
+  const int r = c->r[split], RK = rk_slot(r);
+  double *L = nullptr, *ifb = nullptr, *Rp = nullptr;
+  hipError_t e = ws_alloc((void**)&ifb, sizeof(double) * tt_interfaces_doubles(c, split), s);
+  if (e == hipSuccess) e = ws_alloc((void**)&Rp, sizeof(double) * RK * C, s);
+  if (e == hipSuccess) e = tt_interfaces_in(c, split, ifb, RK, Rp, &L, s);
+  if (e == hipSuccess && count > 0) {
+    if (dtype == PSTT2_F64) launch_rec_r(RK, (double*)out, first, count, R, r, L, Rp, s);
+    else launch_rec_r(RK, (float*)out, first, count, R, r, L, Rp, s);
     e = hipGetLastError();
   }
+  ws_free(Rp, s);
   ws_free(ifb, s);
   hipError_t e2 = hipStreamSynchronize(s);
   return e != hipSuccess ? e : e2;
