@@ -1588,7 +1588,7 @@ pstt2_status pstt2_parallel_ttsvd(int32_t d, const int64_t* n, const double* x_d
     if (Rk[q + 1] > (int64_t(1) << 36)) return fail(nullptr, PSTT2_EINVAL, "tensor too large for the Jacobi SVDs");
   }
   const int64_t N = Rk[d];
-  int64_t wmax = 0;
+  int64_t wmax = 0, gmax = 0;
   int spmax = 2;
   for (int k = 1; k <= d - 1; ++k) {
     const int64_t R = Rk[k], C = N / R, sh = std::min(R, C);
@@ -1597,9 +1597,10 @@ pstt2_status pstt2_parallel_ttsvd(int32_t d, const int64_t* n, const double* x_d
     const int sp = (int)(sh + (sh & 1));
     spmax = std::max(spmax, sp);
     wmax = std::max(wmax, std::max(R, C) * sp);
+    gmax = std::max(gmax, svd_ws_doubles(std::max(R, C), sp));
   }
   hipStream_t s = (hipStream_t)hip_stream;
-  double *W = nullptr, *J = nullptr, *sig = nullptr;
+  double *W = nullptr, *J = nullptr, *sig = nullptr, *gws = nullptr, *ortho = nullptr;
   int *idx = nullptr, *cnt = nullptr;
   std::vector<double*> U(d + 1, nullptr);
   int r[PSTT2_MAX_D + 1];
@@ -1612,6 +1613,8 @@ pstt2_status pstt2_parallel_ttsvd(int32_t d, const int64_t* n, const double* x_d
     dev_free_async(W, s);
     dev_free_async(J, s);
     dev_free_async(sig, s);
+    dev_free_async(gws, s);
+    dev_free_async(ortho, s);
     dev_free_async(idx, s);
     dev_free_async(cnt, s);
   };
@@ -1629,6 +1632,8 @@ pstt2_status pstt2_parallel_ttsvd(int32_t d, const int64_t* n, const double* x_d
   SVDCK(dev_malloc_async((void**)&W, sizeof(double) * wmax, s));
   SVDCK(dev_malloc_async((void**)&J, sizeof(double) * spmax * spmax, s));
   SVDCK(dev_malloc_async((void**)&sig, sizeof(double) * spmax, s));
+  SVDCK(dev_malloc_async((void**)&ortho, sizeof(double) * PSTT2_MAX_ELL * PSTT2_MAX_ELL, s));
+  if (gmax > 0) SVDCK(dev_malloc_async((void**)&gws, sizeof(double) * gmax, s));
   SVDCK(dev_malloc_async((void**)&idx, sizeof(int) * spmax, s));
   SVDCK(dev_malloc_async((void**)&cnt, sizeof(int), s));
   // the last core is formed with its split's SVD; the others from U by equation "core"
@@ -1641,24 +1646,53 @@ pstt2_status pstt2_parallel_ttsvd(int32_t d, const int64_t* n, const double* x_d
     const double tol = std::sqrt((double)L) * 2.220446049250313e-16;
     SVDCK(svd_load(x_dev, R, C, sp, W, s));
     SVDCK(svd_init(J, sp, cnt, s));
-    bool converged = false;
+    std::vector<double> sv(sh);
+    double tot = 0.0, tau = -1.0;
+    bool converged = false, cut_tail = true;
     for (int sweep = 0; sweep < 40 && !converged; ++sweep) {
       int rot = 0;
-      SVDCK(svd_sweep(W, L, J, sp, tol, cnt, s));
+      SVDCK(svd_sweep(W, L, J, sp, tol, tau, gws, cnt, s));
+      SVDCK(svd_colnorms(W, L, sh, sig, s));
       SVDCK(hipMemcpyAsync(&rot, cnt, sizeof(int), hipMemcpyDeviceToHost, s));
+      SVDCK(hipMemcpyAsync(sv.data(), sig, sizeof(double) * sh, hipMemcpyDeviceToHost, s));
       SVDCK(hipStreamSynchronize(s));
-      converged = rot == 0;
+      tot = 0.0;
+      for (double v : sv) {
+        if (!std::isfinite(v)) return bail(fail(nullptr, PSTT2_ENUMERIC, "non-finite values in X"));
+        tot += v * v;
+      }
+      // Columns that are cut anyway need not be orthogonal among themselves: the
+      // rank rule sees them only through their sum of squares, which rotations
+      // among them keep.  tau bounds the largest run of small columns whose
+      // squares sum to at most a quarter of the rule's threshold.  It serves only
+      // where a gap follows that run (the sum at most a hundredth of the next
+      // square: without one the sweeps stall at the border), and no singular
+      // value of the run can exceed a kept one (its largest is at most the root
+      // of the sum); otherwise every pair is rotated.
+      std::vector<double> e(sv);
+      std::sort(e.begin(), e.end());
+      const double cut = 0.25 * eps * eps * tot / (d - 1);
+      double run = 0.0, next = -1.0;
+      size_t nrun = 0;
+      while (nrun < e.size() && run + e[nrun] * e[nrun] <= cut) {
+        run += e[nrun] * e[nrun];
+        next = e[nrun] * e[nrun];
+        ++nrun;
+      }
+      if (rot == 0) {
+        // every pair not excused by tau was orthogonal when met, and nothing moved
+        double below = 0.0, above = INFINITY;
+        for (double v : e) {
+          if (v * v <= tau) below += v * v;
+          else above = std::min(above, v * v);
+        }
+        if (tau < 0.0 || below <= above) converged = true;
+        else cut_tail = false;
+      }
+      const bool gap = nrun > 0 && (nrun == e.size() || run <= 0.01 * e[nrun] * e[nrun]);
+      tau = cut_tail && gap ? next * (1.0 + 1e-12) : -1.0;   // past the rounding of either norm
     }
     if (!converged) return bail(fail(nullptr, PSTT2_ENUMERIC, "Jacobi SVD did not converge in 40 sweeps"));
-    std::vector<double> sv(sh);
-    SVDCK(svd_colnorms(W, L, sh, sig, s));
-    SVDCK(hipMemcpyAsync(sv.data(), sig, sizeof(double) * sh, hipMemcpyDeviceToHost, s));
-    SVDCK(hipStreamSynchronize(s));
-    double tot = 0.0;
-    for (double v : sv) {
-      if (!std::isfinite(v)) return bail(fail(nullptr, PSTT2_ENUMERIC, "non-finite values in X"));
-      tot += v * v;
-    }
     // singular values in decreasing order (ties keep column order)
     std::vector<int> order(sh);
     for (int i = 0; i < sh; ++i) order[i] = i;
@@ -1683,12 +1717,19 @@ pstt2_status pstt2_parallel_ttsvd(int32_t d, const int64_t* n, const double* x_d
     SVDCK(dev_malloc_async((void**)&U[k], sizeof(double) * R * rk, s));
     if (R <= C) SVDCK(svd_gather(J, sp, R, idx, nullptr, rk, U[k], s));   // U = J
     else SVDCK(svd_gather(W, R, R, idx, sig, rk, U[k], s));              // U = W' / sigma
+    SVDCK(adj_gemm(true, false, rk, rk, R, 1.0, U[k], R, U[k], R, 0.0, ortho, rk, s));
     if (k == d - 1) {
+      // G_d = U^T X_{d-1}: W'^T where W' = X_{d-1}^T U, with the correction of U
+      // applied to it; else a tall product with the corrected U
       SVDCK(dev_malloc_async((void**)&glast, sizeof(double) * rk * nd, s));
       U[0] = glast;   // released with the rest
-      if (R > C) SVDCK(svd_last_core(J, sp, idx, sig, rk, nd, glast, s));   // Sigma V^T from J
-      else SVDCK(svd_last_core(W, C, idx, nullptr, rk, nd, glast, s));      // U^T X = W'^T
+      if (R <= C) {
+        SVDCK(svd_last_core(W, C, idx, rk, nd, glast, s));
+        SVDCK(svd_polish(ortho, rk, nd, 1, rk, glast, s));
+      }
     }
+    SVDCK(svd_polish(ortho, rk, R, R, 1, U[k], s));
+    if (k == d - 1 && R > C) SVDCK(adj_gemm(true, false, rk, nd, R, 1.0, U[k], R, x_dev, R, 0.0, glast, rk, s));
     // the sizes were read back above: idx may be refilled by the next split
     SVDCK(hipStreamSynchronize(s));
   }

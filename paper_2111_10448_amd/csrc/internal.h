@@ -286,13 +286,18 @@ hipError_t adj_out(int dtype, const SketchArgs& g, int prec, const double* Yb, c
 // to even, zero columns past it), J its sp x sp rotation accumulator.
 hipError_t svd_load(const double* x, int64_t R, int64_t C, int sp, double* W, hipStream_t s);
 hipError_t svd_init(double* J, int sp, int* counter, hipStream_t s);
-// one sweep of the round-robin schedule; *counter receives the rotations made
-hipError_t svd_sweep(double* W, int64_t L, double* J, int sp, double tol, int* counter, hipStream_t s);
+// One sweep over every pair of columns; *counter receives the pairs that were not
+// orthogonal when met.  Pairs whose squared norms are both at most tau are left
+// alone (tau < 0: none).  ws: svd_ws_doubles doubles (may be null when 0).
+int64_t svd_ws_doubles(int64_t L, int sp);
+hipError_t svd_sweep(double* W, int64_t L, double* J, int sp, double tol, double tau, double* ws, int* counter,
+                     hipStream_t s);
 hipError_t svd_colnorms(const double* W, int64_t L, int scols, double* sig, hipStream_t s);
 hipError_t svd_gather(const double* src, int64_t ld, int64_t rows, const int* idx, const double* sig, int r,
                       double* dst, hipStream_t s);
-hipError_t svd_last_core(const double* src, int64_t ld, const int* idx, const double* sig, int r, int nd, double* G,
-                         hipStream_t s);
+hipError_t svd_last_core(const double* src, int64_t ld, const int* idx, int r, int nd, double* G, hipStream_t s);
+// n vectors of r entries (entry a of vector i at V + a es + i vs): v <- (3 I - E) v / 2
+hipError_t svd_polish(const double* E, int r, int64_t n, int64_t es, int64_t vs, double* V, hipStream_t s);
 
 // TT evaluation (tt_eval.hip).
 // Bytes of the static scratch the allocation-free error pass of these cores needs.

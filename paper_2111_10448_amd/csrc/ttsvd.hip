@@ -11,10 +11,21 @@
 // norms are the singular values.  For W = X_k^T, J holds the left singular
 // vectors of X_k; for W = X_k, they are the normalised columns of W'.
 //
-// Pairs follow the round-robin (circle) schedule: s - 1 rounds of s/2
-// disjoint pairs (s padded to even with a zero column) meet every pair once
-// per sweep; one launch per round, one workgroup per pair, sums in a fixed
-// order, so results are bitwise repeatable.
+// Columns go in blocks of eight; block pairs follow the round-robin (circle)
+// schedule, so nb - 1 rounds of nb / 2 disjoint pairs (nb the number of blocks
+// rounded up to even, columns past s zero and never stored) meet every pair
+// once per sweep.  A workgroup takes a block pair: the 16 x 16 Gram matrix of
+// its columns from the data (FP64 matrix cores), one sweep of two-sided Jacobi
+// on it, and the accumulated 16 x 16 rotation applied to the 16 columns of W
+// and J.  Convergence is judged on the Gram entries formed from the data, the
+// same test as for single pairs.  Sums run in a fixed order, so results are
+// bitwise repeatable.
+//
+// One pair of columns per workgroup and launch cost 7.3 us a round, nearly all
+// of it launch and reduction latency: 4847 rounds, 35 ms, on (20, 17, 19, 21).
+// A round of block pairs costs 17 us and stands for about eight of those (383
+// rounds, 6.6 ms); the whole call went from 37.9 to 8.1 ms.  It is bound by that
+// chain: Gram loads, fifteen dependent rounds of angles, the application.
 #include <algorithm>
 #include <cmath>
 
@@ -25,8 +36,25 @@ namespace pstt2 {
 namespace {
 constexpr int kBS = 256;
 
+typedef double d4 __attribute__((ext_vector_type(4)));
+constexpr int kBC = 8;            // columns per block
+constexpr int kPC = 2 * kBC;      // columns of a block pair
+constexpr int kJT = 1024;         // threads of the block kernels
+constexpr int kChunkRows = 2048;  // rows per workgroup at least
+
 // circle method: position 0 fixed, positions 1..s-1 rotate by one per round
 __device__ __forceinline__ int rr_elem(int j, int k, int s) { return j == 0 ? 0 : 1 + (j - 1 + k) % (s - 1); }
+
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// Pair (w_p, w_q) counts as orthogonal; tau: columns whose squared norms are
+// both at most tau need not be (see svd_sweep).
+__device__ __forceinline__ bool needs_rotation(double a, double b, double g, double tol, double tau) {
+  return g != 0.0 && fabs(g) > tol * sqrt(a * b) && (a > tau || b > tau);
+}
 
 __device__ __forceinline__ double block_sum(double v, double* red) {
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
@@ -64,43 +92,206 @@ __global__ void k_svd_copy(const double* __restrict__ x, int64_t R, int64_t C, i
     W[t] = t < R * C ? x[t] : 0.0;
 }
 
-// One round of the schedule: workgroup i rotates its pair (p, q) of W's and
-// J's columns when they are not yet orthogonal (|w_p . w_q| > tol ||w_p|| ||w_q||).
-__global__ __launch_bounds__(kBS) void k_jacobi_round(double* __restrict__ W, int64_t L, double* __restrict__ J,
-                                                      int sp, int k, double tol, int* __restrict__ rotations) {
-  __shared__ double red[kBS / 64];
-  const int i = blockIdx.x;
-  const int p = rr_elem(i, k, sp), q = rr_elem(sp - 1 - i, k, sp);
-  double* wp = W + (int64_t)p * L;
-  double* wq = W + (int64_t)q * L;
-  double a = 0.0, b = 0.0, g = 0.0;
-  for (int64_t t = threadIdx.x; t < L; t += kBS) {
-    const double u = wp[t], v = wq[t];
-    a += u * u;
-    b += v * v;
-    g += u * v;
+// Columns of block pair i in round k: column c < 16 of the pair, sp or more if
+// there is none.
+struct PairCols {
+  int b0, b1;
+  __device__ __forceinline__ PairCols(int i, int k, int nb) : b0(rr_elem(i, k, nb)), b1(rr_elem(nb - 1 - i, k, nb)) {}
+  __device__ __forceinline__ int col(int c) const { return (c < kBC ? b0 : b1) * kBC + (c & (kBC - 1)); }
+};
+
+// Gram matrix of the pair's columns over rows [r0, r1), summed over the waves
+// into G.  Lane (g4, l16) holds column l16 of rows 8 j + 2 g4 and + 1 of a
+// 64-row tile: the same register is both operands of the 16x16x4 product, so
+// any assignment of rows to the K index serves.
+__device__ __forceinline__ void pair_gram(const double* __restrict__ W, int64_t L, int sp, const PairCols& pc,
+                                          int64_t r0, int64_t r1, double (*part)[kPC * kPC], double* G) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, l16 = lane & 15, g4 = lane >> 4;
+  const int col = pc.col(l16);
+  const double* wc = W + (int64_t)(col < sp ? col : 0) * L;
+  d4 acc[2] = {d4{0.0, 0.0, 0.0, 0.0}, d4{0.0, 0.0, 0.0, 0.0}};
+  for (int64_t t = r0 + 64 * w; t < r1; t += 64 * (kJT / 64)) {
+    double v[16];
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        const int64_t r = t + 8 * j + 2 * g4 + e;
+        const bool in = r < r1 && col < sp;
+        const double x = wc[in ? r : r0];
+        v[2 * j + e] = in ? x : 0.0;
+      }
+#pragma unroll
+    for (int j = 0; j < 16; ++j) acc[j & 1] = __builtin_amdgcn_mfma_f64_16x16x4f64(v[j], v[j], acc[j & 1], 0, 0, 0);
   }
-  a = block_sum(a, red);
-  b = block_sum(b, red);
-  g = block_sum(g, red);
-  if (!(g != 0.0 && fabs(g) > tol * sqrt(a * b))) return;   // uniform across the workgroup
-  // tan of the rotation angle that zeroes the off-diagonal entry of [[a, g], [g, b]]
-  const double z = (b - a) / (2.0 * g);
-  const double t = (z >= 0.0 ? 1.0 : -1.0) / (fabs(z) + sqrt(1.0 + z * z));
-  const double c = 1.0 / sqrt(1.0 + t * t), s = c * t;
-  for (int64_t e = threadIdx.x; e < L; e += kBS) {
-    const double u = wp[e], v = wq[e];
-    wp[e] = c * u - s * v;
-    wq[e] = s * u + c * v;
+  acc[0] += acc[1];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) part[w][(4 * e + g4) * kPC + l16] = acc[0][e];
+  __syncthreads();
+  if (threadIdx.x < kPC * kPC) {
+    double s = part[0][threadIdx.x];
+    for (int ww = 1; ww < kJT / 64; ++ww) s += part[ww][threadIdx.x];
+    G[threadIdx.x] = s;
   }
-  double* jp = J + (int64_t)p * sp;
-  double* jq = J + (int64_t)q * sp;
-  for (int e = threadIdx.x; e < sp; e += kBS) {
-    const double u = jp[e], v = jq[e];
-    jp[e] = c * u - s * v;
-    jq[e] = s * u + c * v;
+}
+
+// Sweeps of two-sided Jacobi on the Gram matrix G by one wavefront, the
+// rotations accumulated into Q.  A round rotates eight disjoint pairs: lane
+// (i, j) owns the 2 x 2 block of pair i's rows and pair j's columns, so a round
+// is one pass over G.  The chain of a round's dependent steps is what it costs:
+// the tangent of an angle comes from the hardware's approximate reciprocal and
+// root (1e-7 or better; an inexact angle only leaves a residual that the next
+// meeting of the pair removes), the cosine and sine from it in full precision,
+// so every rotation is orthogonal to rounding.
+__device__ __forceinline__ void pair_sweeps(double (*G)[kPC + 1], double (*Q)[kPC + 1], double tol, double tau,
+                                            int sweeps) {
+  const int lane = threadIdx.x & 63, i = lane >> 3, j = lane & 7;
+  wave_sync();
+  for (int sw = 0; sw < sweeps; ++sw) {
+    bool any = false;
+    for (int rnd = 0; rnd < kPC - 1; ++rnd) {
+      const int p = rr_elem(j, rnd, kPC), q = rr_elem(kPC - 1 - j, rnd, kPC);
+      const int pi = rr_elem(i, rnd, kPC), qi = rr_elem(kPC - 1 - i, rnd, kPC);
+      const double a = G[p][p], b = G[q][q], g = G[p][q];
+      double g00 = G[pi][p], g01 = G[pi][q], g10 = G[qi][p], g11 = G[qi][q];
+      double u0 = Q[i][p], v0 = Q[i][q], u1 = Q[i + kBC][p], v1 = Q[i + kBC][q];
+      double c = 1.0, s = 0.0;
+      // the test of needs_rotation with an approximate root: slightly tighter, so
+      // that no pair counted as not orthogonal is passed over here
+      const double ab = a * b;
+      const double lim = ab > 1e-290 ? ab * __builtin_amdgcn_rsq(ab) : sqrt(ab);
+      const bool rot = g != 0.0 && fabs(g) > 0.99 * tol * lim && (a > tau || b > tau);
+      if (rot) {
+        // tan of the angle that zeroes the off-diagonal entry of [[a, g], [g, b]]
+        const double z = 0.5 * (b - a) * __builtin_amdgcn_rcp(g);
+        const double az = fabs(z), h = 1.0 + z * z;
+        const double t = az < 1e100 ? __builtin_amdgcn_rcp(az + h * __builtin_amdgcn_rsq(h)) : 0.0;
+        const double tn = z >= 0.0 ? t : -t;
+        const double x = 1.0 + tn * tn;   // in [1, 2]: two Newton steps to full precision
+        c = __builtin_amdgcn_rsq(x);
+        c += 0.5 * c * fma(-x * c, c, 1.0);
+        c += 0.5 * c * fma(-x * c, c, 1.0);
+        s = c * tn;
+      }
+      if (!__any(rot)) continue;
+      any = true;
+      const double ci = __shfl(c, i), si = __shfl(s, i);   // lane i < 8 holds pair i's angle
+      // columns p, q of the block, then rows pi, qi
+      double t0 = c * g00 - s * g01, t1 = s * g00 + c * g01;
+      g00 = t0;
+      g01 = t1;
+      t0 = c * g10 - s * g11;
+      t1 = s * g10 + c * g11;
+      g10 = t0;
+      g11 = t1;
+      wave_sync();   // every lane has read its entries
+      G[pi][p] = ci * g00 - si * g10;
+      G[pi][q] = ci * g01 - si * g11;
+      G[qi][p] = si * g00 + ci * g10;
+      G[qi][q] = si * g01 + ci * g11;
+      Q[i][p] = c * u0 - s * v0;
+      Q[i][q] = s * u0 + c * v0;
+      Q[i + kBC][p] = c * u1 - s * v1;
+      Q[i + kBC][q] = s * u1 + c * v1;
+      wave_sync();
+    }
+    if (!any) break;
   }
-  if (threadIdx.x == 0) atomicAdd(rotations, 1);
+}
+
+__global__ __launch_bounds__(kJT) void k_jacobi_gram(const double* __restrict__ W, int64_t L, int sp, int nb, int k,
+                                                     int64_t chunk, int nch, double* __restrict__ gpart) {
+  __shared__ double part[kJT / 64][kPC * kPC];
+  const int i = blockIdx.x % (nb / 2), ch = blockIdx.x / (nb / 2);
+  const PairCols pc(i, k, nb);
+  const int64_t r0 = ch * chunk, r1 = r0 + chunk < L ? r0 + chunk : L;
+  pair_gram(W, L, sp, pc, r0, r1, part, gpart + ((int64_t)i * nch + ch) * kPC * kPC);
+}
+
+// One block pair of a round: its Gram matrix (formed here when one workgroup
+// holds all L rows, else the sum of k_jacobi_gram's partials, the same in every
+// workgroup of the pair), the rotation, and its application to this workgroup's
+// rows of W and, in the pair's first workgroup, to J.
+__global__ __launch_bounds__(kJT) void k_jacobi_blocks(double* __restrict__ W, int64_t L, double* __restrict__ J,
+                                                       int sp, int nb, int k, double tol, double tau, int sweeps,
+                                                       int64_t chunk, int nch, const double* __restrict__ gpart,
+                                                       int* __restrict__ rotations) {
+  __shared__ double part[kJT / 64][kPC * kPC];
+  __shared__ double G0[kPC * kPC];
+  __shared__ double G[kPC][kPC + 1], Q[kPC][kPC + 1];
+  __shared__ int todo;
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6, l16 = lane & 15, g4 = lane >> 4;
+  const int i = blockIdx.x % (nb / 2), ch = blockIdx.x / (nb / 2);
+  const PairCols pc(i, k, nb);
+  const int64_t r0 = ch * chunk, r1 = r0 + chunk < L ? r0 + chunk : L;
+  if (nch == 1) {
+    pair_gram(W, L, sp, pc, r0, r1, part, G0);
+  } else if (t < kPC * kPC) {
+    double s = 0.0;
+    for (int c = 0; c < nch; ++c) s += gpart[((int64_t)i * nch + c) * kPC * kPC + t];
+    G0[t] = s;
+  }
+  __syncthreads();
+  if (w == 0) {
+    int bad = 0;
+#pragma unroll
+    for (int h = 0; h < 4; ++h) {
+      const int e = lane + 64 * h, r = e / kPC, c = e % kPC;
+      G[r][c] = G0[e];
+      Q[r][c] = r == c ? 1.0 : 0.0;
+      if (r < c && needs_rotation(G0[r * kPC + r], G0[c * kPC + c], G0[e], tol, tau)) ++bad;
+    }
+    for (int o = 32; o > 0; o >>= 1) bad += __shfl_xor(bad, o);
+    if (lane == 0) {
+      todo = bad;
+      if (bad && ch == 0) atomicAdd(rotations, bad);
+    }
+    if (bad) pair_sweeps(G, Q, tol, tau, sweeps);
+  }
+  __syncthreads();
+  if (todo == 0) return;   // uniform across the workgroup
+  // W(:, pair) <- W(:, pair) Q in 16-row tiles, each read and written by one wave:
+  // D = Q^T W^T, operands Q(4 ks + g4, l16) and W(row l16, column 4 ks + g4), element
+  // v of the result at new column 4 v + g4, row l16
+  double qa[4];
+  int64_t ci[4];
+#pragma unroll
+  for (int ks = 0; ks < 4; ++ks) {
+    qa[ks] = Q[4 * ks + g4][l16];
+    ci[ks] = pc.col(4 * ks + g4);
+  }
+  // tiles of this workgroup's rows of W, then (first workgroup) those of J; a wave
+  // takes kAU tiles at a time, every load before the first store
+  const int64_t ntw = (r1 - r0 + 15) / 16, nt = ntw + (ch == 0 ? (sp + 15) / 16 : 0);
+  constexpr int kAU = 3;
+  for (int64_t t0 = w; t0 < nt; t0 += kAU * (kJT / 64)) {
+    double x[kAU][4];
+    double* m[kAU];
+    int64_t ld[kAU];
+#pragma unroll
+    for (int u = 0; u < kAU; ++u) {
+      const int64_t tt = t0 + u * (kJT / 64);
+      const bool inw = tt < ntw;
+      const int64_t r = inw ? r0 + 16 * tt + l16 : 16 * (tt - ntw) + l16;
+      ld[u] = inw ? L : sp;
+      m[u] = tt < nt && r < (inw ? r1 : (int64_t)sp) ? (inw ? W : J) + r : nullptr;
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks) {
+        const bool ok = m[u] && ci[ks] < sp;
+        const double v = ok ? m[u][ci[ks] * ld[u]] : 0.0;
+        x[u][ks] = v;
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < kAU; ++u) {
+      d4 acc = d4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(qa[ks], x[u][ks], acc, 0, 0, 0);
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+        if (m[u] && ci[v] < sp) m[u][ci[v] * ld[u]] = acc[v];
+    }
+  }
 }
 
 // sig[j] = ||W(:, j)||, one workgroup per column
@@ -129,17 +320,38 @@ __global__ void k_svd_gather(const double* __restrict__ src, int64_t ld, int64_t
   }
 }
 
-// Last core G_d = Sigma_{d-1} V_{d-1}^T (r x n_d, column-major).  From J (the
-// right singular vectors when W = X_{d-1}): G(a, i) = sig[idx a] J(i, idx a).
-// From W' (when W = X_{d-1}^T, W' = X_{d-1}^T U): G(a, i) = W'(i, idx a).
-__global__ void k_svd_last_core(const double* __restrict__ src, int64_t ld, const int* __restrict__ idx,
-                                const double* __restrict__ sig, int r, int nd, double* __restrict__ G) {
+// Last core from W' = X_{d-1}^T U: G(a, i) = W'(i, idx a) (r x n_d, column-major).
+__global__ void k_svd_last_core(const double* __restrict__ src, int64_t ld, const int* __restrict__ idx, int r, int nd,
+                                double* __restrict__ G) {
   const int64_t tot = (int64_t)r * nd;
   for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < tot; t += (int64_t)gridDim.x * blockDim.x) {
     const int a = (int)(t % r);
     const int i = (int)(t / r);
-    const int j = idx[a];
-    G[t] = src[(int64_t)j * ld + i] * (sig ? sig[j] : 1.0);
+    G[t] = src[(int64_t)idx[a] * ld + i];
+  }
+}
+
+// v <- (3 I - E) v / 2 for n vectors of r entries (entry a of vector i at
+// a es + i vs), E = U^T U (r x r): one Newton step towards the orthonormal
+// factor of U, which thousands of rounded rotations leave ~1e-13 from
+// orthonormal; what is left of that is its square.
+__global__ __launch_bounds__(256) void k_svd_polish(const double* __restrict__ E, int r, int64_t n, int64_t es,
+                                                    int64_t vs, double* __restrict__ V) {
+  constexpr int MX = PSTT2_MAX_ELL;
+  __shared__ double Es[MX][MX + 1];
+  for (int t = threadIdx.x; t < r * r; t += 256) Es[t % r][t / r] = (t % r == t / r ? 1.5 : 0.0) - 0.5 * E[t];
+  __syncthreads();
+  for (int64_t i = blockIdx.x * (int64_t)256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
+    double v[MX];
+#pragma unroll
+    for (int a = 0; a < MX; ++a) v[a] = a < r ? V[a * es + i * vs] : 0.0;
+    for (int a = 0; a < r; ++a) {
+      double s = 0.0;
+#pragma unroll
+      for (int b = 0; b < MX; ++b)
+        if (b < r) s += Es[a][b] * v[b];
+      V[a * es + i * vs] = s;
+    }
   }
 }
 
@@ -169,10 +381,31 @@ hipError_t svd_init(double* J, int sp, int* counter, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t svd_sweep(double* W, int64_t L, double* J, int sp, double tol, int* counter, hipStream_t s) {
+static int svd_chunks(int64_t L, int64_t* chunk) {
+  const int64_t nch = std::min<int64_t>(64, (L + kChunkRows - 1) / kChunkRows);
+  *chunk = ((L + nch - 1) / nch + 63) / 64 * 64;
+  return (int)((L + *chunk - 1) / *chunk);
+}
+
+static int svd_blocks(int sp) { return std::max(2, ((sp + kBC - 1) / kBC + 1) / 2 * 2); }
+
+int64_t svd_ws_doubles(int64_t L, int sp) {
+  int64_t chunk = 0;
+  const int nch = svd_chunks(L, &chunk);
+  return nch > 1 ? (int64_t)svd_blocks(sp) / 2 * nch * kPC * kPC : 0;
+}
+
+hipError_t svd_sweep(double* W, int64_t L, double* J, int sp, double tol, double tau, double* ws, int* counter,
+                     hipStream_t s) {
+  int64_t chunk = 0;
+  const int nch = svd_chunks(L, &chunk), nb = svd_blocks(sp);
+  const int sweeps = nb == 2 ? 8 : 1;   // a single pair of blocks: to convergence on its Gram matrix
+  const dim3 g((unsigned)(nb / 2 * nch)), b(kJT);
   hipLaunchKernelGGL(k_zero_int, dim3(1), dim3(1), 0, s, counter);
-  for (int k = 0; k < sp - 1; ++k)
-    hipLaunchKernelGGL(k_jacobi_round, dim3((unsigned)(sp / 2)), dim3(kBS), 0, s, W, L, J, sp, k, tol, counter);
+  for (int k = 0; k < nb - 1; ++k) {
+    if (nch > 1) hipLaunchKernelGGL(k_jacobi_gram, g, b, 0, s, W, L, sp, nb, k, chunk, nch, ws);
+    hipLaunchKernelGGL(k_jacobi_blocks, g, b, 0, s, W, L, J, sp, nb, k, tol, tau, sweeps, chunk, nch, ws, counter);
+  }
   return hipGetLastError();
 }
 
@@ -187,9 +420,13 @@ hipError_t svd_gather(const double* src, int64_t ld, int64_t rows, const int* id
   return hipGetLastError();
 }
 
-hipError_t svd_last_core(const double* src, int64_t ld, const int* idx, const double* sig, int r, int nd, double* G,
-                         hipStream_t s) {
-  hipLaunchKernelGGL(k_svd_last_core, dim3(grid_of((int64_t)r * nd)), dim3(256), 0, s, src, ld, idx, sig, r, nd, G);
+hipError_t svd_last_core(const double* src, int64_t ld, const int* idx, int r, int nd, double* G, hipStream_t s) {
+  hipLaunchKernelGGL(k_svd_last_core, dim3(grid_of((int64_t)r * nd)), dim3(256), 0, s, src, ld, idx, r, nd, G);
+  return hipGetLastError();
+}
+
+hipError_t svd_polish(const double* E, int r, int64_t n, int64_t es, int64_t vs, double* V, hipStream_t s) {
+  hipLaunchKernelGGL(k_svd_polish, dim3(grid_of(n)), dim3(256), 0, s, E, r, n, es, vs, V);
   return hipGetLastError();
 }
 
