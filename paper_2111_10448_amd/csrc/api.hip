@@ -47,6 +47,7 @@ struct pstt2_ctx {
   std::vector<double*> basis;  // Q_k (k < m) or P_k (k >= m)
   Arena arena;                 // recovery workspace: sketches, bases, temporaries
   Arena varena;                // workspace of pstt2_vjp (rewound at every call)
+  Arena farena;                // workspace of the calls on a tensor function (see FnScope)
   double* Bk = nullptr;        // two-sided sketches, split k at Bk + k ell^2 (ell x ell)
   int64_t* chain_dev = nullptr;  // per split: factor offsets of its left / right DRM chains, then n
   double* H = nullptr;         // two-sided middle sketch, (ell n_m) x ell (TWOSIDED only)
@@ -681,6 +682,7 @@ void pstt2_destroy(pstt2_ctx* c) {
   free_recovery(c);
   arena_release(&c->arena, c->stream);
   arena_release(&c->varena, c->stream);
+  arena_release(&c->farena, c->stream);
   (void)hipStreamSynchronize(c->stream);
   dev_free(c->fac);
   dev_free(c->Y);
@@ -720,6 +722,17 @@ pstt2_status pstt2_sketch(pstt2_ctx* c, const void* x_dev, int64_t first, int64_
   return PSTT2_OK;
 }
 
+// Workspace of the calls on a tensor function (tables, evaluated columns): the
+// context keeps it between calls, up to PSTT2_GAUSS_CHUNK_BYTES and the tables,
+// and gives it back with itself.  A request of several GiB that the stream-ordered
+// pool cannot serve from one free block costs the host ~100 ms.  What is
+// allocated inside the scope is not freed by the call; where the kept block
+// cannot grow, the exact sizes are taken (and released by the next call).
+struct FnScope {
+  ArenaScope scope;
+  explicit FnScope(pstt2_ctx* c) : scope((((void)arena_begin(&c->farena, c->stream)), &c->farena)) {}
+};
+
 // fields of a tensor function (kind, and for GAUSS the bump parameters)
 static const char* fn_invalid(const pstt2_fn* fn) {
   if (fn->kind == PSTT2_FN_HILBERT) return nullptr;
@@ -735,25 +748,28 @@ static const char* fn_invalid(const pstt2_fn* fn) {
 static pstt2_status sketch_gauss(pstt2_ctx* c, const pstt2_fn* fn, int64_t first, int64_t count) {
   hipStream_t s = c->stream;
   double* tabs = nullptr;
-  hipError_t e = ws_alloc((void**)&tabs, sizeof(double) * gauss_table_doubles(c->n, c->d, c->m, fn->n_terms), s);
-  if (e != hipSuccess) return hfail(c, e, "Gaussian-bump tables");
-  GaussTabs g;
-  e = gauss_tables(c->n, c->d, c->m, fn->centers, fn->n_terms, fn->gamma, tabs, &g, s);
-  const int esz = c->dtype == PSTT2_F64 ? 8 : 4;
-  const int64_t ncmax = e == hipSuccess ? gauss_chunk_cols(g, esz) : 1;   // g is set only on success
   void* W = nullptr;
-  if (e == hipSuccess) e = ws_alloc(&W, (size_t)esz * c->R * std::min(ncmax, count / c->R), s);
-  pstt2_status st = PSTT2_OK;
-  if (e != hipSuccess) st = hfail(c, e, "Gaussian-bump workspace");
-  for (int64_t c0 = first / c->R; st == PSTT2_OK && c0 < (first + count) / c->R; c0 += ncmax) {
+  GaussTabs g;
+  int64_t ncmax = 1;
+  hipError_t e;
+  {
+    FnScope scope(c);
+    e = ws_alloc((void**)&tabs, sizeof(double) * gauss_table_doubles(c->n, c->d, c->m, fn->n_terms), s);
+    if (e != hipSuccess) return hfail(c, e, "Gaussian-bump tables");
+    e = gauss_tables(c->n, c->d, c->m, fn->centers, fn->n_terms, fn->gamma, tabs, &g, s);
+    const int esz = c->dtype == PSTT2_F64 ? 8 : 4;
+    if (e == hipSuccess) ncmax = gauss_chunk_cols(g, esz);
+    if (e == hipSuccess) e = ws_alloc(&W, (size_t)esz * c->R * std::min(ncmax, count / c->R), s);
+    if (e != hipSuccess) return hfail(c, e, "Gaussian-bump workspace");
+  }
+  for (int64_t c0 = first / c->R; c0 < (first + count) / c->R; c0 += ncmax) {
     const int64_t nc = std::min(ncmax, (first + count) / c->R - c0);
     e = gauss_columns(g, c0, nc, c->dtype, W, s);
-    if (e != hipSuccess) st = hfail(c, e, "Gaussian-bump columns");
-    else st = run_slabs(c, {Piece{W, c0 * c->R, nc * c->R}});
+    if (e != hipSuccess) return hfail(c, e, "Gaussian-bump columns");
+    const pstt2_status st = run_slabs(c, {Piece{W, c0 * c->R, nc * c->R}});
+    if (st != PSTT2_OK) return st;
   }
-  if (W) ws_free(W, s);
-  ws_free(tabs, s);
-  return st;
+  return PSTT2_OK;
 }
 
 pstt2_status pstt2_sketch_fn(pstt2_ctx* c, const pstt2_fn* fn, int64_t first, int64_t count) {
@@ -1210,21 +1226,24 @@ pstt2_status pstt2_middle_pass_fn(pstt2_ctx* c, tt_cores* cores, const pstt2_fn*
   GaussTabs g;
   double* tabs = nullptr;
   int32_t *row_t = nullptr, *col_t = nullptr;
+  void* W = nullptr;
   hipError_t e = hipSuccess;
   int64_t ncmax = 1;   // set from the tables once they exist
-  if (fn->kind == PSTT2_FN_GAUSS) {
-    e = ws_alloc((void**)&tabs, sizeof(double) * gauss_table_doubles(c->n, c->d, c->m, fn->n_terms), s);
-    if (e == hipSuccess) e = gauss_tables(c->n, c->d, c->m, fn->centers, fn->n_terms, fn->gamma, tabs, &g, s);
-    if (e == hipSuccess) ncmax = gauss_chunk_cols(g, esz);
-  } else {
-    e = ws_alloc((void**)&tabs, sizeof(double) * hilbert_rec_len(c->n, c->d), s);
-    if (e == hipSuccess) e = ws_alloc((void**)&row_t, sizeof(int32_t) * c->R, s);
-    if (e == hipSuccess) e = ws_alloc((void**)&col_t, sizeof(int32_t) * c->C, s);
-    if (e == hipSuccess) e = hilbert_tables(c->n, c->d, c->m, c->R, c->C, tabs, row_t, col_t, s);
-    ncmax = std::min(c->C, std::max<int64_t>(1, PSTT2_GAUSS_CHUNK_BYTES / (c->R * esz)));
+  {
+    FnScope scope(c);
+    if (fn->kind == PSTT2_FN_GAUSS) {
+      e = ws_alloc((void**)&tabs, sizeof(double) * gauss_table_doubles(c->n, c->d, c->m, fn->n_terms), s);
+      if (e == hipSuccess) e = gauss_tables(c->n, c->d, c->m, fn->centers, fn->n_terms, fn->gamma, tabs, &g, s);
+      if (e == hipSuccess) ncmax = gauss_chunk_cols(g, esz);
+    } else {
+      e = ws_alloc((void**)&tabs, sizeof(double) * hilbert_rec_len(c->n, c->d), s);
+      if (e == hipSuccess) e = ws_alloc((void**)&row_t, sizeof(int32_t) * c->R, s);
+      if (e == hipSuccess) e = ws_alloc((void**)&col_t, sizeof(int32_t) * c->C, s);
+      if (e == hipSuccess) e = hilbert_tables(c->n, c->d, c->m, c->R, c->C, tabs, row_t, col_t, s);
+      ncmax = std::min(c->C, std::max<int64_t>(1, PSTT2_GAUSS_CHUNK_BYTES / (c->R * esz)));
+    }
+    if (e == hipSuccess) e = ws_alloc(&W, (size_t)esz * c->R * std::min(ncmax, count / c->R), s);
   }
-  void* W = nullptr;
-  if (e == hipSuccess) e = ws_alloc(&W, (size_t)esz * c->R * std::min(ncmax, count / c->R), s);
   pstt2_status st = e == hipSuccess ? PSTT2_OK : hfail(c, e, "tensor-function workspace");
   bool added = false;   // a chunk already added into the middle core
   for (int64_t c0 = first / c->R; st == PSTT2_OK && c0 < (first + count) / c->R; c0 += ncmax) {
@@ -1235,10 +1254,6 @@ pstt2_status pstt2_middle_pass_fn(pstt2_ctx* c, tt_cores* cores, const pstt2_fn*
     if (st == PSTT2_OK) added = true;
   }
   if (st != PSTT2_OK && added) c->poisoned = true;
-  if (W) ws_free(W, s);
-  if (col_t) ws_free(col_t, s);
-  if (row_t) ws_free(row_t, s);
-  if (tabs) ws_free(tabs, s);
   return st;
 }
 

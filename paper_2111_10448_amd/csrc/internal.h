@@ -126,8 +126,8 @@ inline int64_t hilbert_rec_len(const int64_t* n, int d) {
 // split X_m: X(row, col) = sum_j e1(i_1, j) ahi(row / n_1, j) bc(col, j), the
 // per-mode factors multiplied out over modes 1, 2..m and m+1..d.  Tables are
 // j-major: e1[j * n1 + i_1], ahi[j * rhi + row / n_1], bc[j * bstride + col]
-// with bstride = C + kGaussCols and zero padding after column C - 1.
-constexpr int kGaussCols = 32;   // columns of X_m per thread in gauss_columns
+// with bstride = C + kGaussPad and zero padding after column C - 1.
+constexpr int kGaussPad = 32;
 struct GaussTabs {
   const double* e1;
   const double* ahi;
@@ -142,10 +142,15 @@ int64_t gauss_table_doubles(const int64_t* n, int d, int m, int nterms);
 hipError_t gauss_tables(const int64_t* n, int d, int m, const double* centers_host, int nterms, double gamma,
                         double* buf, GaussTabs* out, hipStream_t s);
 // Columns of X_m per workspace chunk: at most PSTT2_GAUSS_CHUNK_BYTES (one column
-// if larger; a multiple of kGaussCols when above it), at most 65535 column blocks, at most C.
+// if larger; whole 64-column tiles above that), at most C.
 int64_t gauss_chunk_cols(const GaussTabs& g, int elem_bytes);
 // Evaluate columns [c0, c0 + nc) of X_m into W (R x nc column-major, dtype F64 or F32).
 hipError_t gauss_columns(const GaussTabs& g, int64_t c0, int64_t nc, int dtype, void* W, hipStream_t s);
+// Workgroup partials (sum (x - x~)^2, sum x^2) over every entry, x~ = L Rt with L
+// R x r and Rp = Rt padded to RK rows (a multiple of 4) with zeros: gauss_error_parts pairs.
+int64_t gauss_error_parts(const GaussTabs& g);
+hipError_t gauss_error(const GaussTabs& g, const double* L, const double* Rp, int r, int RK, double* part,
+                       hipStream_t s);
 
 // Launch the streaming dual-sketch kernel for the configured precision.
 hipError_t launch_sketch(int prec, int lp, const SketchArgs& a, hipStream_t s);

@@ -18,7 +18,8 @@
 // the factors of modes 2..m and b that of modes m+1..d.  The three tables are
 // small (N (n_1 + R_m / n_1 + C_m) doubles); gauss_columns evaluates chunks of
 // whole columns of X_m from them into a workspace that the memory kernels
-// stream, at 2N FP64 flops per entry.
+// stream, at 2N FP64 flops per entry, and gauss_error compares every entry with
+// a train's without storing any.
 #include <hip/hip_runtime.h>
 
 #include "internal.h"
@@ -75,50 +76,180 @@ __global__ void k_fill(double* __restrict__ p, int64_t n, double v) {
   for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < n; t += (int64_t)gridDim.x * blockDim.x) p[t] = v;
 }
 
-constexpr int kGaussBlock = 256;   // threads per workgroup of k_gauss_cols
+typedef double d4 __attribute__((ext_vector_type(4)));
+constexpr int kGaussRows = 256;   // rows of X_m per workgroup of k_gauss_tiles
+constexpr int kGaussTile = 64;    // columns per step
 
-// W(row, c) = sum_j a(row, j) b(c0 + c, j) for the columns [c0, c0 + nc) of X_m
-// (W is R_m x nc, column-major).  A thread owns two rows (kGaussBlock apart)
-// and kGaussCols columns: a row's a(row, j) is two lane-contiguous loads, the
-// columns' b(col, j) are the same for the whole wave (uniform loads, each
-// feeding both rows), and each j costs 2 kGaussCols FMAs.  The bumps are added
-// in increasing j.
-template <typename T>
-__global__ __launch_bounds__(kGaussBlock) void k_gauss_cols(const GaussTabs g, int64_t c0, int64_t nc, T* __restrict__ W) {
-  constexpr int CB = kGaussCols;
-  const int64_t r0 = blockIdx.x * (int64_t)(2 * kGaussBlock) + threadIdx.x;
-  const int64_t cb = c0 + (int64_t)blockIdx.y * CB;
-  const int ncb = (int)std::min<int64_t>(CB, c0 + nc - cb);
-  if (r0 >= g.R) return;
-  // the second row is clamped into the matrix and dropped at the store
-  const bool two = r0 + kGaussBlock < g.R;
-  const int64_t r1 = two ? r0 + kGaussBlock : r0;
-  const double* __restrict__ e1a = g.e1 + r0 % g.n1;
-  const double* __restrict__ aha = g.ahi + r0 / g.n1;
-  const double* __restrict__ e1b = g.e1 + r1 % g.n1;
-  const double* __restrict__ ahb = g.ahi + r1 / g.n1;
-  const double* __restrict__ bc = g.bc + cb;   // columns past C read the table's zero padding
-  double acc0[CB], acc1[CB];
+// Tiles of X_m = sum_j a(:, j) b(:, j)^T on FP64 matrix cores: a product with the
+// bumps as its inner dimension.  A workgroup owns 256 rows and a share of the
+// 64-column tiles; a wave holds 64 x 64 entries in 16 accumulator tiles, so a
+// step of four bumps costs 16 matrix instructions (1024 cycles) for twelve
+// loads of cached table entries, requested one step ahead.  The columns are the
+// M index and the rows the N index: element v of a tile is (row l16, column
+// 4 v + g4), so a store instruction covers 16 consecutive rows.
+// ERR: nothing is stored.  The sum of x^2 is taken from the tile, then -L Rt is
+// added on the matrix cores (RK more inner steps) and the sum of squares taken
+// again: sum (x - x~)^2 by entrywise differences.
+// Bound by the FP64 matrix cores (2 nterms flops per entry).  At n = 960^3 with
+// 100 bumps the vector version (39 TFLOP/s) took 4.5 ms into workspace chunks of
+// 4 GiB, and the error pass then 1.4 ms to read them back; the chunks now take
+// 3.9 ms and the error pass, at rank 12, 3.7 ms in all (53 TFLOP/s).
+struct GaussErr {
+  const double* L;    // R x r
+  const double* Rp;   // RK x C, zero past r
+  int r, RK;
+  double* part;       // (sum (x - x~)^2, sum x^2) per workgroup
+};
+
+template <bool ERR, typename T>
+__global__ __launch_bounds__(256, 2) void k_gauss_tiles(const GaussTabs g, int64_t c0, int64_t nc, T* __restrict__ W,
+                                                        const GaussErr er, int gi_count, int gj_count) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, l16 = lane & 15, g4 = lane >> 4;
+  const int64_t gi = blockIdx.x % gi_count, gj = blockIdx.x / gi_count;
+  const int64_t row0 = gi * kGaussRows + 64 * w;
+  const int64_t ntile = (nc + kGaussTile - 1) / kGaussTile;
+  const int nt = g.nterms;
+  // rows past the matrix read its last row, columns past it its last column; both are dropped at the end
+  const double *pe[4], *ph[4];
+  int64_t row[4];
 #pragma unroll
-  for (int c = 0; c < CB; ++c) acc0[c] = acc1[c] = 0.0;
-  for (int j = 0; j < g.nterms; ++j) {
-    const double a0 = e1a[(int64_t)j * g.n1] * aha[(int64_t)j * g.rhi];
-    const double a1 = e1b[(int64_t)j * g.n1] * ahb[(int64_t)j * g.rhi];
-    const double* __restrict__ b = bc + (int64_t)j * g.bstride;
+  for (int t = 0; t < 4; ++t) {
+    row[t] = row0 + 16 * t + l16;
+    const int64_t rr = row[t] < g.R ? row[t] : g.R - 1;
+    pe[t] = g.e1 + rr % g.n1;
+    ph[t] = g.ahi + rr / g.n1;
+  }
+  double e2 = 0.0, x2 = 0.0;
+  for (int64_t tile = gj * ntile / gj_count; tile < (gj + 1) * ntile / gj_count; ++tile) {
+    const int64_t cc = c0 + tile * kGaussTile;
+    const double* pb[4];
 #pragma unroll
-    for (int c = 0; c < CB; ++c) {
-      acc0[c] += a0 * b[c];
-      acc1[c] += a1 * b[c];
+    for (int t = 0; t < 4; ++t) {
+      const int64_t c = cc + 16 * t + l16;
+      pb[t] = g.bc + (c < g.C ? c : g.C - 1);
+    }
+    d4 acc[4][4];   // [column tile][row tile]
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+#pragma unroll
+      for (int b = 0; b < 4; ++b) acc[a][b] = d4{0.0, 0.0, 0.0, 0.0};
+    // table offsets of this lane's bump; a lane whose next bump would be past the
+    // last one stays (its operand is zeroed)
+    int64_t oe = 0, oh = 0, ob = 0;
+    {
+      const int64_t j = g4 < nt ? g4 : nt - 1;
+      oe = j * g.n1;
+      oh = j * g.rhi;
+      ob = j * g.bstride;
+    }
+    double ve[4], vh[4], vb[4];
+    auto load = [&]() {
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        ve[t] = pe[t][oe];
+        vh[t] = ph[t][oh];
+        vb[t] = pb[t][ob];
+      }
+    };
+    load();
+    for (int j0 = 0; j0 < nt; j0 += 4) {
+      double a[4], b[4];
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        a[t] = ve[t] * vh[t];
+        b[t] = j0 + g4 < nt ? vb[t] : 0.0;
+      }
+      const bool more = j0 + 4 + g4 < nt;
+      oe += more ? 4 * g.n1 : 0;
+      oh += more ? 4 * g.rhi : 0;
+      ob += more ? 4 * g.bstride : 0;
+      load();
+#pragma unroll
+      for (int ct = 0; ct < 4; ++ct)
+#pragma unroll
+        for (int rt = 0; rt < 4; ++rt) acc[ct][rt] = __builtin_amdgcn_mfma_f64_16x16x4f64(b[ct], a[rt], acc[ct][rt], 0, 0, 0);
+    }
+    if constexpr (ERR) {
+      const bool whole = row0 + 64 <= g.R && cc + kGaussTile <= c0 + nc;   // uniform
+      auto squares = [&]() {
+        double s = 0.0;
+        if (whole) {
+#pragma unroll
+          for (int ct = 0; ct < 4; ++ct)
+#pragma unroll
+            for (int rt = 0; rt < 4; ++rt)
+#pragma unroll
+              for (int v = 0; v < 4; ++v) s += acc[ct][rt][v] * acc[ct][rt][v];
+          return s;
+        }
+#pragma unroll
+        for (int ct = 0; ct < 4; ++ct)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            const bool cok = cc + 16 * ct + 4 * v + g4 < c0 + nc;
+#pragma unroll
+            for (int rt = 0; rt < 4; ++rt) {
+              const double x = cok && row[rt] < g.R ? acc[ct][rt][v] : 0.0;
+              s += x * x;
+            }
+          }
+        return s;
+      };
+      x2 += squares();
+      for (int b0 = 0; b0 < er.RK; b0 += 4) {
+        const int b = b0 + g4;
+        double lv[4], rv[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+          const int64_t rr = row[t] < g.R ? row[t] : g.R - 1;
+          lv[t] = b < er.r ? er.L[(int64_t)b * g.R + rr] : 0.0;
+          rv[t] = -er.Rp[(pb[t] - g.bc) * er.RK + b];
+        }
+#pragma unroll
+        for (int ct = 0; ct < 4; ++ct)
+#pragma unroll
+          for (int rt = 0; rt < 4; ++rt)
+            acc[ct][rt] = __builtin_amdgcn_mfma_f64_16x16x4f64(rv[ct], lv[rt], acc[ct][rt], 0, 0, 0);
+      }
+      e2 += squares();
+    } else {
+#pragma unroll
+      for (int ct = 0; ct < 4; ++ct)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int64_t c = cc + 16 * ct + 4 * v + g4;
+          if (c < c0 + nc) {
+#pragma unroll
+            for (int rt = 0; rt < 4; ++rt)
+              if (row[rt] < g.R) W[(c - c0) * g.R + row[rt]] = (T)acc[ct][rt][v];
+          }
+        }
     }
   }
-  T* w0 = W + (cb - c0) * g.R + r0;
-  T* w1 = W + (cb - c0) * g.R + r1;
-#pragma unroll
-  for (int c = 0; c < CB; ++c)
-    if (c < ncb) {
-      w0[(int64_t)c * g.R] = (T)acc0[c];
-      if (two) w1[(int64_t)c * g.R] = (T)acc1[c];
+  if constexpr (ERR) {
+    __shared__ double red[2][4];
+    for (int o = 32; o > 0; o >>= 1) {
+      e2 += __shfl_xor(e2, o);
+      x2 += __shfl_xor(x2, o);
     }
+    if (lane == 0) {
+      red[0][w] = e2;
+      red[1][w] = x2;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      er.part[2 * (int64_t)blockIdx.x] = red[0][0] + red[0][1] + red[0][2] + red[0][3];
+      er.part[2 * (int64_t)blockIdx.x + 1] = red[1][0] + red[1][1] + red[1][2] + red[1][3];
+    }
+  }
+}
+
+// Row blocks and column shares: about 10000 workgroups, so that the last of the
+// (two per compute unit) rounds they run in is a small part of the whole.
+void gauss_grid(const GaussTabs& g, int64_t nc, int* gi, int* gj) {
+  *gi = (int)((g.R + kGaussRows - 1) / kGaussRows);
+  const int64_t ntile = (nc + kGaussTile - 1) / kGaussTile;
+  *gj = (int)std::max<int64_t>(1, std::min<int64_t>(ntile, (10240 + *gi - 1) / *gi));
 }
 
 // W(row, c) = rec[row_t[row] + col_t[c0 + c]] for the columns [c0, c0 + nc) of X_m
@@ -141,7 +272,7 @@ int64_t gauss_table_doubles(const int64_t* n, int d, int m, int nterms) {
   int64_t R = 1, C = 1;
   for (int q = 0; q < m; ++q) R *= n[q];
   for (int q = m; q < d; ++q) C *= n[q];
-  return (int64_t)nterms * (d + n[0] + R / n[0] + C + kGaussCols);
+  return (int64_t)nterms * (d + n[0] + R / n[0] + C + kGaussPad);
 }
 
 hipError_t gauss_tables(const int64_t* n, int d, int m, const double* centers_host, int nterms, double gamma,
@@ -158,7 +289,7 @@ hipError_t gauss_tables(const int64_t* n, int d, int m, const double* centers_ho
   g.rhi = R / n[0];
   g.R = R;
   g.C = C;
-  g.bstride = C + kGaussCols;
+  g.bstride = C + kGaussPad;
   double* ctr = buf;
   double* e1 = ctr + (int64_t)nterms * d;
   double* ahi = e1 + (int64_t)nterms * g.n1;
@@ -185,20 +316,38 @@ hipError_t gauss_tables(const int64_t* n, int d, int m, const double* centers_ho
 
 int64_t gauss_chunk_cols(const GaussTabs& g, int elem_bytes) {
   int64_t by_bytes = std::max<int64_t>(1, PSTT2_GAUSS_CHUNK_BYTES / (g.R * elem_bytes));
-  if (by_bytes > kGaussCols) by_bytes -= by_bytes % kGaussCols;   // whole column blocks
-  const int64_t by_grid = (int64_t)65535 * kGaussCols;
-  return std::min(std::min(by_bytes, by_grid), g.C);
+  if (by_bytes > kGaussTile) by_bytes -= by_bytes % kGaussTile;   // whole column tiles
+  return std::min(by_bytes, g.C);
 }
 
 hipError_t gauss_columns(const GaussTabs& g, int64_t c0, int64_t nc, int dtype, void* W, hipStream_t s) {
   if (nc <= 0) return hipSuccess;
   if (fault_take()) return hipErrorLaunchFailure;
-  const dim3 grid((unsigned)((g.R + 2 * kGaussBlock - 1) / (2 * kGaussBlock)),
-                  (unsigned)((nc + kGaussCols - 1) / kGaussCols));
+  int gi = 1, gj = 1;
+  gauss_grid(g, nc, &gi, &gj);
+  const dim3 grid((unsigned)((int64_t)gi * gj)), b(256);
+  const GaussErr none = {};
   if (dtype == PSTT2_F64)
-    hipLaunchKernelGGL(k_gauss_cols<double>, grid, dim3(kGaussBlock), 0, s, g, c0, nc, (double*)W);
+    hipLaunchKernelGGL((k_gauss_tiles<false, double>), grid, b, 0, s, g, c0, nc, (double*)W, none, gi, gj);
   else
-    hipLaunchKernelGGL(k_gauss_cols<float>, grid, dim3(kGaussBlock), 0, s, g, c0, nc, (float*)W);
+    hipLaunchKernelGGL((k_gauss_tiles<false, float>), grid, b, 0, s, g, c0, nc, (float*)W, none, gi, gj);
+  return hipGetLastError();
+}
+
+int64_t gauss_error_parts(const GaussTabs& g) {
+  int gi = 1, gj = 1;
+  gauss_grid(g, g.C, &gi, &gj);
+  return (int64_t)gi * gj;
+}
+
+hipError_t gauss_error(const GaussTabs& g, const double* L, const double* Rp, int r, int RK, double* part,
+                       hipStream_t s) {
+  if (fault_take()) return hipErrorLaunchFailure;
+  int gi = 1, gj = 1;
+  gauss_grid(g, g.C, &gi, &gj);
+  const GaussErr er{L, Rp, r, RK, part};
+  hipLaunchKernelGGL((k_gauss_tiles<true, double>), dim3((unsigned)((int64_t)gi * gj)), dim3(256), 0, s, g, (int64_t)0,
+                     g.C, (double*)nullptr, er, gi, gj);
   return hipGetLastError();
 }
 

@@ -455,61 +455,33 @@ hipError_t tt_error_noalloc_run(const tt_cores* c, const void* x, int dtype, dou
   return err_launch(c, p, x, dtype, FnTabs{nullptr, nullptr, nullptr}, iface, part, Rp, err_dev, true, s);
 }
 
-// The Gaussian-bump tensor: chunks of whole columns of X_m are evaluated into a
-// workspace (gauss_columns) and run through the memory kernel against the
-// matching columns of Rt; every chunk's workgroup partials are kept and summed
-// in one fixed-order pass at the end.
+// The Gaussian-bump tensor: its tiles are evaluated on the matrix cores and
+// compared with the train's in place (gauss_error), the workgroup partials
+// summed in one fixed-order pass.
 hipError_t tt_error_run_gauss(const tt_cores* c, const double* centers_host, int nterms, double gamma,
                               double* e2x2, hipStream_t s) {
-  const int d = c->d;
-  const int split = (d + 1) / 2;
-  int64_t R = 1, C = 1;
-  for (int k = 0; k < split; ++k) R *= c->n[k];
-  for (int k = split; k < d; ++k) C *= c->n[k];
-  double* tabs = nullptr;
-  hipError_t e = ws_alloc((void**)&tabs, sizeof(double) * gauss_table_doubles(c->n, d, split, nterms), s);
-  if (e != hipSuccess) return e;
-  GaussTabs g;
-  e = gauss_tables(c->n, d, split, centers_host, nterms, gamma, tabs, &g, s);
-  const int r = c->r[split];
-  const int RK = rk_slot(r);
-  double *L = nullptr, *ifb = nullptr;
-  if (e == hipSuccess) e = ws_alloc((void**)&ifb, sizeof(double) * tt_interfaces_doubles(c, split), s);
-  if (e != hipSuccess) {
-    ws_free(tabs, s);
-    return e;
-  }
-  const int64_t ncmax = gauss_chunk_cols(g, sizeof(double));
-  const int64_t nchunk = (C + ncmax - 1) / ncmax;
-  const int gi = (int)((R + 511) / 512);
-  const int gjmax = (int)std::max<int64_t>(1, std::min<int64_t>(ncmax, (4096 + gi - 1) / gi));
-  double *part = nullptr, *Rp = nullptr, *W = nullptr;
-  e = ws_alloc((void**)&part, sizeof(double) * 2 * ((int64_t)gi * gjmax * nchunk + 1), s);
-  if (e == hipSuccess) e = ws_alloc((void**)&Rp, sizeof(double) * RK * C, s);
-  if (e == hipSuccess) e = ws_alloc((void**)&W, sizeof(double) * R * ncmax, s);
+  const ErrPlan p = err_plan(c);
+  double *tabs = nullptr, *iface = nullptr, *part = nullptr, *Rp = nullptr, *L = nullptr;
+  GaussTabs g = {};
+  int64_t np = 0;
+  hipError_t e = ws_alloc((void**)&tabs, sizeof(double) * gauss_table_doubles(c->n, c->d, p.split, nterms), s);
+  if (e == hipSuccess) e = gauss_tables(c->n, c->d, p.split, centers_host, nterms, gamma, tabs, &g, s);
   if (e == hipSuccess) {
-    e = tt_interfaces_in(c, split, ifb, RK, Rp, &L, s);
-    const bool pair = (R % 2) == 0;
-    const FnTabs none{nullptr, nullptr, nullptr};
-    int64_t np = 0;   // partial pairs written so far
-    for (int64_t c0 = 0; c0 < C && e == hipSuccess; c0 += ncmax) {
-      const int64_t nc = std::min(ncmax, C - c0);
-      const int gj = (int)std::max<int64_t>(1, std::min<int64_t>(nc, (4096 + gi - 1) / gi));
-      e = gauss_columns(g, c0, nc, PSTT2_F64, W, s);
-      if (e != hipSuccess) break;
-      e = pair ? launch_err_p<double, true, false>(W, R, nc, r, L, Rp + RK * c0, gi, gj, part + 2 * np, none, s)
-               : launch_err_p<double, false, false>(W, R, nc, r, L, Rp + RK * c0, gi, gj, part + 2 * np, none, s);
-      np += (int64_t)gi * gj;
-    }
-    if (e == hipSuccess) {
-      hipLaunchKernelGGL(k_sum_parts, dim3(1), dim3(256), 0, s, part, (int)np, part + 2 * np, false);
-      e = hipMemcpyAsync(e2x2, part + 2 * np, 2 * sizeof(double), hipMemcpyDeviceToHost, s);
-    }
+    np = gauss_error_parts(g);
+    e = ws_alloc((void**)&iface, sizeof(double) * std::max<int64_t>(p.n_iface, 1), s);
   }
-  if (part) ws_free(part, s);
-  if (Rp) ws_free(Rp, s);
-  if (W) ws_free(W, s);
-  ws_free(ifb, s);
+  if (e == hipSuccess) e = ws_alloc((void**)&part, sizeof(double) * 2 * (np + 1), s);
+  if (e == hipSuccess) e = ws_alloc((void**)&Rp, sizeof(double) * p.n_rp, s);
+  if (e == hipSuccess) e = tt_interfaces_in(c, p.split, iface, p.RK, Rp, &L, s);
+  if (e == hipSuccess) e = gauss_error(g, L, Rp, p.r, p.RK, part, s);
+  if (e == hipSuccess) {
+    hipLaunchKernelGGL(k_sum_parts, dim3(1), dim3(256), 0, s, part, (int)np, part + 2 * np, false);
+    e = hipGetLastError();
+  }
+  if (e == hipSuccess) e = hipMemcpyAsync(e2x2, part + 2 * np, 2 * sizeof(double), hipMemcpyDeviceToHost, s);
+  ws_free(part, s);
+  ws_free(Rp, s);
+  ws_free(iface, s);
   ws_free(tabs, s);
   hipError_t e2 = hipStreamSynchronize(s);
   return e != hipSuccess ? e : e2;
