@@ -348,9 +348,11 @@ def run_function(name, steps, warmup, prec="f64", mid="onepass"):
            "ms_per_step": round((t1 - t0) * 1e3 / steps, 4), "sketch_fn_ms": round(t_sk * 1e3 / steps, 4),
            "sketch_kernel_ms": round(kms, 4), "error_pass_ms": round(t_err * 1e3 / steps, 4)}
     if w.kind == "gauss":
-        # evaluation at 2 x terms FP64 flops per entry, then the memory sketch of the chunks
-        ev = 2.0 * w.terms * w.numel
-        out["evaluation_fp64_tflops_in_sketch_fn"] = round(ev / (t_sk / steps) / 1e12, 2)
+        # FP32 contexts: evaluation at 2 x terms FP64 flops per entry, then the memory sketch
+        # of the chunks (FP64 contexts sketch the factors' moments and form no entries)
+        if prec != "f64":
+            ev = 2.0 * w.terms * w.numel
+            out["evaluation_fp64_tflops_in_sketch_fn"] = round(ev / (t_sk / steps) / 1e12, 2)
     else:
         out.update({"sketch_entries_per_s": round(w.numel / (kms * 1e-3), 1),
                     "sketch_fp64_tflops": round(flops / (kms * 1e-3) / 1e12, 2),

@@ -199,11 +199,14 @@ pstt2_status pstt2_sketch_slabs(pstt2_ctx* ctx, int32_t nslabs, const void* cons
  *            n_terms x d row-major (c_{j,q} at centers[j * d + q]), read during
  *            the call only; 1 <= n_terms <= PSTT2_GAUSS_MAX_TERMS, gamma > 0.
  *            Each bump is a product of one factor per mode, so the library
- *            tabulates those factors (FP64 exp) and evaluates chunks of whole
- *            columns of X_m into a workspace of at most PSTT2_GAUSS_CHUNK_BYTES
- *            (one column if that is larger), which the memory kernels then
- *            stream: the tensor is never stored whole.  The bumps are added in
- *            increasing j. */
+ *            tabulates those factors (FP64 exp).  FP64 sketches are formed from
+ *            the factors' moments: X_m Omega = sum_j a_j (b_j^T Omega) and its
+ *            mirror, with no entry evaluated.  FP32 contexts and the two-pass
+ *            middle core evaluate chunks of whole columns of X_m into a workspace
+ *            of at most PSTT2_GAUSS_CHUNK_BYTES (one column if that is larger),
+ *            which the memory kernels then stream; the error pass evaluates
+ *            tiles in registers.  The tensor is never stored whole.  Entries add
+ *            their bumps in increasing j. */
 typedef enum { PSTT2_FN_HILBERT = 0, PSTT2_FN_GAUSS = 1 } pstt2_fn_kind;
 #define PSTT2_GAUSS_MAX_TERMS 1024
 #define PSTT2_GAUSS_CHUNK_BYTES (1LL << 32)
@@ -223,9 +226,10 @@ typedef struct {
  * middle unfolding X_m); the same coverage rules as pstt2_sketch apply, and
  * slabs from memory and from fn may be mixed.  HILBERT builds small index
  * tables (R_m + C_m int32 and sum_q n_q doubles) on first use and keeps them
- * with the context; GAUSS builds its tables on every call.  async (GAUSS first
+ * with the context; GAUSS builds its tables on every call (their workspace, and
+ * that of the evaluated columns, stays with the context).  async (GAUSS first
  * waits for the stream's earlier work and its own table set-up, so the centers
- * may be freed on return, then queues the chunks).  Errors: EINVAL (kind, fields,
+ * may be freed on return, then queues the rest).  Errors: EINVAL (kind, fields,
  * dtype / prec, alignment, range), ESTATE (overlap, after recover), ENOMEM, EDEVICE. */
 pstt2_status pstt2_sketch_fn(pstt2_ctx* ctx, const pstt2_fn* fn, int64_t first, int64_t count);
 

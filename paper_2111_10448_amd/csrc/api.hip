@@ -317,6 +317,26 @@ pstt2_status run_slabs(pstt2_ctx* c, const std::vector<Piece>& ps) {
   return PSTT2_OK;
 }
 
+// Events around a streaming launch while pstt2_profile is on.
+hipError_t profile_begin(pstt2_ctx* c, std::pair<hipEvent_t, hipEvent_t>* ev) {
+  if (!c->profile) return hipSuccess;
+  if (c->ev_pool.empty()) {
+    hipError_t e = hipEventCreate(&ev->first);
+    if (e == hipSuccess) e = hipEventCreate(&ev->second);
+    if (e != hipSuccess) return e;
+  } else {
+    *ev = c->ev_pool.back();
+    c->ev_pool.pop_back();
+  }
+  return hipEventRecord(ev->first, c->stream);
+}
+
+hipError_t profile_end(pstt2_ctx* c, const std::pair<hipEvent_t, hipEvent_t>& ev) {
+  if (!c->profile) return hipSuccess;
+  c->ev_used.push_back(ev);
+  return hipEventRecord(ev.second, c->stream);
+}
+
 // One pass group over runs of whole columns: up to kMaxSeg runs per launch of
 // the streaming kernel, then the fixed-order reduction of its partials.
 pstt2_status launch_segs(pstt2_ctx* c, const SketchArgs& ga, const std::vector<Seg>& segs, double* Yd, double* Td) {
@@ -342,23 +362,11 @@ pstt2_status launch_segs(pstt2_ctx* c, const SketchArgs& ga, const std::vector<S
       }
       if (Yd == c->Y && c->y_unset && !a.ystore) HIPCK(c, y_settle(c));
       std::pair<hipEvent_t, hipEvent_t> ev{nullptr, nullptr};
-      if (c->profile) {
-        if (c->ev_pool.empty()) {
-          HIPCK(c, hipEventCreate(&ev.first));
-          HIPCK(c, hipEventCreate(&ev.second));
-        } else {
-          ev = c->ev_pool.back();
-          c->ev_pool.pop_back();
-        }
-        HIPCK(c, hipEventRecord(ev.first, c->stream));
-      }
+      HIPCK(c, profile_begin(c, &ev));
       HIPCK(c, launch_sketch(c->prec, c->lp, a, c->stream));
       if (a.ystore) c->y_unset = false;
       if (a.ydirect) ++c->accum;   // Y_R already holds this launch's data
-      if (c->profile) {
-        HIPCK(c, hipEventRecord(ev.second, c->stream));
-        c->ev_used.push_back(ev);
-      }
+      HIPCK(c, profile_end(c, ev));
       HIPCK(c, launch_reduce(c->prec, a, Yd, Td, c->flag, c->stream));
       if (!a.ydirect) ++c->accum;
     }
@@ -743,11 +751,14 @@ static const char* fn_invalid(const pstt2_fn* fn) {
   return nullptr;
 }
 
-// Gaussian bumps: chunks of whole columns of X_m evaluated into a workspace in
-// the context's dtype, each streamed by the memory path like a slab.
+// Gaussian bumps.  FP64 contexts: both sketches from the factors' moments, no
+// entry formed.  FP32 contexts, whose entries are rounded to FP32 first: chunks
+// of whole columns of X_m evaluated into a workspace, each streamed by the
+// memory path like a slab.
 static pstt2_status sketch_gauss(pstt2_ctx* c, const pstt2_fn* fn, int64_t first, int64_t count) {
   hipStream_t s = c->stream;
-  double* tabs = nullptr;
+  const bool f64 = c->dtype == PSTT2_F64;
+  double *tabs = nullptr, *mom = nullptr;
   void* W = nullptr;
   GaussTabs g;
   int64_t ncmax = 1;
@@ -757,10 +768,28 @@ static pstt2_status sketch_gauss(pstt2_ctx* c, const pstt2_fn* fn, int64_t first
     e = ws_alloc((void**)&tabs, sizeof(double) * gauss_table_doubles(c->n, c->d, c->m, fn->n_terms), s);
     if (e != hipSuccess) return hfail(c, e, "Gaussian-bump tables");
     e = gauss_tables(c->n, c->d, c->m, fn->centers, fn->n_terms, fn->gamma, tabs, &g, s);
-    const int esz = c->dtype == PSTT2_F64 ? 8 : 4;
-    if (e == hipSuccess) ncmax = gauss_chunk_cols(g, esz);
-    if (e == hipSuccess) e = ws_alloc(&W, (size_t)esz * c->R * std::min(ncmax, count / c->R), s);
+    if (e == hipSuccess && f64) e = ws_alloc((void**)&mom, sizeof(double) * 64 * fn->n_terms, s);
+    if (e == hipSuccess && !f64) {
+      ncmax = gauss_chunk_cols(g, 4);
+      e = ws_alloc(&W, (size_t)4 * c->R * std::min(ncmax, count / c->R), s);
+    }
     if (e != hipSuccess) return hfail(c, e, "Gaussian-bump workspace");
+  }
+  if (f64) {
+    for (int gr = 0; gr < pass_groups(c); ++gr) {
+      double *Yd = nullptr, *Td = nullptr;
+      const SketchArgs a = group_args(c, gr, &Yd, &Td);
+      const bool store = Yd == c->Y && c->y_unset;   // Y still stands for zero
+      HIPCK(c, gauss_moments(g, a, c->n, fn->gamma, first / c->R, count / c->R, mom, s));
+      std::pair<hipEvent_t, hipEvent_t> ev{nullptr, nullptr};
+      HIPCK(c, profile_begin(c, &ev));
+      HIPCK(c, gauss_sketch_y(g, mom, c->ell, store, Yd, c->flag, s));
+      if (store) c->y_unset = false;
+      ++c->accum;
+      HIPCK(c, gauss_sketch_t(g, mom, c->ell, first / c->R, count / c->R, Td, c->flag, s));
+      HIPCK(c, profile_end(c, ev));
+    }
+    return PSTT2_OK;
   }
   for (int64_t c0 = first / c->R; c0 < (first + count) / c->R; c0 += ncmax) {
     const int64_t nc = std::min(ncmax, (first + count) / c->R - c0);

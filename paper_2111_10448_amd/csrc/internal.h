@@ -129,6 +129,7 @@ inline int64_t hilbert_rec_len(const int64_t* n, int d) {
 // with bstride = C + kGaussPad and zero padding after column C - 1.
 constexpr int kGaussPad = 32;
 struct GaussTabs {
+  const double* centers;   // nterms x d
   const double* e1;
   const double* ahi;
   const double* bc;
@@ -146,6 +147,16 @@ hipError_t gauss_tables(const int64_t* n, int d, int m, const double* centers_ho
 int64_t gauss_chunk_cols(const GaussTabs& g, int elem_bytes);
 // Evaluate columns [c0, c0 + nc) of X_m into W (R x nc column-major, dtype F64 or F32).
 hipError_t gauss_columns(const GaussTabs& g, int64_t c0, int64_t nc, int dtype, void* W, hipStream_t s);
+// FP64 sketches of the columns [c0, c0 + nc) with the factors of a (fac, psi_off,
+// om_tab, m, ell) without forming entries: the moments (64 nterms doubles at
+// mom), then Y += (or = with store) and Tt += from them.  Non-finite sums raise
+// bit 0 of *flag.
+hipError_t gauss_moments(const GaussTabs& g, const SketchArgs& a, const int64_t* n, double gamma, int64_t c0,
+                         int64_t nc, double* mom, hipStream_t s);
+hipError_t gauss_sketch_y(const GaussTabs& g, const double* mom, int ell, bool store, double* Y, int* flag,
+                          hipStream_t s);
+hipError_t gauss_sketch_t(const GaussTabs& g, const double* mom, int ell, int64_t c0, int64_t nc, double* Tt, int* flag,
+                          hipStream_t s);
 // Workgroup partials (sum (x - x~)^2, sum x^2) over every entry, x~ = L Rt with L
 // R x r and Rp = Rt padded to RK rows (a multiple of 4) with zeros: gauss_error_parts pairs.
 int64_t gauss_error_parts(const GaussTabs& g);

@@ -18,8 +18,9 @@
 // the factors of modes 2..m and b that of modes m+1..d.  The three tables are
 // small (N (n_1 + R_m / n_1 + C_m) doubles); gauss_columns evaluates chunks of
 // whole columns of X_m from them into a workspace that the memory kernels
-// stream, at 2N FP64 flops per entry, and gauss_error compares every entry with
-// a train's without storing any.
+// stream, at 2N FP64 flops per entry; gauss_error compares every entry with a
+// train's without storing any; and FP64 contexts sketch the tensor from the
+// factors' moments (gauss_moments and the two kernels after it).
 #include <hip/hip_runtime.h>
 
 #include "internal.h"
@@ -252,6 +253,143 @@ void gauss_grid(const GaussTabs& g, int64_t nc, int* gi, int* gj) {
   *gj = (int)std::max<int64_t>(1, std::min<int64_t>(ntile, (10240 + *gi - 1) / *gi));
 }
 
+// ---- sketches of the Gaussian bumps without their entries ----
+// X_m = sum_j a_j b_j^T, so X_m Omega = sum_j a_j (b_j^T Omega) and Psi^T X_m =
+// sum_j (a_j^T Psi)^T b_j^T: the sketches need the bumps' moments, nterms x ell
+// numbers on either side.  Psi is a Khatri-Rao product and a_j a product of one
+// factor per mode, so a_j^T Psi is a product over modes of length-n_q dots.  All
+// in FP64; every term of the sums is the one that the entries would give, added
+// in another order.  At n = 960^3, 100 bumps, ell = 32 this is 0.012 TFLOP of
+// work in place of 0.29 (evaluation and sketch), bound by writing Y_R: the call
+// went from 7.1 to 0.30 ms (0.22 ms of it k_gauss_y).
+//
+// moments: workgroup j < nterms: mpsi[32 j + a] = a_j^T Psi(:, a); the others:
+// mom[32 j + c] = sum over the columns [c0, c0 + nc) of b_j(col) Omega(col, c).
+// 32 groups of 32 threads (one sketch column each), summed in group order.
+__global__ __launch_bounds__(1024) void k_gauss_moments(const GaussTabs g, const SketchArgs A, const Modes M, int d,
+                                                        double gamma, int64_t c0, int64_t nc,
+                                                        double* __restrict__ mpsi, double* __restrict__ mom) {
+  __shared__ double red[32][33];
+  const int c = threadIdx.x & 31, grp = threadIdx.x >> 5;
+  const int ell = A.ell;
+  const int j = blockIdx.x < (unsigned)g.nterms ? blockIdx.x : blockIdx.x - g.nterms;
+  const int cl = c < ell ? c : 0;
+  auto total = [&](double v) {
+    __syncthreads();
+    red[grp][c] = v;
+    __syncthreads();
+    double s = 0.0;
+#pragma unroll
+    for (int k = 0; k < 32; ++k) s += red[k][c];
+    return s;
+  };
+  if (blockIdx.x < (unsigned)g.nterms) {
+    double prod = 1.0;
+    for (int q = 1; q <= A.m; ++q) {
+      const int64_t nq = M.n[q - 1];
+      const double* f = A.fac + A.psi_off[q - 1] + cl;
+      // the tables hold mode 1's factor, and mode 2's where it is the last row mode
+      const double* tab = q == 1 ? g.e1 + (int64_t)j * g.n1 : (q == 2 && A.m == 2 ? g.ahi + (int64_t)j * g.rhi : nullptr);
+      const double ctr = g.centers[(int64_t)j * d + q - 1];
+      double s = 0.0;
+#pragma unroll 4
+      for (int64_t i = grp; i < nq; i += 32) {
+        double e;
+        if (tab) {
+          e = tab[i];
+        } else {
+          const double dl = 2.0 * (double)(i + 1) / (double)nq - 1.0 - ctr;
+          e = exp(-gamma * (dl * dl));
+        }
+        s += e * f[i * ell];
+      }
+      prod *= total(s);
+    }
+    if (grp == 0) mpsi[32 * j + c] = c < ell ? prod : 0.0;
+  } else {
+    const double* b = g.bc + (int64_t)j * g.bstride + c0;
+    const double* om = A.om_tab + c0 * A.L4 + cl;
+    double s = 0.0;
+#pragma unroll 4
+    for (int64_t i = grp; i < nc; i += 32) s += b[i] * om[i * A.L4];
+    s = total(s);
+    if (grp == 0) mom[32 * j + c] = c < ell ? s : 0.0;
+  }
+}
+
+// Y(row, c) = [Y(row, c)] + sum_j a(row, j) mom(j, c): 256 rows per workgroup, a wave
+// 64 rows x 16 CT sketch columns on the matrix cores, four bumps per step.
+template <int CT>
+__global__ __launch_bounds__(256) void k_gauss_y(const GaussTabs g, const double* __restrict__ mom, int ell, bool store,
+                                                 double* __restrict__ Y, int* flag) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, l16 = lane & 15, g4 = lane >> 4;
+  const int64_t row0 = blockIdx.x * (int64_t)256 + 64 * w;
+  const double *pe[4], *ph[4];
+  int64_t row[4];
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    row[t] = row0 + 16 * t + l16;
+    const int64_t rr = row[t] < g.R ? row[t] : g.R - 1;
+    pe[t] = g.e1 + rr % g.n1;
+    ph[t] = g.ahi + rr / g.n1;
+  }
+  d4 acc[CT][4];
+#pragma unroll
+  for (int a = 0; a < CT; ++a)
+#pragma unroll
+    for (int b = 0; b < 4; ++b) acc[a][b] = d4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll 2
+  for (int j0 = 0; j0 < g.nterms; j0 += 4) {
+    const int j = j0 + g4;
+    const bool in = j < g.nterms;
+    const int64_t jj = in ? j : g.nterms - 1;
+    double a[4], m[CT];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) a[t] = pe[t][jj * g.n1] * ph[t][jj * g.rhi];
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct) {
+      const double v = mom[32 * jj + 16 * ct + l16];
+      m[ct] = in ? v : 0.0;
+    }
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+      for (int t = 0; t < 4; ++t) acc[ct][t] = __builtin_amdgcn_mfma_f64_16x16x4f64(m[ct], a[t], acc[ct][t], 0, 0, 0);
+  }
+  bool bad = false;
+#pragma unroll
+  for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int c = 16 * ct + 4 * v + g4;
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+        if (c < ell && row[t] < g.R) {
+          double* y = Y + (int64_t)c * g.R + row[t];
+          const double s = (store ? 0.0 : *y) + acc[ct][t][v];
+          *y = s;
+          bad = bad || !isfinite(s);
+        }
+    }
+  if (bad) atomicOr(flag, 1);
+}
+
+// T(a, col) += sum_j b_j(col) mpsi(j, a) for the columns [c0, c0 + nc)
+__global__ __launch_bounds__(256) void k_gauss_t(const GaussTabs g, const double* __restrict__ mpsi, int64_t c0,
+                                                 int64_t nc, double* __restrict__ Tt, int* flag) {
+  const int a = blockIdx.y;
+  for (int64_t i = blockIdx.x * (int64_t)256 + threadIdx.x; i < nc; i += (int64_t)gridDim.x * 256) {
+    const double* b = g.bc + c0 + i;
+    double s = 0.0;
+#pragma unroll 8
+    for (int j = 0; j < g.nterms; ++j) s += b[(int64_t)j * g.bstride] * mpsi[32 * j + a];
+    double* t = Tt + (int64_t)a * g.C + c0 + i;
+    s += *t;
+    *t = s;
+    if (!isfinite(s)) atomicOr(flag, 1);
+  }
+}
+
 // W(row, c) = rec[row_t[row] + col_t[c0 + c]] for the columns [c0, c0 + nc) of X_m
 template <typename T>
 __global__ void k_hilbert_cols(const double* __restrict__ rec, const int32_t* __restrict__ row_t,
@@ -294,6 +432,7 @@ hipError_t gauss_tables(const int64_t* n, int d, int m, const double* centers_ho
   double* e1 = ctr + (int64_t)nterms * d;
   double* ahi = e1 + (int64_t)nterms * g.n1;
   double* bc = ahi + (int64_t)nterms * g.rhi;
+  g.centers = ctr;
   g.e1 = e1;
   g.ahi = ahi;
   g.bc = bc;
@@ -331,6 +470,32 @@ hipError_t gauss_columns(const GaussTabs& g, int64_t c0, int64_t nc, int dtype, 
     hipLaunchKernelGGL((k_gauss_tiles<false, double>), grid, b, 0, s, g, c0, nc, (double*)W, none, gi, gj);
   else
     hipLaunchKernelGGL((k_gauss_tiles<false, float>), grid, b, 0, s, g, c0, nc, (float*)W, none, gi, gj);
+  return hipGetLastError();
+}
+
+hipError_t gauss_moments(const GaussTabs& g, const SketchArgs& a, const int64_t* n, double gamma, int64_t c0,
+                         int64_t nc, double* mom, hipStream_t s) {
+  if (fault_take()) return hipErrorLaunchFailure;
+  Modes M;
+  for (int q = 0; q < PSTT2_MAX_D; ++q) M.n[q] = q < a.d ? n[q] : 1;
+  hipLaunchKernelGGL(k_gauss_moments, dim3(2 * (unsigned)g.nterms), dim3(1024), 0, s, g, a, M, a.d, gamma, c0, nc, mom,
+                     mom + 32 * (int64_t)g.nterms);
+  return hipGetLastError();
+}
+
+hipError_t gauss_sketch_y(const GaussTabs& g, const double* mom, int ell, bool store, double* Y, int* flag,
+                          hipStream_t s) {
+  const dim3 grid((unsigned)((g.R + 255) / 256)), b(256);
+  const double* m = mom + 32 * (int64_t)g.nterms;
+  if (ell <= 16) hipLaunchKernelGGL(k_gauss_y<1>, grid, b, 0, s, g, m, ell, store, Y, flag);
+  else hipLaunchKernelGGL(k_gauss_y<2>, grid, b, 0, s, g, m, ell, store, Y, flag);
+  return hipGetLastError();
+}
+
+hipError_t gauss_sketch_t(const GaussTabs& g, const double* mom, int ell, int64_t c0, int64_t nc, double* Tt, int* flag,
+                          hipStream_t s) {
+  const dim3 grid((unsigned)std::max<int64_t>(1, std::min<int64_t>((nc + 255) / 256, 4096)), (unsigned)ell);
+  hipLaunchKernelGGL(k_gauss_t, grid, dim3(256), 0, s, g, mom, c0, nc, Tt, flag);
   return hipGetLastError();
 }
 
