@@ -11,8 +11,8 @@
 //    workgroup per 512- or 1024-row block, all splits in one launch per tree
 //    level; the pivots of a matrix equal the pivots of its R factor, so the
 //    pivoted QR runs on the final ell x ell R.  Signs are fixed so that
-//    diag(R) >= 0.  Singular values (tolerance mode) come from a one-sided
-//    Jacobi sweep on that R.
+//    diag(R) >= 0.  Singular values (tolerance mode) come from one-sided
+//    Jacobi sweeps on the pivoted R.
 //  * core_left / core_right: equation "core" and its row-space mirror.
 //  * middle_z / middle_a / middle_ls: the one-pass middle core, two products and
 //    a least-squares solve (Section 4.2, "PSTT2-onepass").
@@ -333,103 +333,169 @@ __global__ __launch_bounds__(256) void k_qr_apply(const ApplyBatch B, int ell) {
   }
 }
 
-// Column-pivoted QR of the ell x ell matrix R, one wavefront per problem.
-// Lane t holds column t in registers; pivoting swaps positions, not data: pos
-// is the lane's current column position.  Pivot: the column of largest
-// remaining norm, first position on ties (norms recomputed exactly each
-// step).  Outputs: piv (ell; piv[position] = original column) and Qc
-// (ell x ell, columns sign-fixed so that diag(R) >= 0).
+// ---- the pivoted QR of the small R factors, one wavefront per problem ----
+template <int CTRL>
+__device__ __forceinline__ double dpp_f64(double v) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)u, CTRL, 0xf, 0xf, true);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)(u >> 32), CTRL, 0xf, 0xf, true);
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+constexpr int kXor1 = 0xB1, kXor2 = 0x4E;               // within a quad
+constexpr int kHalfMirror = 0x141, kMirror = 0x140;     // within 8 and 16 lanes
+
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// Column-pivoted QR of the ell x ell matrix R.  Lane t holds column t in
+// registers; pivoting swaps positions, not data: pos is the lane's current
+// column position.  Pivot: the column of largest remaining norm, first position
+// on ties (norms recomputed exactly each step).  Outputs: piv (ell;
+// piv[position] = original column), Qc (ell x ell, columns sign-fixed so that
+// diag(R) >= 0) and, with SV, the singular values in decreasing order.
+//
+// A step is a chain of dependent operations of one wavefront, so the code
+// shortens that chain: the column array moves up by one row per step (register
+// indices stay constants without unrolling the steps), the pivot column is
+// broadcast through the scalar unit, the maximum found with lane permutations
+// inside the vector unit, the reflector applied unscaled while its scale (root
+// and quotients) is still being formed, and the arrays shortened every eight
+// steps.  ell = 24: 39 -> 22.6 us; ell = 32 with the singular values, which had a
+// kernel of their own: 62 + 255 -> 156 us.
+//
+// Singular values by one-sided (Hestenes) Jacobi on the rows of the pivoted R
+// factor, whose decreasing diagonal makes them nearly orthogonal already (about
+// half the sweeps that its columns take): a round rotates E / 2 disjoint pairs
+// (round-robin ordering, E = ell rounded up to even), four lanes per pair with
+// eight entries each.  Sweeps end when no pair needed a rotation (at most 40).
 struct CpqrBatch {
   const double* R[MAXB];
   int64_t ldr[MAXB];
   int* piv[MAXB];
   double* Qc[MAXB];
+  double* sv[MAXB];
 };
 
-template <int LP>
+template <int LP, bool SV>
 __global__ __launch_bounds__(64) void k_cpqr(const CpqrBatch B, int ell) {
-  __shared__ double Vs[LP][LP + 1];
+  constexpr int VS = LP + 2;   // even row stride: 16-byte reads
+  constexpr int MX = PSTT2_MAX_ELL, US = MX + 2;
+  __shared__ __align__(16) double Vs[LP][VS];
   __shared__ double taus[LP], diag[LP];
+  __shared__ __align__(16) double U[SV ? MX : 1][US];   // rows of the pivoted R
   const int pb = blockIdx.x;
   const double* __restrict__ R = B.R[pb];
   const int64_t ldr = B.ldr[pb];
   const int t = threadIdx.x;
   const bool act = t < ell;
-  double a[LP];
+  double a[LP];   // the column's rows j, j + 1, ... at step j, then zeros
 #pragma unroll
   for (int i = 0; i < LP; ++i) a[i] = (act && i < ell) ? R[(int64_t)t * ldr + i] : 0.0;
+  if constexpr (SV) {
+    for (int i = t; i < MX * US; i += 64) (&U[0][0])[i] = 0.0;
+    wave_sync();
+  }
   int pos = t;
-#pragma clang loop unroll(full)
-  for (int j = 0; j < LP; ++j) {
-    if (j < ell) {   // uniform
-      double nrm = 0.0;
+  // Steps j0 .. min(j1, ell) - 1 on arrays of N rows (the rows that can still be
+  // nonzero); a finished column's array is never read again
+  auto steps = [&](auto nrows, int j0, int j1) {
+    constexpr int N = decltype(nrows)::value;
+    for (int j = j0; j < j1 && j < ell; ++j) {
+      double s4[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-      for (int i = j; i < LP; ++i) nrm += a[i] * a[i];
-      double key = (act && pos >= j) ? nrm : -1.0;
-      int kpos = pos, klane = t;
-      for (int o = 32; o > 0; o >>= 1) {
-        const double ok = __shfl_xor(key, o);
-        const int op = __shfl_xor(kpos, o), ol = __shfl_xor(klane, o);
-        if (ok > key || (ok == key && op < kpos)) {
-          key = ok;
-          kpos = op;
-          klane = ol;
-        }
+      for (int i = 1; i < N; ++i) s4[i & 3] += a[i] * a[i];
+      const double below = (s4[0] + s4[1]) + (s4[2] + s4[3]);
+      const double key = (act && pos >= j) ? below + a[0] * a[0] : -1.0;
+      // maximum over lanes 0..31 (the others hold -1)
+      double m = key;
+      m = fmax(m, dpp_f64<kXor1>(m));
+      m = fmax(m, dpp_f64<kXor2>(m));
+      m = fmax(m, dpp_f64<kHalfMirror>(m));
+      m = fmax(m, dpp_f64<kMirror>(m));
+      m = fmax(lane_f64(m, 0), lane_f64(m, 16));
+      uint64_t tied = __ballot(act && pos >= j && key == m);
+      if (tied == 0) tied = __ballot(act && pos == j);   // no comparable norm (NaN): no exchange
+      int w = __builtin_ctzll(tied);
+      while ((tied &= tied - 1) != 0) {                  // ties: the first position
+        const int o = __builtin_ctzll(tied);
+        if (__builtin_amdgcn_readlane(pos, o) < __builtin_amdgcn_readlane(pos, w)) w = o;
       }
-      const int w = __shfl(klane, 0);
-      const int wpos = __shfl(pos, w);
+      w = __builtin_amdgcn_readfirstlane(w);
+      const int wpos = __builtin_amdgcn_readlane(pos, w);
       if (t == w) pos = j;
       else if (pos == j) pos = wpos;
+      // pivot column (uniform) and the unscaled products with it
+      double u[N], d4v[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int i = 0; i < N; ++i) u[i] = lane_f64(a[i], w);
+#pragma unroll
+      for (int i = 1; i < N; ++i) d4v[i & 3] += u[i] * a[i];
+      const double dot = (d4v[0] + d4v[1]) + (d4v[2] + d4v[3]);
+      const double sigma = lane_f64(below, w), alpha = u[0];
+      double tj = 0.0, beta = alpha, scal = 0.0;
+      if (sigma != 0.0) {   // uniform
+        beta = -copysign(sqrt(alpha * alpha + sigma), alpha);
+        tj = (beta - alpha) / beta;
+        scal = 1.0 / (alpha - beta);
+      }
+      // reflector j for the formation of Qc: v_0 = 1, v_i = scal u_i
       if (t == w) {
-        double sigma = 0.0;
+        Vs[j][0] = 1.0;
 #pragma unroll
-        for (int i = j + 1; i < LP; ++i) sigma += a[i] * a[i];
-        const double alpha = a[j];
-        double tj, beta, scal;
-        if (sigma == 0.0) {
-          tj = 0.0;
-          beta = alpha;
-          scal = 0.0;
-        } else {
-          beta = -copysign(sqrt(alpha * alpha + sigma), alpha);
-          tj = (beta - alpha) / beta;
-          scal = 1.0 / (alpha - beta);
-        }
-#pragma unroll
-        for (int i = 0; i < LP; ++i) Vs[j][i] = i < j ? 0.0 : (i == j ? 1.0 : a[i] * scal);
+        for (int i = 1; i < N; ++i) Vs[j][i] = scal * a[i];
         taus[j] = tj;
         diag[j] = beta;
-        a[j] = beta;
-#pragma unroll
-        for (int i = j + 1; i < LP; ++i) a[i] = 0.0;
       }
-      __syncthreads();
-      if (act && pos > j) {
-        double pd = 0.0;
+      const double p = (act && pos > j) ? tj * (a[0] + scal * dot) : 0.0;
+      const double top = a[0] - p;   // row j of R (the pivot's is beta)
+      const double ps = p * scal;
 #pragma unroll
-        for (int i = j; i < LP; ++i) pd += Vs[j][i] * a[i];
-        pd *= taus[j];
-#pragma unroll
-        for (int i = j; i < LP; ++i) a[i] -= pd * Vs[j][i];
+      for (int i = 0; i + 1 < N; ++i) a[i] = a[i + 1] - ps * u[i + 1];
+      a[N - 1] = 0.0;
+      if constexpr (SV) {
+        if (act && pos >= j) U[j][t] = t == w ? beta : top;   // by column: positions still change
       }
     }
-  }
-  // Qc = H_0 ... H_{ell-1} I: lane t forms column t (position t), sign-fixed
+  };
+  if constexpr (LP >= 32) steps(std::integral_constant<int, 32>{}, 0, LP - 24);
+  if constexpr (LP >= 24) steps(std::integral_constant<int, 24>{}, LP - 24, LP - 16);
+  if constexpr (LP >= 16) steps(std::integral_constant<int, 16>{}, LP - 16, LP - 8);
+  steps(std::integral_constant<int, 8>{}, LP - 8, LP);
+  wave_sync();
+  // Qc = H_0 ... H_{ell-1} I: lane t forms column t, sign-fixed.  At step j, q holds
+  // rows j, j + 1, ... (the rows before are still the identity's)
+  double q[LP];
+#pragma unroll
+  for (int i = 0; i < LP; ++i) q[i] = 0.0;
+  auto back = [&](auto nrows, int j0, int j1) {   // steps min(j1, ell) - 1 .. j0 on N rows
+    constexpr int N = decltype(nrows)::value;
+    for (int j = (j1 < ell ? j1 : ell) - 1; j >= j0; --j) {
+      double v[N];
+#pragma unroll
+      for (int i = 0; i < N; i += 2) {
+        const double2 x = *(const double2*)&Vs[j][i];
+        v[i] = x.x;
+        v[i + 1] = x.y;
+      }
+      const double tj = taus[j];
+#pragma unroll
+      for (int i = N - 1; i > 0; --i) q[i] = q[i - 1];
+      q[0] = t == j ? 1.0 : 0.0;
+      double d4v[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int i = 0; i < N; ++i) d4v[i & 3] += v[i] * q[i];
+      const double pd = tj * ((d4v[0] + d4v[1]) + (d4v[2] + d4v[3]));
+#pragma unroll
+      for (int i = 0; i < N; ++i) q[i] -= pd * v[i];
+    }
+  };
+  back(std::integral_constant<int, 8>{}, LP - 8, LP);
+  if constexpr (LP >= 16) back(std::integral_constant<int, 16>{}, LP - 16, LP - 8);
+  if constexpr (LP >= 24) back(std::integral_constant<int, 24>{}, LP - 24, LP - 16);
+  if constexpr (LP >= 32) back(std::integral_constant<int, 32>{}, 0, LP - 24);
   if (act) {
-    double q[LP];
-#pragma unroll
-    for (int i = 0; i < LP; ++i) q[i] = i == t ? 1.0 : 0.0;
-#pragma clang loop unroll(full)
-    for (int j = LP - 1; j >= 0; --j) {
-      if (j < ell) {
-        double pd = 0.0;
-#pragma unroll
-        for (int i = j; i < LP; ++i) pd += Vs[j][i] * q[i];
-        pd *= taus[j];
-#pragma unroll
-        for (int i = j; i < LP; ++i) q[i] -= pd * Vs[j][i];
-      }
-    }
     const double sg = diag[t] < 0.0 ? -1.0 : 1.0;
     double* Qc = B.Qc[pb];
 #pragma unroll
@@ -437,108 +503,89 @@ __global__ __launch_bounds__(64) void k_cpqr(const CpqrBatch B, int ell) {
       if (i < ell) Qc[(int64_t)t * ell + i] = sg * q[i];
     B.piv[pb][pos] = t;
   }
-}
-
-// Singular values of an ell x ell matrix by one-sided (Hestenes) Jacobi.
-// 16 wavefront halves; half h rotates pair h of the round-robin schedule, one
-// row per lane.
-struct SvBatch {
-  const double* R[MAXB];
-  int64_t ldr[MAXB];
-  double* sv[MAXB];
-};
-
-// One-sided (Hestenes) Jacobi on the ell x ell R factor, one wavefront per
-// problem: a round rotates E/2 disjoint column pairs (round-robin ordering,
-// E = ell rounded up to even), four lanes per pair with eight rows each, so a
-// round is a few LDS accesses, two shuffle steps and one rotation per lane.
-// Sweeps end when no pair needed a rotation (at most 40); the singular values
-// are the final column norms, sorted in decreasing order.
-__global__ __launch_bounds__(64) void k_jacobi_sv(const SvBatch B, int ell) {
-  const double* __restrict__ R = B.R[blockIdx.x];
-  const int64_t ldr = B.ldr[blockIdx.x];
-  double* __restrict__ sv = B.sv[blockIdx.x];
-  constexpr int MX = PSTT2_MAX_ELL;
-  __shared__ double U[MX][MX + 1];  // [col][row], zero outside ell x ell
-  const int t = threadIdx.x;
-  for (int i = t; i < MX * MX; i += 64) {
-    const int c = i / MX, r = i % MX;
-    U[c][r] = (c < ell && r < ell) ? R[(int64_t)c * ldr + r] : 0.0;
-  }
-  __syncthreads();
-  const int E = (ell + 1) & ~1;
-  const int pr = t >> 2, r0 = (t & 3) * 8;
-  // a pair counts as orthogonal once |u_p . u_q| <= ell eps |u_p| |u_q|, the
-  // rounding level of the dot product itself (a tighter test keeps rotating on
-  // rounding noise and never ends before the sweep cap)
-  const double tol = ell * 2.220446049250313e-16;
-  for (int sweep = 0; sweep < 40; ++sweep) {
-    int rot = 0;
-    for (int rnd = 0; rnd < E - 1; ++rnd) {
-      int p = -1, q = -1;
-      if (pr < E / 2) {
-        if (pr == 0) {
-          p = E - 1;
-          q = rnd;
-        } else {
-          p = (rnd + pr) % (E - 1);
-          q = (rnd - pr + (E - 1)) % (E - 1);
+  if constexpr (SV) {
+    const int E = (ell + 1) & ~1;
+    const int pr = t >> 2, r0 = (t & 3) * 8;
+    // a pair counts as orthogonal once |u_p . u_q| <= ell eps |u_p| |u_q|, the
+    // rounding level of the dot product itself (a tighter test keeps rotating on
+    // rounding noise and never ends before the sweep cap)
+    const double tol = ell * 2.220446049250313e-16;
+    wave_sync();
+    for (int sweep = 0; sweep < 40; ++sweep) {
+      bool any = false;
+      // round rnd: pair 0 is (E - 1, rnd), pair k is (rnd + k, rnd - k) mod E - 1
+      int fwd = pr, bwd = pr == 0 || pr >= E / 2 ? 0 : E - 1 - pr;
+      for (int rnd = 0; rnd < E - 1; ++rnd) {
+        const int x1 = pr == 0 ? E - 1 : fwd, x2 = bwd;
+        fwd = fwd + 1 == E - 1 ? 0 : fwd + 1;
+        bwd = bwd + 1 == E - 1 ? 0 : bwd + 1;
+        const int p = x1 < x2 ? x1 : x2, q2 = x1 < x2 ? x2 : x1;
+        const bool on = pr < E / 2 && q2 < ell;
+        const int pp = on ? p : 0, qq = on ? q2 : 0;
+        double up[8], uq[8];
+#pragma unroll
+        for (int i = 0; i < 8; i += 2) {
+          const double2 x = *(const double2*)&U[pp][r0 + i], y = *(const double2*)&U[qq][r0 + i];
+          up[i] = x.x;
+          up[i + 1] = x.y;
+          uq[i] = y.x;
+          uq[i + 1] = y.y;
         }
-        if (p > q) {
-          const int tmp = p;
-          p = q;
-          q = tmp;
-        }
-      }
-      const bool act = q >= 0 && q < ell;
-      double up[8], uq[8];
-      double app = 0.0, aqq = 0.0, apq = 0.0;
-      if (act) {
+        double app = 0.0, aqq = 0.0, apq = 0.0;
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
-          up[i] = U[p][r0 + i];
-          uq[i] = U[q][r0 + i];
           app += up[i] * up[i];
           aqq += uq[i] * uq[i];
           apq += up[i] * uq[i];
         }
-      }
-      // the four lanes of a pair are adjacent: two xor steps finish the sums
-      for (int o = 1; o <= 2; o <<= 1) {
-        app += __shfl_xor(app, o);
-        aqq += __shfl_xor(aqq, o);
-        apq += __shfl_xor(apq, o);
-      }
-      if (act && fabs(apq) > tol * sqrt(app * aqq) && apq != 0.0) {
-        const double zeta = (aqq - app) / (2.0 * apq);
-        const double tt = copysign(1.0, zeta) / (fabs(zeta) + sqrt(1.0 + zeta * zeta));
-        const double cs = 1.0 / sqrt(1.0 + tt * tt);
-        const double sn = cs * tt;
+        // the four lanes of a pair are one quad
+        app += dpp_f64<kXor1>(app);
+        aqq += dpp_f64<kXor1>(aqq);
+        apq += dpp_f64<kXor1>(apq);
+        app += dpp_f64<kXor2>(app);
+        aqq += dpp_f64<kXor2>(aqq);
+        apq += dpp_f64<kXor2>(apq);
+        const double ab = app * aqq;
+        const double lim = ab > 1e-290 ? ab * __builtin_amdgcn_rsq(ab) : sqrt(ab);
+        const bool rot = on && apq != 0.0 && fabs(apq) > tol * lim;
+        if (__any(rot)) {
+          any = true;
+          if (rot) {
+            // the tangent from the approximate reciprocal and root (an inexact angle
+            // leaves a residual for the next meeting), cosine and sine exact
+            const double z = 0.5 * (aqq - app) * __builtin_amdgcn_rcp(apq);
+            const double az = fabs(z), h = 1.0 + z * z;
+            const double tg = az < 1e100 ? __builtin_amdgcn_rcp(az + h * __builtin_amdgcn_rsq(h)) : 0.0;
+            const double tn = z >= 0.0 ? tg : -tg;
+            const double x = 1.0 + tn * tn;
+            double cs = __builtin_amdgcn_rsq(x);
+            cs += 0.5 * cs * fma(-x * cs, cs, 1.0);
+            cs += 0.5 * cs * fma(-x * cs, cs, 1.0);
+            const double sn = cs * tn;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          U[p][r0 + i] = cs * up[i] - sn * uq[i];
-          U[q][r0 + i] = sn * up[i] + cs * uq[i];
+            for (int i = 0; i < 8; i += 2) {
+              *(double2*)&U[pp][r0 + i] = double2{cs * up[i] - sn * uq[i], cs * up[i + 1] - sn * uq[i + 1]};
+              *(double2*)&U[qq][r0 + i] = double2{sn * up[i] + cs * uq[i], sn * up[i + 1] + cs * uq[i + 1]};
+            }
+          }
+          wave_sync();
         }
-        rot = 1;
       }
-      __syncthreads();
+      if (!any) break;
     }
-    if (!__any(rot)) break;
-  }
-  // lane c < ell holds column c's norm; its place in decreasing order (ties
-  // by column index) is the number of columns ranked before it
-  __shared__ double nrm[MX];
-  if (t < ell) {
-    double v = 0.0;
-    for (int i = 0; i < ell; ++i) v += U[t][i] * U[t][i];
-    nrm[t] = sqrt(v);
-  }
-  __syncthreads();
-  if (t < ell) {
-    const double v = nrm[t];
-    int pos = 0;
-    for (int c = 0; c < ell; ++c) pos += (nrm[c] > v || (nrm[c] == v && c < t)) ? 1 : 0;
-    sv[pos] = v;
+    wave_sync();
+    // lane c < ell holds row c's norm; its place in decreasing order (ties by
+    // index) is the number of rows ranked before it
+    double nrm = 0.0;
+    if (act)
+      for (int i = 0; i < ell; ++i) nrm += U[t][i] * U[t][i];
+    nrm = sqrt(nrm);
+    int place = 0;
+    for (int c = 0; c < ell; ++c) {
+      const double o = lane_f64(nrm, c);
+      place += (o > nrm || (o == nrm && c < t)) ? 1 : 0;
+    }
+    if (act) B.sv[pb][place] = nrm;
   }
 }
 
@@ -582,6 +629,15 @@ static void launch_leaf(const LeafBatch& B, int64_t nblk, int ell, hipStream_t s
   else if (ell <= 16) hipLaunchKernelGGL((k_qr_leaf<16, 4>), g, b, 0, s, B, ell);
   else if (ell <= 24) hipLaunchKernelGGL((k_qr_leaf<24, 4>), g, b, 0, s, B, ell);
   else hipLaunchKernelGGL((k_qr_leaf<32, 2>), g, b, 0, s, B, ell);
+}
+
+template <bool SV>
+static void launch_cpqr(const CpqrBatch& C, int n, int ell, hipStream_t s) {
+  const dim3 g(n), b(64);
+  if (ell <= 8) hipLaunchKernelGGL((k_cpqr<8, SV>), g, b, 0, s, C, ell);
+  else if (ell <= 16) hipLaunchKernelGGL((k_cpqr<16, SV>), g, b, 0, s, C, ell);
+  else if (ell <= 24) hipLaunchKernelGGL((k_cpqr<24, SV>), g, b, 0, s, C, ell);
+  else hipLaunchKernelGGL((k_cpqr<32, SV>), g, b, 0, s, C, ell);
 }
 
 hipError_t basis_factor_batch(int n, const double* const* A, const int64_t* M, int ell, int* const* piv,
@@ -655,25 +711,17 @@ hipError_t basis_factor_batch(int n, const double* const* A, const int64_t* M, i
     HCK(hipGetLastError());
   }
   CpqrBatch C;
-  SvBatch S;
   std::memset(&C, 0, sizeof(C));
-  std::memset(&S, 0, sizeof(S));
   for (int p = 0; p < n; ++p) {
-    C.R[p] = S.R[p] = w->lv[p].back().Rst;
-    C.ldr[p] = S.ldr[p] = ell;
+    C.R[p] = w->lv[p].back().Rst;
+    C.ldr[p] = ell;
     C.piv[p] = piv[p];
     C.Qc[p] = w->Qc[p];
-    S.sv[p] = w->sv[p];
+    C.sv[p] = w->sv[p];
   }
-  if (ell <= 8) hipLaunchKernelGGL((k_cpqr<8>), dim3(n), dim3(64), 0, s, C, ell);
-  else if (ell <= 16) hipLaunchKernelGGL((k_cpqr<16>), dim3(n), dim3(64), 0, s, C, ell);
-  else if (ell <= 24) hipLaunchKernelGGL((k_cpqr<24>), dim3(n), dim3(64), 0, s, C, ell);
-  else hipLaunchKernelGGL((k_cpqr<32>), dim3(n), dim3(64), 0, s, C, ell);
+  if (want_sv) launch_cpqr<true>(C, n, ell, s);
+  else launch_cpqr<false>(C, n, ell, s);
   HCK(hipGetLastError());
-  if (want_sv) {
-    hipLaunchKernelGGL(k_jacobi_sv, dim3(n), dim3(64), 0, s, S, ell);
-    HCK(hipGetLastError());
-  }
   return hipSuccess;
 }
 
