@@ -12,8 +12,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 ROOT = os.path.dirname(HERE)
 LIB = os.path.join(HERE, "libpstt2.so")
-SOURCES = ["api.hip", "sketch.hip", "partial.hip", "reduce.hip", "recover.hip", "tt_eval.hip", "adjoint.hip", "workspace.hip",
-           "tensor_fn.hip", "rng.hip", "ttsvd.hip"]
+SOURCES = ["api.hip", "sketch.hip", "partial.hip", "reduce.hip", "recover.hip", "gemm.hip", "tt_eval.hip",
+           "adjoint.hip", "workspace.hip", "tensor_fn.hip", "rng.hip", "ttsvd.hip"]
 ARCH = os.environ.get("PSTT2_OFFLOAD_ARCH", "gfx950")
 
 

@@ -40,144 +40,6 @@ __device__ __forceinline__ double wsum(double v) {
   return v;
 }
 
-// ---- small dense FP64 products, column-major: C = alpha op(A) op(B) + beta C ----
-__device__ __forceinline__ double at(const double* A, int64_t lda, bool t, int64_t i, int64_t k) {
-  return t ? A[k + lda * i] : A[i + lda * k];
-}
-
-// one thread per entry of C (short contractions)
-__global__ void k_gemm_t(bool ta, bool tb, int64_t M, int64_t N, int64_t K, double alpha, const double* __restrict__ A,
-                         int64_t lda, const double* __restrict__ B, int64_t ldb, double beta, double* __restrict__ C,
-                         int64_t ldc) {
-  const int64_t tot = M * N;
-  for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < tot; t += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t i = t % M, j = t / M;
-    double s = 0.0;
-    for (int64_t k = 0; k < K; ++k) s += at(A, lda, ta, i, k) * at(B, ldb, !tb, j, k);
-    double* c = C + i + ldc * j;
-    *c = alpha * s + (beta == 0.0 ? 0.0 : beta * *c);
-  }
-}
-
-// one wavefront per entry of C (long contractions)
-__global__ __launch_bounds__(256) void k_gemm_w(bool ta, bool tb, int64_t M, int64_t N, int64_t K, double alpha,
-                                                const double* __restrict__ A, int64_t lda, const double* __restrict__ B,
-                                                int64_t ldb, double beta, double* __restrict__ C, int64_t ldc) {
-  const int lane = threadIdx.x & 63;
-  const int64_t tot = M * N;
-  for (int64_t t = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6; t < tot;
-       t += ((int64_t)gridDim.x * blockDim.x) >> 6) {
-    const int64_t i = t % M, j = t / M;
-    double s = 0.0;
-    for (int64_t k = lane; k < K; k += 64) s += at(A, lda, ta, i, k) * at(B, ldb, !tb, j, k);
-    s = wsum(s);
-    if (lane == 0) {
-      double* c = C + i + ldc * j;
-      *c = alpha * s + (beta == 0.0 ? 0.0 : beta * *c);
-    }
-  }
-}
-
-// C = A^T B for tall, narrow A (K x M) and B (K x N), M, N <= 32, in two
-// steps: workgroup g stages rows [g TN_ROWS, (g+1) TN_ROWS) of both operands in
-// LDS, 64 rows at a time, and writes the partial product of its slice; a
-// wavefront per entry of C then adds the slices' partials in slice order with a
-// fixed butterfly (deterministic for any K).  A batch of products with the same
-// A, C_i = A^T B_i (B_i = B + i sb, C_i = C + i sc), shares each launch: the
-// batch index runs fastest over the workgroups, so the products of one row
-// slice run together and read that slice of A once from HBM.
-constexpr int TN_ROWS = 128;
-constexpr int TN_SUB = 64;
-
-__global__ __launch_bounds__(256) void k_gemm_tn_part(int M, int N, int64_t K, const double* __restrict__ A,
-                                                      int64_t lda, const double* __restrict__ B, int64_t ldb,
-                                                      double* __restrict__ part, int nbatch, int64_t sb, int nb) {
-  __shared__ double As[TN_SUB][33];
-  __shared__ double Bs[TN_SUB][33];
-  const int t = threadIdx.x;
-  const int nout = M * N;
-  const int bi = (int)(blockIdx.x % nbatch);
-  const int64_t g = blockIdx.x / nbatch;
-  B += bi * sb;
-  part += ((int64_t)bi * nb + g) * nout;
-  double acc[4] = {0.0, 0.0, 0.0, 0.0};
-  const int64_t r0 = g * TN_ROWS;
-  const int64_t r1 = std::min<int64_t>(K, r0 + TN_ROWS);
-  for (int64_t k0 = r0; k0 < r1; k0 += TN_SUB) {
-    const int nr = (int)std::min<int64_t>(TN_SUB, r1 - k0);
-    for (int e = t; e < TN_SUB * M; e += 256) {
-      const int r = e % TN_SUB, c = e / TN_SUB;
-      As[r][c] = r < nr ? A[k0 + r + lda * c] : 0.0;
-    }
-    for (int e = t; e < TN_SUB * N; e += 256) {
-      const int r = e % TN_SUB, c = e / TN_SUB;
-      Bs[r][c] = r < nr ? B[k0 + r + ldb * c] : 0.0;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int o = t + 256 * q;
-      if (o < nout) {
-        const int i = o % M, j = o / M;
-        double sacc = acc[q];
-        for (int r = 0; r < TN_SUB; ++r) sacc += As[r][i] * Bs[r][j];
-        acc[q] = sacc;
-      }
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int o = t + 256 * q;
-    if (o < nout) part[o] = acc[q];
-  }
-}
-
-__global__ __launch_bounds__(256) void k_gemm_tn_sum(const double* __restrict__ part, int nb, int M, int N,
-                                                     double alpha, double beta, double* __restrict__ C, int64_t ldc,
-                                                     int nbatch, int64_t sc) {
-  const int lane = threadIdx.x & 63;
-  const int64_t ow = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6;
-  const int nout = M * N;
-  if (ow >= (int64_t)nout * nbatch) return;
-  const int bi = (int)(ow / nout), o = (int)(ow % nout);
-  part += (int64_t)bi * nb * nout;
-  C += bi * sc;
-  double s = 0.0;
-  for (int g = lane; g < nb; g += 64) s += part[(int64_t)g * nout + o];
-  s = wsum(s);
-  if (lane == 0) {
-    double* c = C + (o % M) + ldc * (o / M);
-    *c = alpha * s + (beta == 0.0 ? 0.0 : beta * *c);
-  }
-}
-
-// op(B)(k, j): B is K x N (tb false) or N x K (tb true); at(B, ldb, !tb, j, k) reads it.
-static hipError_t gemm(bool ta, bool tb, int64_t M, int64_t N, int64_t K, double alpha, const double* A, int64_t lda,
-                       const double* B, int64_t ldb, double beta, double* C, int64_t ldc, hipStream_t s) {
-  if (M <= 0 || N <= 0) return hipSuccess;
-  if (ta && !tb && M <= 32 && N <= 32 && K >= 2 * TN_ROWS) {
-    const int nb = (int)((K + TN_ROWS - 1) / TN_ROWS);
-    double* part = nullptr;
-    hipError_t e = ws_alloc((void**)&part, sizeof(double) * nb * M * N, s);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_gemm_tn_part, dim3(nb), dim3(256), 0, s, (int)M, (int)N, K, A, lda, B, ldb, part, 1,
-                       (int64_t)0, nb);
-    hipLaunchKernelGGL(k_gemm_tn_sum, dim3((unsigned)((M * N + 3) / 4)), dim3(256), 0, s, part, nb, (int)M, (int)N,
-                       alpha, beta, C, ldc, 1, (int64_t)0);
-    e = hipGetLastError();
-    ws_free(part, s);
-    return e;
-  }
-  if (K >= 256)
-    hipLaunchKernelGGL(k_gemm_w, dim3((unsigned)std::max<int64_t>(1, std::min<int64_t>((M * N + 3) / 4, 16384))),
-                       dim3(256), 0, s, ta, tb, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc);
-  else
-    hipLaunchKernelGGL(k_gemm_t, dim3(grid_for(M * N, 256)), dim3(256), 0, s, ta, tb, M, N, K, alpha, A, lda, B, ldb,
-                       beta, C, ldc);
-  return hipGetLastError();
-}
-
 // out[i * L4 + c] = in[i * si + c * sc] for c < cnt, 0 for cnt <= c < L4 (i < rows)
 __global__ void k_table(const double* __restrict__ in, int64_t rows, int cnt, int64_t si, int64_t sc, int L4,
                         double* __restrict__ out) {
@@ -507,35 +369,6 @@ __global__ __launch_bounds__(256) void k_adj_out(const AdjOutArgs A, const T* __
 // ---------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------
-hipError_t adj_gemm(bool ta, bool tb, int64_t M, int64_t N, int64_t K, double alpha, const double* A, int64_t lda,
-                    const double* B, int64_t ldb, double beta, double* C, int64_t ldc, hipStream_t s) {
-  return gemm(ta, tb, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, s);
-}
-
-hipError_t adj_gemm_tn_batch(int64_t M, int64_t N, int64_t K, int nbatch, const double* A, int64_t lda,
-                             const double* B, int64_t ldb, int64_t sb, double* C, int64_t ldc, int64_t sc,
-                             hipStream_t s) {
-  if (M <= 0 || N <= 0 || nbatch <= 0) return hipSuccess;
-  if (!(M <= 32 && N <= 32 && K >= 2 * TN_ROWS)) {
-    hipError_t e = hipSuccess;
-    for (int i = 0; i < nbatch && e == hipSuccess; ++i)
-      e = gemm(true, false, M, N, K, 1.0, A, lda, B + i * sb, ldb, 0.0, C + i * sc, ldc, s);
-    return e;
-  }
-  const int nb = (int)((K + TN_ROWS - 1) / TN_ROWS);
-  const int64_t nout = M * N;
-  double* part = nullptr;
-  hipError_t e = ws_alloc((void**)&part, sizeof(double) * nb * nbatch * nout, s);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_gemm_tn_part, dim3((unsigned)((int64_t)nb * nbatch)), dim3(256), 0, s, (int)M, (int)N, K, A,
-                     lda, B, ldb, part, nbatch, sb, nb);
-  hipLaunchKernelGGL(k_gemm_tn_sum, dim3((unsigned)((nout * nbatch + 3) / 4)), dim3(256), 0, s, part, nb, (int)M,
-                     (int)N, 1.0, 0.0, C, ldc, nbatch, sc);
-  e = hipGetLastError();
-  ws_free(part, s);
-  return e;
-}
-
 hipError_t adj_table(const double* in, int64_t rows, int cnt, int64_t si, int64_t sc, int L4, double* out,
                      hipStream_t s) {
   hipLaunchKernelGGL(k_table, dim3(grid_for(rows * L4, 256)), dim3(256), 0, s, in, rows, cnt, si, sc, L4, out);
@@ -582,8 +415,8 @@ hipError_t adj_qr(const double* S, const double* Q, const double* Qb, int64_t M,
   if (e == hipSuccess) e = ws_alloc((void**)&RM, sizeof(double) * 2 * r * r, s);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_gather_cols, dim3(grid_for(M * r, 256)), dim3(256), 0, s, S, M, piv, r, B);
-  e = gemm(true, false, r, r, M, 1.0, Q, M, B, M, 0.0, RM, r, s);                 // R = Q^T B
-  if (e == hipSuccess) e = gemm(true, false, r, r, M, -1.0, Qb, M, Q, M, 0.0, RM + r * r, r, s);  // -Qbar^T Q
+  e = adj_gemm(true, false, r, r, M, 1.0, Q, M, B, M, 0.0, RM, r, s);                 // R = Q^T B
+  if (e == hipSuccess) e = adj_gemm(true, false, r, r, M, -1.0, Qb, M, Q, M, 0.0, RM + r * r, r, s);  // -Qbar^T Q
   if (e == hipSuccess) {
     hipLaunchKernelGGL(k_qr_adj_rows, dim3(grid_for(M, 256)), dim3(256), 0, s, Q, Qb, M, r, RM, RM + r * r, piv, Sb);
     e = hipGetLastError();

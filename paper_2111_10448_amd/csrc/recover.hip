@@ -805,147 +805,25 @@ hipError_t basis_form_q_batch(BasisBatch* w, const int* r, double* const* Q, hip
 }
 
 // ---------------------------------------------------------------------------
-// cores: one wavefront per output entry, lanes split the contraction
+// cores and the middle core's Z: batches of tall, narrow products
 // ---------------------------------------------------------------------------
-// G(a, i, b) = sum_{row < Rprev} Qprev(row, a) Qk(row + Rprev i, b)
-__global__ __launch_bounds__(256) void k_core_left(const double* __restrict__ Qp, int64_t Rp, int rp,
-                                                   const double* __restrict__ Qk, int nk, int rk,
-                                                   double* __restrict__ G) {
-  const int64_t tot = (int64_t)rp * nk * rk;
-  const int lane = threadIdx.x & 63;
-  const int64_t Rk = Rp * nk;
-  for (int64_t t = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6; t < tot;
-       t += ((int64_t)gridDim.x * blockDim.x) >> 6) {
-    const int a = (int)(t % rp);
-    const int i = (int)((t / rp) % nk);
-    const int b = (int)(t / ((int64_t)rp * nk));
-    double s = 0.0;
-    for (int64_t row = lane; row < Rp; row += 64) s += Qp[(int64_t)a * Rp + row] * Qk[(int64_t)b * Rk + row + Rp * i];
-    s = wave_sum(s);
-    if (lane == 0) G[t] = s;
-  }
-}
-
-// G(a, i, b) = sum_{c < Ck} Pprev(i + nk c, a) Pk(c, b)
-__global__ __launch_bounds__(256) void k_core_right(const double* __restrict__ Pp, int64_t Cp, int rp,
-                                                    const double* __restrict__ Pk, int64_t Ck, int nk, int rk,
-                                                    double* __restrict__ G) {
-  const int64_t tot = (int64_t)rp * nk * rk;
-  const int lane = threadIdx.x & 63;
-  for (int64_t t = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6; t < tot;
-       t += ((int64_t)gridDim.x * blockDim.x) >> 6) {
-    const int a = (int)(t % rp);
-    const int i = (int)((t / rp) % nk);
-    const int b = (int)(t / ((int64_t)rp * nk));
-    double s = 0.0;
-    for (int64_t c = lane; c < Ck; c += 64) s += Pp[(int64_t)a * Cp + i + (int64_t)nk * c] * Pk[(int64_t)b * Ck + c];
-    s = wave_sum(s);
-    if (lane == 0) G[t] = s;
-  }
-}
-
-static unsigned waves_grid(int64_t nout) { return (unsigned)std::max<int64_t>(1, std::min<int64_t>((nout + 3) / 4, 16384)); }
-
+// G(a, i, b) = sum_{row < Rprev} Qprev(row, a) Qk(row + Rprev i, b): one product per i
 hipError_t core_left(const double* Qprev, int64_t Rprev, int rprev, const double* Qk, int nk, int rk, double* G,
                      hipStream_t s) {
-  if (Rprev >= 4096) {
-    // tall Q_{k-1}: one wave per entry would read Q_{k-1} r_{k-1} n_k r_k / R... times
-    // over; per i, G(:, i, :) = Q_{k-1}^T Q_k(rows R_{k-1} i ..) is a tall-skinny
-    // product with fixed-order partial sums, writing G with leading dimension r_{k-1} n_k;
-    // the n_k products share one launch (and each row slice of Q_{k-1})
-    const int64_t Rk = Rprev * nk;
-    return adj_gemm_tn_batch(rprev, rk, Rprev, nk, Qprev, Rprev, Qk, Rk, Rprev, G, (int64_t)rprev * nk, rprev, s);
-  }
-  const int64_t tot = (int64_t)rprev * nk * rk;
-  hipLaunchKernelGGL(k_core_left, dim3(waves_grid(tot)), dim3(256), 0, s, Qprev, Rprev, rprev, Qk, nk, rk, G);
-  return hipGetLastError();
+  return adj_gemm_tn_batch(rprev, rk, Rprev, nk, Qprev, Rprev, 1, 0, Qk, Rprev * nk, Rprev, G, (int64_t)rprev * nk,
+                           rprev, s);
 }
 
+// G(a, i, b) = sum_{c < Ck} Pprev(i + nk c, a) Pk(c, b): the rows of product i are nk apart
 hipError_t core_right(const double* Pprev, int64_t Cprev, int rprev, const double* Pk, int64_t Ck, int nk, int rk,
                       double* G, hipStream_t s) {
-  const int64_t tot = (int64_t)rprev * nk * rk;
-  hipLaunchKernelGGL(k_core_right, dim3(waves_grid(tot)), dim3(256), 0, s, Pprev, Cprev, rprev, Pk, Ck, nk, rk, G);
-  return hipGetLastError();
+  return adj_gemm_tn_batch(rprev, rk, Ck, nk, Pprev, Cprev, nk, 1, Pk, Ck, 0, G, (int64_t)rprev * nk, rprev, s);
 }
 
 // Z(a + rp i, c) = sum_{row < Rp} Qprev(row, a) Y(row + Rp i, c);  Z is (rp nm) x ell.
-// Z(a + rp i, c) = sum_row Qp(row, a) Y(row + Rp i, c): for each i a small
-// (rp x Rp)(Rp x ell) product.  A workgroup owns one i and a contiguous share
-// of the rows, stages 64-row tiles of Qp and of Y's slice in LDS and keeps up to
-// four of the rp x ell outputs per thread in registers across the tiles; with
-// nsplit > 1 shares it writes partials that k_sum_splits adds in a fixed order.
-__global__ __launch_bounds__(256) void k_middle_z(const double* __restrict__ Qp, int64_t Rp, int rp,
-                                                  const double* __restrict__ Y, int64_t Rm, int nm, int ell,
-                                                  int nsplit, double* __restrict__ out) {
-  constexpr int MX = PSTT2_MAX_ELL, TR = 64;
-  __shared__ double Qs[TR][MX + 1], Ys[TR][MX + 1];
-  const int i = (int)(blockIdx.x % nm);
-  const int sp = (int)(blockIdx.x / nm);
-  const int64_t r0 = sp * Rp / nsplit, r1 = (sp + 1) * Rp / nsplit;
-  const int nout = rp * ell;
-  double acc[4] = {0.0, 0.0, 0.0, 0.0};
-  for (int64_t base = r0; base < r1; base += TR) {
-    const int nr = (int)(r1 - base < TR ? r1 - base : TR);
-    __syncthreads();
-    for (int e = threadIdx.x; e < TR * MX; e += blockDim.x) {
-      const int r = e % TR, j = e / TR;
-      Qs[r][j] = (r < nr && j < rp) ? Qp[(int64_t)j * Rp + base + r] : 0.0;
-      Ys[r][j] = (r < nr && j < ell) ? Y[(int64_t)j * Rm + base + r + Rp * i] : 0.0;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const int o = threadIdx.x + 256 * k;
-      if (o < nout) {
-        const int a = o % rp, c = o / rp;
-        double sum = acc[k];
-        for (int r = 0; r < nr; ++r) sum += Qs[r][a] * Ys[r][c];
-        acc[k] = sum;
-      }
-    }
-  }
-  const int64_t nz = (int64_t)rp * nm;
-#pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    const int o = threadIdx.x + 256 * k;
-    if (o < nout) {
-      const int a = o % rp, c = o / rp;
-      out[sp * nz * ell + a + (int64_t)rp * i + nz * c] = acc[k];
-    }
-  }
-}
-
-__global__ void k_sum_splits(const double* __restrict__ part, int nsplit, int64_t n, double* __restrict__ out) {
-  for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < n; t += (int64_t)gridDim.x * blockDim.x) {
-    double sum = 0.0;
-    for (int sp = 0; sp < nsplit; ++sp) sum += part[sp * n + t];
-    out[t] = sum;
-  }
-}
-
 hipError_t middle_z(const double* Qprev, int64_t Rprev, int rprev, const double* Y, int64_t Rm, int nm, int ell,
                     double* Z, hipStream_t s) {
-  if (rprev * ell > 1024 || rprev > PSTT2_MAX_ELL || ell > PSTT2_MAX_ELL) return hipErrorInvalidValue;
-  // enough workgroups to spread over the chip: split the rows when n_m is small
-  const int64_t want = (256 + nm - 1) / nm;
-  const int nsplit = (int)std::max<int64_t>(1, std::min<int64_t>(want, (Rprev + 255) / 256));
-  const int64_t n = (int64_t)rprev * nm * ell;
-  double* part = Z;
-  if (nsplit > 1) {
-    hipError_t e = ws_alloc((void**)&part, sizeof(double) * n * nsplit, s);
-    if (e != hipSuccess) return e;
-  }
-  hipLaunchKernelGGL(k_middle_z, dim3((unsigned)(nm * nsplit)), dim3(256), 0, s, Qprev, Rprev, rprev, Y, Rm, nm, ell,
-                     nsplit, part);
-  hipError_t e = hipGetLastError();
-  if (nsplit > 1) {
-    if (e == hipSuccess) {
-      hipLaunchKernelGGL(k_sum_splits, dim3(grid_for(n, 256)), dim3(256), 0, s, part, nsplit, n, Z);
-      e = hipGetLastError();
-    }
-    ws_free(part, s);
-  }
-  return e;
+  return adj_gemm_tn_batch(rprev, ell, Rprev, nm, Qprev, Rprev, 1, 0, Y, Rm, Rprev, Z, (int64_t)rprev * nm, rprev, s);
 }
 
 __global__ void k_kr_table(const double* __restrict__ fac, const KRChain ch, int64_t rows, int ell,
