@@ -28,6 +28,7 @@
 #include <cstring>
 
 #include "internal.h"
+#include "linalg.h"
 
 namespace pstt2 {
 
@@ -68,71 +69,81 @@ __global__ void k_axpy(int64_t n, double alpha, const double* __restrict__ X, do
 
 // ---- middle least-squares adjoint (one workgroup; p = r_{m-1} n_m rows) ----
 // G (p x r), Gbar (p x r), Z (p x ell), A (r x ell) -> Zbar (p x ell), Abar (r x ell).
-__global__ __launch_bounds__(256) void k_ls_adjoint(const double* __restrict__ G, const double* __restrict__ Gb,
-                                                    const double* __restrict__ Z, const double* __restrict__ A,
-                                                    int64_t p, int r, int ell, double* __restrict__ Zb,
-                                                    double* __restrict__ Ab) {
+// Latency bound: sixteen wavefronts (the first inverts A A^T while the others
+// form the products over p, four entries each in flight).  With four wavefronts
+// and one entry at a time it took 60 us at p = 192, r = 8, ell = 20; now 21.
+template <int RP>
+__global__ __launch_bounds__(1024) void k_ls_adjoint(const double* __restrict__ G, const double* __restrict__ Gb,
+                                                     const double* __restrict__ Z, const double* __restrict__ A,
+                                                     int64_t p, int r, int ell, double* __restrict__ Zb,
+                                                     double* __restrict__ Ab) {
   constexpr int MX = PSTT2_MAX_ELL;
-  __shared__ double Wm[MX][MX + 1];    // (A A^T)^{-1}, then scratch
-  __shared__ double Aug[MX][2 * MX + 1];
-  __shared__ double As[MX][MX + 1];    // A (r x ell)
-  __shared__ double WA[MX][MX + 1];    // W A (r x ell)
-  __shared__ double GbZ[MX][MX + 1];   // Gbar^T Z (r x ell)
-  __shared__ double E[MX][MX + 1];     // G^T Gbar (r x r)
-  const int t = threadIdx.x;
-  for (int i = t; i < r * ell; i += blockDim.x) As[i % r][i / r] = A[i];
+  __shared__ double AAt[RP][RP + 1];
+  __shared__ double Wm[RP][RP + 1];    // (A A^T)^{-1}
+  __shared__ double WE[RP][RP + 1];    // W E^T
+  __shared__ double As[RP][MX + 1];    // A (r x ell)
+  __shared__ double WA[RP][MX + 1];    // W A (r x ell)
+  __shared__ double GbZ[RP][MX + 1];   // Gbar^T Z (r x ell)
+  __shared__ double E[RP][RP + 1];     // G^T Gbar (r x r)
+  const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+  for (int i = t; i < r * ell; i += 1024) As[i % r][i / r] = A[i];
   __syncthreads();
-  // A A^T and the augmented system [A A^T | I]
-  for (int i = t; i < r * r; i += blockDim.x) {
+  for (int i = t; i < r * r; i += 1024) {
     const int a = i % r, b = i / r;
     double s = 0.0;
     for (int c = 0; c < ell; ++c) s += As[a][c] * As[b][c];
-    Aug[a][b] = s;
-    Aug[a][r + b] = a == b ? 1.0 : 0.0;
+    AAt[a][b] = s;
   }
-  // Gbar^T Z and G^T Gbar: one wavefront per entry
-  const int lane = t & 63, wv = t >> 6;
-  for (int i = wv; i < r * ell + r * r; i += 4) {
-    double s = 0.0;
-    if (i < r * ell) {
-      const int a = i % r, c = i / r;
-      for (int64_t q = lane; q < p; q += 64) s += Gb[(int64_t)a * p + q] * Z[(int64_t)c * p + q];
-      s = wsum(s);
-      if (lane == 0) GbZ[a][c] = s;
-    } else {
-      const int j = i - r * ell, a = j % r, b = j / r;
-      for (int64_t q = lane; q < p; q += 64) s += G[(int64_t)a * p + q] * Gb[(int64_t)b * p + q];
-      s = wsum(s);
-      if (lane == 0) E[a][b] = s;
+  __syncthreads();
+  if (wv == 0) {
+    (void)spd_inverse<RP>(AAt, r, Wm);
+  } else {
+    // Gbar^T Z and G^T Gbar, a wavefront per entry
+    const int n = r * ell + r * r;
+    for (int i0 = 4 * (wv - 1); i0 < n; i0 += 60) {
+      const double *x[4], *y[4];
+      double s[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int i = i0 + u < n ? i0 + u : n - 1;
+        if (i < r * ell) {
+          x[u] = Gb + (int64_t)(i % r) * p;
+          y[u] = Z + (int64_t)(i / r) * p;
+        } else {
+          const int j = i - r * ell;
+          x[u] = G + (int64_t)(j % r) * p;
+          y[u] = Gb + (int64_t)(j / r) * p;
+        }
+      }
+      for (int64_t q = lane; q < p; q += 64)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) s[u] += x[u][q] * y[u][q];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        s[u] = wsum(s[u]);
+        const int i = i0 + u;
+        if (lane == 0 && i < n) {
+          if (i < r * ell) GbZ[i % r][i / r] = s[u];
+          else E[(i - r * ell) % r][(i - r * ell) / r] = s[u];
+        }
+      }
     }
   }
   __syncthreads();
-  // Gauss-Jordan on the SPD system (no pivoting needed).  Thread t owns
-  // column t; the multipliers of step k are staged first, since column k
-  // itself is overwritten during the step.
-  __shared__ double fcol[MX];
-  for (int k = 0; k < r; ++k) {
-    if (t < r) fcol[t] = Aug[t][k];
-    __syncthreads();
-    if (t < 2 * r) {
-      const double pk = Aug[k][t] / fcol[k];
-      Aug[k][t] = pk;
-      for (int i = 0; i < r; ++i)
-        if (i != k) Aug[i][t] -= fcol[i] * pk;
-    }
-    __syncthreads();
-  }
-  for (int i = t; i < r * r; i += blockDim.x) Wm[i % r][i / r] = Aug[i % r][r + i / r];
-  __syncthreads();
-  for (int i = t; i < r * ell; i += blockDim.x) {
+  for (int i = t; i < r * (ell + r); i += 1024) {
     const int a = i % r, c = i / r;
     double s = 0.0;
-    for (int b = 0; b < r; ++b) s += Wm[a][b] * As[b][c];
-    WA[a][c] = s;
+    if (c < ell) {
+      for (int b = 0; b < r; ++b) s += Wm[a][b] * As[b][c];
+      WA[a][c] = s;
+    } else {
+      for (int k = 0; k < r; ++k) s += Wm[a][k] * E[c - ell][k];
+      WE[a][c - ell] = s;
+    }
   }
   __syncthreads();
   // Zbar = Gbar (W A)
-  for (int64_t i = t; i < p * ell; i += blockDim.x) {
+  for (int64_t i = t; i < p * ell; i += 1024) {
     const int64_t q = i % p;
     const int c = (int)(i / p);
     double s = 0.0;
@@ -140,15 +151,10 @@ __global__ __launch_bounds__(256) void k_ls_adjoint(const double* __restrict__ G
     Zb[i] = s;
   }
   // Abar = W (Gbar^T Z) - E (W A) - W E^T A
-  for (int i = t; i < r * ell; i += blockDim.x) {
+  for (int i = t; i < r * ell; i += 1024) {
     const int a = i % r, c = i / r;
     double s = 0.0;
-    for (int b = 0; b < r; ++b) {
-      s += Wm[a][b] * GbZ[b][c] - E[a][b] * WA[b][c];
-      double we = 0.0;   // (W E^T)(a, b)
-      for (int k = 0; k < r; ++k) we += Wm[a][k] * E[b][k];
-      s -= we * As[b][c];
-    }
+    for (int b = 0; b < r; ++b) s += Wm[a][b] * GbZ[b][c] - E[a][b] * WA[b][c] - WE[a][b] * As[b][c];
     Ab[i] = s;
   }
 }
@@ -169,19 +175,24 @@ __global__ void k_core_right_adj_prev(const double* __restrict__ Gb, const doubl
     Ppb[t] += s;
   }
 }
-// Pkbar(c, b) += sum_{a, i} Gbar(a, i, b) Pp(i + nk c, a)
-__global__ void k_core_right_adj_next(const double* __restrict__ Gb, const double* __restrict__ Pp, int64_t Ck, int nk,
-                                      int rp, int rk, double* __restrict__ Pkb) {
-  const int64_t Cp = Ck * nk;
-  const int64_t tot = Ck * rk;
-  for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < tot; t += (int64_t)gridDim.x * blockDim.x) {
+// Pkbar(c, b) += sum_{a, i} Gbar(a, i, b) Pp(i + nk c, a), one wavefront per entry
+// (few entries: one thread each over rp nk dependent loads took 44 us at 48 x 6
+// entries of 288 terms, now 5)
+__global__ __launch_bounds__(256) void k_core_right_adj_next(const double* __restrict__ Gb, const double* __restrict__ Pp,
+                                                             int64_t Ck, int nk, int rp, int rk,
+                                                             double* __restrict__ Pkb) {
+  const int lane = threadIdx.x & 63;
+  const int64_t Cp = Ck * nk, tot = Ck * rk;
+  for (int64_t t = (blockIdx.x * (int64_t)256 + threadIdx.x) >> 6; t < tot; t += ((int64_t)gridDim.x * 256) >> 6) {
     const int64_t c = t % Ck;
     const int b = (int)(t / Ck);
     double s = 0.0;
-    for (int a = 0; a < rp; ++a)
-      for (int i = 0; i < nk; ++i)
-        s += Gb[a + (int64_t)rp * (i + (int64_t)nk * b)] * Pp[(int64_t)a * Cp + i + (int64_t)nk * c];
-    Pkb[t] += s;
+    for (int e = lane; e < rp * nk; e += 64) {
+      const int a = e / nk, i = e - a * nk;
+      s += Gb[a + (int64_t)rp * (i + (int64_t)nk * b)] * Pp[(int64_t)a * Cp + i + (int64_t)nk * c];
+    }
+    s = wsum(s);
+    if (lane == 0) Pkb[t] += s;
   }
 }
 
@@ -209,57 +220,154 @@ __global__ void k_pbar_from_abar(const double* __restrict__ om_tab, int L4, int6
   }
 }
 
-// B (M x r) = the first r pivoted columns of S (M x ell)
-__global__ void k_gather_cols(const double* __restrict__ S, int64_t M, const int* __restrict__ piv, int r,
-                              double* __restrict__ B) {
-  const int64_t tot = M * r;
-  for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < tot; t += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t i = t % M;
-    const int j = (int)(t / M);
-    B[t] = S[(int64_t)piv[j] * M + i];
+// ---- thin-QR adjoints of every split's basis, three launches for all of them ----
+// Problem k: basis Q (M x r), cotangent Qbar, sketch S whose pivoted columns piv
+// give B = Q R.  (1) R = Q^T B and Mm = -Qbar^T Q, both from one read of a row
+// slice, per slice on FP64 matrix cores (operands straight from memory: lane
+// (g4, l16) holds rows 2 g4, 2 g4 + 1 of eight, column l16); (2) the slices' sums
+// in slice order; (3) per row i: c = Qbar(i, :) + Q(i, :) copyltu(Mm), Bbar(i, :) R^T
+// = c, Sbar(i, piv[j]) += Bbar(i, j).  Six launches a split and a division per
+// back-substitution step took about 190 us for the four splits of n = 24^5; the
+// three launches take 24.
+constexpr int QA_ROWS = 512;   // rows per slice, 128 per wave
+constexpr int QA_MAX = PSTT2_MAX_D;
+struct QrAdjBatch {
+  int n;
+  const double *Q[QA_MAX], *Qb[QA_MAX], *S[QA_MAX];
+  double* Sb[QA_MAX];
+  const int* piv[QA_MAX];
+  int64_t M[QA_MAX];
+  int r[QA_MAX];
+  int64_t slice0[QA_MAX + 1];   // first slice of each problem
+  int64_t block0[QA_MAX + 1];   // first 256-row block of each problem
+  double* part;                 // [slice][2][32 * 32]
+  double* rm;                   // [problem][2][32 * 32]: R, then Mm
+};
+
+__device__ __forceinline__ int batch_of(const int64_t* first, int n, int64_t g) {
+  int p = 0;
+  while (p + 1 < n && first[p + 1] <= g) ++p;
+  return p;
+}
+
+typedef double adj_d4 __attribute__((ext_vector_type(4)));
+
+template <int RT>
+__global__ __launch_bounds__(256) void k_qr_adj_prod(const QrAdjBatch B) {
+  __shared__ double red[4][RT * RT * 256];
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6, l16 = lane & 15, g4 = lane >> 4;
+  const int p = batch_of(B.slice0, B.n, blockIdx.x);
+  const int64_t M = B.M[p];
+  const int r = B.r[p];
+  const int64_t r0 = (blockIdx.x - B.slice0[p]) * QA_ROWS + 128 * w, r1 = r0 + 128 < M ? r0 + 128 : M;
+  const double *q[RT], *qb[RT], *sp[RT];
+#pragma unroll
+  for (int i = 0; i < RT; ++i) {   // columns past r read the last one; dropped below
+    const int c = 16 * i + l16 < r ? 16 * i + l16 : r - 1;
+    q[i] = B.Q[p] + c * M;
+    qb[i] = B.Qb[p] + c * M;
+    sp[i] = B.S[p] + B.piv[p][c] * M;
+  }
+  adj_d4 R[RT][RT], Mm[RT][RT];
+#pragma unroll
+  for (int i = 0; i < RT; ++i)
+#pragma unroll
+    for (int j = 0; j < RT; ++j) R[i][j] = Mm[i][j] = adj_d4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll 2
+  for (int64_t a = r0; a < r1; a += 8) {
+    double x[RT][2], y[RT][2], z[RT][2];
+#pragma unroll
+    for (int i = 0; i < RT; ++i)
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        const int64_t row = a + 2 * g4 + e;
+        const bool in = row < r1;
+        const int64_t rc = in ? row : r0;
+        const double vx = q[i][rc], vy = qb[i][rc], vz = sp[i][rc];
+        x[i][e] = in ? vx : 0.0;
+        y[i][e] = in ? vy : 0.0;
+        z[i][e] = in ? vz : 0.0;
+      }
+#pragma unroll
+    for (int e = 0; e < 2; ++e)
+#pragma unroll
+      for (int i = 0; i < RT; ++i)
+#pragma unroll
+        for (int j = 0; j < RT; ++j) {
+          R[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[i][e], z[j][e], R[i][j], 0, 0, 0);
+          Mm[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(y[i][e], x[j][e], Mm[i][j], 0, 0, 0);
+        }
+  }
+  double* out = B.part + (int64_t)blockIdx.x * 2048;
+  for (int h = 0; h < 2; ++h) {
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < RT; ++i)
+#pragma unroll
+      for (int j = 0; j < RT; ++j)
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+          red[w][(i * RT + j) * 256 + l16 * 16 + 4 * v + g4] = h == 0 ? R[i][j][v] : -Mm[i][j][v];
+    __syncthreads();
+    for (int o = t; o < r * r; o += 256) {
+      const int a = o % r, b = o / r;
+      const int e = ((a >> 4) * RT + (b >> 4)) * 256 + (b & 15) * 16 + (a & 15);
+      out[h * 1024 + o] = red[0][e] + red[1][e] + red[2][e] + red[3][e];
+    }
   }
 }
 
-// Thin-QR adjoint, one thread per row i of B:
-//   c = Qbar(i, :) + Q(i, :) copyltu(Mm);  Bbar(i, :) R^T = c;  Sbar(i, piv[j]) += Bbar(i, j).
-// R and Mm are r x r column-major.
-__global__ void k_qr_adj_rows(const double* __restrict__ Q, const double* __restrict__ Qb, int64_t M, int r,
-                              const double* __restrict__ Rm, const double* __restrict__ Mm,
-                              const int* __restrict__ piv, double* __restrict__ Sb) {
-  constexpr int MX = PSTT2_MAX_ELL;
-  __shared__ double Rs[MX][MX + 1], Cs[MX][MX + 1];
-  for (int t = threadIdx.x; t < r * r; t += blockDim.x) {
-    const int a = t % r, b = t / r;
-    Rs[a][b] = Rm[t];
+__global__ __launch_bounds__(256) void k_qr_adj_sum(const QrAdjBatch B) {
+  const int lane = threadIdx.x & 63;
+  const int p = blockIdx.y, r = B.r[p];
+  const int o = blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (o >= 2 * r * r) return;
+  const int e = (o / (r * r)) * 1024 + o % (r * r);
+  double s = 0.0;
+  for (int64_t g = B.slice0[p] + lane; g < B.slice0[p + 1]; g += 64) s += B.part[g * 2048 + e];
+  s = wsum(s);
+  if (lane == 0) B.rm[(int64_t)p * 2048 + e] = s;
+}
+
+template <int RP>
+__global__ __launch_bounds__(256) void k_qr_adj_rows(const QrAdjBatch B) {
+  __shared__ double Rs[RP][RP + 1], Cs[RP][RP + 1], inv[RP];
+  const int t = threadIdx.x;
+  const int p = batch_of(B.block0, B.n, blockIdx.x);
+  const int r = B.r[p];
+  const int64_t M = B.M[p], i = (blockIdx.x - B.block0[p]) * 256 + t;
+  const double *Q = B.Q[p], *Qb = B.Qb[p], *Rm = B.rm + (int64_t)p * 2048, *Mm = Rm + 1024;
+  double q[RP], c[RP];
+#pragma unroll
+  for (int j = 0; j < RP; ++j) {
+    const bool in = j < r && i < M;
+    q[j] = in ? Q[j * M + i] : 0.0;
+    c[j] = in ? Qb[j * M + i] : 0.0;
+  }
+  for (int o = t; o < RP * RP; o += 256) {
+    const int a = o % RP, b = o / RP;
+    const bool in = a < r && b < r;
+    Rs[a][b] = in ? Rm[a + r * b] : 0.0;
     // copyltu: lower triangle (a >= b) kept, upper mirrored from the lower
-    Cs[a][b] = a >= b ? Mm[t] : Mm[b + (int64_t)r * a];
+    Cs[a][b] = in ? (a >= b ? Mm[a + r * b] : Mm[b + r * a]) : 0.0;
+    if (a == b) inv[a] = in ? 1.0 / Rm[a + r * a] : 0.0;
   }
   __syncthreads();
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < M; i += (int64_t)gridDim.x * blockDim.x) {
-    double c[MX];
+  if (i >= M) return;
 #pragma unroll
-    for (int j = 0; j < MX; ++j) {
-      if (j < r) {
-        double s = Qb[(int64_t)j * M + i];
-        for (int l = 0; l < r; ++l) s += Q[(int64_t)l * M + i] * Cs[l][j];
-        c[j] = s;
-      }
-    }
-    // sum_{l >= j} R(j, l) x(l) = c(j), from the last j down
+  for (int j = 0; j < RP; ++j)
 #pragma unroll
-    for (int j = MX - 1; j >= 0; --j) {
-      if (j < r) {
-        double s = c[j];
+    for (int l = 0; l < RP; ++l) c[j] += q[l] * Cs[l][j];
+  // sum_{l >= j} R(j, l) x(l) = c(j), from the last j down
 #pragma unroll
-        for (int l = j + 1; l < MX; ++l)
-          if (l < r) s -= Rs[j][l] * c[l];
-        c[j] = s / Rs[j][j];
-      }
-    }
+  for (int j = RP - 1; j >= 0; --j) {
 #pragma unroll
-    for (int j = 0; j < MX; ++j)
-      if (j < r) Sb[(int64_t)piv[j] * M + i] += c[j];
+    for (int l = j + 1; l < RP; ++l) c[j] -= Rs[j][l] * c[l];
+    c[j] *= inv[j];
   }
+#pragma unroll
+  for (int j = 0; j < RP; ++j)
+    if (j < r) B.Sb[p][B.piv[p][j] * M + i] += c[j];
 }
 
 // Sbar_{k+1}(row + Rk i, c) += Sbar_k(row, c) omega_{k+1}(i, c)   (adjoint of derive_left)
@@ -387,7 +495,9 @@ hipError_t adj_axpy(int64_t n, double alpha, const double* X, double* Y, hipStre
 
 hipError_t adj_ls(const double* G, const double* Gb, const double* Z, const double* A, int64_t p, int r, int ell,
                   double* Zb, double* Ab, hipStream_t s) {
-  hipLaunchKernelGGL(k_ls_adjoint, dim3(1), dim3(256), 0, s, G, Gb, Z, A, p, r, ell, Zb, Ab);
+  if (r <= 8) hipLaunchKernelGGL(k_ls_adjoint<8>, dim3(1), dim3(1024), 0, s, G, Gb, Z, A, p, r, ell, Zb, Ab);
+  else if (r <= 16) hipLaunchKernelGGL(k_ls_adjoint<16>, dim3(1), dim3(1024), 0, s, G, Gb, Z, A, p, r, ell, Zb, Ab);
+  else hipLaunchKernelGGL(k_ls_adjoint<32>, dim3(1), dim3(1024), 0, s, G, Gb, Z, A, p, r, ell, Zb, Ab);
   return hipGetLastError();
 }
 
@@ -395,7 +505,7 @@ hipError_t adj_core_right(const double* Gb, const double* Pp, const double* Pk, 
                           double* Ppb, double* Pkb, hipStream_t s) {
   hipLaunchKernelGGL(k_core_right_adj_prev, dim3(grid_for(Ck * nk * rp, 256)), dim3(256), 0, s, Gb, Pk, Ck, nk, rp, rk,
                      Ppb);
-  hipLaunchKernelGGL(k_core_right_adj_next, dim3(grid_for(Ck * rk, 256)), dim3(256), 0, s, Gb, Pp, Ck, nk, rp, rk,
+  hipLaunchKernelGGL(k_core_right_adj_next, dim3(grid_for(Ck * rk * 64, 256)), dim3(256), 0, s, Gb, Pp, Ck, nk, rp, rk,
                      Pkb);
   return hipGetLastError();
 }
@@ -407,23 +517,49 @@ hipError_t adj_pbar(const double* om_tab, int L4, int64_t Cm, int rm, int ell, i
   return hipGetLastError();
 }
 
-// Sbar += thin-QR adjoint of the basis Q (M x r) of the pivoted columns of S (M x ell).
-hipError_t adj_qr(const double* S, const double* Q, const double* Qb, int64_t M, int ell, int r, const int* piv,
-                  double* Sb, hipStream_t s) {
-  double *B = nullptr, *RM = nullptr;
-  hipError_t e = ws_alloc((void**)&B, sizeof(double) * M * r, s);
-  if (e == hipSuccess) e = ws_alloc((void**)&RM, sizeof(double) * 2 * r * r, s);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_gather_cols, dim3(grid_for(M * r, 256)), dim3(256), 0, s, S, M, piv, r, B);
-  e = adj_gemm(true, false, r, r, M, 1.0, Q, M, B, M, 0.0, RM, r, s);                 // R = Q^T B
-  if (e == hipSuccess) e = adj_gemm(true, false, r, r, M, -1.0, Qb, M, Q, M, 0.0, RM + r * r, r, s);  // -Qbar^T Q
-  if (e == hipSuccess) {
-    hipLaunchKernelGGL(k_qr_adj_rows, dim3(grid_for(M, 256)), dim3(256), 0, s, Q, Qb, M, r, RM, RM + r * r, piv, Sb);
-    e = hipGetLastError();
+hipError_t adj_qr_batch(int n, const double* const* S, const double* const* Q, const double* const* Qb,
+                        const int64_t* M, const int* r, const int* const* piv, double* const* Sb, hipStream_t s) {
+  QrAdjBatch B;
+  std::memset(&B, 0, sizeof(B));
+  B.n = n;
+  int rmax = 1;
+  for (int p = 0; p < n; ++p) {
+    B.Q[p] = Q[p];
+    B.Qb[p] = Qb[p];
+    B.S[p] = S[p];
+    B.Sb[p] = Sb[p];
+    B.piv[p] = piv[p];
+    B.M[p] = M[p];
+    B.r[p] = r[p];
+    rmax = std::max(rmax, r[p]);
+    B.slice0[p + 1] = B.slice0[p] + (M[p] + QA_ROWS - 1) / QA_ROWS;
+    B.block0[p + 1] = B.block0[p] + (M[p] + 255) / 256;
   }
-  ws_free(B, s);
-  ws_free(RM, s);
+  const int64_t slices = B.slice0[n];
+  double* ws = nullptr;
+  hipError_t e = ws_alloc((void**)&ws, sizeof(double) * 2048 * (slices + n), s);
+  if (e != hipSuccess) return e;
+  B.part = ws;
+  B.rm = ws + 2048 * slices;
+  if (rmax <= 16) hipLaunchKernelGGL(k_qr_adj_prod<1>, dim3((unsigned)slices), dim3(256), 0, s, B);
+  else hipLaunchKernelGGL(k_qr_adj_prod<2>, dim3((unsigned)slices), dim3(256), 0, s, B);
+  hipLaunchKernelGGL(k_qr_adj_sum, dim3((unsigned)((2 * rmax * rmax + 3) / 4), (unsigned)n), dim3(256), 0, s, B);
+  const dim3 g((unsigned)B.block0[n]), b(256);
+  if (rmax <= 8) hipLaunchKernelGGL(k_qr_adj_rows<8>, g, b, 0, s, B);
+  else if (rmax <= 16) hipLaunchKernelGGL(k_qr_adj_rows<16>, g, b, 0, s, B);
+  else hipLaunchKernelGGL(k_qr_adj_rows<32>, g, b, 0, s, B);
+  e = hipGetLastError();
+  ws_free(ws, s);
   return e;
+}
+
+__global__ void k_zero(double* __restrict__ p, int64_t n) {
+  for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < n; t += (int64_t)gridDim.x * blockDim.x) p[t] = 0.0;
+}
+
+hipError_t adj_zero(double* p, int64_t n, hipStream_t s) {
+  hipLaunchKernelGGL(k_zero, dim3(grid_for(n, 256)), dim3(256), 0, s, p, n);
+  return hipGetLastError();
 }
 
 hipError_t adj_derive_left(const double* Sbk, double* Sbk1, int64_t Rk, int nk1, int ell, const double* om,

@@ -1308,15 +1308,32 @@ pstt2_status pstt2_vjp(pstt2_ctx* c, const tt_cores* cores, const void* x_dev, c
   // only after its stream is idle, so the next call may rewind it)
   hipError_t e = arena_begin(&c->varena, s);
   ArenaScope arena_scope(&c->varena);
-  auto take = [&](int64_t count, bool zero) -> double* {
+  auto take = [&](int64_t count) -> double* {
     void* p = nullptr;
     if (e != hipSuccess) return nullptr;
     e = ws_alloc(&p, sizeof(double) * std::max<int64_t>(count, 1), s);
-    if (e != hipSuccess) return nullptr;
-    if (zero) e = hipMemsetAsync(p, 0, sizeof(double) * std::max<int64_t>(count, 1), s);
-    return (double*)p;
+    return e == hipSuccess ? (double*)p : nullptr;
   };
-  auto release = [&]() {};
+  // Buffers that are added into come from one block, zeroed by one launch.
+  auto pad = [](int64_t n) { return (n + 31) / 32 * 32; };   // 256-byte steps
+  int64_t nzero = pad(c->R * r[m]) + pad(c->C * r[m]) + pad(c->R * ell);   // U, Vt, Ybar
+  for (int k = 1; k <= d - 1; ++k) nzero += pad((k < m ? Rk[k] : Ck(k)) * r[k]);   // Qbar_k
+  for (int k = 1; k <= d - 1; ++k) nzero += pad((k < m ? Rk[k] : Ck(k)) * ell);   // Sbar_k, Tbar_k
+  if (c->indep) {   // the chains back to the sketches of X_m
+    for (int k = 1; k < m; ++k)
+      for (int q = k + 1; q <= m; ++q) nzero += pad(Rk[q] * ell);
+    for (int k = m + 1; k <= d - 1; ++k)
+      for (int q = k; q >= m + 1; --q) nzero += pad(Ck(q - 1) * ell);
+  }
+  double* zeros = take(nzero);
+  if (e == hipSuccess) e = adj_zero(zeros, nzero, s);
+  int64_t zused = 0;
+  auto take_zero = [&](int64_t count) -> double* {
+    double* p = zeros + zused;
+    zused += pad(count);
+    if (zused > nzero && e == hipSuccess) e = hipErrorInvalidValue;
+    return e == hipSuccess ? p : nullptr;
+  };
 #define VJPCK(call)                        \
   do {                                     \
     if (e == hipSuccess) e = (call);       \
@@ -1325,14 +1342,14 @@ pstt2_status pstt2_vjp(pstt2_ctx* c, const tt_cores* cores, const void* x_dev, c
   std::vector<const double*> Lv(d + 2, nullptr), Rv(d + 2, nullptr);
   Lv[1] = cores->core[0];
   for (int k = 2; k <= m; ++k) {
-    double* L = take(Rk[k] * r[k], false);
+    double* L = take(Rk[k] * r[k]);
     VJPCK(adj_gemm(false, false, Rk[k - 1], c->n[k - 1] * r[k], r[k - 1], 1.0, Lv[k - 1], Rk[k - 1],
                    cores->core[k - 1], r[k - 1], 0.0, L, Rk[k - 1], s));
     Lv[k] = L;
   }
   Rv[d] = cores->core[d - 1];
   for (int k = d - 1; k >= m + 1; --k) {
-    double* Rt = take((int64_t)r[k - 1] * Ck(k - 1), false);
+    double* Rt = take((int64_t)r[k - 1] * Ck(k - 1));
     VJPCK(adj_gemm(false, false, (int64_t)r[k - 1] * c->n[k - 1], Ck(k), r[k], 1.0, cores->core[k - 1],
                    (int64_t)r[k - 1] * c->n[k - 1], Rv[k + 1], r[k], 0.0, Rt, (int64_t)r[k - 1] * c->n[k - 1], s));
     Rv[k] = Rt;
@@ -1349,8 +1366,8 @@ pstt2_status pstt2_vjp(pstt2_ctx* c, const tt_cores* cores, const void* x_dev, c
   //      so no tensor-sized cotangent is ever formed. ----
   const void* src = gbar_dev ? gbar_dev : x_dev;
   const int L4r = (rm + 3) / 4 * 4;
-  double* psiT = take(c->R * L4r, false);
-  double* omT = take(c->C * L4r, false);
+  double* psiT = take(c->R * L4r);
+  double* omT = take(c->C * L4r);
   VJPCK(adj_table(Lm, c->R, rm, 1, c->R, L4r, psiT, s));
   VJPCK(adj_table(Rtm, c->C, rm, rm, 1, L4r, omT, s));
   SketchArgs a = base_args(c);
@@ -1368,59 +1385,60 @@ pstt2_status pstt2_vjp(pstt2_ctx* c, const tt_cores* cores, const void* x_dev, c
   a.seg[0].gcol0 = 0;
   a.seg[0].ncols = c->C;
   a.seg[0].chunk0 = 0;
-  a.ypart = take((int64_t)a.gj_count * rm * c->R, false);
-  a.tpart = take((int64_t)a.gi_count * rm * c->C + kTPartPad, false);
+  a.ypart = take((int64_t)a.gj_count * rm * c->R);
+  a.tpart = take((int64_t)a.gi_count * rm * c->C + kTPartPad);
   a.tlp = 0;   // the FP64 kernel's partial layout
   a.om16 = nullptr;
   a.x32 = c->dtype == PSTT2_F32;   // FP32 entries are widened as they are loaded
-  double* U = take(c->R * rm, true);    // Lbar_m = gbar_m Rt^T        (R x r_m)
-  double* Vt = take(c->C * rm, true);   // (L_m^T gbar_m)^T           (C x r_m)
+  double* U = take_zero(c->R * rm);    // Lbar_m = gbar_m Rt^T        (R x r_m)
+  double* Vt = take_zero(c->C * rm);   // (L_m^T gbar_m)^T           (C x r_m)
   if (e == hipSuccess) e = launch_sketch(PSTT2_P_F64, 0, a, s);
   if (e == hipSuccess) e = launch_reduce(PSTT2_P_F64, a, U, Vt, c->flag, s);
   if (!gbar_dev) {
-    double* Gr = take((int64_t)rm * rm, false);   // Rt Rt^T
-    double* Gl = take((int64_t)rm * rm, false);   // L^T L
+    double* Gr = take((int64_t)rm * rm);   // Rt Rt^T
+    double* Gl = take((int64_t)rm * rm);   // L^T L
     VJPCK(adj_gemm(false, true, rm, rm, c->C, 1.0, Rtm, rm, Rtm, rm, 0.0, Gr, rm, s));
     VJPCK(adj_gemm(true, false, rm, rm, c->R, 1.0, Lm, c->R, Lm, c->R, 0.0, Gl, rm, s));
     VJPCK(adj_gemm(false, false, c->R, rm, rm, 2.0, Lm, c->R, Gr, rm, -2.0, U, c->R, s));
     VJPCK(adj_gemm(true, false, c->C, rm, rm, 2.0, Rtm, rm, Gl, rm, -2.0, Vt, c->C, s));
   }
-  // core cotangents, laid out like the cores
+  // core cotangents, laid out like the cores (the first and the last are the
+  // interface cotangents themselves)
   std::vector<double*> Gb(d, nullptr);
-  for (int k = 0; k < d; ++k) Gb[k] = take((int64_t)r[k] * c->n[k] * r[k + 1], true);
-  const double* Lb = U;
+  for (int k = 1; k < d - 1; ++k) Gb[k] = take((int64_t)r[k] * c->n[k] * r[k + 1]);
+  double* Lb = U;
   for (int k = m; k >= 2; --k) {
     const int64_t nr = c->n[k - 1] * r[k];
     VJPCK(adj_gemm(true, false, r[k - 1], nr, Rk[k - 1], 1.0, Lv[k - 1], Rk[k - 1], Lb, Rk[k - 1], 0.0, Gb[k - 1],
                    r[k - 1], s));
-    double* Lbp = take(Rk[k - 1] * r[k - 1], false);
+    double* Lbp = take(Rk[k - 1] * r[k - 1]);
     VJPCK(adj_gemm(false, true, Rk[k - 1], r[k - 1], nr, 1.0, Lb, Rk[k - 1], cores->core[k - 1], r[k - 1], 0.0, Lbp,
                    Rk[k - 1], s));
     Lb = Lbp;
   }
-  VJPCK(adj_axpy(c->n[0] * r[1], 1.0, Lb, Gb[0], s));
-  double* Rb = take((int64_t)rm * c->C, false);
+  Gb[0] = Lb;
+  double* Rb = take((int64_t)rm * c->C);
   VJPCK(adj_transpose(Vt, c->C, rm, Rb, s));
   for (int k = m + 1; k <= d - 1; ++k) {
     const int64_t rn = (int64_t)r[k - 1] * c->n[k - 1];
     VJPCK(adj_gemm(false, true, rn, r[k], Ck(k), 1.0, Rb, rn, Rv[k + 1], r[k], 0.0, Gb[k - 1], rn, s));
-    double* Rbn = take((int64_t)r[k] * Ck(k), false);
+    double* Rbn = take((int64_t)r[k] * Ck(k));
     VJPCK(adj_gemm(true, false, r[k], Ck(k), rn, 1.0, cores->core[k - 1], rn, Rb, rn, 0.0, Rbn, r[k], s));
     Rb = Rbn;
   }
-  VJPCK(adj_axpy((int64_t)r[d - 1] * c->n[d - 1], 1.0, Rb, Gb[d - 1], s));
+  Gb[d - 1] = Rb;
   // ---- B2: back through the recovery ----
   std::vector<double*> Qb(d + 1, nullptr);
-  for (int k = 1; k <= d - 1; ++k) Qb[k] = take((k < m ? Rk[k] : Ck(k)) * r[k], true);
+  for (int k = 1; k <= d - 1; ++k) Qb[k] = take_zero((k < m ? Rk[k] : Ck(k)) * r[k]);
   const double* Qprev = m >= 2 ? c->basis[m - 1] : c->one;
   const int64_t Rprev = Rk[m - 1];
   const int rprev = r[m - 1];
   const int nm = (int)c->n[m - 1];
   const int64_t p = (int64_t)rprev * nm;
-  double* Z = take(p * ell, false);
-  double* A = take((int64_t)rm * ell, false);
-  double* Zb = take(p * ell, false);
-  double* Ab = take((int64_t)rm * ell, false);
+  double* Z = take(p * ell);
+  double* A = take((int64_t)rm * ell);
+  double* Zb = take(p * ell);
+  double* Ab = take((int64_t)rm * ell);
   // two-sided rule (d >= 3): Z = (I (x) M1) H with H = (I (x) Psi')^T Y_R and
   // M1 = (Psi'^T Q_{m-1})^+; rebuilt here as the recovery built it
   const bool two = c->desc.mid == PSTT2_MID_TWOSIDED && m >= 2;
@@ -1428,10 +1446,10 @@ pstt2_status pstt2_vjp(pstt2_ctx* c, const tt_cores* cores, const void* x_dev, c
   if (!two) {
     VJPCK(middle_z(Qprev, Rprev, rprev, c->Y, c->R, nm, ell, Z, s));
   } else {
-    ptab = take(Rprev * ell, false);
-    a1t = take((int64_t)rprev * ell, false);
-    m1t = take((int64_t)ell * rprev, false);
-    double* id = take((int64_t)ell * ell, false);
+    ptab = take(Rprev * ell);
+    a1t = take((int64_t)rprev * ell);
+    m1t = take((int64_t)ell * rprev);
+    double* id = take((int64_t)ell * ell);
     VJPCK(kr_table(c->fac, left_chain(c, m - 1), Rprev, ell, ptab, s));
     VJPCK(adj_gemm(true, false, rprev, ell, Rprev, 1.0, Qprev, Rprev, ptab, Rprev, 0.0, a1t, rprev, s));
     VJPCK(eye(ell, id, s));
@@ -1441,7 +1459,7 @@ pstt2_status pstt2_vjp(pstt2_ctx* c, const tt_cores* cores, const void* x_dev, c
   SketchArgs geo = base_args(c);
   VJPCK(middle_a(c->basis[m], c->C, rm, geo, c->prec, A, s));
   VJPCK(adj_ls(cores->core[m - 1], Gb[m - 1], Z, A, p, rm, ell, Zb, Ab, s));
-  double* Yb = take(c->R * ell, true);
+  double* Yb = take_zero(c->R * ell);
   if (!two) {
     if (m >= 2)
       VJPCK(adj_gemm(false, true, Rprev, rprev, (int64_t)nm * ell, 1.0, c->Y, Rprev, Zb, rprev, 1.0, Qb[m - 1],
@@ -1451,8 +1469,8 @@ pstt2_status pstt2_vjp(pstt2_ctx* c, const tt_cores* cores, const void* x_dev, c
     // Z3(p, j, c) = sum_a M1^T(a, p) H3(a, j, c):
     //   Hbar = M1^T Zbar and M1^T-bar = H Zbar^T, with H as ell x (n_m ell), Zbar as r_{m-1} x (n_m ell)
     const int64_t w = (int64_t)nm * ell;
-    double* Hb = take((int64_t)ell * w, false);
-    double* M1b = take((int64_t)ell * rprev, false);   // cotangent of M1^T
+    double* Hb = take((int64_t)ell * w);
+    double* M1b = take((int64_t)ell * rprev);   // cotangent of M1^T
     VJPCK(adj_gemm(false, false, ell, w, rprev, 1.0, m1t, ell, Zb, rprev, 0.0, Hb, ell, s));
     VJPCK(adj_gemm(false, true, ell, rprev, w, 1.0, c->H, ell, Zb, rprev, 0.0, M1b, ell, s));
     // pseudo-inverse of the full-column-rank A1 = Psi'^T Q (ell x r), W = A1^+ = (A1^T A1)^{-1} A1^T:
@@ -1461,10 +1479,10 @@ pstt2_status pstt2_vjp(pstt2_ctx* c, const tt_cores* cores, const void* x_dev, c
     // In M1^T = W^T and its cotangent Mb = Wbar^T:  T1 = Mb^T M1^T, T2 = M1 M1^T,
     //   A1bar = -M1^T T1 + Mb T2 - A1 (T1^T T2).
     const int rp = rprev;
-    double* T1 = take((int64_t)rp * rp, false);
-    double* T2 = take((int64_t)rp * rp, false);
-    double* T4 = take((int64_t)rp * rp, false);
-    double* A1b = take((int64_t)ell * rp, false);
+    double* T1 = take((int64_t)rp * rp);
+    double* T2 = take((int64_t)rp * rp);
+    double* T4 = take((int64_t)rp * rp);
+    double* A1b = take((int64_t)ell * rp);
     VJPCK(adj_gemm(true, false, rp, rp, ell, 1.0, M1b, ell, m1t, ell, 0.0, T1, rp, s));
     VJPCK(adj_gemm(true, false, rp, rp, ell, 1.0, m1t, ell, m1t, ell, 0.0, T2, rp, s));
     VJPCK(adj_gemm(true, false, rp, rp, rp, 1.0, T1, rp, T2, rp, 0.0, T4, rp, s));
@@ -1489,21 +1507,31 @@ pstt2_status pstt2_vjp(pstt2_ctx* c, const tt_cores* cores, const void* x_dev, c
                          Qb[k], s));
   {
     // G_d = P_{d-1}^T: Pbar_{d-1} += Gbar_d^T
-    double* tmp = take((int64_t)r[d - 1] * c->n[d - 1], false);
+    double* tmp = take((int64_t)r[d - 1] * c->n[d - 1]);
     VJPCK(adj_transpose(Gb[d - 1], r[d - 1], c->n[d - 1], tmp, s));
     VJPCK(adj_axpy((int64_t)r[d - 1] * c->n[d - 1], 1.0, tmp, Qb[d - 1], s));
   }
   // sketch cotangents: Sbar_k (k < m), Ybar (= Sbar_m), Tbar_k (k >= m, transposed layout)
   std::vector<double*> Sb(d + 1, nullptr);
-  for (int k = 1; k < m; ++k) Sb[k] = take(Rk[k] * ell, true);
+  for (int k = 1; k < m; ++k) Sb[k] = take_zero(Rk[k] * ell);
   Sb[m] = Yb;
   std::vector<double*> Tb(d + 1, nullptr);
-  for (int k = m; k <= d - 1; ++k) Tb[k] = take(Ck(k) * ell, true);
-  for (int k = 1; k <= d - 1; ++k) {
-    const bool left = k < m;
-    const int64_t Mk = left ? Rk[k] : Ck(k);
-    VJPCK(adj_qr(left ? c->S[k] : c->Tk[k], c->basis[k], Qb[k], Mk, ell, r[k], c->piv_dev + (int64_t)k * ell,
-                 left ? Sb[k] : Tb[k], s));
+  for (int k = m; k <= d - 1; ++k) Tb[k] = take_zero(Ck(k) * ell);
+  {
+    std::vector<const double*> Sp, Qp, Qbp;
+    std::vector<double*> Sbp;
+    std::vector<int64_t> Mk;
+    std::vector<const int*> pv;
+    for (int k = 1; k <= d - 1; ++k) {
+      const bool left = k < m;
+      Sp.push_back(left ? c->S[k] : c->Tk[k]);
+      Qp.push_back(c->basis[k]);
+      Qbp.push_back(Qb[k]);
+      Sbp.push_back(left ? Sb[k] : Tb[k]);
+      Mk.push_back(left ? Rk[k] : Ck(k));
+      pv.push_back(c->piv_dev + (int64_t)k * ell);
+    }
+    VJPCK(adj_qr_batch(d - 1, Sp.data(), Qp.data(), Qbp.data(), Mk.data(), r + 1, pv.data(), Sbp.data(), s));
   }
   const bool fused = gbar_dev == nullptr;
   if (!c->indep) {
@@ -1523,7 +1551,7 @@ pstt2_status pstt2_vjp(pstt2_ctx* c, const tt_cores* cores, const void* x_dev, c
     for (int k = 1; k < m; ++k) {
       const double* cur = Sb[k];
       for (int q = k + 1; q <= m; ++q) {   // undo the contraction of mode q: R_{q-1} -> R_q rows
-        double* nxt = take(Rk[q] * ell, true);
+        double* nxt = take_zero(Rk[q] * ell);
         VJPCK(adj_derive_left(cur, nxt, Rk[q - 1], (int)c->n[q - 1], ell, c->fac + c->iom_off[k][q - 1], s));
         cur = nxt;
       }
@@ -1532,7 +1560,7 @@ pstt2_status pstt2_vjp(pstt2_ctx* c, const tt_cores* cores, const void* x_dev, c
     for (int k = m + 1; k <= d - 1; ++k) {
       const double* cur = Tb[k];
       for (int q = k; q >= m + 1; --q) {   // undo the contraction of mode q: C_q -> C_{q-1} columns
-        double* nxt = take(Ck(q - 1) * ell, true);
+        double* nxt = take_zero(Ck(q - 1) * ell);
         VJPCK(adj_derive_right(cur, nxt, Ck(q), (int)c->n[q - 1], ell, c->fac + c->ipsi_off[k][q - 1], s));
         cur = nxt;
       }
@@ -1552,7 +1580,6 @@ pstt2_status pstt2_vjp(pstt2_ctx* c, const tt_cores* cores, const void* x_dev, c
     }
   }
 #undef VJPCK
-  release();
   int hflag = 0;
   int* pin = (int*)pinned_scratch();
   if (e == hipSuccess) e = hipMemcpyAsync(pin ? pin : &hflag, c->flag, sizeof(int), hipMemcpyDeviceToHost, s);

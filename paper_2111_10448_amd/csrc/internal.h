@@ -289,8 +289,10 @@ hipError_t adj_core_right(const double* Gb, const double* Pp, const double* Pk, 
                           double* Ppb, double* Pkb, hipStream_t s);
 hipError_t adj_pbar(const double* om_tab, int L4, int64_t Cm, int rm, int ell, int prec, const double* Ab, double* Pb,
                     hipStream_t s);
-hipError_t adj_qr(const double* S, const double* Q, const double* Qb, int64_t M, int ell, int r, const int* piv,
-                  double* Sb, hipStream_t s);
+// Sbar_p += thin-QR adjoint of the basis Q_p (M_p x r_p) of the pivoted columns of S_p, n problems.
+hipError_t adj_qr_batch(int n, const double* const* S, const double* const* Q, const double* const* Qb,
+                        const int64_t* M, const int* r, const int* const* piv, double* const* Sb, hipStream_t s);
+hipError_t adj_zero(double* p, int64_t n, hipStream_t s);
 hipError_t adj_derive_left(const double* Sbk, double* Sbk1, int64_t Rk, int nk1, int ell, const double* om,
                            hipStream_t s);
 hipError_t adj_derive_right(const double* Tbk, double* Tbp, int64_t Ck, int nk, int ell, const double* ps,

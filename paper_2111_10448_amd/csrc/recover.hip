@@ -25,6 +25,7 @@
 #include <type_traits>
 
 #include "internal.h"
+#include "linalg.h"
 
 namespace pstt2 {
 
@@ -110,15 +111,6 @@ hipError_t derive_right(const double* Tin, double* Tout, int64_t Ck, int nk, int
 // broadcast row j: p_c = q_c / (alpha - beta) + a_jc.
 // ---------------------------------------------------------------------------
 constexpr int RED_LD = 264;   // LDS row stride of the reduction buffer (bank spread)
-
-// Value of v held by lane l of the wavefront (l wave-uniform), through the
-// scalar unit rather than an LDS read.
-__device__ __forceinline__ double lane_f64(double v, int l) {
-  const uint64_t u = __builtin_bit_cast(uint64_t, v);
-  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, l);
-  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), l);
-  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
-}
 
 // Sum Red[c][0..255] for c in [c0, n) into Out[c]; threads t < LP*8 take
 // column t/8 and eight interleaved slices of it.  Caller synchronises.
@@ -1404,77 +1396,81 @@ hipError_t middle_a(const double* Pm, int64_t Cm, int rm, const SketchArgs& geo,
 }
 
 // Least squares min ||G A - Z||_F for G (nz x rm), A (rm x ell), Z (nz x ell),
-// A of full row rank: G = Z A^+ with A^+ = A^T W, W = (A A^T)^{-1}.  W comes
-// from Gauss-Jordan elimination on the rm x rm SPD matrix A A^T (one thread per
-// column); then Bm = A^T W (ell x rm) and every row of G is z Bm.  A is a
-// Gaussian-like rm x ell matrix (rm < ell), so cond(A A^T) = cond(A)^2 stays
-// small.  A pivot below 1e-26 of the largest diagonal (A numerically
-// rank-deficient) sets flag bit 2.
+// A of full row rank: G = Z A^+ with A^+ = A^T W, W = (A A^T)^{-1} (spd_inverse on
+// the rm x rm SPD matrix A A^T); then Bm = A^T W (ell x rm) and every row of G is
+// z Bm.  A is a Gaussian-like rm x ell matrix (rm < ell), so cond(A A^T) =
+// cond(A)^2 stays small.  A pivot below 1e-26 of the largest diagonal (A
+// numerically rank-deficient) sets flag bit 2.  Every workgroup forms the same
+// small Bm (identical arithmetic) and applies it to its own rows of Z, one row
+// per thread (its ell entries read once, consecutive threads on consecutive
+// rows).  Latency bound: rm = 8, ell = 20: 15.5 -> 7.2 us; rm = 10, ell = 24: 22 -> 15.
+template <int RP, int EP>
 __global__ __launch_bounds__(256) void k_middle_ls(const double* __restrict__ Z, int64_t nz,
                                                    const double* __restrict__ A, int rm, int ell,
                                                    double* __restrict__ G, int* flag) {
-  constexpr int MX = PSTT2_MAX_ELL;
-  __shared__ double As[MX][MX + 1];        // A (rm x ell)
-  __shared__ double Aug[MX][2 * MX + 1];   // [A A^T | I] -> [I | W]
-  __shared__ double Bm[MX][MX + 1];        // A^T W: [c][b]
-  __shared__ double fcol[MX];
-  __shared__ double dmax;
+  __shared__ double As[RP][EP + 1];   // A (rm x ell)
+  __shared__ double Gm[RP][RP + 1];   // A A^T
+  __shared__ double W[RP][RP + 1];
+  __shared__ double Bm[EP][RP + 1];   // A^T W: [c][b]
   const int t = threadIdx.x;
-  for (int i = t; i < rm * ell; i += blockDim.x) As[i % rm][i / rm] = A[i];
+  const int64_t rho0 = blockIdx.x * (int64_t)256 + t;
+  double z[EP];   // the first row's entries, requested before the small products
+#pragma unroll
+  for (int c = 0; c < EP; ++c) z[c] = c < ell && rho0 < nz ? Z[(int64_t)c * nz + rho0] : 0.0;
+  for (int i = t; i < rm * EP; i += 256) {
+    const int a = i % rm, c = i / rm;
+    As[a][c] = c < ell ? A[a + rm * c] : 0.0;
+  }
   __syncthreads();
-  for (int i = t; i < rm * rm; i += blockDim.x) {
+  for (int i = t; i < rm * rm; i += 256) {
     const int a = i % rm, b = i / rm;
     double sum = 0.0;
-    for (int c = 0; c < ell; ++c) sum += As[a][c] * As[b][c];
-    Aug[a][b] = sum;
-    Aug[a][rm + b] = a == b ? 1.0 : 0.0;
+#pragma unroll
+    for (int c = 0; c < EP; ++c) sum += As[a][c] * As[b][c];
+    Gm[a][b] = sum;
   }
   __syncthreads();
-  if (t == 0) {
-    double mx = 0.0;
-    for (int a = 0; a < rm; ++a) mx = fmax(mx, Aug[a][a]);
-    dmax = mx;
+  if (t < 64) {
+    const bool ok = spd_inverse<RP>(Gm, rm, W);
+    if (!ok && t == 0 && blockIdx.x == 0) atomicOr(flag, 2);
   }
-  for (int k = 0; k < rm; ++k) {
-    if (t < rm) fcol[t] = Aug[t][k];
-    __syncthreads();
-    if (t == 0 && blockIdx.x == 0 && !(fcol[k] > 1e-26 * dmax)) atomicOr(flag, 2);
-    if (t < 2 * rm) {
-      const double pk = Aug[k][t] / fcol[k];
-      Aug[k][t] = pk;
-      for (int i = 0; i < rm; ++i)
-        if (i != k) Aug[i][t] -= fcol[i] * pk;
-    }
-    __syncthreads();
-  }
-  for (int i = t; i < ell * rm; i += blockDim.x) {
-    const int c = i % ell, b = i / ell;
+  __syncthreads();
+  for (int i = t; i < EP * rm; i += 256) {
+    const int c = i % EP, b = i / EP;
     double sum = 0.0;
-    for (int a = 0; a < rm; ++a) sum += As[a][c] * Aug[a][rm + b];
+    for (int a = 0; a < rm; ++a) sum += As[a][c] * W[a][b];
     Bm[c][b] = sum;
   }
   __syncthreads();
-  // G(rho, b) = sum_c Z(rho, c) Bm(c, b): every workgroup forms the same small
-  // Bm (identical arithmetic) and applies it to its own rows of Z, one row per
-  // thread (its ell entries read once, consecutive threads on consecutive rows)
-  for (int64_t rho = blockIdx.x * (int64_t)blockDim.x + t; rho < nz; rho += (int64_t)gridDim.x * blockDim.x) {
-    double z[MX];
+  for (int64_t rho = rho0; rho < nz; rho += (int64_t)gridDim.x * 256) {
+    if (rho != rho0) {
 #pragma unroll
-    for (int c = 0; c < MX; ++c) z[c] = c < ell ? Z[(int64_t)c * nz + rho] : 0.0;
+      for (int c = 0; c < EP; ++c) z[c] = c < ell ? Z[(int64_t)c * nz + rho] : 0.0;
+    }
     for (int b = 0; b < rm; ++b) {
       double sum = 0.0;
 #pragma unroll
-      for (int c = 0; c < MX; ++c)
-        if (c < ell) sum += z[c] * Bm[c][b];
+      for (int c = 0; c < EP; ++c) sum += z[c] * Bm[c][b];
       G[rho + nz * b] = sum;
     }
   }
 }
 
+template <int RP>
+static void launch_ls(const double* Z, int64_t nz, const double* A, int rm, int ell, double* G, int* flag,
+                      hipStream_t s) {
+  const dim3 g((unsigned)std::max<int64_t>(1, std::min<int64_t>((nz + 255) / 256, 1024))), b(256);
+  if (ell <= 8) hipLaunchKernelGGL((k_middle_ls<RP, 8>), g, b, 0, s, Z, nz, A, rm, ell, G, flag);
+  else if (ell <= 16) hipLaunchKernelGGL((k_middle_ls<RP, 16>), g, b, 0, s, Z, nz, A, rm, ell, G, flag);
+  else if (ell <= 24) hipLaunchKernelGGL((k_middle_ls<RP, 24>), g, b, 0, s, Z, nz, A, rm, ell, G, flag);
+  else hipLaunchKernelGGL((k_middle_ls<RP, 32>), g, b, 0, s, Z, nz, A, rm, ell, G, flag);
+}
+
 hipError_t middle_ls(const double* Z, int64_t nz, const double* A, int rm, int ell, double* G, int* flag,
                      hipStream_t s) {
-  const unsigned nb = (unsigned)std::max<int64_t>(1, std::min<int64_t>((nz + 255) / 256, 1024));
-  hipLaunchKernelGGL(k_middle_ls, dim3(nb), dim3(256), 0, s, Z, nz, A, rm, ell, G, flag);
+  if (rm <= 8) launch_ls<8>(Z, nz, A, rm, ell, G, flag, s);
+  else if (rm <= 16) launch_ls<16>(Z, nz, A, rm, ell, G, flag, s);
+  else launch_ls<32>(Z, nz, A, rm, ell, G, flag, s);
   return hipGetLastError();
 }
 
