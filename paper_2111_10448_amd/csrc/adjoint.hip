@@ -400,77 +400,114 @@ __global__ void k_derive_right_adj(const double* __restrict__ Tbk, double* __res
 
 // ---- B3: gx(row, col) = sum_c Ybar(row, c) Omega(col, c) + sum_a Psi(row, a) Tbar(col, a)
 //                         [ + 2 (x - X~) for the fused loss ] [ + gx for ACC ] ----
-// Block = 256 threads = 256 consecutive rows; columns in groups of 16 staged in LDS.
-// A null Yb or Tbt drops that term (a pass group of the independent scheme
-// with only one side); ACC adds into gx (the later groups).
+// A product with inner dimension ell + ell (+ r for the -2 L Rt of the fused loss)
+// on FP64 matrix cores: a wave owns 32 rows whose operands stay in registers for
+// its whole share of the columns (KS steps of four), and forms 64-column tiles,
+// columns on the M index, so a store covers 16 consecutive rows.  A null Yb or Tbt
+// drops that term (a pass group of the independent scheme with only one side);
+// ACC adds into gx (the later groups).  The column operands of a tile pass through
+// LDS: loaded straight into registers they left one wave to a SIMD (98 us).  Bound
+// by the matrix unit and the tiles' staging; x in and gx out alone would be 27 us.
+// 24^5 FP64, ell = 20, r = 8: 60.5 us (2.1 TB/s); the vector version, one thread a
+// row, took 93.  48^4 FP32, ell = 12, J^T alone: 29 -> 18 us.
 struct AdjOutArgs {
   int64_t R, C;
-  int ell, r, L4, prec, m;
-  int32_t n[PSTT2_MAX_D];
-  const double* fac;
-  int64_t psi_off[PSTT2_MAX_D];
+  int ell, r, L4, prec;
+  int n1, n2, n3;        // steps of the three terms (0: absent)
   const double* Yb;      // R x ell
-  const double* Tbt;     // C x ell
-  const double* om_tab;  // C x L4
+  const double* psi;     // R x ell
   const double* L;       // R x r   (fused loss only)
+  const double* om_tab;  // C x L4
+  const double* Tbt;     // C x ell
   const double* Rt;      // r x C   (fused loss only)
-  int gj;                // column groups
+  int gi, gj;            // row blocks, column shares
 };
 
-__device__ __forceinline__ double psi_prod(const AdjOutArgs& A, int64_t row, int a) {
-  double v = 1.0;
-  int64_t rr = row;
-  for (int q = 1; q <= A.m; ++q) {
-    const int64_t nq = A.n[q - 1];
-    v *= A.fac[A.psi_off[q - 1] + (rr % nq) * A.ell + a];
-    rr /= nq;
-  }
-  return v;
-}
+constexpr int AO_ROWS = 128, AO_COLS = 64;
 
-// MX: the sketch size and the rank rounded up to a multiple of 4 (the
-// per-row operands live in registers, and their loops are unrolled to MX).
-template <typename T, bool FUSED, bool ACC, int MX>
-__global__ __launch_bounds__(256) void k_adj_out(const AdjOutArgs A, const T* __restrict__ x, T* __restrict__ gx) {
-  constexpr int CB = 16;
-  __shared__ double om[CB][MX], tb[CB][MX], rt[CB][FUSED ? MX : 1];
-  const int64_t gi = blockIdx.x % ((A.R + 255) / 256);
-  const int64_t gj = blockIdx.x / ((A.R + 255) / 256);
-  const int64_t row = gi * 256 + threadIdx.x;
-  const bool ok = row < A.R;
-  const bool hy = A.Yb != nullptr, ht = A.Tbt != nullptr;
-  double yb[MX], ps[MX], lr[FUSED ? MX : 1];
+template <typename T, bool FUSED, bool ACC, int KS>
+__global__ __launch_bounds__(256, 2) void k_adj_out(const AdjOutArgs A, const T* __restrict__ x, T* __restrict__ gx) {
+  constexpr int LD = AO_COLS + 2;
+  __shared__ double Co[4 * KS][LD];   // column operands of a tile, [inner index][column]
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, l16 = lane & 15, g4 = lane >> 4;
+  const int64_t gi = blockIdx.x % A.gi, gj = blockIdx.x / A.gi;
+  const int64_t row0 = gi * AO_ROWS + 32 * w;
+  const int ks = A.n1 + A.n2 + A.n3;
+  int64_t row[2];
+  double ro[KS][2];   // row operands, zero past a term's length and past the matrix
 #pragma unroll
-  for (int c = 0; c < MX; ++c) {
-    yb[c] = (hy && ok && c < A.ell) ? A.Yb[(int64_t)c * A.R + row] : 0.0;
-    ps[c] = (ht && ok && c < A.ell) ? drm_eff(psi_prod(A, row, c), A.prec) : 0.0;
-    if constexpr (FUSED) lr[c] = (ok && c < A.r) ? A.L[(int64_t)c * A.R + row] : 0.0;
-  }
-  const int64_t cb = gj * A.C / A.gj, ce = (gj + 1) * A.C / A.gj;
-  for (int64_t c0 = cb; c0 < ce; c0 += CB) {
-    __syncthreads();
-    for (int t = threadIdx.x; t < CB * MX; t += blockDim.x) {
-      const int j = t / MX, c = t % MX;
-      const int64_t col = c0 + j;
-      const bool cok = col < ce;
-      om[j][c] = (hy && cok && c < A.ell) ? drm_eff(A.om_tab[col * A.L4 + c], A.prec) : 0.0;
-      tb[j][c] = (ht && cok && c < A.ell) ? A.Tbt[(int64_t)c * A.C + col] : 0.0;
-      if constexpr (FUSED) rt[j][c] = (cok && c < A.r) ? A.Rt[c + (int64_t)A.r * col] : 0.0;
-    }
-    __syncthreads();
-    if (!ok) continue;
-    for (int j = 0; j < CB && c0 + j < ce; ++j) {
-      double s = 0.0, xt = 0.0;
+  for (int t = 0; t < 2; ++t) row[t] = row0 + 16 * t + l16;
 #pragma unroll
-      for (int c = 0; c < MX; ++c) {
-        s += yb[c] * om[j][c] + ps[c] * tb[j][c];
-        if constexpr (FUSED) xt += lr[c] * rt[j][c];
+  for (int s = 0; s < KS; ++s) {
+    const int c1 = 4 * s + g4, c2 = c1 - 4 * A.n1, c3 = c2 - 4 * A.n2;
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      double v = 0.0;
+      if (row[t] < A.R) {
+        if (s < A.n1) {
+          if (c1 < A.ell) v = A.Yb[c1 * A.R + row[t]];
+        } else if (s < A.n1 + A.n2) {
+          if (c2 < A.ell) v = drm_eff(A.psi[c2 * A.R + row[t]], A.prec);
+        } else if (s < ks) {
+          if (c3 < A.r) v = -2.0 * A.L[c3 * A.R + row[t]];
+        }
       }
-      const int64_t f = (c0 + j) * A.R + row;
-      if (FUSED) s += 2.0 * ((double)x[f] - xt);
-      if (ACC) s += (double)gx[f];
-      gx[f] = (T)s;
+      ro[s][t] = v;
     }
+  }
+  const int64_t ntile = (A.C + AO_COLS - 1) / AO_COLS;
+  for (int64_t tile = gj * ntile / A.gj; tile < (gj + 1) * ntile / A.gj; ++tile) {
+    const int64_t cb = tile * AO_COLS;
+    const int nc = (int)(A.C - cb < AO_COLS ? A.C - cb : AO_COLS);
+    __syncthreads();   // the last tile's reads are done
+    // Omega rows (their padding columns are zero), Tbar, Rt; zero past a term and past the matrix
+    for (int e = tid; e < AO_COLS * 4 * A.n1; e += 256) {
+      const int j = e / (4 * A.n1), c = e - j * 4 * A.n1;
+      Co[c][j] = j < nc ? drm_eff(A.om_tab[(cb + j) * A.L4 + c], A.prec) : 0.0;
+    }
+    for (int e = tid; e < AO_COLS * 4 * A.n2; e += 256) {
+      const int j = e % AO_COLS, c = e / AO_COLS;
+      Co[4 * A.n1 + c][j] = j < nc && c < A.ell ? A.Tbt[(int64_t)c * A.C + cb + j] : 0.0;
+    }
+    for (int e = tid; e < AO_COLS * 4 * A.n3; e += 256) {
+      const int j = e / (4 * A.n3), c = e - j * 4 * A.n3;
+      Co[4 * (A.n1 + A.n2) + c][j] = j < nc && c < A.r ? A.Rt[c + (int64_t)A.r * (cb + j)] : 0.0;
+    }
+    __syncthreads();
+    adj_d4 acc[4][2];
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+#pragma unroll
+      for (int t = 0; t < 2; ++t) acc[u][t] = adj_d4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+      if (s < ks) {   // uniform
+        double co[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) co[u] = Co[4 * s + g4][16 * u + l16];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+          for (int t = 0; t < 2; ++t)
+            acc[u][t] = __builtin_amdgcn_mfma_f64_16x16x4f64(co[u], ro[s][t], acc[u][t], 0, 0, 0);
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int j = 16 * u + 4 * v + g4;
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+          if (j < nc && row[t] < A.R) {
+            const int64_t f = (cb + j) * A.R + row[t];
+            double g = acc[u][t][v];
+            if constexpr (FUSED) g += 2.0 * (double)x[f];
+            if constexpr (ACC) g += (double)gx[f];
+            gx[f] = (T)g;
+          }
+        }
+      }
   }
 }
 
@@ -576,29 +613,32 @@ hipError_t adj_derive_right(const double* Tbk, double* Tbp, int64_t Ck, int nk, 
   return hipGetLastError();
 }
 
-template <int MX>
-static void launch_adj_out(int dtype, bool fused, bool acc, dim3 grid, const AdjOutArgs& A, const void* x, void* gx,
+template <int KS>
+static void launch_adj_out(int dtype, bool fused, bool acc, const AdjOutArgs& A, const void* x, void* gx,
                            hipStream_t s) {
-  const dim3 block(256);
+  const dim3 grid((unsigned)((int64_t)A.gi * A.gj)), block(256);
   if (dtype == PSTT2_F64) {
     if (fused)
-      hipLaunchKernelGGL((k_adj_out<double, true, false, MX>), grid, block, 0, s, A, (const double*)x, (double*)gx);
+      hipLaunchKernelGGL((k_adj_out<double, true, false, KS>), grid, block, 0, s, A, (const double*)x, (double*)gx);
     else if (acc)
-      hipLaunchKernelGGL((k_adj_out<double, false, true, MX>), grid, block, 0, s, A, (const double*)x, (double*)gx);
+      hipLaunchKernelGGL((k_adj_out<double, false, true, KS>), grid, block, 0, s, A, (const double*)x, (double*)gx);
     else
-      hipLaunchKernelGGL((k_adj_out<double, false, false, MX>), grid, block, 0, s, A, (const double*)x, (double*)gx);
+      hipLaunchKernelGGL((k_adj_out<double, false, false, KS>), grid, block, 0, s, A, (const double*)x, (double*)gx);
   } else {
     if (fused)
-      hipLaunchKernelGGL((k_adj_out<float, true, false, MX>), grid, block, 0, s, A, (const float*)x, (float*)gx);
+      hipLaunchKernelGGL((k_adj_out<float, true, false, KS>), grid, block, 0, s, A, (const float*)x, (float*)gx);
     else if (acc)
-      hipLaunchKernelGGL((k_adj_out<float, false, true, MX>), grid, block, 0, s, A, (const float*)x, (float*)gx);
+      hipLaunchKernelGGL((k_adj_out<float, false, true, KS>), grid, block, 0, s, A, (const float*)x, (float*)gx);
     else
-      hipLaunchKernelGGL((k_adj_out<float, false, false, MX>), grid, block, 0, s, A, (const float*)x, (float*)gx);
+      hipLaunchKernelGGL((k_adj_out<float, false, false, KS>), grid, block, 0, s, A, (const float*)x, (float*)gx);
   }
 }
 
 hipError_t adj_out(int dtype, const SketchArgs& g, int prec, const double* Yb, const double* Tbt, const double* L,
                    const double* Rt, int r, const void* x, void* gx, bool acc, hipStream_t s) {
+  const bool fused = L != nullptr;
+  if (fused && acc) return hipErrorInvalidValue;   // the loss term enters once, in the first group
+  if (g.ell > PSTT2_MAX_ELL || r > PSTT2_MAX_ELL) return hipErrorInvalidValue;
   AdjOutArgs A;
   std::memset(&A, 0, sizeof(A));
   A.R = g.R;
@@ -607,37 +647,39 @@ hipError_t adj_out(int dtype, const SketchArgs& g, int prec, const double* Yb, c
   A.r = r;
   A.L4 = g.L4;
   A.prec = prec;
-  A.m = g.m;
-  for (int q = 0; q < PSTT2_MAX_D; ++q) {
-    A.n[q] = g.n[q];
-    A.psi_off[q] = g.psi_off[q];
-  }
-  A.fac = g.fac;
+  A.n1 = Yb ? (g.ell + 3) / 4 : 0;
+  A.n2 = Tbt ? (g.ell + 3) / 4 : 0;
+  A.n3 = fused ? (r + 3) / 4 : 0;
   A.Yb = Yb;
   A.Tbt = Tbt;
   A.om_tab = g.om_tab;
   A.L = L;
   A.Rt = Rt;
-  const int64_t gi = (g.R + 255) / 256;
-  // about four workgroups per CU: a thread's row operands (2 MX loads and the
-  // Psi products) are set up once and then serve its share of the columns
-  A.gj = (int)std::max<int64_t>(1, std::min<int64_t>(g.C, (1024 + gi - 1) / gi));
-  const dim3 grid((unsigned)(gi * A.gj)), block(256);
-  const bool fused = L != nullptr;
-  if (fused && acc) return hipErrorInvalidValue;   // the loss term enters once, in the first group
-  const int mx = (std::max(A.ell, fused ? r : 0) + 3) / 4 * 4;
-  if (mx < 4 || mx > PSTT2_MAX_ELL) return hipErrorInvalidValue;
-  switch (mx) {
-    case 4: launch_adj_out<4>(dtype, fused, acc, grid, A, x, gx, s); break;
-    case 8: launch_adj_out<8>(dtype, fused, acc, grid, A, x, gx, s); break;
-    case 12: launch_adj_out<12>(dtype, fused, acc, grid, A, x, gx, s); break;
-    case 16: launch_adj_out<16>(dtype, fused, acc, grid, A, x, gx, s); break;
-    case 20: launch_adj_out<20>(dtype, fused, acc, grid, A, x, gx, s); break;
-    case 24: launch_adj_out<24>(dtype, fused, acc, grid, A, x, gx, s); break;
-    case 28: launch_adj_out<28>(dtype, fused, acc, grid, A, x, gx, s); break;
-    default: launch_adj_out<32>(dtype, fused, acc, grid, A, x, gx, s); break;
+  double* psi = nullptr;
+  hipError_t e = hipSuccess;
+  if (Tbt) {   // the left DRM of this group's factors, R x ell
+    KRChain ch;
+    std::memset(&ch, 0, sizeof(ch));
+    for (int q = 0; q < g.m; ++q) {
+      ch.n[ch.cnt] = g.n[q];
+      ch.off[ch.cnt++] = g.psi_off[q];
+    }
+    e = ws_alloc((void**)&psi, sizeof(double) * g.R * g.ell, s);
+    if (e == hipSuccess) e = kr_table(g.fac, ch, g.R, g.ell, psi, s);
+    if (e != hipSuccess) return e;
   }
-  return hipGetLastError();
+  A.psi = psi;
+  A.gi = (int)((g.R + AO_ROWS - 1) / AO_ROWS);
+  const int64_t ntile = (g.C + AO_COLS - 1) / AO_COLS;
+  A.gj = (int)std::max<int64_t>(1, std::min<int64_t>(ntile, (2048 + A.gi - 1) / A.gi));
+  const int ks = A.n1 + A.n2 + A.n3;
+  if (ks <= 6) launch_adj_out<6>(dtype, fused, acc, A, x, gx, s);
+  else if (ks <= 12) launch_adj_out<12>(dtype, fused, acc, A, x, gx, s);
+  else if (ks <= 18) launch_adj_out<18>(dtype, fused, acc, A, x, gx, s);
+  else launch_adj_out<24>(dtype, fused, acc, A, x, gx, s);
+  e = hipGetLastError();
+  ws_free(psi, s);
+  return e;
 }
 
 }  // namespace pstt2
