@@ -8,7 +8,7 @@
 //  * basis_factor_batch / basis_form_q_batch: orthonormal bases of the sketches' ranges
 //    by a column-pivoted QR (Algorithm PSTT, CPQR step).  Tall sketches are
 //    first reduced by Householder TSQR (the skinny QR of Section 4.2), one
-//    workgroup per 512- or 1024-row block, all splits in one launch per tree
+//    workgroup per 512-row block, all splits in one launch per tree
 //    level; the pivots of a matrix equal the pivots of its R factor, so the
 //    pivoted QR runs on the final ell x ell R.  Signs are fixed so that
 //    diag(R) >= 0.  Singular values (tolerance mode) come from one-sided
@@ -99,37 +99,38 @@ hipError_t derive_right(const double* Tin, double* Tout, int64_t Ck, int nk, int
 }
 
 // ---------------------------------------------------------------------------
-// TSQR leaves.  One workgroup (256 threads) factors a block of BR = 256 * RPT
-// rows by Householder reflections (LAPACK dlarfg convention: H = I - tau v v^T,
-// v(j) = 1, beta = -sign(alpha) ||x||, tau = 0 when the column below the
-// diagonal is already zero).  Thread t holds block rows t + 256 k (k < RPT), so
-// row j < ell sits in thread j.  Rows past M are zero.
+// TSQR leaves.  One workgroup factors a block of up to 512 rows by Householder
+// reflections (LAPACK dlarfg convention: H = I - tau v v^T, v(j) = 1,
+// beta = -sign(alpha) ||x||, tau = 0 when the column below the diagonal is already
+// zero) and, from the T of the block's Q = I - V T V^T (dlarft, forward, columnwise)
+// and V's top ell rows V1, the upper triangular K = T V1^T.
 //
-// Step j needs sigma = sum_{i>j} a_ij^2 and p_c = sum_i v_i a_ic for c > j.
-// With v_i = a_ij / (alpha - beta) below the diagonal and v_j = 1, both come
-// from one reduction q_c = sum_{i>j} a_ij a_ic (c >= j; sigma = q_j) and the
-// broadcast row j: p_c = q_c / (alpha - beta) + a_jc.
+// Step j needs sigma = sum_{i>j} a_ij^2 and p_c = sum_i v_i a_ic.  With
+// v_i = a_ij / (alpha - beta) below the diagonal and v_j = 1, both come from one sum
+// q_c = sum_{i>j} a_ij a_ic (sigma = q_j) and row j: p_c = q_c / (alpha - beta) + a_jc.
+// For c < j, where a_ic holds an earlier reflector, the same p_c is v_c . v_j, which
+// T is made of.  Reflectors stay unscaled (scale in sc) until they are stored.
+//
+// A lane holds column 8 s + n (n = lane % 8) of set s < NS of the rows 8 i + g
+// (g = lane / 8, i < QI) of its wave: column j reaches its row's lanes within the
+// vector unit, a sum over rows is in registers but for three lane exchanges shared
+// between the sets, and one exchange through LDS and one barrier per step remain.
+// Bound by the issue of vector instructions, about half of them the multiplications:
+// a level fills few compute units, and each loads and stores at some 10 bytes a
+// cycle, which is why blocks are not larger.  Sixteen lanes to a column's row and 1024
+// rows, or four: 43 us at ell = 20; a lane a row, two exchanges of every sum through
+// LDS a step, 1024 rows: 52 us.  Now 30 us for 512 rows and 40 to 46 for 1024 at
+// ell = 20 and 24 (0.8 us a step), 73 us at ell = 32 (two waves to a SIMD), 17 at ell = 12;
+// 1.86 M rows at ell = 20: 270 us.
+//
+// V (stride M) receives the reflectors strictly below the block's diagonal and K in
+// the rest of its top ell x ell; a last block of fewer than ell rows has tau = 0
+// from there on, so what does not fit is not needed.
 // ---------------------------------------------------------------------------
-constexpr int RED_LD = 264;   // LDS row stride of the reduction buffer (bank spread)
-
-// Sum Red[c][0..255] for c in [c0, n) into Out[c]; threads t < LP*8 take
-// column t/8 and eight interleaved slices of it.  Caller synchronises.
-template <int LP>
-__device__ __forceinline__ void wg_colsum(double (*Red)[RED_LD], int c0, int n, double* Out) {
-  const int t = threadIdx.x;
-  if (t < LP * 8) {
-    const int c = t >> 3, s8 = t & 7;
-    double sum = 0.0;
-    if (c >= c0 && c < n) {
-#pragma unroll 8
-      for (int i = 0; i < 32; ++i) sum += Red[c][s8 + 8 * i];
-    }
-    sum += __shfl_xor(sum, 1);
-    sum += __shfl_xor(sum, 2);
-    sum += __shfl_xor(sum, 4);
-    if (s8 == 0 && c >= c0 && c < n) Out[c] = sum;
-  }
-}
+constexpr int QI = 16, QR = 8 * QI;   // rows of a lane and of a wave
+// Rows of a level's blocks: 512, unless its largest matrix is one block of 1024 (40 us
+// and 8 for Q at ell = 20, two levels of 512 rows 55 and 16).
+static int leaf_rows(int64_t M) { return M <= 8 * QR ? 8 * QR : 4 * QR; }
 
 // Independent problems (one per split) share each launch: workgroup g belongs
 // to problem p with blk0[p] <= g < blk0[p + 1].
@@ -137,11 +138,11 @@ constexpr int MAXB = PSTT2_MAX_D;
 struct LeafBatch {
   int n;
   const double* A[MAXB];
-  int64_t M[MAXB], lda[MAXB];
+  int64_t M[MAXB];    // rows, and the stride of A's and V's columns
   double* V[MAXB];
-  double* tau[MAXB];
   double* Rst[MAXB];
   int64_t ldr[MAXB];
+  int qb;             // rows of a block
   int64_t blk0[MAXB + 1];
 };
 
@@ -151,181 +152,6 @@ __device__ __forceinline__ int batch_find(const int64_t* blk0, int n, int64_t g)
   return p;
 }
 
-template <int LP, int RPT>
-__global__ __launch_bounds__(256) void k_qr_leaf(const LeafBatch B, int ell) {
-  constexpr int BR = 256 * RPT;
-  __shared__ double Red[LP][RED_LD];
-  __shared__ double Qs[LP];
-  __shared__ double Rowj[2][LP];
-  const int t = threadIdx.x;
-  const int pb = batch_find(B.blk0, B.n, blockIdx.x);
-  const double* __restrict__ A = B.A[pb];
-  const int64_t M = B.M[pb], lda = B.lda[pb], ldr = B.ldr[pb];
-  double* __restrict__ V = B.V[pb];
-  double* __restrict__ tau = B.tau[pb];
-  double* __restrict__ Rst = B.Rst[pb];
-  const int64_t b = blockIdx.x - B.blk0[pb];
-  const int64_t rb = b * BR;
-  // columns ell..LP-1 are zero: their steps are exact no-ops (sigma = alpha = 0)
-  double a[RPT][LP];
-#pragma unroll
-  for (int k = 0; k < RPT; ++k) {
-    const int64_t row = rb + t + 256 * k;
-#pragma unroll
-    for (int c = 0; c < LP; ++c) a[k][c] = (c < ell && row < M) ? A[(int64_t)c * lda + row] : 0.0;
-  }
-  // fully unrolled over the reflectors: every register index is a constant
-#pragma unroll
-  for (int j = 0; j < LP; ++j) {
-    if (j < ell) {   // uniform: every thread takes the same branch
-    // q_c partials over this thread's rows below j
-#pragma unroll
-    for (int c = j; c < LP; ++c) {
-      double q = 0.0;
-#pragma unroll
-      for (int k = 0; k < RPT; ++k)
-        if (t + 256 * k > j) q += a[k][j] * a[k][c];
-      Red[c][t] = q;
-    }
-    if (t == j) {
-#pragma unroll
-      for (int c = j; c < LP; ++c) Rowj[j & 1][c] = a[0][c];
-    }
-    __syncthreads();
-    wg_colsum<LP>(Red, j, LP, Qs);
-    __syncthreads();
-    const double sigma = Qs[j];
-    const double alpha = Rowj[j & 1][j];
-    double tj, beta, scal;
-    if (sigma == 0.0) {
-      tj = 0.0;
-      beta = alpha;
-      scal = 0.0;
-    } else {
-      beta = -copysign(sqrt(alpha * alpha + sigma), alpha);
-      tj = (beta - alpha) / beta;
-      scal = 1.0 / (alpha - beta);
-    }
-    double v[RPT];
-#pragma unroll
-    for (int k = 0; k < RPT; ++k) {
-      const int lr = t + 256 * k;
-      v[k] = lr == j ? 1.0 : (lr > j ? a[k][j] * scal : 0.0);
-    }
-    // p_c is formed by lane c of every wave and broadcast from there (one LDS
-    // read per lane instead of two per column)
-    const int lane = t & 63;
-    const double pl = lane < LP ? tj * (scal * Qs[lane] + Rowj[j & 1][lane]) : 0.0;
-#pragma unroll
-    for (int c = j + 1; c < LP; ++c) {
-      const double pc = lane_f64(pl, c);
-#pragma unroll
-      for (int k = 0; k < RPT; ++k) a[k][c] -= pc * v[k];
-    }
-#pragma unroll
-    for (int k = 0; k < RPT; ++k) {
-      const int lr = t + 256 * k;
-      a[k][j] = lr > j ? v[k] : (lr == j ? beta : a[k][j]);
-    }
-    if (t == 0) tau[b * ell + j] = tj;
-    }
-  }
-#pragma unroll
-  for (int k = 0; k < RPT; ++k) {
-    const int lr = t + 256 * k;
-#pragma unroll
-    for (int c = 0; c < LP; ++c) {
-      if (c < ell) {
-        V[(b * ell + c) * BR + lr] = lr > c ? a[k][c] : (lr == c ? 1.0 : 0.0);
-        if (k == 0 && lr < ell) Rst[(int64_t)c * ldr + b * ell + lr] = lr <= c ? a[0][c] : 0.0;
-      }
-    }
-  }
-}
-
-// Apply one block's Q (BR x ell reflectors) to [Zin(b*ell .. b*ell+ell-1, :); 0]
-// and write rows [b*BR, b*BR + BR) of Zout (masked to Mout rows).
-struct ApplyBatch {
-  int n;
-  const double* V[MAXB];
-  const double* tau[MAXB];
-  const double* Zin[MAXB];
-  int64_t ldzi[MAXB];
-  int r[MAXB];
-  double* Zout[MAXB];
-  int64_t ldzo[MAXB], Mout[MAXB];
-  int64_t blk0[MAXB + 1];
-};
-
-template <int RP, int RPT>
-__global__ __launch_bounds__(256) void k_qr_apply(const ApplyBatch B, int ell) {
-  constexpr int BR = 256 * RPT;
-  __shared__ double Red[RP][RED_LD];
-  __shared__ double Ws[RP];
-  const int t = threadIdx.x;
-  const int pb = batch_find(B.blk0, B.n, blockIdx.x);
-  const double* __restrict__ V = B.V[pb];
-  const double* __restrict__ tau = B.tau[pb];
-  const double* __restrict__ Zin = B.Zin[pb];
-  const int64_t ldzi = B.ldzi[pb], ldzo = B.ldzo[pb], Mout = B.Mout[pb];
-  const int r = B.r[pb];
-  double* __restrict__ Zout = B.Zout[pb];
-  const int64_t b = blockIdx.x - B.blk0[pb];
-  double z[RPT][RP];
-#pragma unroll
-  for (int k = 0; k < RPT; ++k) {
-    const int lr = t + 256 * k;
-#pragma unroll
-    for (int c = 0; c < RP; ++c) z[k][c] = (c < r && lr < ell) ? Zin[(int64_t)c * ldzi + b * ell + lr] : 0.0;
-  }
-  // reflector j is loaded one step ahead of its use
-  double vn[RPT];
-  double tn = 0.0;
-  if (ell > 0) {
-    tn = tau[b * ell + ell - 1];
-#pragma unroll
-    for (int k = 0; k < RPT; ++k) vn[k] = V[(b * ell + ell - 1) * BR + t + 256 * k];
-  }
-  for (int j = ell - 1; j >= 0; --j) {
-    const double tj = tn;
-    double v[RPT];
-#pragma unroll
-    for (int k = 0; k < RPT; ++k) v[k] = vn[k];
-    if (j > 0) {
-      tn = tau[b * ell + j - 1];
-#pragma unroll
-      for (int k = 0; k < RPT; ++k) vn[k] = V[(b * ell + j - 1) * BR + t + 256 * k];
-    }
-#pragma unroll
-    for (int c = 0; c < RP; ++c) {
-      double q = 0.0;
-#pragma unroll
-      for (int k = 0; k < RPT; ++k) q += v[k] * z[k][c];
-      if (c < r) Red[c][t] = q;
-    }
-    __syncthreads();
-    wg_colsum<RP>(Red, 0, r, Ws);
-    __syncthreads();
-    const double wl = (t & 63) < r ? tj * Ws[t & 63] : 0.0;   // lane c holds w_c
-#pragma unroll
-    for (int c = 0; c < RP; ++c) {
-      if (c < r) {
-        const double wc = lane_f64(wl, c);
-#pragma unroll
-        for (int k = 0; k < RPT; ++k) z[k][c] -= wc * v[k];
-      }
-    }
-  }
-#pragma unroll
-  for (int k = 0; k < RPT; ++k) {
-    const int64_t row = b * BR + t + 256 * k;
-#pragma unroll
-    for (int c = 0; c < RP; ++c)
-      if (c < r && row < Mout) Zout[(int64_t)c * ldzo + row] = z[k][c];
-  }
-}
-
-// ---- the pivoted QR of the small R factors, one wavefront per problem ----
 template <int CTRL>
 __device__ __forceinline__ double dpp_f64(double v) {
   const uint64_t u = __builtin_bit_cast(uint64_t, v);
@@ -333,13 +159,427 @@ __device__ __forceinline__ double dpp_f64(double v) {
   const uint32_t hi = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)(u >> 32), CTRL, 0xf, 0xf, true);
   return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
 }
-constexpr int kXor1 = 0xB1, kXor2 = 0x4E;               // within a quad
-constexpr int kHalfMirror = 0x141, kMirror = 0x140;     // within 8 and 16 lanes
 
+// lanes 0..31: u summed over the halves of the wave, lanes 32..63: v
+__device__ __forceinline__ double halves_sum(double u, double v) {
+  const uint64_t a = __builtin_bit_cast(uint64_t, u), b = __builtin_bit_cast(uint64_t, v);
+  const auto l = __builtin_amdgcn_permlane32_swap((uint32_t)a, (uint32_t)b, false, false);
+  const auto h = __builtin_amdgcn_permlane32_swap((uint32_t)(a >> 32), (uint32_t)(b >> 32), false, false);
+  return __builtin_bit_cast(double, ((uint64_t)h[0] << 32) | l[0]) +
+         __builtin_bit_cast(double, ((uint64_t)h[1] << 32) | l[1]);
+}
+
+// rows of sixteen lanes 0 and 2: u summed over the rows of the half, rows 1 and 3: v
+__device__ __forceinline__ double rows_sum(double u, double v) {
+  const uint64_t a = __builtin_bit_cast(uint64_t, u), b = __builtin_bit_cast(uint64_t, v);
+  const auto l = __builtin_amdgcn_permlane16_swap((uint32_t)a, (uint32_t)b, false, false);
+  const auto h = __builtin_amdgcn_permlane16_swap((uint32_t)(a >> 32), (uint32_t)(b >> 32), false, false);
+  return __builtin_bit_cast(double, ((uint64_t)h[0] << 32) | l[0]) +
+         __builtin_bit_cast(double, ((uint64_t)h[1] << 32) | l[1]);
+}
+
+// v of lane J of each eight lanes
+template <int J>
+__device__ __forceinline__ double bcast8(double v) {
+  const long u = __builtin_bit_cast(long, v);
+  const long t = __builtin_amdgcn_update_dpp(0L, u, 0x150 + J, 0xf, 0xf, true);
+  return __builtin_bit_cast(double, (long)__builtin_amdgcn_update_dpp(t, u, 0x158 + J, 0xf, 0xc, false));
+}
+
+template <int NS, int QW>   // QW: most waves of a block
+struct Leaf {
+  static constexpr int C = 8 * NS, RS = QW + 2;
+  static constexpr int L = NS == 3 ? 32 : C;   // G and T, a power of two
+  double a[NS][QI];   // set (s + rd) % NS in index s after rd rounds of eight columns;
+                      // wave 0's first four elements move up by one a round
+  double sc[NS];      // scale of this lane's reflector
+  int ell, w, n, g;
+  int64_t M, rb, ldr;
+  double* V;
+  double* R;          // the block's R in the stack
+
+  __device__ __forceinline__ int col(int s, int rd) const { return 8 * (s + rd < NS ? s + rd : s + rd - NS) + n; }
+
+  // wave 0's element i, row lr < 32 of the block, once final
+  __device__ __forceinline__ void put_top(int i, int lr, int rd, double (*V1)[L + 1]) {
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+      const int c = col(s, rd);
+      if (c < ell) {
+        if (lr < ell) R[c * ldr + lr] = lr <= c ? a[s][i] : 0.0;
+        if (lr > c) {
+          const double v = a[s][i] * sc[s];
+          if (rb + lr < M) V[c * M + rb + lr] = v;
+          if (lr < L) V1[lr][c] = v;
+        }
+      }
+    }
+  }
+
+  // Step j = 8 rd + JJ: column j is lane JJ of set 0, row j element 0 of group JJ of
+  // wave 0.  red: [C][RS], of each column the waves' sums and row j; G: [j][c] =
+  // v_c . v_j for c < j, tau_j at c = j.
+  template <int JJ>
+  __device__ __forceinline__ void step(int rd, double* red, double* G) {
+    const int j = 8 * rd + JJ;
+    const bool w0 = w == 0;
+    double x[QI];
+#pragma unroll
+    for (int i = 0; i < QI; ++i) x[i] = bcast8<JJ>(a[0][i]);
+    if (w0) x[0] = g > JJ ? x[0] : 0.0;   // rows up to j
+    double q[NS], rj[NS];
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+      double q0 = 0.0, q1 = 0.0;
+#pragma unroll
+      for (int i = 0; i < QI; i += 2) {
+        q0 += x[i] * a[s][i];
+        q1 += x[i + 1] * a[s][i + 1];
+      }
+      q[s] = q0 + q1;
+    }
+    const int row = (threadIdx.x & 63) >> 4;   // of sixteen lanes
+    {   // sets by row of sixteen lanes: 0 0 0 0, 0 0 1 1, 0 2 1 2, 0 2 1 3
+      const double u = halves_sum(q[0], q[NS > 1 ? 1 : 0]);
+      const double v = NS > 2 ? halves_sum(q[NS > 2 ? 2 : 0], q[NS > 3 ? 3 : (NS > 2 ? 2 : 0)]) : u;
+      double t = rows_sum(u, v);
+      t += dpp_f64<0x128>(t);   // the two groups of a row: rotated by eight lanes
+      const int st = NS == 1 ? 0 : (NS == 2 ? row >> 1 : ((row & 1) == 0 ? row >> 1 : (NS == 3 ? 2 : 2 + (row >> 1))));
+      if ((g & 1) == 0) red[(8 * st + n) * RS + w] = t;
+    }
+    if (w0 && g == JJ) {
+#pragma unroll
+      for (int s = 0; s < NS; ++s) red[(8 * s + n) * RS + QW] = a[s][0];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+      const double* r = red + (8 * s + n) * RS;
+      q[s] = (r[0] + r[1]) + (r[2] + r[3]);
+      if constexpr (QW == 8) q[s] += (r[4] + r[5]) + (r[6] + r[7]);
+      rj[s] = r[QW];
+    }
+    const double sigma = bcast8<JJ>(q[0]), alpha = bcast8<JJ>(rj[0]);
+    // beta and 1 / beta by a Goldschmidt step for the root, 1 / (alpha - beta) by two
+    // Newton steps, to within 2 ulp: half the operations of the root and quotients
+    // rounded exactly, which every wave repeats.  |alpha - beta| >= sqrt(sigma).
+    double tj = 0.0, beta = alpha, rbeta = 0.0, scal = 0.0;
+    if (sigma != 0.0) {   // uniform
+      const double m = alpha * alpha + sigma;
+      const double r0 = __builtin_amdgcn_rsq(m);
+      double z = m * r0, h = 0.5 * r0;
+      const double e = __builtin_fma(-h, z, 0.5);
+      z = __builtin_fma(z, e, z);
+      h = __builtin_fma(h, e, h);
+      z = __builtin_fma(__builtin_fma(-z, z, m), h, z);   // sqrt(m)
+      beta = -copysign(z, alpha);
+      const double den = alpha - beta;
+      double y = __builtin_amdgcn_rcp(den);
+      y = __builtin_fma(y, __builtin_fma(-den, y, 1.0), y);
+      scal = __builtin_fma(y, __builtin_fma(-den, y, 1.0), y);
+      h += h;
+      h = __builtin_fma(h, __builtin_fma(-z, h, 1.0), h);   // 1 / sqrt(m)
+      rbeta = -copysign(h, alpha);
+      tj = -den * rbeta;
+    }
+    double p[NS];
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+      p[s] = scal * q[s] + rj[s];
+      if (s + rd < NS) {   // uniform; an unfinished set: a_ic -= tau scal p_c x_i, tau scal = -1 / beta
+        double us = p[s] * rbeta;
+        if (s == 0) us = n > JJ ? us : 0.0;
+#pragma unroll
+        for (int i = 0; i < QI; ++i) a[s][i] += us * x[i];
+      }
+    }
+    if (w0) {
+      if (g == 0) {   // entries c > j are not read
+#pragma unroll
+        for (int s = 0; s < NS; ++s) G[j * L + col(s, rd)] = s == 0 && n == JJ ? tj : sc[s] * p[s];
+      }
+#pragma unroll
+      for (int s = 0; s < NS; ++s) {
+        const double r = s == 0 && n == JJ ? beta : rj[s] - tj * p[s];
+        a[s][0] = g == JJ && (s == 0 ? n >= JJ : s + rd < NS) ? r : a[s][0];
+      }
+    }
+    if (n == JJ) sc[0] = scal;
+  }
+};
+
+// Stage H of the doubling of T: of two neighbouring runs of H reflectors,
+// T12 = -T1 (V1^T V2) T2.
+template <int L, int H>
+__device__ __forceinline__ void leaf_t(const double* G, double (*T)[L + 1], double (*X)[L / 2 + 1]) {
+  if constexpr (H < L) {
+    for (int e = threadIdx.x; e < L * H / 2; e += blockDim.x) {
+      const int i = e % H, j = e / H % H, b1 = e / (H * H) * 2 * H, b2 = b1 + H;
+      double x = 0.0;
+#pragma unroll
+      for (int k = 0; k < H; ++k) x += G[(b2 + k) * L + b1 + i] * T[b2 + k][b2 + j];
+      X[b1 + i][j] = x;
+    }
+    __syncthreads();
+    for (int e = threadIdx.x; e < L * H / 2; e += blockDim.x) {
+      const int i = e % H, j = e / H % H, b1 = e / (H * H) * 2 * H, b2 = b1 + H;
+      double x = 0.0;
+#pragma unroll
+      for (int k = 0; k < H; ++k) x += T[b1 + i][b1 + k] * X[b1 + k][j];
+      T[b1 + i][b2 + j] = -x;
+    }
+    __syncthreads();
+    leaf_t<L, 2 * H>(G, T, X);
+  }
+}
+
+template <int NS, int QW>
+__global__ __launch_bounds__(64 * QW) void k_qr_leaf(const LeafBatch B, int ell) {
+  using S_ = Leaf<NS, QW>;
+  constexpr int L = S_::L, RED = S_::C * S_::RS;
+  __shared__ __attribute__((aligned(16))) double red[2][RED];   // one a step: a barrier lies between its reads and its next writes
+  __shared__ double G[L * L];   // G[j][c]
+  __shared__ double T[L][L + 1], X[L][L / 2 + 1], V1[L][L + 1];
+  const int tid = threadIdx.x;
+  const int pb = batch_find(B.blk0, B.n, blockIdx.x);
+  const int64_t b = blockIdx.x - B.blk0[pb];
+  S_ S;
+  S.ell = ell;
+  S.w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  S.n = tid & 7;
+  S.g = (tid & 63) >> 3;
+  S.M = B.M[pb];
+  S.rb = b * B.qb;
+  S.ldr = B.ldr[pb];
+  S.V = B.V[pb];
+  S.R = B.Rst[pb] + b * ell;
+  const int64_t wr = S.rb + QR * S.w + S.g;   // row of element 0 at first
+  const bool full = S.rb + QR * (S.w + 1) <= S.M;
+#pragma unroll
+  for (int s = 0; s < NS; ++s) {
+    const int c = 8 * s + S.n;
+    const double* __restrict__ ac = B.A[pb] + c * S.M + wr;
+    S.sc[s] = 0.0;
+#pragma unroll
+    for (int i = 0; i < QI; ++i) S.a[s][i] = 0.0;   // zero columns: exact no-ops
+    if (c < ell) {
+      if (full) {
+#pragma unroll
+        for (int i = 0; i < QI; ++i) S.a[s][i] = ac[8 * i];
+      } else {
+#pragma unroll
+        for (int i = 0; i < QI; ++i)
+          if (wr + 8 * i < S.M) S.a[s][i] = ac[8 * i];
+      }
+    }
+  }
+  for (int e = tid; e < 2 * RED; e += blockDim.x) (&red[0][0])[e] = 0.0;   // waves of a small block that do not run
+  for (int e = tid; e < L * L; e += blockDim.x) {
+    G[e] = 0.0;
+    T[e / L][e % L] = 0.0;
+    V1[e / L][e % L] = e / L == e % L ? 1.0 : 0.0;
+  }
+  __syncthreads();
+  // Eight columns a round, the sets moving down by one between rounds and wave 0's top
+  // rows up by one element: lane and register numbers are constants of a loop body.
+  int rd = 0;
+  for (; 8 * rd < ell; ++rd) {
+    const int left = ell - 8 * rd;
+    S.template step<0>(rd, red[0], G);
+    if (left > 1) S.template step<1>(rd, red[1], G);
+    if (left > 2) S.template step<2>(rd, red[0], G);
+    if (left > 3) S.template step<3>(rd, red[1], G);
+    if (left > 4) S.template step<4>(rd, red[0], G);
+    if (left > 5) S.template step<5>(rd, red[1], G);
+    if (left > 6) S.template step<6>(rd, red[0], G);
+    if (left > 7) S.template step<7>(rd, red[1], G);
+    if (S.w == 0) {
+      S.put_top(0, 8 * rd + S.g, rd, V1);
+#pragma unroll
+      for (int s = 0; s < NS; ++s)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) S.a[s][i] = i < 3 ? S.a[s][i + 1] : 0.0;
+    }
+    if constexpr (NS > 1) {
+#pragma unroll
+      for (int i = 0; i < QI; ++i) {
+        const double t = S.a[0][i];
+#pragma unroll
+        for (int s = 0; s + 1 < NS; ++s) S.a[s][i] = S.a[s + 1][i];
+        S.a[NS - 1][i] = t;
+      }
+      const double t = S.sc[0];
+#pragma unroll
+      for (int s = 0; s + 1 < NS; ++s) S.sc[s] = S.sc[s + 1];
+      S.sc[NS - 1] = t;
+    }
+  }
+  if (S.w == 0) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (i + rd < 4) S.put_top(i, 8 * (i + rd) + S.g, rd, V1);
+  }
+#pragma unroll
+  for (int s = 0; s < NS; ++s) {
+    const int c = S.col(s, rd);
+    if (c < ell) {
+      double* __restrict__ vc = S.V + c * S.M + wr;
+      if (S.w != 0) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (full || wr + 8 * i < S.M) vc[8 * i] = S.a[s][i] * S.sc[s];
+      }
+      if (full) {
+#pragma unroll
+        for (int i = 4; i < QI; ++i) vc[8 * i] = S.a[s][i] * S.sc[s];
+      } else {
+#pragma unroll
+        for (int i = 4; i < QI; ++i)
+          if (wr + 8 * i < S.M) vc[8 * i] = S.a[s][i] * S.sc[s];
+      }
+    }
+  }
+  __syncthreads();
+  if (tid < L) T[tid][tid] = G[tid * L + tid];
+  __syncthreads();
+  leaf_t<L, 1>(G, T, X);
+  for (int e = tid; e < L * L; e += blockDim.x) {
+    const int i = e % L, j = e / L;
+    if (i <= j && j < ell && S.rb + i < S.M) {
+      double k = 0.0;
+#pragma unroll 8
+      for (int u = 0; u < L; ++u) k += T[i][u] * V1[j][u];
+      S.V[j * S.M + S.rb + i] = k;
+    }
+  }
+}
+
+// Rows of Q Z for a block's Q = I - V T V^T and Z = [Zin(b*ell .. b*ell+ell-1, :); 0]:
+// Z - V (K Zin) with K = T V1^T, so a workgroup takes QA rows of a block by itself (all
+// of a block's where there are many blocks): the small product in LDS, then V's rows
+// against it on FP64 matrix cores.  Bound by latency (loads, small product, loads,
+// stores) or, over many blocks, by memory.  The reflectors one after another, as 2 ell
+// sums over the block's rows through LDS, took 41 us at ell = 24, r = 12; now 8.3 us.
+// 1.86 M rows at ell = 20, r = 8: 98 -> 100 us (4.2 TB/s).
+struct ApplyBatch {
+  int n;
+  const double* V[MAXB];
+  int64_t M[MAXB];       // rows, and the stride of V's and Zout's columns
+  const double* Zin[MAXB];
+  int64_t ldzi[MAXB];
+  int r[MAXB];
+  double* Zout[MAXB];
+  int qb[MAXB], parts[MAXB];   // rows of a block, workgroups that share it
+  int64_t blk0[MAXB + 1];      // in workgroups
+};
+constexpr int QA = 128;
+typedef double qr_d4 __attribute__((ext_vector_type(4)));
+
+// CS: 16-wide tiles of the columns of Z; LP: 16 or 32, at least ell
+template <int CS, int LP>
+__global__ __launch_bounds__(256) void k_qr_apply(const ApplyBatch B, int ell) {
+  constexpr int LD = LP + 1;
+  __shared__ double Kt[LP][LD];                       // [column][row]
+  __shared__ double Z[16 * CS][LD], U[16 * CS][LD];   // [column][row]
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, l16 = lane & 15, g4 = lane >> 4;
+  const int pb = batch_find(B.blk0, B.n, blockIdx.x);
+  const double* __restrict__ V = B.V[pb];
+  const double* __restrict__ Zin = B.Zin[pb];
+  const int64_t M = B.M[pb], ldzi = B.ldzi[pb];
+  const int r = B.r[pb];
+  double* __restrict__ Zout = B.Zout[pb];
+  const int64_t wg = blockIdx.x - B.blk0[pb], b = wg / B.parts[pb], rb = b * B.qb[pb];
+  int64_t row0 = rb + wg % B.parts[pb] * QA;
+  for (int e = tid; e < LP * LP; e += 256) {
+    const int c = e / LP, i = e % LP;
+    Kt[c][i] = (i <= c && c < ell && rb + i < M) ? V[c * M + rb + i] : 0.0;
+  }
+  for (int e = tid; e < 16 * CS * LP; e += 256) {
+    const int c = e / LP, i = e % LP;
+    Z[c][i] = (c < r && i < ell) ? Zin[c * ldzi + b * ell + i] : 0.0;
+  }
+  // This wave's reflector entries of the rows at row0, the first in flight across the
+  // small product.  Past the last column and row the last is read: K's rows are zero
+  // there, and nothing is stored.
+  double v[LP / 4][2];
+  auto load = [&](int64_t row0) {
+    const int64_t ra = row0 + 32 * w + l16, rb2 = ra + 16;
+    const int64_t r0 = ra < M ? ra : M - 1, r1 = rb2 < M ? rb2 : M - 1;
+#pragma unroll
+    for (int s = 0; s < LP / 4; ++s) {
+      if (4 * s < ell) {   // uniform
+        const int k = 4 * s + g4;
+        const double* __restrict__ vk = V + (k < ell ? k : ell - 1) * M;
+        v[s][0] = vk[r0];
+        v[s][1] = vk[r1];
+      }
+    }
+    if (row0 == rb) {   // the block's top rows: unit lower triangle
+#pragma unroll
+      for (int s = 0; s < LP / 4; ++s)
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+          const int k = 4 * s + g4, lr = 32 * w + 16 * t + l16;
+          v[s][t] = lr > k ? v[s][t] : (lr == k ? 1.0 : 0.0);
+        }
+    }
+  };
+  load(row0);
+  __syncthreads();
+  for (int e = tid; e < 16 * CS * LP; e += 256) {   // K Z
+    const int c = e / LP, j = e % LP;
+    double u = 0.0;
+    if (c < r) {
+#pragma unroll 8
+      for (int k = 0; k < LP; ++k) u += Kt[k][j] * Z[c][k];
+    }
+    U[c][j] = u;
+  }
+  __syncthreads();
+  const int64_t end = B.parts[pb] == 1 ? rb + B.qb[pb] : row0 + QA;
+  for (;;) {
+    qr_d4 acc[CS][2];
+#pragma unroll
+    for (int u = 0; u < CS; ++u)
+#pragma unroll
+      for (int t = 0; t < 2; ++t) acc[u][t] = qr_d4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int s = 0; s < LP / 4; ++s) {
+      if (4 * s < ell) {
+#pragma unroll
+        for (int u = 0; u < CS; ++u) {
+          const double wk = U[16 * u + l16][4 * s + g4];
+#pragma unroll
+          for (int t = 0; t < 2; ++t) acc[u][t] = __builtin_amdgcn_mfma_f64_16x16x4f64(wk, v[s][t], acc[u][t], 0, 0, 0);
+        }
+      }
+    }
+    if (row0 + QA < end) load(row0 + QA);
+#pragma unroll
+    for (int u = 0; u < CS; ++u)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int c = 16 * u + 4 * e + g4;
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+          const int64_t row = row0 + 32 * w + 16 * t + l16;
+          const int lr = (int)(row - rb);
+          if (c < r && row < M) Zout[c * M + row] = (lr < ell ? Z[c][lr] : 0.0) - acc[u][t][e];
+        }
+      }
+    row0 += QA;
+    if (row0 >= end) break;
+  }
+}
+
+// ---- the pivoted QR of the small R factors, one wavefront per problem ----
 __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   __builtin_amdgcn_wave_barrier();
 }
+
+constexpr int kXor1 = 0xB1, kXor2 = 0x4E;               // within a quad
+constexpr int kHalfMirror = 0x141, kMirror = 0x140;     // within 8 and 16 lanes
 
 // Column-pivoted QR of the ell x ell matrix R.  Lane t holds column t in
 // registers; pivoting swaps positions, not data: pos is the lane's current
@@ -583,14 +823,14 @@ __global__ __launch_bounds__(64) void k_cpqr(const CpqrBatch B, int ell) {
 
 struct Level {
   int64_t M;      // rows at this level
+  int qb;         // rows of a block
   int64_t nb;     // blocks
-  double* V;      // nb * ell * br
-  double* tau;    // nb * ell
+  double* V;      // M x ell, reflectors and K of every block
   double* Rst;    // stacked R of this level (nb*ell x ell), input of the next level
 };
 
 struct BasisBatch {
-  int n = 0, ell = 0, rpt = 2;
+  int n = 0, ell = 0;
   hipStream_t s = nullptr;
   std::vector<std::vector<Level>> lv;   // per problem, leaves first
   double* ws = nullptr;                 // one stream-ordered workspace for everything
@@ -611,16 +851,14 @@ void basis_batch_free(BasisBatch* w) {
     if (e_ != hipSuccess) return e_;   \
   } while (0)
 
-// Sketches of up to 16 columns use 1024-row leaves (4 rows per thread); wider
-// ones 512-row leaves, so the registers of a thread stay within 64 values.
-static int leaf_rpt(int ell) { return ell <= 24 ? 4 : 2; }
-
-static void launch_leaf(const LeafBatch& B, int64_t nblk, int ell, hipStream_t s) {
-  const dim3 g((unsigned)nblk), b(256);
-  if (ell <= 8) hipLaunchKernelGGL((k_qr_leaf<8, 4>), g, b, 0, s, B, ell);
-  else if (ell <= 16) hipLaunchKernelGGL((k_qr_leaf<16, 4>), g, b, 0, s, B, ell);
-  else if (ell <= 24) hipLaunchKernelGGL((k_qr_leaf<24, 4>), g, b, 0, s, B, ell);
-  else hipLaunchKernelGGL((k_qr_leaf<32, 2>), g, b, 0, s, B, ell);
+// As many waves as the level's largest block has rows for.
+template <int QW>
+static void launch_leaf(const LeafBatch& B, int64_t nblk, int64_t max_rows, int ell, hipStream_t s) {
+  const dim3 g((unsigned)nblk), b(64 * (unsigned)((std::min<int64_t>(B.qb, max_rows) + QR - 1) / QR));
+  if (ell <= 8) hipLaunchKernelGGL((k_qr_leaf<1, QW>), g, b, 0, s, B, ell);
+  else if (ell <= 16) hipLaunchKernelGGL((k_qr_leaf<2, QW>), g, b, 0, s, B, ell);
+  else if (ell <= 24) hipLaunchKernelGGL((k_qr_leaf<3, QW>), g, b, 0, s, B, ell);
+  else hipLaunchKernelGGL((k_qr_leaf<4, QW>), g, b, 0, s, B, ell);
 }
 
 template <bool SV>
@@ -638,27 +876,27 @@ hipError_t basis_factor_batch(int n, const double* const* A, const int64_t* M, i
   *out = w;
   w->n = n;
   w->ell = ell;
-  w->rpt = leaf_rpt(ell);
   w->s = s;
   w->lv.resize(n);
-  const int64_t br = 256 * (int64_t)w->rpt;
   // level shapes and one workspace
   int64_t tot = 0;
   int maxL = 0;
-  for (int p = 0; p < n; ++p) {
-    int64_t curM = M[p];
-    for (;;) {
+  for (std::vector<int64_t> curM(M, M + n);; ++maxL) {   // 0 rows: done
+    int64_t most = 0;
+    for (int p = 0; p < n; ++p) most = std::max(most, curM[p]);
+    if (most == 0) break;
+    for (int p = 0; p < n; ++p) {
+      if (curM[p] == 0) continue;
       Level l;
-      l.M = curM;
-      l.nb = (curM + br - 1) / br;
-      tot += l.nb * ell * br + l.nb * ell + l.nb * ell * ell;
+      l.M = curM[p];
+      l.qb = leaf_rows(most);
+      l.nb = (l.M + l.qb - 1) / l.qb;
+      tot += ell * l.M + l.nb * ell * ell;
       w->lv[p].push_back(l);
-      if (l.nb == 1) break;
-      curM = l.nb * ell;
+      curM[p] = l.nb == 1 ? 0 : l.nb * ell;
     }
-    maxL = std::max(maxL, (int)w->lv[p].size());
-    tot += ell * ell + (want_sv ? ell : 0);
   }
+  tot += (int64_t)n * (ell * ell + (want_sv ? ell : 0));
   HCK(ws_alloc((void**)&w->ws, sizeof(double) * tot, s));
   double* cur = w->ws;
   w->Qc.resize(n);
@@ -666,9 +904,7 @@ hipError_t basis_factor_batch(int n, const double* const* A, const int64_t* M, i
   for (int p = 0; p < n; ++p) {
     for (Level& l : w->lv[p]) {
       l.V = cur;
-      cur += l.nb * ell * br;
-      l.tau = cur;
-      cur += l.nb * ell;
+      cur += ell * l.M;
       l.Rst = cur;
       cur += l.nb * ell * ell;
     }
@@ -683,23 +919,24 @@ hipError_t basis_factor_batch(int n, const double* const* A, const int64_t* M, i
   for (int L = 0; L < maxL; ++L) {
     LeafBatch B;
     std::memset(&B, 0, sizeof(B));
-    int64_t nblk = 0;
+    int64_t nblk = 0, max_rows = 0;
     for (int p = 0; p < n; ++p) {
       if ((int)w->lv[p].size() <= L) continue;
       const Level& l = w->lv[p][L];
       const int i = B.n++;
       B.A[i] = L == 0 ? A[p] : w->lv[p][L - 1].Rst;
       B.M[i] = l.M;
-      B.lda[i] = l.M;
       B.V[i] = l.V;
-      B.tau[i] = l.tau;
+      B.qb = l.qb;
       B.Rst[i] = l.Rst;
       B.ldr[i] = l.nb * ell;
       B.blk0[i] = nblk;
       nblk += l.nb;
+      max_rows = std::max(max_rows, l.M);
     }
     B.blk0[B.n] = nblk;
-    launch_leaf(B, nblk, ell, s);
+    if (std::min<int64_t>(B.qb, max_rows) <= 4 * QR) launch_leaf<4>(B, nblk, max_rows, ell, s);
+    else launch_leaf<8>(B, nblk, max_rows, ell, s);
     HCK(hipGetLastError());
   }
   CpqrBatch C;
@@ -719,18 +956,11 @@ hipError_t basis_factor_batch(int n, const double* const* A, const int64_t* M, i
 
 const double* basis_batch_sv(BasisBatch* w, int p) { return w->sv[p]; }
 
-static void launch_apply(const ApplyBatch& B, int64_t nblk, int rpt, int rmax, int ell, hipStream_t s) {
+static void launch_apply(const ApplyBatch& B, int64_t nblk, int rmax, int ell, hipStream_t s) {
   const dim3 g((unsigned)nblk), b(256);
-  if (rpt == 4) {
-    if (rmax <= 8) hipLaunchKernelGGL((k_qr_apply<8, 4>), g, b, 0, s, B, ell);
-    else if (rmax <= 16) hipLaunchKernelGGL((k_qr_apply<16, 4>), g, b, 0, s, B, ell);
-    else hipLaunchKernelGGL((k_qr_apply<24, 4>), g, b, 0, s, B, ell);
-  } else {
-    if (rmax <= 8) hipLaunchKernelGGL((k_qr_apply<8, 2>), g, b, 0, s, B, ell);
-    else if (rmax <= 16) hipLaunchKernelGGL((k_qr_apply<16, 2>), g, b, 0, s, B, ell);
-    else if (rmax <= 24) hipLaunchKernelGGL((k_qr_apply<24, 2>), g, b, 0, s, B, ell);
-    else hipLaunchKernelGGL((k_qr_apply<32, 2>), g, b, 0, s, B, ell);
-  }
+  if (ell <= 16) hipLaunchKernelGGL((k_qr_apply<1, 16>), g, b, 0, s, B, ell);
+  else if (rmax <= 16) hipLaunchKernelGGL((k_qr_apply<1, 32>), g, b, 0, s, B, ell);
+  else hipLaunchKernelGGL((k_qr_apply<2, 32>), g, b, 0, s, B, ell);
 }
 
 // Q_p (M_p x r_p) = first r_p columns of each problem's pivoted orthogonal
@@ -756,7 +986,11 @@ hipError_t basis_form_q_batch(BasisBatch* w, const int* r, double* const* Q, hip
   for (int step = 0; step < maxL; ++step) {
     ApplyBatch B;
     std::memset(&B, 0, sizeof(B));
-    int64_t nblk = 0;
+    int64_t nblk = 0, nb = 0;
+    for (int p = 0; p < n; ++p) {
+      const int i_l = (int)w->lv[p].size() - 1 - step;
+      if (i_l >= 0) nb += w->lv[p][i_l].nb;
+    }
     std::vector<std::pair<int, double*>> outs;
     for (int p = 0; p < n; ++p) {
       const int L = (int)w->lv[p].size();
@@ -773,19 +1007,19 @@ hipError_t basis_form_q_batch(BasisBatch* w, const int* r, double* const* Q, hip
       }
       const int i = B.n++;
       B.V[i] = l.V;
-      B.tau[i] = l.tau;
+      B.M[i] = l.M;
       B.Zin[i] = zin[p];
       B.ldzi[i] = ldzi[p];
       B.r[i] = r[p];
       B.Zout[i] = zout;
-      B.ldzo[i] = l.M;
-      B.Mout[i] = l.M;
+      B.qb[i] = l.qb;
+      B.parts[i] = nb >= 1024 ? 1 : l.qb / QA;   // about four workgroups to a compute unit
       B.blk0[i] = nblk;
-      nblk += l.nb;
+      nblk += l.nb * B.parts[i];
       outs.push_back({p, zout});
     }
     B.blk0[B.n] = nblk;
-    launch_apply(B, nblk, w->rpt, rmax, ell, s);
+    launch_apply(B, nblk, rmax, ell, s);
     HCK(hipGetLastError());
     for (auto& o : outs) {
       const int L = (int)w->lv[o.first].size();

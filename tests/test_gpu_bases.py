@@ -29,6 +29,10 @@ pytestmark = pytest.mark.gpu
     ((33, 34, 35, 37), 24, 32),          # over one leaf
     ((140, 260, 7), 6, 20),              # 36400 rows: three tree levels
     ((140, 260, 7), 5, 32),
+    ((127, 40), 5, 9), ((129, 40), 8, 16),   # one and two waves
+    ((512, 40), 9, 12), ((513, 40), 9, 17),  # half a block of eight waves
+    ((1024, 33), 20, 24), ((1025, 33), 20, 24), ((1025, 35), 27, 32),   # one block, two levels
+    ((900, 640, 4), 3, 6),               # over a thousand blocks: a workgroup a block forms Q
 ])
 def test_bases_fixed_rank(n, rank, ell):
     say(f"[gpu] bases n={n} rank={rank} ell={ell}")
