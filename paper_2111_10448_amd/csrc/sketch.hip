@@ -1049,6 +1049,7 @@ __global__ __launch_bounds__(nwf_for(L4) * 64, f64_wg_per_cu(L4)) void k_sketch_
   constexpr int NT = NWF * 64;         // threads
   constexpr int NOM = (KC * L4 + NT - 1) / NT;   // staged Omega / T entries per thread
   static_assert(L4 % 4 == 0 && L4 >= 4, "ell padded to a multiple of 4");
+  static_assert(KC / 4 == 4 && NLD % 4 == 0, "a quarter of a chunk's loads with each K step");
 
   __shared__ double Xl[NWF][KC * ST];
   __shared__ double Tred[2][NWF][L4 * KC];
@@ -1112,27 +1113,37 @@ __global__ __launch_bounds__(nwf_for(L4) * 64, f64_wg_per_cu(L4)) void k_sketch_
   // X32: the prefetched pairs stay FP32 in registers and are widened when the
   // chunk is staged (widening at the load would wait for every load in turn)
   typename std::conditional<X32, float, double>::type xr[NLD][2];
-  // FN: index-table entries of this lane's two rows (fixed for the launch)
-  int fr0 = 0, fr1 = 0;
+  // FN: index-table entries of this lane's two rows (fixed for the launch) and of its
+  // columns of the next chunk to load, themselves loaded a chunk ahead
+  int fr0 = 0, fr1 = 0, fcol[FN ? NLD : 1];
   if constexpr (FN) {
     const int64_t row = row0w + (lane & 31) * 2;
     fr0 = row < A.R ? A.fn_row[row] : 0;
     fr1 = row + 1 < A.R ? A.fn_row[row + 1] : 0;
   }
-  auto load_chunk = [&](int64_t ci) {
+  auto load_cols = [&](int64_t ci) {
+    ChunkInfo ch = info(cx, ci);
+#pragma unroll
+    for (int i = 0; i < (FN ? NLD : 0); ++i) {
+      const int cc = 2 * i + (lane >> 5);
+      fcol[i] = A.fn_col[ch.gcol0 + (cc < ch.ncols ? cc : 0)];
+    }
+  };
+  // loads i0 .. i1 - 1 of a chunk's NLD per lane (constants once unrolled)
+  auto load_part = [&](int64_t ci, int i0, int i1) {
     ChunkInfo ch = info(cx, ci);
     const double* base = (const double*)ch.ptr;
 #pragma unroll
     for (int i = 0; i < NLD; ++i) {
+      if (i < i0 || i >= i1) continue;
       const int cc = 2 * i + (lane >> 5);
       const int r = (lane & 31) * 2;
       const int64_t row = row0w + r;
       const bool colok = cc < ch.ncols;
       const double* p = base + (ch.lcol0 + cc) * A.R + row;
       if constexpr (FN) {
-        const int fc = colok ? A.fn_col[ch.gcol0 + cc] : 0;
-        xr[i][0] = (colok && row < A.R) ? A.fn_rec[fr0 + fc] : 0.0;
-        xr[i][1] = (colok && row + 1 < A.R) ? A.fn_rec[fr1 + fc] : 0.0;
+        xr[i][0] = (colok && row < A.R) ? A.fn_rec[fr0 + fcol[i]] : 0.0;
+        xr[i][1] = (colok && row + 1 < A.R) ? A.fn_rec[fr1 + fcol[i]] : 0.0;
       } else if constexpr (X32) {
         const float* pf = (const float*)ch.ptr + (ch.lcol0 + cc) * A.R + row;
         if constexpr (ALIGNED) {   // R even, 8-byte pairs
@@ -1201,7 +1212,11 @@ __global__ __launch_bounds__(nwf_for(L4) * 64, f64_wg_per_cu(L4)) void k_sketch_
     store_omega(0);
     load_omega(cb + 1);
     store_omega(1);
-    load_chunk(cb);
+    if constexpr (FN) load_cols(cb);
+    load_part(cb, 0, NLD);
+    if constexpr (FN) {
+      if (cb + 1 < ce) load_cols(cb + 1);
+    }
     load_omega(cb + 2);
   }
   int it = 0;
@@ -1212,10 +1227,19 @@ __global__ __launch_bounds__(nwf_for(L4) * 64, f64_wg_per_cu(L4)) void k_sketch_
     store_omega((it + 2) % 4);
     __syncthreads();
     // (b) prefetch the next chunk; Omega three chunks ahead
-    if (ci + 1 < ce) load_chunk(ci + 1);
-    load_omega(ci + 3);
     // (c) finish the previous chunk's left sketch
-    if (it >= 1) reduce_t((it - 1) & 1, ci - 1);
+    // FN does both among the tiles of (d): a gather from the index tables is many
+    // vector instructions for an entry, during which the matrix unit would wait, and
+    // with two waves to a SIMD the other rarely covers it (64^5, ell = 32: 3075 ->
+    // 2786 us, 2951 of it with the column indices a chunk ahead alone).  Loads from
+    // memory lose by it (2088 -> 2140 us at 32^6, ell = 20): they are issued later.
+    if constexpr (!FN) {
+      if (ci + 1 < ce) load_part(ci + 1, 0, NLD);
+    }
+    load_omega(ci + 3);
+    if constexpr (!FN) {
+      if (it >= 1) reduce_t((it - 1) & 1, ci - 1);
+    }
     const double* xw = Xl[w];
     const double* om = Om[it % 4];
     // (d) matrix-core tiles; the left sketch uses two accumulator chains
@@ -1256,6 +1280,11 @@ __global__ __launch_bounds__(nwf_for(L4) * 64, f64_wg_per_cu(L4)) void k_sketch_
 #pragma unroll
         for (int s = 0; s < NS; ++s)
           ts[kk & 1][s] = __builtin_amdgcn_mfma_f64_4x4x4f64(psis[k2][s], b, ts[kk & 1][s], 0, 0, 0);
+      }
+      if constexpr (FN) {
+        if (ci + 1 < ce) load_part(ci + 1, ks * (NLD / 4), (ks + 1) * (NLD / 4));
+        if (ks == 1 && it >= 1) reduce_t((it - 1) & 1, ci - 1);
+        if (ks == 3 && ci + 2 < ce) load_cols(ci + 2);
       }
     }
 #pragma unroll
