@@ -1271,14 +1271,25 @@ __global__ void k_two_sided_htab(const TwoSidedBatch B) {
 // order of every sum are those of k_two_sided_part.  FTAB: the first mode's
 // factor rows (n_0 ell <= TS_FTAB entries for every problem) sit in LDS, so a
 // lane keeps only their row indices, and three workgroups fit on a compute unit.
+// Of the ell columns 16 NQ, and with TAIL four more, are formed: 16x16x4 tiles,
+// the four on the 4x4x4 instruction, whose operands have the same lanes.  Bound by
+// vector instructions around the tiles (a row's place in the first mode and H is
+// carried from slice to slice, not divided out again) and the tiles' rate.
+// 1.86 M rows, ell = 20: 162 -> 85 us with both; 32 columns always and a division a
+// slice before.
 constexpr int TS_FTAB = 1024;
 
-template <bool FTAB>
+template <bool FTAB, int NQ, bool TAIL>
 __global__ __launch_bounds__(256, FTAB ? 3 : 2) void k_two_sided_part_h(const TwoSidedBatch B,
                                                                         double* __restrict__ part) {
-  __shared__ double Ss[PSTT2_MAX_ELL][TS_ROWS + 1];   // operand slice, [column][row]; reused for the wave sums
-  __shared__ double Hs[TS_HMAX][PSTT2_MAX_ELL + 1];
-  __shared__ double F1[FTAB ? TS_FTAB : 1];
+  static_assert(NQ == 1 || !TAIL, "16, 20 or 32 columns");
+  constexpr int W = 16 * NQ + (TAIL ? 4 : 0);   // columns formed
+  constexpr int NA = NQ + (TAIL ? 1 : 0);       // operands of a lane and side
+  // operand slice, [column][row]; reused for the wave sums
+  __shared__ double Ss[W][TS_ROWS + 1];
+  // rows of ell; columns past ell, read with the next row's, reach only outputs that are not kept
+  __shared__ double Hs[(TS_HMAX + 1) * PSTT2_MAX_ELL];
+  __shared__ double F1[FTAB ? TS_FTAB + PSTT2_MAX_ELL : 1];
   const int t = threadIdx.x;
   const int lane = t & 63, w = t >> 6, g = lane >> 4, l = lane & 15;
   const int ell = B.ell, d = B.d;
@@ -1296,22 +1307,31 @@ __global__ __launch_bounds__(256, FTAB ? 3 : 2) void k_two_sided_part_h(const Tw
   const int64_t n0 = nmode[q0];
   const int64_t off0 = off[0];
   const int nout = ell * ell;
+  int ucol[NA];   // this lane's columns
+#pragma unroll
+  for (int a = 0; a < NA; ++a) ucol[a] = a < NQ ? 16 * a + l : 16 + (lane & 3);
   if constexpr (FTAB) {
     for (int e = t; e < n0 * ell; e += 256) F1[e] = B.fac[off0 + e];   // visible after the first barrier
   }
-  ts_d4 acc[2][2];
+  ts_d4 acc[NQ][NQ];
+  double tx = 0.0, ty = 0.0, tt = 0.0;   // TAIL: its columns as rows, as columns, as both
 #pragma unroll
-  for (int a = 0; a < 2; ++a)
+  for (int a = 0; a < NQ; ++a)
 #pragma unroll
-    for (int c = 0; c < 2; ++c) acc[a][c] = ts_d4{0.0, 0.0, 0.0, 0.0};
-  constexpr int NPRE = PSTT2_MAX_ELL * TS_ROWS / 256;
-  constexpr int NHP = (TS_HMAX * PSTT2_MAX_ELL + 255) / 256;
+    for (int c = 0; c < NQ; ++c) acc[a][c] = ts_d4{0.0, 0.0, 0.0, 0.0};
+  constexpr int NPRE = W * TS_ROWS / 256;
+  constexpr int NHP = (TS_HMAX * W + 255) / 256;
   double pre[NPRE], hpre[NHP];
-  // lane operands: rows 32 w + 4 kk + g of the slice, columns 16 a + l
-  double fv[FTAB ? 1 : 2][8][2];
-  int fi[FTAB ? 2 : 1][8];   // FTAB: first-mode index of each of the lane's rows
-  int rh[2][8];
-  uint32_t rok[2];
+  // lane operands: rows 32 w + 4 kk + g of the slice
+  double fv[FTAB ? 1 : 2][8][NA];
+  int fi[FTAB ? 2 : 1][8];   // FTAB: offset of each row's first-mode factor row in F1
+  int rh[2][8];              // offset of its H row in Hs
+  // first-mode index and H row of the next slice's first row, and of this lane's first
+  // row in it (the H row relative to the slice's)
+  const int m0 = (int)n0, dh = TS_ROWS / m0, di = TS_ROWS % m0;
+  int64_t sh = r0 / m0;
+  int si = (int)(r0 % m0), li = (int)((r0 + 32 * w + g) % m0), lh = (int)((r0 + 32 * w + g) / m0 - sh);
+  int nhe = 0;               // entries of the loaded slice's H rows, <= TS_HMAX ell
   // the register buffer is a template argument, so every index stays static
   auto load_slice = [&](int64_t rb, auto bsel) {
     constexpr int b = decltype(bsel)::value;
@@ -1321,79 +1341,81 @@ __global__ __launch_bounds__(256, FTAB ? 3 : 2) void k_two_sided_part_h(const Tw
       const int u = t / TS_ROWS + (256 / TS_ROWS) * j;
       pre[j] = (row < K && u < sc) ? S[(int64_t)u * K + row] : 0.0;
     }
-    const int64_t h0 = rb / n0;
-    const int64_t rl = std::min<int64_t>(rb + TS_ROWS, K) - 1;
-    const int64_t nhe = (rl / n0 - h0 + 1) * ell;   // <= TS_HMAX ell
+    const int rows = (int)std::min<int64_t>(TS_ROWS, K - rb);
+    nhe = (int)(((uint32_t)si + rows - 1) / (uint32_t)m0 + 1) * ell;
 #pragma unroll
     for (int m = 0; m < NHP; ++m) {
       const int e = t + 256 * m;
-      hpre[m] = e < nhe ? H[h0 * ell + e] : 0.0;
+      hpre[m] = e < nhe ? H[sh * ell + e] : 0.0;
     }
     // first-mode index and H row of each of the lane's rows (n_0 >= 4: a step
-    // of four rows wraps the first mode at most once)
-    const int64_t base = rb + 32 * w + g;
-    int64_t i = base % n0, hq = base / n0;
-    uint32_t ok = 0;
+    // of four rows wraps the first mode at most once); rows past K, where S is zero,
+    // take the slice's first
+    int i = li, hq = lh;
+    const int left = rows - 32 * w - g;
 #pragma unroll
     for (int kk = 0; kk < 8; ++kk) {
       if (kk > 0) {
         i += 4;
-        if (i >= n0) {
-          i -= n0;
+        if (i >= m0) {
+          i -= m0;
           ++hq;
         }
       }
-      const bool in = base + 4 * kk < K;
-      ok |= (in ? 1u : 0u) << kk;
-      rh[b][kk] = (int)(hq - h0);
+      const bool in = 4 * kk < left;
+      rh[b][kk] = in ? hq * ell : 0;
       if constexpr (FTAB) {
-        fi[b][kk] = (int)i;
+        fi[b][kk] = in ? i * ell : 0;
       } else {
 #pragma unroll
-        for (int a = 0; a < 2; ++a) {
-          const int u = 16 * a + l;
-          fv[b][kk][a] = (in && u < ell) ? B.fac[off0 + i * ell + u] : 0.0;
-        }
+        for (int a = 0; a < NA; ++a)
+          fv[b][kk][a] = (in && ucol[a] < ell) ? B.fac[off0 + (int64_t)i * ell + ucol[a]] : 0.0;
       }
     }
-    rok[b] = ok;
+    sh += dh;
+    if (si >= m0 - di) {   // li += di, si += di, each wrapped
+      si -= m0;
+      ++sh;
+      --lh;
+    }
+    si += di;
+    if (li >= m0 - di) {
+      li -= m0;
+      ++lh;
+    }
+    li += di;
   };
   auto slice = [&](int64_t rb, auto bsel) {
     constexpr int b = decltype(bsel)::value;
-    const int64_t h0 = rb / n0;
     __syncthreads();   // the last slice's LDS reads are done
 #pragma unroll
     for (int j = 0; j < NPRE; ++j) Ss[t / TS_ROWS + (256 / TS_ROWS) * j][t % TS_ROWS] = pre[j];
-    {
-      const int64_t rl = std::min<int64_t>(rb + TS_ROWS, K) - 1;
-      const int nhe = (int)((rl / n0 - h0 + 1) * ell);
 #pragma unroll
-      for (int m = 0; m < NHP; ++m) {
-        const int e = t + 256 * m;
-        if (e < nhe) Hs[e / ell][e % ell] = hpre[m];
-      }
-    }
+    for (int m = 0; m < NHP; ++m)
+      if (t + 256 * m < nhe) Hs[t + 256 * m] = hpre[m];
     __syncthreads();
     if (rb + TS_ROWS < std::min<int64_t>(K, r0 + (int64_t)TS_ROWS * nsteps)) load_slice(rb + TS_ROWS, std::integral_constant<int, b ^ 1>{});
 #pragma unroll
     for (int kk = 0; kk < 8; ++kk) {
       const int r = 32 * w + 4 * kk + g;
-      const bool in = (rok[b] >> kk) & 1u;
-      double f[2], sv[2];
+      double x[NA], y[NA];
 #pragma unroll
-      for (int a = 0; a < 2; ++a) {
-        const int u = 16 * a + l;
-        sv[a] = Ss[u][r];
-        if constexpr (FTAB) f[a] = (in && u < ell) ? F1[fi[b][kk] * ell + u] * Hs[rh[b][kk]][u] : 0.0;
-        else f[a] = (in && u < ell) ? fv[b][kk][a] * Hs[rh[b][kk]][u] : 0.0;
+      for (int a = 0; a < NA; ++a) {
+        const double sv = Ss[ucol[a]][r];
+        const double f = (FTAB ? F1[fi[FTAB ? b : 0][kk] + ucol[a]] : fv[FTAB ? 0 : b][kk][a]) * Hs[rh[b][kk] + ucol[a]];
+        // left: Psi_k(row, u) S_k(row, v); right: T_k(u, col) Omega_k(col, v)
+        x[a] = right ? sv : f;
+        y[a] = right ? f : sv;
       }
 #pragma unroll
-      for (int a = 0; a < 2; ++a)
+      for (int a = 0; a < NQ; ++a)
 #pragma unroll
-        for (int c = 0; c < 2; ++c) {
-          const double x = right ? sv[a] : f[a], y = right ? f[c] : sv[c];
-          acc[a][c] = __builtin_amdgcn_mfma_f64_16x16x4f64(x, y, acc[a][c], 0, 0, 0);
-        }
+        for (int c = 0; c < NQ; ++c) acc[a][c] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[a], y[c], acc[a][c], 0, 0, 0);
+      if constexpr (TAIL) {
+        tx = __builtin_amdgcn_mfma_f64_4x4x4f64(x[NQ], y[0], tx, 0, 0, 0);
+        ty = __builtin_amdgcn_mfma_f64_4x4x4f64(x[0], y[NQ], ty, 0, 0, 0);
+        tt = __builtin_amdgcn_mfma_f64_4x4x4f64(x[NQ], y[NQ], tt, 0, 0, 0);
+      }
     }
   };
   const std::integral_constant<int, 0> b0{};
@@ -1412,21 +1434,36 @@ __global__ __launch_bounds__(256, FTAB ? 3 : 2) void k_two_sided_part_h(const Tw
     if (rb < K) slice(rb, b0);
   }
   __syncthreads();
-  double* red = &Ss[0][0];   // 4 waves x 32 x 32 doubles fit in Ss (32 x 129)
+  double* red = &Ss[0][0];
+  static_assert(4 * W <= TS_ROWS + 1, "the four waves' W x W sums fit in Ss");
 #pragma unroll
-  for (int a = 0; a < 2; ++a)
+  for (int a = 0; a < NQ; ++a)
 #pragma unroll
-    for (int c = 0; c < 2; ++c)
+    for (int c = 0; c < NQ; ++c)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) red[w * 1024 + (16 * a + 4 * e + g) * 32 + 16 * c + l] = acc[a][c][e];
+      for (int e = 0; e < 4; ++e) red[(w * W + 16 * a + 4 * e + g) * W + 16 * c + l] = acc[a][c][e];
+  if constexpr (TAIL) {   // block (lane / 4) % 4 of the 4x4x4 results, element (g, lane % 4)
+    const int blk = (lane >> 2) & 3, l4 = lane & 3;
+    red[(w * W + 16 + g) * W + 4 * blk + l4] = tx;
+    red[(w * W + 4 * blk + g) * W + 16 + l4] = ty;
+    if (blk == 0) red[(w * W + 16 + g) * W + 16 + l4] = tt;
+  }
   __syncthreads();
   for (int o = t; o < nout; o += 256) {
     const int u = o % ell, v = o / ell;
-    double sum = red[u * 32 + v];
+    double sum = red[u * W + v];
 #pragma unroll
-    for (int ww = 1; ww < 4; ++ww) sum += red[ww * 1024 + u * 32 + v];
+    for (int ww = 1; ww < 4; ++ww) sum += red[(ww * W + u) * W + v];
     part[(int64_t)blockIdx.x * nout + o] = sum;
   }
+}
+
+template <bool FTAB>
+static void launch_part_h(const TwoSidedBatch& B, int64_t nblk, double* part, hipStream_t s) {
+  const dim3 g((unsigned)nblk), b(256);
+  if (B.ell <= 16) hipLaunchKernelGGL((k_two_sided_part_h<FTAB, 1, false>), g, b, 0, s, B, part);
+  else if (B.ell <= 20) hipLaunchKernelGGL((k_two_sided_part_h<FTAB, 1, true>), g, b, 0, s, B, part);
+  else hipLaunchKernelGGL((k_two_sided_part_h<FTAB, 2, false>), g, b, 0, s, B, part);
 }
 
 __global__ __launch_bounds__(256) void k_two_sided_sum(const TwoSidedBatch B, const double* __restrict__ part) {
@@ -1514,8 +1551,8 @@ hipError_t two_sided_batch(TwoSidedBatch& B, hipStream_t s) {
     hipLaunchKernelGGL(k_two_sided_htab, dim3(gh, (unsigned)B.n), dim3(256), 0, s, B);
     bool ftab = true;
     for (int p = 0; p < B.n; ++p) ftab = ftab && B.nmode[B.right[p] ? B.split[p] : 0] * B.ell <= TS_FTAB;
-    if (ftab) hipLaunchKernelGGL(k_two_sided_part_h<true>, dim3((unsigned)nblk), dim3(256), 0, s, B, part);
-    else hipLaunchKernelGGL(k_two_sided_part_h<false>, dim3((unsigned)nblk), dim3(256), 0, s, B, part);
+    if (ftab) launch_part_h<true>(B, nblk, part, s);
+    else launch_part_h<false>(B, nblk, part, s);
   } else {
     hipLaunchKernelGGL(k_two_sided_part, dim3((unsigned)nblk), dim3(256), 0, s, B, part);
   }
