@@ -400,7 +400,8 @@ void tt_cores_free(tt_cores* cores);
  * matrix: singular values keep their relative accuracy), FP64 throughout.
  * Scope: every unfolding's short side min(R_k, C_k) must be at most
  * PSTT2_TTSVD_MAX_SIDE; the work is about 10 sweeps of short side x N
- * products per split.  x_dev: N = n_1...n_d FP64 entries, column-major,
+ * products per split, or some ten products with 16 columns where a gap follows
+ * fewer than 16 kept singular values.  x_dev: N = n_1...n_d FP64 entries, column-major,
  * read-only.  out receives library-owned cores (release with tt_cores_free).
  * X = 0 gives ranks 1 and X~ = 0.  sync.  Errors: EINVAL (arguments, scope),
  * ENUMERIC (non-finite X, no convergence in 40 sweeps), ENOMEM, EDEVICE. */

@@ -309,8 +309,18 @@ hipError_t svd_init(double* J, int sp, int* counter, hipStream_t s);
 // orthogonal when met.  Pairs whose squared norms are both at most tau are left
 // alone (tau < 0: none).  ws: svd_ws_doubles doubles (may be null when 0).
 int64_t svd_ws_doubles(int64_t L, int sp);
-hipError_t svd_sweep(double* W, int64_t L, double* J, int sp, double tol, double tau, double* ws, int* counter,
-                     hipStream_t s);
+// Columns past sp, and J's rows jr, may be more than the swept sp columns.
+hipError_t svd_sweep(double* W, int64_t L, double* J, int jr, int sp, double tol, double tau, double small, double* ws,
+                     int* counter, hipStream_t s);
+// The leading kSvdLead columns (see svd_lead_init).  lead: svd_lead_doubles(L, sp) doubles.
+constexpr int kSvdLead = 16;
+int64_t svd_lead_doubles(int64_t L, int sp);
+hipError_t svd_lead_init(double* W, int64_t L, double* J, int sp, double* lead, hipStream_t s);
+hipError_t svd_lead_products(const double* W, int64_t L, int sp, double* lead, hipStream_t s);
+hipError_t svd_lead_turn(double* W, int64_t L, double* J, int sp, double* lead, hipStream_t s);
+hipError_t svd_lead_check(const double* sig, int scols, int sp, const double* lead, double tol, double tau, double small,
+                          int* counter, hipStream_t s);
+hipError_t qr_reflectors(const double* A, int64_t M, double* V, double* T, double* R, hipStream_t s);
 hipError_t svd_colnorms(const double* W, int64_t L, int scols, double* sig, hipStream_t s);
 hipError_t svd_gather(const double* src, int64_t ld, int64_t rows, const int* idx, const double* sig, int r,
                       double* dst, hipStream_t s);

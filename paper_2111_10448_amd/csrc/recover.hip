@@ -143,6 +143,7 @@ struct LeafBatch {
   double* Rst[MAXB];
   int64_t ldr[MAXB];
   int qb;             // rows of a block
+  double* T;          // T of the only block (L x L, L: ell rounded up), if asked for
   int64_t blk0[MAXB + 1];
 };
 
@@ -266,12 +267,19 @@ struct Leaf {
     double tj = 0.0, beta = alpha, rbeta = 0.0, scal = 0.0;
     if (sigma != 0.0) {   // uniform
       const double m = alpha * alpha + sigma;
-      const double r0 = __builtin_amdgcn_rsq(m);
-      double z = m * r0, h = 0.5 * r0;
-      const double e = __builtin_fma(-h, z, 0.5);
-      z = __builtin_fma(z, e, z);
-      h = __builtin_fma(h, e, h);
-      z = __builtin_fma(__builtin_fma(-z, z, m), h, z);   // sqrt(m)
+      double z, h;   // sqrt(m), half its reciprocal
+      if (m >= 0x1p-900) {
+        const double r0 = __builtin_amdgcn_rsq(m);
+        z = m * r0;
+        h = 0.5 * r0;
+        const double e = __builtin_fma(-h, z, 0.5);
+        z = __builtin_fma(z, e, z);
+        h = __builtin_fma(h, e, h);
+        z = __builtin_fma(__builtin_fma(-z, z, m), h, z);
+      } else {   // residuals of the steps would be denormal
+        z = sqrt(m);
+        h = 0.5 / z;
+      }
       beta = -copysign(z, alpha);
       const double den = alpha - beta;
       double y = __builtin_amdgcn_rcp(den);
@@ -445,6 +453,7 @@ __global__ __launch_bounds__(64 * QW) void k_qr_leaf(const LeafBatch B, int ell)
   leaf_t<L, 1>(G, T, X);
   for (int e = tid; e < L * L; e += blockDim.x) {
     const int i = e % L, j = e / L;
+    if (B.T) B.T[e] = T[i][j];
     if (i <= j && j < ell && S.rb + i < S.M) {
       double k = 0.0;
 #pragma unroll 8
@@ -859,6 +868,25 @@ static void launch_leaf(const LeafBatch& B, int64_t nblk, int64_t max_rows, int 
   else if (ell <= 16) hipLaunchKernelGGL((k_qr_leaf<2, QW>), g, b, 0, s, B, ell);
   else if (ell <= 24) hipLaunchKernelGGL((k_qr_leaf<3, QW>), g, b, 0, s, B, ell);
   else hipLaunchKernelGGL((k_qr_leaf<4, QW>), g, b, 0, s, B, ell);
+}
+
+// Householder reflectors of the M x 16 matrix A, M <= 1024, stride M: V (strictly below
+// its diagonal), T and R (16 x 16).
+hipError_t qr_reflectors(const double* A, int64_t M, double* V, double* T, double* R, hipStream_t s) {
+  LeafBatch B;
+  std::memset(&B, 0, sizeof(B));
+  B.n = 1;
+  B.A[0] = A;
+  B.M[0] = M;
+  B.V[0] = V;
+  B.Rst[0] = R;
+  B.ldr[0] = 16;
+  B.T = T;
+  B.qb = 8 * QR;
+  B.blk0[1] = 1;
+  if (M <= 4 * QR) launch_leaf<4>(B, 1, M, 16, s);
+  else launch_leaf<8>(B, 1, M, 16, s);
+  return hipGetLastError();
 }
 
 template <bool SV>

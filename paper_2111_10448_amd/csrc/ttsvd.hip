@@ -26,6 +26,11 @@
 // A round of block pairs costs 17 us and stands for about eight of those (383
 // rounds, 6.6 ms); the whole call went from 37.9 to 8.1 ms.  It is bound by that
 // chain: Gram loads, fifteen dependent rounds of angles, the application.
+//
+// Where the rank rule keeps fewer than kSvdLead columns and a gap follows them, power
+// steps on those columns replace the sweeps (see "leading columns" below): 8.1 -> 1.4 ms
+// for the same call, a third of it kernels of some 5 us and their launches, the rest
+// the reflectors' chain, the leading block's rotations and two readbacks a split.
 #include <algorithm>
 #include <cmath>
 
@@ -51,9 +56,12 @@ __device__ __forceinline__ void wave_sync() {
 }
 
 // Pair (w_p, w_q) counts as orthogonal; tau: columns whose squared norms are
-// both at most tau need not be (see svd_sweep).
-__device__ __forceinline__ bool needs_rotation(double a, double b, double g, double tol, double tau) {
-  return g != 0.0 && fabs(g) > tol * sqrt(a * b) && (a > tau || b > tau);
+// both at most tau need not be (see svd_sweep).  Nor need a column that is cut in any
+// case (squared norm at most small) be against one it cannot turn by a rounding: exact
+// zeros leave columns of 1e-150 and less whose products underflow.
+__device__ __forceinline__ bool needs_rotation(double a, double b, double g, double tol, double tau, double small) {
+  const double lo = a < b ? a : b, hi = a < b ? b : a;
+  return g != 0.0 && fabs(g) > tol * sqrt(a * b) && hi > tau && !(lo <= small && lo <= 0x1p-104 * hi);
 }
 
 __device__ __forceinline__ double block_sum(double v, double* red) {
@@ -213,7 +221,8 @@ __global__ __launch_bounds__(kJT) void k_jacobi_gram(const double* __restrict__ 
 // workgroup of the pair), the rotation, and its application to this workgroup's
 // rows of W and, in the pair's first workgroup, to J.
 __global__ __launch_bounds__(kJT) void k_jacobi_blocks(double* __restrict__ W, int64_t L, double* __restrict__ J,
-                                                       int sp, int nb, int k, double tol, double tau, int sweeps,
+                                                       int jr, int sp, int nb, int k, double tol, double tau,
+                                                       double small, int sweeps,
                                                        int64_t chunk, int nch, const double* __restrict__ gpart,
                                                        int* __restrict__ rotations) {
   __shared__ double part[kJT / 64][kPC * kPC];
@@ -239,7 +248,7 @@ __global__ __launch_bounds__(kJT) void k_jacobi_blocks(double* __restrict__ W, i
       const int e = lane + 64 * h, r = e / kPC, c = e % kPC;
       G[r][c] = G0[e];
       Q[r][c] = r == c ? 1.0 : 0.0;
-      if (r < c && needs_rotation(G0[r * kPC + r], G0[c * kPC + c], G0[e], tol, tau)) ++bad;
+      if (r < c && needs_rotation(G0[r * kPC + r], G0[c * kPC + c], G0[e], tol, tau, small)) ++bad;
     }
     for (int o = 32; o > 0; o >>= 1) bad += __shfl_xor(bad, o);
     if (lane == 0) {
@@ -262,7 +271,7 @@ __global__ __launch_bounds__(kJT) void k_jacobi_blocks(double* __restrict__ W, i
   }
   // tiles of this workgroup's rows of W, then (first workgroup) those of J; a wave
   // takes kAU tiles at a time, every load before the first store
-  const int64_t ntw = (r1 - r0 + 15) / 16, nt = ntw + (ch == 0 ? (sp + 15) / 16 : 0);
+  const int64_t ntw = (r1 - r0 + 15) / 16, nt = ntw + (ch == 0 ? (jr + 15) / 16 : 0);
   constexpr int kAU = 3;
   for (int64_t t0 = w; t0 < nt; t0 += kAU * (kJT / 64)) {
     double x[kAU][4];
@@ -273,8 +282,8 @@ __global__ __launch_bounds__(kJT) void k_jacobi_blocks(double* __restrict__ W, i
       const int64_t tt = t0 + u * (kJT / 64);
       const bool inw = tt < ntw;
       const int64_t r = inw ? r0 + 16 * tt + l16 : 16 * (tt - ntw) + l16;
-      ld[u] = inw ? L : sp;
-      m[u] = tt < nt && r < (inw ? r1 : (int64_t)sp) ? (inw ? W : J) + r : nullptr;
+      ld[u] = inw ? L : jr;
+      m[u] = tt < nt && r < (inw ? r1 : (int64_t)jr) ? (inw ? W : J) + r : nullptr;
 #pragma unroll
       for (int ks = 0; ks < 4; ++ks) {
         const bool ok = m[u] && ci[ks] < sp;
@@ -292,6 +301,97 @@ __global__ __launch_bounds__(kJT) void k_jacobi_blocks(double* __restrict__ W, i
         if (m[u] && ci[v] < sp) m[u][ci[v] * ld[u]] = acc[v];
     }
   }
+}
+
+// ---- leading columns ----
+// Where the rank rule cuts a tail that a gap sets off, only the pairs with a kept
+// column matter, and sweeps meet them a block at a time.  Turning the columns by an
+// orthogonal H whose first sixteen columns span those of W^T W_1 (W_1 the first
+// sixteen of W; at first W Omega, Omega random) is a power step for all of them at
+// once: W <- W H, J <- J H, H = I - V T V^T from the reflectors of W^T W_1.  It stays
+// orthogonal to rounding, and near convergence H - I is small, so W's small columns
+// lose nothing by it: with the sixteen made orthogonal among themselves the test of
+// the sweeps is met by every pair with a kept column after a few steps.  Three
+// launches, 35 us, a step (17 us for the reflectors of 340 rows, 11 for the turn),
+// against seventeen microseconds a round of block pairs.
+
+// Omega (s x kSvdLead): mixed bits of the index, in [-1, 1)
+__global__ void k_svd_omega(double* __restrict__ Om, int s) {
+  for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < s * kSvdLead; t += gridDim.x * blockDim.x) {
+    uint32_t h = (uint32_t)t * 2654435761u + 12345u;
+    h = (h ^ (h >> 15)) * 2246822519u;
+    h = (h ^ (h >> 13)) * 3266489917u;
+    h ^= h >> 16;
+    Om[t] = (double)(int32_t)h * 0x1p-31;
+  }
+}
+
+// M <- M H for the rows of W (L x s) and of J (s x s); a workgroup takes 16 rows, its
+// waves share the columns.
+__global__ __launch_bounds__(kBS) void k_svd_turn(double* __restrict__ W, int64_t L, double* __restrict__ J, int s,
+                                                  const double* __restrict__ V, const double* __restrict__ T) {
+  constexpr int P = kSvdLead, NW = kBS / 64;
+  static_assert(P == 16, "one tile");
+  __shared__ double part[NW][P][17], MT[P][17], Ts[P][P];
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6, l16 = lane & 15, g4 = lane >> 4;
+  const int64_t ntw = (L + 15) / 16;
+  const bool inw = blockIdx.x < ntw;
+  double* M = inw ? W : J;
+  const int64_t ld = inw ? L : s, row = 16 * (inw ? blockIdx.x : blockIdx.x - ntw) + l16;
+  const bool ok = row < ld;
+  auto vx = [&](int j, int c) -> double {   // V with its unit diagonal
+    const double v = j < s ? V[(int64_t)c * s + j] : 0.0;
+    return j > c ? v : (j == c ? 1.0 : 0.0);
+  };
+  Ts[t & 15][t >> 4] = T[t];   // [row][column]
+  // M V: result element v at column 4 v + g4, row l16
+  d4 acc = d4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll 4
+  for (int j0 = 4 * w; j0 < s; j0 += 4 * NW) {
+    const int j = j0 + g4;
+    const double x = ok && j < s ? M[row + ld * j] : 0.0;
+    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(vx(j, l16), x, acc, 0, 0, 0);
+  }
+#pragma unroll
+  for (int e = 0; e < 4; ++e) part[w][4 * e + g4][l16] = acc[e];
+  __syncthreads();
+  {
+    const int r = t & 15, c = t >> 4;   // (M V T)(r, c)
+    double sum = 0.0;
+    for (int k = 0; k <= c; ++k) {
+      double p = 0.0;
+      for (int ww = 0; ww < NW; ++ww) p += part[ww][k][r];
+      sum += p * Ts[k][c];
+    }
+    MT[c][r] = sum;
+  }
+  __syncthreads();
+  double mt[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) mt[k] = MT[4 * k + g4][l16];
+#pragma unroll 2
+  for (int j0 = 16 * w; j0 < s; j0 += 16 * NW) {
+    d4 d = d4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int k = 0; k < 4; ++k) d = __builtin_amdgcn_mfma_f64_16x16x4f64(vx(j0 + l16, 4 * k + g4), mt[k], d, 0, 0, 0);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int j = j0 + 4 * e + g4;
+      if (ok && j < s) M[row + ld * j] -= d[e];
+    }
+  }
+}
+
+// Pairs of one of the leading columns (products C = W^T W_1, s x kSvdLead) that the
+// sweeps would still rotate.
+__global__ void k_svd_lead_check(const double* __restrict__ C, int s, const double* __restrict__ sig, int scols,
+                                 double tol, double tau, double small, int* __restrict__ counter) {
+  int bad = 0;
+  for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < scols * kSvdLead; t += gridDim.x * blockDim.x) {
+    const int j = t % scols, i = t / scols;
+    if (j > i && needs_rotation(sig[i] * sig[i], sig[j] * sig[j], C[(int64_t)i * s + j], tol, tau, small)) ++bad;
+  }
+  if (bad) atomicAdd(counter, bad);
 }
 
 // sig[j] = ||W(:, j)||, one workgroup per column
@@ -395,8 +495,8 @@ int64_t svd_ws_doubles(int64_t L, int sp) {
   return nch > 1 ? (int64_t)svd_blocks(sp) / 2 * nch * kPC * kPC : 0;
 }
 
-hipError_t svd_sweep(double* W, int64_t L, double* J, int sp, double tol, double tau, double* ws, int* counter,
-                     hipStream_t s) {
+hipError_t svd_sweep(double* W, int64_t L, double* J, int jr, int sp, double tol, double tau, double small, double* ws,
+                     int* counter, hipStream_t s) {
   int64_t chunk = 0;
   const int nch = svd_chunks(L, &chunk), nb = svd_blocks(sp);
   const int sweeps = nb == 2 ? 8 : 1;   // a single pair of blocks: to convergence on its Gram matrix
@@ -404,8 +504,46 @@ hipError_t svd_sweep(double* W, int64_t L, double* J, int sp, double tol, double
   hipLaunchKernelGGL(k_zero_int, dim3(1), dim3(1), 0, s, counter);
   for (int k = 0; k < nb - 1; ++k) {
     if (nch > 1) hipLaunchKernelGGL(k_jacobi_gram, g, b, 0, s, W, L, sp, nb, k, chunk, nch, ws);
-    hipLaunchKernelGGL(k_jacobi_blocks, g, b, 0, s, W, L, J, sp, nb, k, tol, tau, sweeps, chunk, nch, ws, counter);
+    hipLaunchKernelGGL(k_jacobi_blocks, g, b, 0, s, W, L, J, jr, sp, nb, k, tol, tau, small, sweeps, chunk, nch, ws, counter);
   }
+  return hipGetLastError();
+}
+
+// lead: products C (sp x P), reflectors V (sp x P), T and R (P x P each), W Omega (L x P)
+int64_t svd_lead_doubles(int64_t L, int sp) {
+  return (int64_t)kSvdLead * (2 * (int64_t)sp + 2 * kSvdLead + L);
+}
+
+hipError_t svd_lead_turn(double* W, int64_t L, double* J, int sp, double* lead, hipStream_t s) {
+  double *V = lead + (int64_t)sp * kSvdLead, *T = V + (int64_t)sp * kSvdLead;
+  hipError_t e = qr_reflectors(lead, sp, V, T, T + kSvdLead * kSvdLead, s);
+  if (e != hipSuccess) return e;
+  const unsigned g = (unsigned)((L + 15) / 16 + (sp + 15) / 16);
+  hipLaunchKernelGGL(k_svd_turn, dim3(g), dim3(kBS), 0, s, W, L, J, sp, V, T);
+  return hipGetLastError();
+}
+
+// C = W^T W_1
+hipError_t svd_lead_products(const double* W, int64_t L, int sp, double* lead, hipStream_t s) {
+  return adj_gemm(true, false, sp, kSvdLead, L, 1.0, W, L, W, L, 0.0, lead, sp, s);
+}
+
+// First turn, from W^T (W Omega).
+hipError_t svd_lead_init(double* W, int64_t L, double* J, int sp, double* lead, hipStream_t s) {
+  double* Z = lead + (int64_t)kSvdLead * (2 * (int64_t)sp + 2 * kSvdLead);
+  double* Om = lead + (int64_t)sp * kSvdLead;   // where the reflectors go
+  hipLaunchKernelGGL(k_svd_omega, dim3(grid_of((int64_t)sp * kSvdLead)), dim3(256), 0, s, Om, sp);
+  hipError_t e = adj_gemm(false, false, L, kSvdLead, sp, 1.0, W, L, Om, sp, 0.0, Z, L, s);
+  if (e == hipSuccess) e = adj_gemm(true, false, sp, kSvdLead, L, 1.0, W, L, Z, L, 0.0, lead, sp, s);
+  if (e == hipSuccess) e = svd_lead_turn(W, L, J, sp, lead, s);
+  return e;
+}
+
+hipError_t svd_lead_check(const double* sig, int scols, int sp, const double* lead, double tol, double tau, double small,
+                          int* counter, hipStream_t s) {
+  hipLaunchKernelGGL(k_zero_int, dim3(1), dim3(1), 0, s, counter);
+  hipLaunchKernelGGL(k_svd_lead_check, dim3(grid_of((int64_t)scols * kSvdLead)), dim3(256), 0, s, lead, sp, sig,
+                     scols, tol, tau, small, counter);
   return hipGetLastError();
 }
 
