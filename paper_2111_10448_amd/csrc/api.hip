@@ -392,14 +392,48 @@ hipError_t y_settle(pstt2_ctx* c) {
   return e;
 }
 
-__global__ void k_transpose_last(const double* P, int64_t rows, int r, double* G) {
-  // G_d(a, i) = P(i, a): P is rows x r column-major, G is r x rows column-major
+// G_d(a, i) = P(i, a): P is rows x r column-major, G_d is r x rows column-major.  G_1 is
+// a copy of Q (nq entries, 0: none); both in one launch of a few microseconds.
+__global__ void k_outer_cores(const double* Q, int64_t nq, double* G1, const double* P, int64_t rows, int r,
+                              double* Gd) {
   const int64_t tot = rows * r;
-  for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < tot; t += (int64_t)gridDim.x * blockDim.x) {
-    const int a = (int)(t % r);
-    const int64_t i = t / r;
-    G[t] = P[(int64_t)a * rows + i];
+  for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < tot + nq; t += (int64_t)gridDim.x * blockDim.x) {
+    if (t < tot) {
+      const int a = (int)(t % r);
+      const int64_t i = t / r;
+      Gd[t] = P[(int64_t)a * rows + i];
+    } else {
+      G1[t - tot] = Q[t - tot];
+    }
   }
+}
+
+// The cores of a tensor train into another's buffers, one launch: a copy each cost
+// 2 to 4 us and the gap before it.
+struct CoreCopies {
+  int d;
+  const double* src[PSTT2_MAX_D];
+  double* dst[PSTT2_MAX_D];
+  int64_t end[PSTT2_MAX_D];   // running sum of the sizes
+};
+__global__ void k_copy_cores(const CoreCopies A) {
+  int k = 0;
+  for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < A.end[A.d - 1];
+       t += (int64_t)gridDim.x * blockDim.x) {
+    while (t >= A.end[k]) ++k;   // t increases
+    const int64_t i = t - (k > 0 ? A.end[k - 1] : 0);
+    A.dst[k][i] = A.src[k][i];
+  }
+}
+
+// p and q in the memory of one device
+bool same_device(const void* p, const void* q) {
+  hipPointerAttribute_t a, b;
+  if (hipPointerGetAttributes(&a, p) != hipSuccess || hipPointerGetAttributes(&b, q) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return a.type == hipMemoryTypeDevice && b.type == hipMemoryTypeDevice && a.device == b.device;
 }
 
 // smallest r with sum_{i>r} sigma_i^2 <= eps^2/(d-1) * sum sigma_i^2, at least 1
@@ -1041,12 +1075,12 @@ pstt2_status pstt2_recover(pstt2_ctx* c, tt_cores* out) {
   // column-basis cores G_1 .. G_{m-1} (PSTT: G_1 .. G_{d-1})
   const int kl_end = c->pstt ? d - 1 : m - 1;
   for (int k = 1; k <= kl_end && e == hipSuccess; ++k) {
-    if (k == 1)
-      e = hipMemcpyAsync(tc.core[0], c->basis[1], sizeof(double) * c->n[0] * r[1], hipMemcpyDeviceToDevice, s);
-    else
+    if (k > 1)
       e = core_left(c->basis[k - 1], c->Rk[k - 1], r[k - 1], c->basis[k], (int)c->n[k - 1], r[k], tc.core[k - 1], s);
   }
   if (c->pstt) {
+    if (e == hipSuccess)
+      e = hipMemcpyAsync(tc.core[0], c->basis[1], sizeof(double) * c->n[0] * r[1], hipMemcpyDeviceToDevice, s);
     if (e != hipSuccess) return cfail(e, "cores");
     // last core G_d (r_{d-1} x n_d).  One pass: G_d = (Psi^T Q)^+ T with
     // Psi = Psi_{d-1}, Q = Q_{d-1} and T = T_{d-1} = Psi^T X_{d-1} (kept
@@ -1091,7 +1125,9 @@ pstt2_status pstt2_recover(pstt2_ctx* c, tt_cores* out) {
   for (int k = m + 1; k <= d && e == hipSuccess && !c->pstt; ++k) {
     if (k == d) {
       const int64_t rows = c->n[d - 1];
-      hipLaunchKernelGGL(k_transpose_last, dim3(64), dim3(256), 0, s, c->basis[d - 1], rows, r[d - 1], tc.core[d - 1]);
+      hipLaunchKernelGGL(k_outer_cores, dim3(64), dim3(256), 0, s, kl_end >= 1 ? c->basis[1] : nullptr,
+                         kl_end >= 1 ? c->n[0] * (int64_t)r[1] : 0, tc.core[0], c->basis[d - 1], rows, r[d - 1],
+                         tc.core[d - 1]);
       e = hipGetLastError();
     } else {
       const int64_t Cp = c->N / c->Rk[k - 1], Ck = c->N / c->Rk[k];
@@ -1636,12 +1672,32 @@ pstt2_status tt_cores_copy(const tt_cores* src, tt_cores* dst, void* hip_stream)
         !dst->core[k])
       return fail(nullptr, PSTT2_EINVAL, "core shapes differ");
   hipStream_t s = (hipStream_t)hip_stream;
+  CoreCopies a;
+  a.d = src->d;
+  int64_t tot = 0;
+  bool one = true;   // one device: a kernel reaches every buffer
   for (int k = 0; k < src->d; ++k) {
-    hipError_t e = hipMemcpyAsync(dst->core[k], src->core[k], sizeof(double) * src->r[k] * src->n[k] * src->r[k + 1],
-                                  hipMemcpyDeviceToDevice, s);
-    if (e != hipSuccess) return hfail(nullptr, e, "tt_cores_copy");
+    a.src[k] = src->core[k];
+    a.dst[k] = dst->core[k];
+    a.end[k] = tot += (int64_t)src->r[k] * src->n[k] * src->r[k + 1];
+    one = one && same_device(src->core[k], dst->core[k]) && (k == 0 || same_device(src->core[0], src->core[k]));
   }
-  hipError_t e = hipStreamSynchronize(s);
+  int dev = -1;
+  hipPointerAttribute_t at;
+  one = one && hipGetDevice(&dev) == hipSuccess && hipPointerGetAttributes(&at, src->core[0]) == hipSuccess &&
+        at.device == dev;
+  hipError_t e = hipSuccess;
+  if (one) {
+    hipLaunchKernelGGL(k_copy_cores, dim3((unsigned)std::max<int64_t>(1, std::min<int64_t>((tot + 255) / 256, 2048))),
+                       dim3(256), 0, s, a);
+    e = hipGetLastError();
+  } else {
+    for (int k = 0; k < src->d && e == hipSuccess; ++k)
+      e = hipMemcpyAsync(dst->core[k], src->core[k], sizeof(double) * (a.end[k] - (k > 0 ? a.end[k - 1] : 0)),
+                         hipMemcpyDeviceToDevice, s);
+  }
+  if (e != hipSuccess) return hfail(nullptr, e, "tt_cores_copy");
+  e = hipStreamSynchronize(s);
   if (e != hipSuccess) return hfail(nullptr, e, "tt_cores_copy");
   return PSTT2_OK;
 }
