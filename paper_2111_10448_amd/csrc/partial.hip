@@ -60,23 +60,29 @@ __global__ __launch_bounds__(256, 2) void k_partial_cols(const SketchArgs A, dou
     double psiq[KT][NQ > 0 ? NQ : 1];
     double psis[KT][NS > 0 ? NS : 1];
     {
-      PsiCursor pc;
-      pc.init(A, row0w + g4);
-      double hq[NQ > 0 ? NQ : 1], hs[NS > 0 ? NS : 1];
+      int cols[NQ + NS];
 #pragma unroll
-      for (int ks = 0; ks < KT; ++ks) {
-        if (ks > 0) pc.advance(A, 4);
-        if (pc.refresh(A)) {
+      for (int q = 0; q < NQ; ++q) cols[q] = 16 * q + l16;
 #pragma unroll
-          for (int q = 0; q < NQ; ++q) hq[q] = psi_hi(A, pc.h, 16 * q + l16);
+      for (int s = 0; s < NS; ++s) cols[NQ + s] = 16 * NQ + 4 * s + l4;
+      auto fill = [&](auto rows) {
+        rows.init(A, row0w + g4);
 #pragma unroll
-          for (int s = 0; s < NS; ++s) hs[s] = psi_hi(A, pc.h, 16 * NQ + 4 * s + l4);
+        for (int ks = 0; ks < KT; ++ks) {
+          double v[NQ + NS];
+          if (ks > 0) rows.advance(A, 4);
+          rows.values(A, cols, v);
+#pragma unroll
+          for (int q = 0; q < NQ; ++q) psiq[ks][q] = v[q];
+#pragma unroll
+          for (int s = 0; s < NS; ++s) psis[ks][s] = v[NQ + s];
         }
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) psiq[ks][q] = pc.at(A, 16 * q + l16, hq[q]);
-#pragma unroll
-        for (int s = 0; s < NS; ++s) psis[ks][s] = pc.at(A, 16 * NQ + 4 * s + l4, hs[s]);
-      }
+      };
+      static_assert(psi_stage_size(PC_ROWS, L4) <= 4 * 16 * ST, "the table fits in the X tiles");
+      __syncthreads();   // the last row block's reads of them are done
+      if (A.psi_tab) fill(PsiTable<NQ + NS>(A));
+      else if (psi_stage(A, rb * PC_ROWS, PC_ROWS, &Xl[0][0])) fill(PsiStaged<NQ + NS>(A, &Xl[0][0], rb * PC_ROWS));
+      else fill(PsiDirect<NQ + NS>());
     }
     pc_d4 yq[4][NQ > 0 ? NQ : 1];
     double ys[4][NS > 0 ? NS : 1];

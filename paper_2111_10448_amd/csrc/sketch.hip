@@ -159,6 +159,11 @@ __device__ __forceinline__ int acc_row(int g4, int v) {
   return PREC == P_F64 ? 4 * v + g4 : 4 * g4 + v;
 }
 
+// Sixteen bytes at the alignment of one entry: global loads take any (R not a multiple
+// of the vector; only whole vectors inside a column are loaded so).
+typedef double ud2 __attribute__((ext_vector_type(2), aligned(8)));
+typedef float uf4 __attribute__((ext_vector_type(4), aligned(4)));
+
 struct ChunkInfo {
   const char* ptr;   // column 0 of the chunk's segment
   int64_t lcol0;     // first column of the chunk within its segment
@@ -254,38 +259,61 @@ __global__ __launch_bounds__(NWS * 64, 2) void k_sketch(const SketchArgs A) {
   (void)psiM;
   (void)psiL;
   {
-    PsiCursor pc;
-    double hv[NT];
-    if constexpr (E::KPL == 1) {   // rows row0w + KSTEP ks + g4
-      pc.init(A, row0w + g4);
+    int cols[NT];
 #pragma unroll
-      for (int ks = 0; ks < KT; ++ks) {
-        if (ks > 0) pc.advance(A, E::KSTEP);
-        if (pc.refresh(A)) {
+    for (int mt = 0; mt < NT; ++mt) cols[mt] = 16 * mt + l16;
+    // operands of K step ks, from rows row0w + KSTEP ks + g4, or + 4 g4 + v, v = 0..3
+    auto step = [&](auto& rows, bool first_step, auto& oa, auto& om, auto& ol) {
+      double pv[NT];
+      if constexpr (E::KPL == 1) {
+        if (!first_step) rows.advance(A, E::KSTEP);
+        rows.values(A, cols, pv);
 #pragma unroll
-          for (int mt = 0; mt < NT; ++mt) hv[mt] = psi_hi(A, pc.h, 16 * mt + l16);
-        }
-#pragma unroll
-        for (int mt = 0; mt < NT; ++mt) psiA[ks][mt] = drm_to_lds<PREC>(pc.at(A, 16 * mt + l16, hv[mt]));
-      }
-    } else {   // rows row0w + 16 ks + 4 g4 + v, v = 0..3
-      pc.init(A, row0w + 4 * g4);
-#pragma unroll
-      for (int ks = 0; ks < KT; ++ks) {
+        for (int mt = 0; mt < NT; ++mt) oa[mt] = drm_to_lds<PREC>(pv[mt]);
+      } else {
         float p[4][NT];
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-          if (ks > 0 || v > 0) pc.advance(A, v > 0 ? 1 : 13);
-          if (pc.refresh(A)) {
+          if (v > 0) rows.advance(A, 1);
+          else if (!first_step) rows.advance(A, 13);
+          rows.values(A, cols, pv);
 #pragma unroll
-            for (int mt = 0; mt < NT; ++mt) hv[mt] = psi_hi(A, pc.h, 16 * mt + l16);
-          }
-#pragma unroll
-          for (int mt = 0; mt < NT; ++mt) p[v][mt] = (float)pc.at(A, 16 * mt + l16, hv[mt]);
+          for (int mt = 0; mt < NT; ++mt) p[v][mt] = (float)pv[mt];
         }
 #pragma unroll
-        for (int mt = 0; mt < NT; ++mt)
-          split3x4(p[0][mt], p[1][mt], p[2][mt], p[3][mt], psiA[ks][mt], psiM[ks][mt], psiL[ks][mt]);
+        for (int mt = 0; mt < NT; ++mt) split3x4(p[0][mt], p[1][mt], p[2][mt], p[3][mt], oa[mt], om[mt], ol[mt]);
+      }
+    };
+    const int64_t row_a = row0w + (E::KPL == 1 ? g4 : 4 * g4);
+    auto fill = [&](auto rows) {
+      rows.init(A, row_a);
+#pragma unroll
+      for (int ks = 0; ks < KT; ++ks) step(rows, ks == 0, psiA[ks], psiM[X3 ? ks : 0], psiL[X3 ? ks : 0]);
+    };
+    static_assert(psi_stage_size(NWS * RW, LP) * sizeof(double) <= sizeof(Xl), "the table fits in the X tiles");
+    const int64_t first = (int64_t)gi * (NWS * RW);
+    double* table = (double*)&Xl[0][0];
+    if (A.psi_tab) {
+      fill(PsiTable<NT>(A));
+    } else if (psi_stage(A, first, NWS * RW, table)) {
+      fill(PsiStaged<NT>(A, table, first));
+      __syncthreads();   // the X tiles take its place
+    } else {   // rolled: the arrays move up, the new row last
+      PsiDirect<NT> rows;
+      rows.init(A, row_a);
+#pragma unroll 1
+      for (int ks = 0; ks < KT; ++ks) {
+#pragma unroll
+        for (int u = 0; u + 1 < KT; ++u)
+#pragma unroll
+          for (int mt = 0; mt < NT; ++mt) {
+            psiA[u][mt] = psiA[u + 1][mt];
+            if constexpr (X3) {
+              psiM[u][mt] = psiM[u + 1][mt];
+              psiL[u][mt] = psiL[u + 1][mt];
+            }
+          }
+        step(rows, ks == 0, psiA[KT - 1], psiM[X3 ? KT - 1 : 0], psiL[X3 ? KT - 1 : 0]);
       }
     }
   }
@@ -366,8 +394,16 @@ __global__ __launch_bounds__(NWS * 64, 2) void k_sketch(const SketchArgs A) {
           xr[slot][i][2] = v.z;
           xr[slot][i][3] = v.w;
         } else {
+          if (colok && row + VEC <= A.R) {
+            const uf4 v = *(const uf4*)(col + row);
+            xr[slot][i][0] = v.x;
+            xr[slot][i][1] = v.y;
+            xr[slot][i][2] = v.z;
+            xr[slot][i][3] = v.w;
+          } else {
 #pragma unroll
-          for (int v = 0; v < VEC; ++v) xr[slot][i][v] = (colok && row + v < A.R) ? col[row + v] : (elem)0;
+            for (int v = 0; v < VEC; ++v) xr[slot][i][v] = (colok && row + v < A.R) ? col[row + v] : (elem)0;
+          }
         }
       } else if constexpr (ALIGNED) {
         const bool ok = colok && row < A.R;
@@ -748,28 +784,35 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void k_sketch16(const Ske
 
   // ---- stationary left-DRM operands Psi(row0w + 16 rt + 4 g4 + v, 16 mt + l16) ----
   {
-    PsiCursor pc;
-    pc.init(A, row0w + 4 * g4);
-    double hv[NT];
+    int cols[NT];
 #pragma unroll
-    for (int rt = 0; rt < RT; ++rt) {
-      float p[4][NT];
+    for (int mt = 0; mt < NT; ++mt) cols[mt] = 16 * mt + l16;
+    auto fill = [&](auto rows) {
+      rows.init(A, row0w + 4 * g4);
 #pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        if (rt > 0 || v > 0) pc.advance(A, v > 0 ? 1 : 13);
-        if (pc.refresh(A)) {
+      for (int rt = 0; rt < RT; ++rt) {
+        float p[4][NT];
 #pragma unroll
-          for (int mt = 0; mt < NT; ++mt) hv[mt] = psi_hi(A, pc.h, 16 * mt + l16);
+        for (int v = 0; v < 4; ++v) {
+          double pv[NT];
+          if (rt > 0 || v > 0) rows.advance(A, v > 0 ? 1 : 13);
+          rows.values(A, cols, pv);
+#pragma unroll
+          for (int mt = 0; mt < NT; ++mt) p[v][mt] = (float)pv[mt];
         }
 #pragma unroll
-        for (int mt = 0; mt < NT; ++mt) p[v][mt] = (float)pc.at(A, 16 * mt + l16, hv[mt]);
+        for (int mt = 0; mt < NT; ++mt)
+          Pl[w][rt][mt][lane] = cvt4<PREC>(float4{p[0][mt], p[1][mt], p[2][mt], p[3][mt]}, 0xfu);
       }
-#pragma unroll
-      for (int mt = 0; mt < NT; ++mt)
-        Pl[w][rt][mt][lane] = cvt4<PREC>(float4{p[0][mt], p[1][mt], p[2][mt], p[3][mt]}, 0xfu);
-    }
+    };
+    static_assert(psi_stage_size(NW * 64, LP) * sizeof(double) <= sizeof(Xl), "the table fits in the X tiles");
+    const int64_t first = (int64_t)gi * (NW * 64);
+    double* table = (double*)&Xl[0][0];
+    if (A.psi_tab) fill(PsiTable<NT>(A));
+    else if (psi_stage(A, first, NW * 64, table)) fill(PsiStaged<NT>(A, table, first));
+    else fill(PsiDirect<NT>());
   }
-  __syncthreads();   // the slot counters are zero
+  __syncthreads();   // the slot counters are zero; the X tiles take the table's place
 
   Cursor16 cx, co, ct_;   // X loads (two ahead), Omega loads (one ahead), T partial stores
 
@@ -1070,22 +1113,52 @@ __global__ __launch_bounds__(nwf_for(L4) * 64, f64_wg_per_cu(L4)) void k_sketch_
   double psiq[KT][NQ > 0 ? NQ : 1];
   double psis[KT][NS > 0 ? NS : 1];
   {
-    PsiCursor pc;
-    pc.init(A, row0w + g4);
-    double hq[NQ > 0 ? NQ : 1], hs[NS > 0 ? NS : 1];
+    int cols[NQ + NS];
 #pragma unroll
-    for (int ks = 0; ks < KT; ++ks) {
-      if (ks > 0) pc.advance(A, 4);
-      if (pc.refresh(A)) {
+    for (int q = 0; q < NQ; ++q) cols[q] = 16 * q + l16;
 #pragma unroll
-        for (int q = 0; q < NQ; ++q) hq[q] = psi_hi(A, pc.h, 16 * q + l16);
+    for (int s = 0; s < NS; ++s) cols[NQ + s] = 16 * NQ + 4 * s + l4;
+    auto fill = [&](auto rows) {
+      rows.init(A, row0w + g4);
 #pragma unroll
-        for (int s = 0; s < NS; ++s) hs[s] = psi_hi(A, pc.h, 16 * NQ + 4 * s + l4);
+      for (int ks = 0; ks < KT; ++ks) {
+        double v[NQ + NS];
+        if (ks > 0) rows.advance(A, 4);
+        rows.values(A, cols, v);
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) psiq[ks][q] = v[q];
+#pragma unroll
+        for (int s = 0; s < NS; ++s) psis[ks][s] = v[NQ + s];
       }
+    };
+    static_assert(psi_stage_size(NWF * RW, L4) <= NWF * KC * ST, "the table fits in the X tiles");
+    const int64_t first = (int64_t)gi * (NWF * RW);
+    if (A.psi_tab) {
+      fill(PsiTable<NQ + NS>(A));
+    } else if (psi_stage(A, first, NWF * RW, &Xl[0][0])) {
+      fill(PsiStaged<NQ + NS>(A, &Xl[0][0], first));
+      __syncthreads();   // the X tiles take its place
+    } else {   // rolled: the arrays move up, the new row last
+      PsiDirect<NQ + NS> rows;
+      rows.init(A, row0w + g4);
+#pragma unroll 1
+      for (int ks = 0; ks < KT; ++ks) {
+        double v[NQ + NS];
+        if (ks > 0) rows.advance(A, 4);
+        rows.values(A, cols, v);
 #pragma unroll
-      for (int q = 0; q < NQ; ++q) psiq[ks][q] = pc.at(A, 16 * q + l16, hq[q]);
+        for (int q = 0; q < NQ; ++q) {
 #pragma unroll
-      for (int s = 0; s < NS; ++s) psis[ks][s] = pc.at(A, 16 * NQ + 4 * s + l4, hs[s]);
+          for (int u = 0; u + 1 < KT; ++u) psiq[u][q] = psiq[u + 1][q];
+          psiq[KT - 1][q] = v[q];
+        }
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+#pragma unroll
+          for (int u = 0; u + 1 < KT; ++u) psis[u][s] = psis[u + 1][s];
+          psis[KT - 1][s] = v[NQ + s];
+        }
+      }
     }
   }
 
@@ -1167,8 +1240,14 @@ __global__ __launch_bounds__(nwf_for(L4) * 64, f64_wg_per_cu(L4)) void k_sketch_
           xr[i][0] = xr[i][1] = 0.0;
         }
       } else {
-        xr[i][0] = (colok && row < A.R) ? p[0] : 0.0;
-        xr[i][1] = (colok && row + 1 < A.R) ? p[1] : 0.0;
+        xr[i][1] = 0.0;
+        if (colok && row + 1 < A.R) {
+          const ud2 v = *(const ud2*)p;
+          xr[i][0] = v.x;
+          xr[i][1] = v.y;
+        } else {
+          xr[i][0] = (colok && row < A.R) ? p[0] : 0.0;
+        }
       }
     }
   };
