@@ -193,7 +193,23 @@ __global__ __launch_bounds__(256) void k_tn(const TnArgs P) {
   }
 }
 
+// A wave per entry; with few slices (WAVE false) a thread: 368640 entries of two took 77 us
+// with a wave each.
+template <bool WAVE>
 __global__ __launch_bounds__(256) void k_tn_sum(const TnArgs P) {
+  if constexpr (!WAVE) {
+    const int nout = P.M * P.N;
+    const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if (t >= (int64_t)nout * P.nbatch) return;
+    const int bi = (int)(t / nout), o = (int)(t % nout);
+    const double* part = P.part + (int64_t)bi * P.nb * nout + o;
+    double s = 0.0;
+#pragma unroll 8
+    for (int g = 0; g < P.nb; ++g) s += part[(int64_t)g * nout];
+    double* c = P.C + bi * P.sc + (o % P.M) + P.ldc * (o / P.M);
+    *c = P.alpha * s + (P.beta == 0.0 ? 0.0 : P.beta * *c);
+    return;
+  }
   const int lane = threadIdx.x & 63;
   const int64_t ow = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6;
   const int nout = P.M * P.N;
@@ -225,6 +241,9 @@ hipError_t run_tn(TnArgs P, hipStream_t s) {
   // workgroups remain: the partials, 8 M N bytes a slice, are written and read back
   int64_t rows = 128;
   while (rows < 4096 && (P.K + 2 * rows - 1) / (2 * rows) * P.nbatch >= 1024) rows *= 2;
+  // whole where that leaves two workgroups to a compute unit: no partials (960 products
+  // of K = 960, 12 x 32: 127 us with two slices each, 45 whole)
+  if (P.K <= 2 * rows && P.nbatch >= 512) rows = (P.K + 31) / 32 * 32;
   P.rows = rows;
   P.nb = (int)((P.K + rows - 1) / rows);
   P.part = nullptr;
@@ -238,7 +257,9 @@ hipError_t run_tn(TnArgs P, hipStream_t s) {
   if (pair) launch_tn<true>(P, s);
   else launch_tn<false>(P, s);
   if (P.nb > 1) {
-    hipLaunchKernelGGL(k_tn_sum, dim3((unsigned)(((int64_t)P.M * P.N * P.nbatch + 3) / 4)), dim3(256), 0, s, P);
+    const int64_t out = (int64_t)P.M * P.N * P.nbatch;
+    if (P.nb > 16) hipLaunchKernelGGL(k_tn_sum<true>, dim3((unsigned)((out + 3) / 4)), dim3(256), 0, s, P);
+    else hipLaunchKernelGGL(k_tn_sum<false>, dim3((unsigned)((out + 255) / 256)), dim3(256), 0, s, P);
     ws_free(P.part, s);
   }
   return hipGetLastError();

@@ -33,6 +33,7 @@ pytestmark = pytest.mark.gpu
     ((512, 40), 9, 12), ((513, 40), 9, 17),  # half a block of eight waves
     ((1024, 33), 20, 24), ((1025, 33), 20, 24), ((1025, 35), 27, 32),   # one block, two levels
     ((900, 640, 4), 3, 6),               # over a thousand blocks: a workgroup a block forms Q
+    ((300, 600, 6), 4, 8), ((700, 515, 5), 4, 20),   # many products of one row slice, of two
 ])
 def test_bases_fixed_rank(n, rank, ell):
     say(f"[gpu] bases n={n} rank={rank} ell={ell}")
