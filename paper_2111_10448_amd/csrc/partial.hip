@@ -19,18 +19,28 @@ constexpr int PC_MAXBLK = 1024;     // workgroups per launch at most
 // stages its 64 rows x 16 pieces in LDS and
 //     Y(rows, ell) += X(rows, 16 pieces) Omega(piece columns, ell)
 //     T(ell, 16 pieces) = Psi(rows, ell)^T X(rows, pieces).
-// A workgroup owns 256 rows of Y_R and walks every piece of the launch, so Y is
+// A workgroup owns 256 rows of Y_R and walks the chunks with a piece in them, so Y is
 // read and written once per launch with one writer per entry; T goes to one
-// partial per workgroup, summed in a fixed order by k_partial_t.  Workgroups
-// step over the row blocks when there are more than PC_MAXBLK of them.
+// partial per workgroup, summed in a fixed order by k_partial_t.  The work list
+// holds the row blocks that some piece touches and no others, since a call may
+// bring one fibre of a very tall unfolding (walking all of Y_R for it took 5.4 ms
+// at R = 2^25, ell = 20; now 20 with its launches).  Workgroups step over it when it has more than
+// PC_MAXBLK blocks.
 // Latency bound: one launch pair per kMaxSeg pieces, against a single
 // workgroup per piece before (0.42-0.44 ms each at R = 19575, ell = 20 and
 // R = 20592, ell = 16).  A half-precision pass over 3.5e8 entries in 64 slabs
 // with 112 such pieces: 52.7 -> 3.35 ms; an FP64 pass over 1.2e7 entries in 9
 // slabs with per-split factors (3 x 16 pieces): 21.4 -> 0.68 ms.
 // Pieces: seg[e].ptr the first entry, gcol0 the column, rows [chunk0, ncols).
+struct RowBlocks {
+  int n;                     // runs of consecutive row blocks, increasing and disjoint
+  int64_t tot;               // blocks in all
+  int64_t first[kMaxSeg];    // first block of each run
+  int64_t before[kMaxSeg];   // blocks of the runs before it
+};
+
 template <int L4, typename T>
-__global__ __launch_bounds__(256, 2) void k_partial_cols(const SketchArgs A, double* __restrict__ Y,
+__global__ __launch_bounds__(256, 2) void k_partial_cols(const SketchArgs A, const RowBlocks B, double* __restrict__ Y,
                                                          double* __restrict__ tws) {
   constexpr int ST = 64 + 2;
   constexpr int NQ = L4 / 16;        // 16-wide tiles of the sketch columns
@@ -54,8 +64,14 @@ __global__ __launch_bounds__(256, 2) void k_partial_cols(const SketchArgs A, dou
     ec[t] = in ? A.seg[in ? t : 0].gcol0 : 0;
   }
   for (int i = t; i < nch * L4 * 16; i += 256) (&Tsum[0][0])[i] = 0.0;
-  const int64_t nrb = (A.R + PC_ROWS - 1) / PC_ROWS;
-  for (int64_t rb = blockIdx.x; rb < nrb; rb += gridDim.x) {
+  __syncthreads();   // the piece table
+  for (int64_t i = blockIdx.x; i < B.tot; i += gridDim.x) {
+    int run = 0;
+    while (run + 1 < B.n && B.before[run + 1] <= i) ++run;
+    const int64_t rb = B.first[run] + (i - B.before[run]);
+    // pieces with rows in this block, the same mask in every wave
+    const uint64_t here = __ballot(lane < ne && e0[lane < kMaxSeg ? lane : 0] < (rb + 1) * PC_ROWS &&
+                                   e1[lane < kMaxSeg ? lane : 0] > rb * PC_ROWS);
     const int64_t row0w = rb * PC_ROWS + w * 64;
     double psiq[KT][NQ > 0 ? NQ : 1];
     double psis[KT][NS > 0 ? NS : 1];
@@ -94,7 +110,8 @@ __global__ __launch_bounds__(256, 2) void k_partial_cols(const SketchArgs A, dou
       for (int s = 0; s < NS; ++s) ys[mt][s] = 0.0;
     }
     for (int ch = 0; ch < nch; ++ch) {
-      __syncthreads();   // the piece table; the last chunk's LDS reads are done
+      if ((here >> (16 * ch) & 0xffff) == 0) continue;   // uniform across the workgroup
+      __syncthreads();   // the last chunk's LDS reads are done
       const int64_t row = row0w + lane;
       double v[16];
 #pragma unroll
@@ -195,17 +212,17 @@ __global__ __launch_bounds__(256) void k_partial_t(const SketchArgs A, const dou
 }
 
 template <typename T>
-static void launch_pc(int L4, const SketchArgs& a, int nb, double* Y, double* tws, hipStream_t s) {
+static void launch_pc(int L4, const SketchArgs& a, const RowBlocks& rb, int nb, double* Y, double* tws, hipStream_t s) {
   const dim3 g((unsigned)nb), b(256);
   switch (L4) {
-    case 4: hipLaunchKernelGGL((k_partial_cols<4, T>), g, b, 0, s, a, Y, tws); break;
-    case 8: hipLaunchKernelGGL((k_partial_cols<8, T>), g, b, 0, s, a, Y, tws); break;
-    case 12: hipLaunchKernelGGL((k_partial_cols<12, T>), g, b, 0, s, a, Y, tws); break;
-    case 16: hipLaunchKernelGGL((k_partial_cols<16, T>), g, b, 0, s, a, Y, tws); break;
-    case 20: hipLaunchKernelGGL((k_partial_cols<20, T>), g, b, 0, s, a, Y, tws); break;
-    case 24: hipLaunchKernelGGL((k_partial_cols<24, T>), g, b, 0, s, a, Y, tws); break;
-    case 28: hipLaunchKernelGGL((k_partial_cols<28, T>), g, b, 0, s, a, Y, tws); break;
-    default: hipLaunchKernelGGL((k_partial_cols<32, T>), g, b, 0, s, a, Y, tws); break;
+    case 4: hipLaunchKernelGGL((k_partial_cols<4, T>), g, b, 0, s, a, rb, Y, tws); break;
+    case 8: hipLaunchKernelGGL((k_partial_cols<8, T>), g, b, 0, s, a, rb, Y, tws); break;
+    case 12: hipLaunchKernelGGL((k_partial_cols<12, T>), g, b, 0, s, a, rb, Y, tws); break;
+    case 16: hipLaunchKernelGGL((k_partial_cols<16, T>), g, b, 0, s, a, rb, Y, tws); break;
+    case 20: hipLaunchKernelGGL((k_partial_cols<20, T>), g, b, 0, s, a, rb, Y, tws); break;
+    case 24: hipLaunchKernelGGL((k_partial_cols<24, T>), g, b, 0, s, a, rb, Y, tws); break;
+    case 28: hipLaunchKernelGGL((k_partial_cols<28, T>), g, b, 0, s, a, rb, Y, tws); break;
+    default: hipLaunchKernelGGL((k_partial_cols<32, T>), g, b, 0, s, a, rb, Y, tws); break;
   }
 }
 
@@ -213,15 +230,41 @@ int64_t partial_cols_doubles(int64_t R, int L4, int pieces) {
   return std::min<int64_t>((R + PC_ROWS - 1) / PC_ROWS, PC_MAXBLK) * pieces * L4;
 }
 
+// The row blocks that the pieces touch.
+static RowBlocks touched_blocks(const SketchArgs& a) {
+  int64_t lo[kMaxSeg], hi[kMaxSeg];
+  int order[kMaxSeg];
+  for (int e = 0; e < a.nseg; ++e) {
+    lo[e] = a.seg[e].chunk0 / PC_ROWS;
+    hi[e] = (a.seg[e].ncols + PC_ROWS - 1) / PC_ROWS;
+    order[e] = e;
+  }
+  std::sort(order, order + a.nseg, [&](int p, int q) { return lo[p] < lo[q]; });
+  RowBlocks b = {};
+  int64_t end = 0;   // blocks before it are listed
+  for (int i = 0; i < a.nseg; ++i) {
+    const int64_t from = std::max(lo[order[i]], end), to = hi[order[i]];
+    if (from >= to) continue;
+    if (b.n == 0 || from > end) {
+      b.first[b.n] = from;
+      b.before[b.n++] = b.tot;
+    }
+    b.tot += to - from;
+    end = to;
+  }
+  return b;
+}
+
 hipError_t launch_partial_cols(int dtype, const SketchArgs& a, double* Y, double* Tt, double* ws, int64_t ws_doubles,
                                bool* added, hipStream_t s) {
   if (a.nseg < 1 || a.nseg > kMaxSeg || a.ell < 1 || a.L4 != (a.ell + 3) / 4 * 4) return hipErrorInvalidValue;
+  const RowBlocks rb = touched_blocks(a);
   const int64_t per = (int64_t)a.nseg * a.L4;
-  const int nb = (int)std::min<int64_t>({(a.R + PC_ROWS - 1) / PC_ROWS, (int64_t)PC_MAXBLK, ws_doubles / per});
+  const int nb = (int)std::min<int64_t>({rb.tot, (int64_t)PC_MAXBLK, ws_doubles / per});
   if (nb < 1) return hipErrorInvalidValue;
   if (fault_take()) return hipErrorLaunchFailure;
-  if (dtype == PSTT2_F64) launch_pc<double>(a.L4, a, nb, Y, ws, s);
-  else launch_pc<float>(a.L4, a, nb, Y, ws, s);
+  if (dtype == PSTT2_F64) launch_pc<double>(a.L4, a, rb, nb, Y, ws, s);
+  else launch_pc<float>(a.L4, a, rb, nb, Y, ws, s);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   *added = true;
