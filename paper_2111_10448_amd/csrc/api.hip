@@ -1774,8 +1774,15 @@ pstt2_status pstt2_parallel_ttsvd(int32_t d, const int64_t* n, const double* x_d
     const int64_t R = Rk[k], C = N / R, L = std::max(R, C);
     const int sh = (int)std::min(R, C), sp = sh + (sh & 1);
     const double tol = std::sqrt((double)L) * 2.220446049250313e-16;
-    SVDCK(svd_load(x_dev, R, C, sp, W, s));
-    SVDCK(svd_init(J, sp, cnt, s));
+    const int* place = nullptr;
+    SVDCK(svd_load(x_dev, R, C, sp, nullptr, W, s));
+    if (sh > kSvdLead) {   // the leading columns are turned: in order of decreasing norm
+      SVDCK(svd_colnorms(W, L, sh, sig, s));
+      SVDCK(svd_place(sig, sh, idx, s));
+      SVDCK(svd_load(x_dev, R, C, sp, idx, W, s));
+      place = idx;
+    }
+    SVDCK(svd_init(J, sp, sh, place, cnt, s));
     std::vector<double> sv(sh);
     double tot = 0.0, tau = -1.0, small = 0.0;
     bool converged = false, cut_tail = true;

@@ -303,8 +303,10 @@ hipError_t adj_out(int dtype, const SketchArgs& g, int prec, const double* Yb, c
 // Parallel-TTSVD building blocks (ttsvd.hip).  W is the L x sp work matrix of
 // an unfolding (X_k^T when R_k <= C_k, else X_k; sp = the short side rounded up
 // to even, zero columns past it), J its sp x sp rotation accumulator.
-hipError_t svd_load(const double* x, int64_t R, int64_t C, int sp, double* W, hipStream_t s);
-hipError_t svd_init(double* J, int sp, int* counter, hipStream_t s);
+// place (null: the identity): where each column goes; svd_place orders them by decreasing norm.
+hipError_t svd_load(const double* x, int64_t R, int64_t C, int sp, const int* place, double* W, hipStream_t s);
+hipError_t svd_place(const double* sig, int scols, int* place, hipStream_t s);
+hipError_t svd_init(double* J, int sp, int scols, const int* place, int* counter, hipStream_t s);
 // One sweep over every pair of columns; *counter receives the pairs that were not
 // orthogonal when met.  Pairs whose squared norms are both at most tau are left
 // alone (tau < 0: none).  ws: svd_ws_doubles doubles (may be null when 0).

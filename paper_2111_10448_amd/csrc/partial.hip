@@ -24,8 +24,8 @@ constexpr int PC_MAXBLK = 1024;     // workgroups per launch at most
 // partial per workgroup, summed in a fixed order by k_partial_t.  The work list
 // holds the row blocks that some piece touches and no others, since a call may
 // bring one fibre of a very tall unfolding (walking all of Y_R for it took 5.4 ms
-// at R = 2^25, ell = 20; now 20 with its launches).  Workgroups step over it when it has more than
-// PC_MAXBLK blocks.
+// a call at R = 2^25, ell = 20; now 22 us).  Workgroups step over the list when it
+// has more than PC_MAXBLK blocks.
 // Latency bound: one launch pair per kMaxSeg pieces, against a single
 // workgroup per piece before (0.42-0.44 ms each at R = 19575, ell = 20 and
 // R = 20592, ell = 16).  A half-precision pass over 3.5e8 entries in 64 slabs

@@ -76,9 +76,11 @@ __device__ __forceinline__ double block_sum(double v, double* red) {
 }
 }  // namespace
 
-// W (C x sp, column-major): W(c, r) = X_k(r, c) for r < R, zero columns r >= R.
+// W (C x sp, column-major): W(c, place[r]) = X_k(r, c) for r < R, zero columns past R
+// (place null: the identity).
 // 32 x 32 tiles through LDS so both sides are read and written along rows.
-__global__ void k_svd_transpose(const double* __restrict__ x, int64_t R, int64_t C, int sp, double* __restrict__ W) {
+__global__ void k_svd_transpose(const double* __restrict__ x, int64_t R, int64_t C, int sp,
+                                const int* __restrict__ place, double* __restrict__ W) {
   __shared__ double t[32][33];
   const int64_t c0 = (int64_t)blockIdx.x * 32, r0 = (int64_t)blockIdx.y * 32;
   const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;   // 32 x 8 threads
@@ -89,15 +91,38 @@ __global__ void k_svd_transpose(const double* __restrict__ x, int64_t R, int64_t
   __syncthreads();
   for (int j = ty; j < 32; j += 8) {
     const int64_t c = c0 + tx, r = r0 + j;
-    if (c < C && r < sp) W[c + C * r] = t[tx][j];
+    if (c < C && r < sp) W[c + C * (place && r < R ? place[r] : r)] = t[tx][j];
   }
 }
 
-// W (R x sp): a copy of X_k with zero columns past C.
-__global__ void k_svd_copy(const double* __restrict__ x, int64_t R, int64_t C, int sp, double* __restrict__ W) {
+// W (R x sp): a copy of X_k, its column c at place[c] (null: c), and zero columns past C.
+__global__ void k_svd_copy(const double* __restrict__ x, int64_t R, int64_t C, int sp, const int* __restrict__ place,
+                           double* __restrict__ W) {
   const int64_t tot = R * sp;
-  for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < tot; t += (int64_t)gridDim.x * blockDim.x)
-    W[t] = t < R * C ? x[t] : 0.0;
+  for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < tot; t += (int64_t)gridDim.x * blockDim.x) {
+    const double v = t < R * C ? x[t] : 0.0;
+    int64_t o = t;
+    if (place && t < R * C) {
+      const int64_t c = t / R;
+      o = t + R * (place[c] - c);
+    }
+    W[o] = v;
+  }
+}
+
+// place[j]: column j's position in order of decreasing norm (ties by index); a norm that
+// is not a number counts as infinite, so that place is a permutation all the same.
+__global__ __launch_bounds__(256) void k_svd_place(const double* __restrict__ sig, int s, int* __restrict__ place) {
+  const int j = blockIdx.x * 256 + threadIdx.x;
+  if (j >= s) return;
+  const double own = isnan(sig[j]) ? INFINITY : sig[j];
+  int p = 0;
+#pragma unroll 8
+  for (int i = 0; i < s; ++i) {
+    const double o = isnan(sig[i]) ? INFINITY : sig[i];
+    p += o > own || (o == own && i < j) ? 1 : 0;
+  }
+  place[j] = p;
 }
 
 // Columns of block pair i in round k: column c < 16 of the pair, sp or more if
@@ -309,11 +334,15 @@ __global__ __launch_bounds__(kJT) void k_jacobi_blocks(double* __restrict__ W, i
 // orthogonal H whose first sixteen columns span those of W^T W_1 (W_1 the first
 // sixteen of W; at first W Omega, Omega random) is a power step for all of them at
 // once: W <- W H, J <- J H, H = I - V T V^T from the reflectors of W^T W_1.  It stays
-// orthogonal to rounding, and near convergence H - I is small, so W's small columns
-// lose nothing by it: with the sixteen made orthogonal among themselves the test of
+// orthogonal to rounding; with the sixteen made orthogonal among themselves the test of
 // the sweeps is met by every pair with a kept column after a few steps.  Three
 // launches, 35 us, a step (17 us for the reflectors of 340 rows, 11 for the turn),
 // against seventeen microseconds a round of block pairs.
+//
+// The columns are first put in order of decreasing norm.  H is then graded as they are
+// and a small column gets no rounding of a large one; in any other order the first turn
+// mixes them (90 x 24, column norms 1 .. 1e-23 increasing: singular values of 1e-9 to
+// 1e-11 of the largest off by 1e-9 to 2e-6, in order 1e-15, as by the sweeps alone).
 
 // Omega (s x kSvdLead): mixed bits of the index, in [-1, 1)
 __global__ void k_svd_omega(double* __restrict__ Om, int s) {
@@ -455,10 +484,14 @@ __global__ __launch_bounds__(256) void k_svd_polish(const double* __restrict__ E
   }
 }
 
-__global__ void k_svd_eye(double* __restrict__ J, int sp, int* __restrict__ counter) {
+// J(r, place[r]) = 1 (null: the identity), the columns past s at their own index
+__global__ void k_svd_eye(double* __restrict__ J, int sp, int s, const int* __restrict__ place,
+                          int* __restrict__ counter) {
   const int64_t tot = (int64_t)sp * sp;
-  for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < tot; t += (int64_t)gridDim.x * blockDim.x)
-    J[t] = (t % sp) == (t / sp) ? 1.0 : 0.0;
+  for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < tot; t += (int64_t)gridDim.x * blockDim.x) {
+    const int r = (int)(t % sp), c = (int)(t / sp);
+    J[t] = (place && r < s ? place[r] : r) == c ? 1.0 : 0.0;
+  }
   if (blockIdx.x == 0 && threadIdx.x == 0) *counter = 0;
 }
 
@@ -466,18 +499,23 @@ __global__ void k_zero_int(int* p) { *p = 0; }
 
 static unsigned grid_of(int64_t n) { return (unsigned)std::max<int64_t>(1, std::min<int64_t>((n + 255) / 256, 8192)); }
 
-hipError_t svd_load(const double* x, int64_t R, int64_t C, int sp, double* W, hipStream_t s) {
+hipError_t svd_load(const double* x, int64_t R, int64_t C, int sp, const int* place, double* W, hipStream_t s) {
   if (R <= C) {
     const dim3 g((unsigned)((C + 31) / 32), (unsigned)((sp + 31) / 32));
-    hipLaunchKernelGGL(k_svd_transpose, g, dim3(256), 0, s, x, R, C, sp, W);
+    hipLaunchKernelGGL(k_svd_transpose, g, dim3(256), 0, s, x, R, C, sp, place, W);
   } else {
-    hipLaunchKernelGGL(k_svd_copy, dim3(grid_of(R * sp)), dim3(256), 0, s, x, R, C, sp, W);
+    hipLaunchKernelGGL(k_svd_copy, dim3(grid_of(R * sp)), dim3(256), 0, s, x, R, C, sp, place, W);
   }
   return hipGetLastError();
 }
 
-hipError_t svd_init(double* J, int sp, int* counter, hipStream_t s) {
-  hipLaunchKernelGGL(k_svd_eye, dim3(grid_of((int64_t)sp * sp)), dim3(256), 0, s, J, sp, counter);
+hipError_t svd_place(const double* sig, int scols, int* place, hipStream_t s) {
+  hipLaunchKernelGGL(k_svd_place, dim3((unsigned)((scols + 255) / 256)), dim3(256), 0, s, sig, scols, place);
+  return hipGetLastError();
+}
+
+hipError_t svd_init(double* J, int sp, int scols, const int* place, int* counter, hipStream_t s) {
+  hipLaunchKernelGGL(k_svd_eye, dim3(grid_of((int64_t)sp * sp)), dim3(256), 0, s, J, sp, scols, place, counter);
   return hipGetLastError();
 }
 
