@@ -1728,7 +1728,7 @@ pstt2_status pstt2_parallel_ttsvd(int32_t d, const int64_t* n, const double* x_d
     if (sh > kSvdLead) lmax = std::max(lmax, svd_lead_doubles(std::max(R, C), sp));
   }
   hipStream_t s = (hipStream_t)hip_stream;
-  double *W = nullptr, *J = nullptr, *sig = nullptr, *gws = nullptr, *ortho = nullptr, *lead = nullptr;
+  double *W = nullptr, *J = nullptr, *sig = nullptr, *gws = nullptr, *ortho = nullptr, *lead = nullptr, *xmax = nullptr;
   int *idx = nullptr, *cnt = nullptr;
   std::vector<double*> U(d + 1, nullptr);
   int r[PSTT2_MAX_D + 1];
@@ -1741,6 +1741,7 @@ pstt2_status pstt2_parallel_ttsvd(int32_t d, const int64_t* n, const double* x_d
     dev_free_async(W, s);
     dev_free_async(J, s);
     dev_free_async(sig, s);
+    dev_free_async(xmax, s);
     dev_free_async(gws, s);
     dev_free_async(lead, s);
     dev_free_async(ortho, s);
@@ -1761,11 +1762,13 @@ pstt2_status pstt2_parallel_ttsvd(int32_t d, const int64_t* n, const double* x_d
   SVDCK(dev_malloc_async((void**)&W, sizeof(double) * wmax, s));
   SVDCK(dev_malloc_async((void**)&J, sizeof(double) * spmax * spmax, s));
   SVDCK(dev_malloc_async((void**)&sig, sizeof(double) * spmax, s));
+  SVDCK(dev_malloc_async((void**)&xmax, sizeof(double) * svd_max_parts(), s));
   SVDCK(dev_malloc_async((void**)&ortho, sizeof(double) * PSTT2_MAX_ELL * PSTT2_MAX_ELL, s));
   if (gmax > 0) SVDCK(dev_malloc_async((void**)&gws, sizeof(double) * gmax, s));
   if (lmax > 0) SVDCK(dev_malloc_async((void**)&lead, sizeof(double) * lmax, s));
   SVDCK(dev_malloc_async((void**)&idx, sizeof(int) * spmax, s));
   SVDCK(dev_malloc_async((void**)&cnt, sizeof(int), s));
+  SVDCK(svd_absmax(x_dev, N, xmax, s));
   // the last core is formed with its split's SVD; the others from U by equation "core"
   const int nd = (int)n[d - 1];
   std::vector<double> g_last;
@@ -1775,20 +1778,23 @@ pstt2_status pstt2_parallel_ttsvd(int32_t d, const int64_t* n, const double* x_d
     const int sh = (int)std::min(R, C), sp = sh + (sh & 1);
     const double tol = std::sqrt((double)L) * 2.220446049250313e-16;
     const int* place = nullptr;
-    SVDCK(svd_load(x_dev, R, C, sp, nullptr, W, s));
     if (sh > kSvdLead) {   // the leading columns are turned: in order of decreasing norm
-      SVDCK(svd_colnorms(W, L, sh, sig, s));
+      if (R <= C) {
+        SVDCK(svd_load(x_dev, R, C, sp, xmax, nullptr, W, nullptr, s));
+        SVDCK(svd_colnorms(W, L, sh, nullptr, sig, s));
+      } else {
+        SVDCK(svd_colnorms(x_dev, L, sh, xmax, sig, s));
+      }
       SVDCK(svd_place(sig, sh, idx, s));
-      SVDCK(svd_load(x_dev, R, C, sp, idx, W, s));
       place = idx;
     }
-    SVDCK(svd_init(J, sp, sh, place, cnt, s));
+    SVDCK(svd_load(x_dev, R, C, sp, xmax, place, W, J, s));
     std::vector<double> sv(sh);
     double tot = 0.0, tau = -1.0, small = 0.0;
     bool converged = false, cut_tail = true;
     // norms of W's columns to sv, their squares' sum to tot
     auto read_norms = [&](int* rot) -> pstt2_status {
-      SVDCK(svd_colnorms(W, L, sh, sig, s));
+      SVDCK(svd_colnorms(W, L, sh, nullptr, sig, s));
       if (rot) SVDCK(hipMemcpyAsync(rot, cnt, sizeof(int), hipMemcpyDeviceToHost, s));
       SVDCK(hipMemcpyAsync(sv.data(), sig, sizeof(double) * sh, hipMemcpyDeviceToHost, s));
       SVDCK(hipStreamSynchronize(s));
@@ -1903,7 +1909,7 @@ pstt2_status pstt2_parallel_ttsvd(int32_t d, const int64_t* n, const double* x_d
       SVDCK(dev_malloc_async((void**)&glast, sizeof(double) * rk * nd, s));
       U[0] = glast;   // released with the rest
       if (R <= C) {
-        SVDCK(svd_last_core(W, C, idx, rk, nd, glast, s));
+        SVDCK(svd_last_core(W, C, idx, xmax, rk, nd, glast, s));
         SVDCK(svd_polish(ortho, rk, nd, 1, rk, glast, s));
       }
     }

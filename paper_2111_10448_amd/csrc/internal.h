@@ -303,10 +303,14 @@ hipError_t adj_out(int dtype, const SketchArgs& g, int prec, const double* Yb, c
 // Parallel-TTSVD building blocks (ttsvd.hip).  W is the L x sp work matrix of
 // an unfolding (X_k^T when R_k <= C_k, else X_k; sp = the short side rounded up
 // to even, zero columns past it), J its sp x sp rotation accumulator.
-// place (null: the identity): where each column goes; svd_place orders them by decreasing norm.
-hipError_t svd_load(const double* x, int64_t R, int64_t C, int sp, const int* place, double* W, hipStream_t s);
+// xmax: svd_max_parts() doubles from svd_absmax; W is X over the power of two just below
+// its largest entry.  place (null: the identity): where each column goes; svd_place orders
+// them by decreasing norm.  J (null: not written) starts as that permutation.
+int svd_max_parts();
+hipError_t svd_absmax(const double* x, int64_t n, double* xmax, hipStream_t s);
+hipError_t svd_load(const double* x, int64_t R, int64_t C, int sp, const double* xmax, const int* place, double* W,
+                    double* J, hipStream_t s);
 hipError_t svd_place(const double* sig, int scols, int* place, hipStream_t s);
-hipError_t svd_init(double* J, int sp, int scols, const int* place, int* counter, hipStream_t s);
 // One sweep over every pair of columns; *counter receives the pairs that were not
 // orthogonal when met.  Pairs whose squared norms are both at most tau are left
 // alone (tau < 0: none).  ws: svd_ws_doubles doubles (may be null when 0).
@@ -323,10 +327,12 @@ hipError_t svd_lead_turn(double* W, int64_t L, double* J, int sp, double* lead, 
 hipError_t svd_lead_check(const double* sig, int scols, int sp, const double* lead, double tol, double tau, double small,
                           int* counter, hipStream_t s);
 hipError_t qr_reflectors(const double* A, int64_t M, double* V, double* T, double* R, hipStream_t s);
-hipError_t svd_colnorms(const double* W, int64_t L, int scols, double* sig, hipStream_t s);
+// xmax (may be null): of the columns of X, scaled as W is
+hipError_t svd_colnorms(const double* W, int64_t L, int scols, const double* xmax, double* sig, hipStream_t s);
 hipError_t svd_gather(const double* src, int64_t ld, int64_t rows, const int* idx, const double* sig, int r,
                       double* dst, hipStream_t s);
-hipError_t svd_last_core(const double* src, int64_t ld, const int* idx, int r, int nd, double* G, hipStream_t s);
+hipError_t svd_last_core(const double* src, int64_t ld, const int* idx, const double* xmax, int r, int nd, double* G,
+                         hipStream_t s);
 // n vectors of r entries (entry a of vector i at V + a es + i vs): v <- (3 I - E) v / 2
 hipError_t svd_polish(const double* E, int r, int64_t n, int64_t es, int64_t vs, double* V, hipStream_t s);
 

@@ -76,17 +76,66 @@ __device__ __forceinline__ double block_sum(double v, double* red) {
 }
 }  // namespace
 
-// W (C x sp, column-major): W(c, place[r]) = X_k(r, c) for r < R, zero columns past R
+// Partial maxima of |x|, one per workgroup.
+constexpr int kMaxParts = 256;
+__global__ __launch_bounds__(256) void k_svd_absmax(const double* __restrict__ x, int64_t n, double* __restrict__ part) {
+  __shared__ double red[4];
+  double m = 0.0;
+  int64_t t = blockIdx.x * (int64_t)256 + threadIdx.x;
+  constexpr int64_t ST = kMaxParts * 256;
+  for (; t + 7 * ST < n; t += 8 * ST) {
+    double v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = x[t + u * ST];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) m = fmax(m, fabs(v[u]));
+  }
+  for (; t < n; t += ST) m = fmax(m, fabs(x[t]));
+  for (int o = 32; o > 0; o >>= 1) m = fmax(m, __shfl_xor(m, o));
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
+  __syncthreads();
+  if (threadIdx.x == 0) part[blockIdx.x] = fmax(fmax(red[0], red[1]), fmax(red[2], red[3]));
+}
+
+// e with 2^e <= max |x| < 2^{e+1} (0 for no, no finite or only zero entries), in every
+// thread of the workgroup of 256.  W holds X / 2^e, exactly: Gram entries square the
+// entries and the reflectors of W^T W_1 take their fourth power, so rms entries past
+// 1e75 overflowed and below 1e-78 left denormal squares, whose reflectors are not
+// orthogonal.  The rank rule and the bases do not see the scale; the last core gets it back.
+__device__ __forceinline__ int svd_exponent(const double* __restrict__ part, double* red) {
+  double m = part[threadIdx.x];
+  for (int o = 32; o > 0; o >>= 1) m = fmax(m, __shfl_xor(m, o));
+  __syncthreads();
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
+  __syncthreads();
+  m = fmax(fmax(red[0], red[1]), fmax(red[2], red[3]));
+  return m > 0.0 && isfinite(m) ? ilogb(m) : 0;
+}
+
+// The rotations' start with the columns at place: J(r, place[r]) = 1, those past s at
+// their own index (place null: the identity).
+__device__ __forceinline__ void svd_eye(double* __restrict__ J, int sp, int s, const int* __restrict__ place) {
+  const int64_t tot = (int64_t)sp * sp, stride = (int64_t)gridDim.x * gridDim.y * 256;
+  for (int64_t t = (blockIdx.x + (int64_t)gridDim.x * blockIdx.y) * 256 + threadIdx.x; t < tot; t += stride) {
+    const int r = (int)(t % sp), c = (int)(t / sp);
+    J[t] = (place && r < s ? place[r] : r) == c ? 1.0 : 0.0;
+  }
+}
+
+// W (C x sp, column-major): W(c, place[r]) = X_k(r, c) / 2^e for r < R, zero columns past R
 // (place null: the identity).
 // 32 x 32 tiles through LDS so both sides are read and written along rows.
 __global__ void k_svd_transpose(const double* __restrict__ x, int64_t R, int64_t C, int sp,
-                                const int* __restrict__ place, double* __restrict__ W) {
-  __shared__ double t[32][33];
+                                const double* __restrict__ xmax, const int* __restrict__ place,
+                                double* __restrict__ W, double* __restrict__ J) {
+  __shared__ double t[32][33], red[4];
+  if (J) svd_eye(J, sp, (int)R, place);
+  const int e = svd_exponent(xmax, red);
   const int64_t c0 = (int64_t)blockIdx.x * 32, r0 = (int64_t)blockIdx.y * 32;
   const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;   // 32 x 8 threads
   for (int j = ty; j < 32; j += 8) {
     const int64_t r = r0 + tx, c = c0 + j;
-    t[j][tx] = (r < R && c < C) ? x[r + R * c] : 0.0;
+    t[j][tx] = (r < R && c < C) ? ldexp(x[r + R * c], -e) : 0.0;
   }
   __syncthreads();
   for (int j = ty; j < 32; j += 8) {
@@ -95,12 +144,15 @@ __global__ void k_svd_transpose(const double* __restrict__ x, int64_t R, int64_t
   }
 }
 
-// W (R x sp): a copy of X_k, its column c at place[c] (null: c), and zero columns past C.
-__global__ void k_svd_copy(const double* __restrict__ x, int64_t R, int64_t C, int sp, const int* __restrict__ place,
-                           double* __restrict__ W) {
+// W (R x sp): X_k / 2^e, its column c at place[c] (null: c), and zero columns past C.
+__global__ void k_svd_copy(const double* __restrict__ x, int64_t R, int64_t C, int sp, const double* __restrict__ xmax,
+                           const int* __restrict__ place, double* __restrict__ W, double* __restrict__ J) {
+  __shared__ double red[4];
+  if (J) svd_eye(J, sp, (int)C, place);
+  const int e = svd_exponent(xmax, red);
   const int64_t tot = R * sp;
   for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < tot; t += (int64_t)gridDim.x * blockDim.x) {
-    const double v = t < R * C ? x[t] : 0.0;
+    const double v = t < R * C ? ldexp(x[t], -e) : 0.0;
     int64_t o = t;
     if (place && t < R * C) {
       const int64_t c = t / R;
@@ -423,13 +475,25 @@ __global__ void k_svd_lead_check(const double* __restrict__ C, int s, const doub
   if (bad) atomicAdd(counter, bad);
 }
 
-// sig[j] = ||W(:, j)||, one workgroup per column
+// sig[j] = ||W(:, j)||, of W / 2^e with xmax, one workgroup per column
 __global__ __launch_bounds__(kBS) void k_svd_colnorm(const double* __restrict__ W, int64_t L,
-                                                     double* __restrict__ sig) {
+                                                     const double* __restrict__ xmax, double* __restrict__ sig) {
   __shared__ double red[kBS / 64];
+  const int e = xmax ? svd_exponent(xmax, red) : 0;
   const double* w = W + (int64_t)blockIdx.x * L;
   double a = 0.0;
-  for (int64_t t = threadIdx.x; t < L; t += kBS) a += w[t] * w[t];
+  int64_t t = threadIdx.x;
+  for (; t + 7 * kBS < L; t += 8 * kBS) {   // eight loads in flight, summed in order
+    double v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = ldexp(w[t + u * kBS], -e);
+#pragma unroll
+    for (int u = 0; u < 8; ++u) a += v[u] * v[u];
+  }
+  for (; t < L; t += kBS) {
+    const double v = ldexp(w[t], -e);
+    a += v * v;
+  }
   a = block_sum(a, red);
   if (threadIdx.x == 0) sig[blockIdx.x] = sqrt(a);
 }
@@ -449,14 +513,16 @@ __global__ void k_svd_gather(const double* __restrict__ src, int64_t ld, int64_t
   }
 }
 
-// Last core from W' = X_{d-1}^T U: G(a, i) = W'(i, idx a) (r x n_d, column-major).
-__global__ void k_svd_last_core(const double* __restrict__ src, int64_t ld, const int* __restrict__ idx, int r, int nd,
-                                double* __restrict__ G) {
+// Last core from W' = X_{d-1}^T U / 2^e: G(a, i) = 2^e W'(i, idx a) (r x n_d, column-major).
+__global__ void k_svd_last_core(const double* __restrict__ src, int64_t ld, const int* __restrict__ idx,
+                                const double* __restrict__ xmax, int r, int nd, double* __restrict__ G) {
+  __shared__ double red[4];
+  const int e = svd_exponent(xmax, red);
   const int64_t tot = (int64_t)r * nd;
   for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < tot; t += (int64_t)gridDim.x * blockDim.x) {
     const int a = (int)(t % r);
     const int i = (int)(t / r);
-    G[t] = src[(int64_t)idx[a] * ld + i];
+    G[t] = ldexp(src[(int64_t)idx[a] * ld + i], e);
   }
 }
 
@@ -484,38 +550,30 @@ __global__ __launch_bounds__(256) void k_svd_polish(const double* __restrict__ E
   }
 }
 
-// J(r, place[r]) = 1 (null: the identity), the columns past s at their own index
-__global__ void k_svd_eye(double* __restrict__ J, int sp, int s, const int* __restrict__ place,
-                          int* __restrict__ counter) {
-  const int64_t tot = (int64_t)sp * sp;
-  for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < tot; t += (int64_t)gridDim.x * blockDim.x) {
-    const int r = (int)(t % sp), c = (int)(t / sp);
-    J[t] = (place && r < s ? place[r] : r) == c ? 1.0 : 0.0;
-  }
-  if (blockIdx.x == 0 && threadIdx.x == 0) *counter = 0;
-}
-
 __global__ void k_zero_int(int* p) { *p = 0; }
 
 static unsigned grid_of(int64_t n) { return (unsigned)std::max<int64_t>(1, std::min<int64_t>((n + 255) / 256, 8192)); }
 
-hipError_t svd_load(const double* x, int64_t R, int64_t C, int sp, const int* place, double* W, hipStream_t s) {
+int svd_max_parts() { return kMaxParts; }
+
+hipError_t svd_absmax(const double* x, int64_t n, double* part, hipStream_t s) {
+  hipLaunchKernelGGL(k_svd_absmax, dim3(kMaxParts), dim3(256), 0, s, x, n, part);
+  return hipGetLastError();
+}
+
+hipError_t svd_load(const double* x, int64_t R, int64_t C, int sp, const double* xmax, const int* place, double* W,
+                    double* J, hipStream_t s) {
   if (R <= C) {
     const dim3 g((unsigned)((C + 31) / 32), (unsigned)((sp + 31) / 32));
-    hipLaunchKernelGGL(k_svd_transpose, g, dim3(256), 0, s, x, R, C, sp, place, W);
+    hipLaunchKernelGGL(k_svd_transpose, g, dim3(256), 0, s, x, R, C, sp, xmax, place, W, J);
   } else {
-    hipLaunchKernelGGL(k_svd_copy, dim3(grid_of(R * sp)), dim3(256), 0, s, x, R, C, sp, place, W);
+    hipLaunchKernelGGL(k_svd_copy, dim3(grid_of(R * sp)), dim3(256), 0, s, x, R, C, sp, xmax, place, W, J);
   }
   return hipGetLastError();
 }
 
 hipError_t svd_place(const double* sig, int scols, int* place, hipStream_t s) {
   hipLaunchKernelGGL(k_svd_place, dim3((unsigned)((scols + 255) / 256)), dim3(256), 0, s, sig, scols, place);
-  return hipGetLastError();
-}
-
-hipError_t svd_init(double* J, int sp, int scols, const int* place, int* counter, hipStream_t s) {
-  hipLaunchKernelGGL(k_svd_eye, dim3(grid_of((int64_t)sp * sp)), dim3(256), 0, s, J, sp, scols, place, counter);
   return hipGetLastError();
 }
 
@@ -585,8 +643,8 @@ hipError_t svd_lead_check(const double* sig, int scols, int sp, const double* le
   return hipGetLastError();
 }
 
-hipError_t svd_colnorms(const double* W, int64_t L, int scols, double* sig, hipStream_t s) {
-  hipLaunchKernelGGL(k_svd_colnorm, dim3((unsigned)scols), dim3(kBS), 0, s, W, L, sig);
+hipError_t svd_colnorms(const double* W, int64_t L, int scols, const double* xmax, double* sig, hipStream_t s) {
+  hipLaunchKernelGGL(k_svd_colnorm, dim3((unsigned)scols), dim3(kBS), 0, s, W, L, xmax, sig);
   return hipGetLastError();
 }
 
@@ -596,8 +654,9 @@ hipError_t svd_gather(const double* src, int64_t ld, int64_t rows, const int* id
   return hipGetLastError();
 }
 
-hipError_t svd_last_core(const double* src, int64_t ld, const int* idx, int r, int nd, double* G, hipStream_t s) {
-  hipLaunchKernelGGL(k_svd_last_core, dim3(grid_of((int64_t)r * nd)), dim3(256), 0, s, src, ld, idx, r, nd, G);
+hipError_t svd_last_core(const double* src, int64_t ld, const int* idx, const double* xmax, int r, int nd, double* G,
+                         hipStream_t s) {
+  hipLaunchKernelGGL(k_svd_last_core, dim3(grid_of((int64_t)r * nd)), dim3(256), 0, s, src, ld, idx, xmax, r, nd, G);
   return hipGetLastError();
 }
 
