@@ -1910,11 +1910,20 @@ pstt2_status pstt2_parallel_ttsvd(int32_t d, const int64_t* n, const double* x_d
       U[0] = glast;   // released with the rest
       if (R <= C) {
         SVDCK(svd_last_core(W, C, idx, xmax, rk, nd, glast, s));
-        SVDCK(svd_polish(ortho, rk, nd, 1, rk, glast, s));
+        SVDCK(svd_polish(ortho, rk, false, nd, 1, rk, glast, s));
       }
     }
-    SVDCK(svd_polish(ortho, rk, R, R, 1, U[k], s));
-    if (k == d - 1 && R > C) SVDCK(adj_gemm(true, false, rk, nd, R, 1.0, U[k], R, x_dev, R, 0.0, glast, rk, s));
+    SVDCK(svd_polish(ortho, rk, R > C, R, R, 1, U[k], s));
+    if (k == d - 1 && R > C) {
+      SVDCK(adj_gemm(true, false, rk, nd, R, 1.0, U[k], R, x_dev, R, 0.0, glast, rk, s));
+      // The product's error is a rounding of the largest row in every row (5e-16 of
+      // sigma_1), Sigma J^T's is that of the rotations (2e-15 to 5e-14 of the row itself):
+      // rows of 1/64 of the largest and less come from J (rows of 1e-11 of the largest:
+      // off by 4e-11 of themselves, now 2e-15).
+      int a0 = 0;
+      while (a0 < rk && sv[order[a0]] > 0x1p-6 * sv[order[0]]) ++a0;
+      if (a0 > 0 && a0 < rk) SVDCK(svd_small_rows(J, sp, ortho, sig, idx, xmax, rk, a0, nd, glast, s));
+    }
     // the sizes were read back above: idx may be refilled by the next split
     SVDCK(hipStreamSynchronize(s));
   }

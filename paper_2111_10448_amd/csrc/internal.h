@@ -333,8 +333,11 @@ hipError_t svd_gather(const double* src, int64_t ld, int64_t rows, const int* id
                       double* dst, hipStream_t s);
 hipError_t svd_last_core(const double* src, int64_t ld, const int* idx, const double* xmax, int r, int nd, double* G,
                          hipStream_t s);
-// n vectors of r entries (entry a of vector i at V + a es + i vs): v <- (3 I - E) v / 2
-hipError_t svd_polish(const double* E, int r, int64_t n, int64_t es, int64_t vs, double* V, hipStream_t s);
+// U (n vectors of r entries, entry a of vector i at V + a es + i vs) to orthonormal, E = U^T U,
+// by a lower or upper triangular factor; the last core's rows a0 .. r - 1 from J.
+hipError_t svd_polish(const double* E, int r, bool up, int64_t n, int64_t es, int64_t vs, double* V, hipStream_t s);
+hipError_t svd_small_rows(const double* J, int sp, const double* E, const double* sig, const int* idx,
+                          const double* xmax, int r, int a0, int nd, double* G, hipStream_t s);
 
 // TT evaluation (tt_eval.hip).
 // Bytes of the static scratch the allocation-free error pass of these cores needs.

@@ -526,15 +526,22 @@ __global__ void k_svd_last_core(const double* __restrict__ src, int64_t ld, cons
   }
 }
 
-// v <- (3 I - E) v / 2 for n vectors of r entries (entry a of vector i at
-// a es + i vs), E = U^T U (r x r): one Newton step towards the orthonormal
-// factor of U, which thousands of rounded rotations leave ~1e-13 from
-// orthonormal; what is left of that is its square.
-__global__ __launch_bounds__(256) void k_svd_polish(const double* __restrict__ E, int r, int64_t n, int64_t es,
+// v <- P^T v for n vectors of r entries (entry a of vector i at a es + i vs): U <- U P is
+// orthonormal to the square of what U (columns by decreasing singular value, E = U^T U)
+// was, which thousands of rounded rotations leave up to 1e-13 from orthonormal.  P is
+// triangular, P^T E P = I to first order: lower, a column takes its correction from those
+// of smaller singular values, upper (up) from those of larger ones.  A row of the last
+// core changes by rows of smaller singular values only, lower where the core is W'^T
+// (P^T W'^T), upper where it is Sigma J^T (P^{-1} Sigma J^T): relative accuracy of small
+// rows does not rest on how small E's entries happen to be, as with a symmetric P.
+__global__ __launch_bounds__(256) void k_svd_polish(const double* __restrict__ E, int r, bool up, int64_t n, int64_t es,
                                                     int64_t vs, double* __restrict__ V) {
   constexpr int MX = PSTT2_MAX_ELL;
   __shared__ double Es[MX][MX + 1];
-  for (int t = threadIdx.x; t < r * r; t += 256) Es[t % r][t / r] = (t % r == t / r ? 1.5 : 0.0) - 0.5 * E[t];
+  for (int t = threadIdx.x; t < r * r; t += 256) {
+    const int a = t % r, b = t / r;
+    Es[a][b] = a == b ? 1.5 - 0.5 * E[t] : ((b < a) == up ? -E[t] : 0.0);
+  }
   __syncthreads();
   for (int64_t i = blockIdx.x * (int64_t)256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
     double v[MX];
@@ -547,6 +554,25 @@ __global__ __launch_bounds__(256) void k_svd_polish(const double* __restrict__ E
         if (b < r) s += Es[a][b] * v[b];
       V[a * es + i * vs] = s;
     }
+  }
+}
+
+// Rows a0 .. r - 1 of the last core from J: 2^e P^{-1} Sigma J^T with the upper P of
+// k_svd_polish, to first order.
+__global__ __launch_bounds__(256) void k_svd_small_rows(const double* __restrict__ J, int sp,
+                                                        const double* __restrict__ E, const double* __restrict__ sig,
+                                                        const int* __restrict__ idx, const double* __restrict__ xmax,
+                                                        int r, int a0, int nd, double* __restrict__ G) {
+  __shared__ double red[4];
+  const int e = svd_exponent(xmax, red);
+  const int64_t tot = (int64_t)(r - a0) * nd;
+  for (int64_t t = blockIdx.x * (int64_t)256 + threadIdx.x; t < tot; t += (int64_t)gridDim.x * 256) {
+    const int a = a0 + (int)(t / nd);
+    const int64_t i = t % nd;
+    double s = 0.0;
+    for (int b = a; b < r; ++b)
+      s += (b == a ? 0.5 + 0.5 * E[a + r * a] : E[a + r * b]) * (sig[idx[b]] * J[(int64_t)idx[b] * sp + i]);
+    G[a + (int64_t)r * i] = ldexp(s, e);
   }
 }
 
@@ -660,8 +686,15 @@ hipError_t svd_last_core(const double* src, int64_t ld, const int* idx, const do
   return hipGetLastError();
 }
 
-hipError_t svd_polish(const double* E, int r, int64_t n, int64_t es, int64_t vs, double* V, hipStream_t s) {
-  hipLaunchKernelGGL(k_svd_polish, dim3(grid_of(n)), dim3(256), 0, s, E, r, n, es, vs, V);
+hipError_t svd_polish(const double* E, int r, bool up, int64_t n, int64_t es, int64_t vs, double* V, hipStream_t s) {
+  hipLaunchKernelGGL(k_svd_polish, dim3(grid_of(n)), dim3(256), 0, s, E, r, up, n, es, vs, V);
+  return hipGetLastError();
+}
+
+hipError_t svd_small_rows(const double* J, int sp, const double* E, const double* sig, const int* idx,
+                          const double* xmax, int r, int a0, int nd, double* G, hipStream_t s) {
+  hipLaunchKernelGGL(k_svd_small_rows, dim3(grid_of((int64_t)(r - a0) * nd)), dim3(256), 0, s, J, sp, E, sig, idx, xmax, r,
+                     a0, nd, G);
   return hipGetLastError();
 }
 

@@ -55,3 +55,24 @@ def test_short_side_first(s, order):
     say(f"    rank {tt.ranks[1]}, worst singular value {off.max():.1e}")
     assert tt.ranks[1] >= 11 and off.max() < 5e-13
     tt.free()
+
+
+@pytest.mark.parametrize("s", [12, 24])
+@pytest.mark.parametrize("order", ["increasing", "mixed", "decreasing"])
+def test_short_side_last(s, order):
+    """n = (rows, s): the graded side is the last mode, small rows of G_2 = Sigma V^T."""
+    import torch
+    import paper_2111_10448_amd as P
+    say(f"[gpu] Parallel-TTSVD graded (90, {s}) {order}")
+    a = _graded(90, s, order)
+    ref = _singular_values(a)
+    tt = P.parallel_ttsvd(torch.from_numpy(np.ascontiguousarray(a.reshape(-1, order="F"))).cuda(), (90, s), 1e-11)
+    u = tt.cores_numpy()[0].reshape(90, tt.ranks[1], order="F")
+    g = tt.cores_numpy()[1].reshape(tt.ranks[1], s, order="F").astype(np.longdouble)
+    off = np.abs(np.sqrt((g * g).sum(axis=1)) / ref[:tt.ranks[1]] - 1).astype(float)
+    res = np.linalg.norm(a - u @ g.astype(np.float64)) / np.linalg.norm(a)
+    say(f"    rank {tt.ranks[1]}, worst singular value {off.max():.1e}, U^T U - I "
+        f"{np.linalg.norm(u.T @ u - np.eye(tt.ranks[1])):.1e}, X~ {res:.1e}")
+    assert tt.ranks[1] >= 11 and off.max() < 5e-13
+    assert np.linalg.norm(u.T @ u - np.eye(tt.ranks[1])) < 1e-14 and res < 1e-11 + 1e-14
+    tt.free()
