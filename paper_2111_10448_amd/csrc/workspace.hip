@@ -73,6 +73,7 @@ hipError_t dev_malloc_raw(void** p, size_t bytes) {
   if (!book_reserve(bytes)) return hipErrorOutOfMemory;
   const hipError_t e = hipMalloc(p, bytes);
   if (e != hipSuccess) {
+    (void)hipGetLastError();   // HIP keeps it for the next launch check otherwise; callers may do without
     *p = nullptr;
     book_cancel(bytes);
     return e;
@@ -86,6 +87,7 @@ hipError_t dev_malloc_async(void** p, size_t bytes, hipStream_t s) {
   if (!book_reserve(bytes)) return hipErrorOutOfMemory;
   const hipError_t e = hipMallocAsync(p, bytes, s);
   if (e != hipSuccess) {
+    (void)hipGetLastError();
     *p = nullptr;
     book_cancel(bytes);
     return e;
