@@ -227,7 +227,8 @@ typedef struct {
  * slabs from memory and from fn may be mixed.  HILBERT builds small index
  * tables (R_m + C_m int32 and sum_q n_q doubles) on first use and keeps them
  * with the context; GAUSS builds its tables on every call (their workspace, and
- * that of the evaluated columns, stays with the context).  async (GAUSS first
+ * that of the evaluated columns, stays with the context as a cache: see
+ * pstt2_memory_stats).  async (GAUSS first
  * waits for the stream's earlier work and its own table set-up, so the centers
  * may be freed on return, then queues the rest).  Errors: EINVAL (kind, fields,
  * dtype / prec, alignment, range), ESTATE (overlap, after recover), ENOMEM, EDEVICE. */
@@ -429,8 +430,12 @@ pstt2_status pstt2_drm_factors(const pstt2_desc* desc, double* host_out, int64_t
 pstt2_status pstt2_set_memory_limit(int64_t bytes);
 
 /* Live and peak bytes of device memory held by the library (contexts,
- * workspaces, cores not yet released) and the budget (-1: none).  Any pointer
- * may be NULL.  Never fails. */
+ * workspaces, cores not yet released) and the budget (-1: none).  Blocks cached
+ * between calls are not live: a context's for tensor functions (tables and
+ * evaluated columns, as large as its largest call needed) and those of
+ * tt_reconstruct (at most 1 GiB for each call running at once).  They count
+ * while a call uses them, and are freed when an allocation of the library finds
+ * the device full.  Any pointer may be NULL.  Never fails. */
 pstt2_status pstt2_memory_stats(int64_t* live_bytes, int64_t* peak_bytes, int64_t* limit_bytes);
 
 /* Testing hook for the failure paths: after this call the next `count` kernel

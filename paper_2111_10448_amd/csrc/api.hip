@@ -5,6 +5,7 @@
 #include <cstdio>
 #include <cstring>
 #include <map>
+#include <optional>
 #include <string>
 #include <vector>
 
@@ -19,6 +20,7 @@ namespace pstt2 {
 hipError_t tt_error_run(const tt_cores* c, const void* x, int dtype, double* e2x2, hipStream_t s, int fn);
 hipError_t tt_error_run_gauss(const tt_cores* c, const double* centers_host, int nterms, double gamma,
                               double* e2x2, hipStream_t s);
+int64_t tt_reconstruct_doubles(const tt_cores* c);   // workspace of tt_reconstruct_run
 hipError_t tt_reconstruct_run(const tt_cores* c, void* out, int dtype, int64_t first, int64_t count, hipStream_t s);
 }
 
@@ -47,7 +49,8 @@ struct pstt2_ctx {
   std::vector<double*> basis;  // Q_k (k < m) or P_k (k >= m)
   Arena arena;                 // recovery workspace: sketches, bases, temporaries
   Arena varena;                // workspace of pstt2_vjp (rewound at every call)
-  Arena farena;                // workspace of the calls on a tensor function (see FnScope)
+  Arena farena;                // kept workspace of the calls on a tensor function: tables and evaluated
+                               // columns, at most PSTT2_GAUSS_CHUNK_BYTES (or one column) of these
   double* Bk = nullptr;        // two-sided sketches, split k at Bk + k ell^2 (ell x ell)
   int64_t* chain_dev = nullptr;  // per split: factor offsets of its left / right DRM chains, then n
   double* H = nullptr;         // two-sided middle sketch, (ell n_m) x ell (TWOSIDED only)
@@ -724,7 +727,7 @@ void pstt2_destroy(pstt2_ctx* c) {
   free_recovery(c);
   arena_release(&c->arena, c->stream);
   arena_release(&c->varena, c->stream);
-  arena_release(&c->farena, c->stream);
+  kept_drop(&c->farena, c->stream);
   (void)hipStreamSynchronize(c->stream);
   dev_free(c->fac);
   dev_free(c->Y);
@@ -764,17 +767,6 @@ pstt2_status pstt2_sketch(pstt2_ctx* c, const void* x_dev, int64_t first, int64_
   return PSTT2_OK;
 }
 
-// Workspace of the calls on a tensor function (tables, evaluated columns): the
-// context keeps it between calls, up to PSTT2_GAUSS_CHUNK_BYTES and the tables,
-// and gives it back with itself.  A request of several GiB that the stream-ordered
-// pool cannot serve from one free block costs the host ~100 ms.  What is
-// allocated inside the scope is not freed by the call; where the kept block
-// cannot grow, the exact sizes are taken (and released by the next call).
-struct FnScope {
-  ArenaScope scope;
-  explicit FnScope(pstt2_ctx* c) : scope((((void)arena_begin(&c->farena, c->stream)), &c->farena)) {}
-};
-
 // fields of a tensor function (kind, and for GAUSS the bump parameters)
 static const char* fn_invalid(const pstt2_fn* fn) {
   if (fn->kind == PSTT2_FN_HILBERT) return nullptr;
@@ -796,19 +788,17 @@ static pstt2_status sketch_gauss(pstt2_ctx* c, const pstt2_fn* fn, int64_t first
   void* W = nullptr;
   GaussTabs g;
   int64_t ncmax = 1;
-  hipError_t e;
-  {
-    FnScope scope(c);
-    e = ws_alloc((void**)&tabs, sizeof(double) * gauss_table_doubles(c->n, c->d, c->m, fn->n_terms), s);
-    if (e != hipSuccess) return hfail(c, e, "Gaussian-bump tables");
-    e = gauss_tables(c->n, c->d, c->m, fn->centers, fn->n_terms, fn->gamma, tabs, &g, s);
-    if (e == hipSuccess && f64) e = ws_alloc((void**)&mom, sizeof(double) * 64 * fn->n_terms, s);
-    if (e == hipSuccess && !f64) {
-      ncmax = gauss_chunk_cols(g, 4);
-      e = ws_alloc(&W, (size_t)4 * c->R * std::min(ncmax, count / c->R), s);
-    }
-    if (e != hipSuccess) return hfail(c, e, "Gaussian-bump workspace");
+  KeptScope scope(&c->farena, s);
+  hipError_t e = ws_alloc((void**)&tabs, sizeof(double) * gauss_table_doubles(c->n, c->d, c->m, fn->n_terms), s);
+  if (e != hipSuccess) return hfail(c, e, "Gaussian-bump tables");
+  e = gauss_tables(c->n, c->d, c->m, fn->centers, fn->n_terms, fn->gamma, tabs, &g, s);
+  if (e == hipSuccess && f64) e = ws_alloc((void**)&mom, sizeof(double) * 64 * fn->n_terms, s);
+  if (e == hipSuccess && !f64) {
+    ncmax = gauss_chunk_cols(g, 4);
+    e = ws_alloc(&W, (size_t)4 * c->R * std::min(ncmax, count / c->R), s);
   }
+  if (e != hipSuccess) return hfail(c, e, "Gaussian-bump workspace");
+  scope.leave();
   if (f64) {
     for (int gr = 0; gr < pass_groups(c); ++gr) {
       double *Yd = nullptr, *Td = nullptr;
@@ -1294,21 +1284,20 @@ pstt2_status pstt2_middle_pass_fn(pstt2_ctx* c, tt_cores* cores, const pstt2_fn*
   void* W = nullptr;
   hipError_t e = hipSuccess;
   int64_t ncmax = 1;   // set from the tables once they exist
-  {
-    FnScope scope(c);
-    if (fn->kind == PSTT2_FN_GAUSS) {
-      e = ws_alloc((void**)&tabs, sizeof(double) * gauss_table_doubles(c->n, c->d, c->m, fn->n_terms), s);
-      if (e == hipSuccess) e = gauss_tables(c->n, c->d, c->m, fn->centers, fn->n_terms, fn->gamma, tabs, &g, s);
-      if (e == hipSuccess) ncmax = gauss_chunk_cols(g, esz);
-    } else {
-      e = ws_alloc((void**)&tabs, sizeof(double) * hilbert_rec_len(c->n, c->d), s);
-      if (e == hipSuccess) e = ws_alloc((void**)&row_t, sizeof(int32_t) * c->R, s);
-      if (e == hipSuccess) e = ws_alloc((void**)&col_t, sizeof(int32_t) * c->C, s);
-      if (e == hipSuccess) e = hilbert_tables(c->n, c->d, c->m, c->R, c->C, tabs, row_t, col_t, s);
-      ncmax = std::min(c->C, std::max<int64_t>(1, PSTT2_GAUSS_CHUNK_BYTES / (c->R * esz)));
-    }
-    if (e == hipSuccess) e = ws_alloc(&W, (size_t)esz * c->R * std::min(ncmax, count / c->R), s);
+  KeptScope scope(&c->farena, s);
+  if (fn->kind == PSTT2_FN_GAUSS) {
+    e = ws_alloc((void**)&tabs, sizeof(double) * gauss_table_doubles(c->n, c->d, c->m, fn->n_terms), s);
+    if (e == hipSuccess) e = gauss_tables(c->n, c->d, c->m, fn->centers, fn->n_terms, fn->gamma, tabs, &g, s);
+    if (e == hipSuccess) ncmax = gauss_chunk_cols(g, esz);
+  } else {
+    e = ws_alloc((void**)&tabs, sizeof(double) * hilbert_rec_len(c->n, c->d), s);
+    if (e == hipSuccess) e = ws_alloc((void**)&row_t, sizeof(int32_t) * c->R, s);
+    if (e == hipSuccess) e = ws_alloc((void**)&col_t, sizeof(int32_t) * c->C, s);
+    if (e == hipSuccess) e = hilbert_tables(c->n, c->d, c->m, c->R, c->C, tabs, row_t, col_t, s);
+    ncmax = std::min(c->C, std::max<int64_t>(1, PSTT2_GAUSS_CHUNK_BYTES / (c->R * esz)));
   }
+  if (e == hipSuccess) e = ws_alloc(&W, (size_t)esz * c->R * std::min(ncmax, count / c->R), s);
+  scope.leave();
   pstt2_status st = e == hipSuccess ? PSTT2_OK : hfail(c, e, "tensor-function workspace");
   bool added = false;   // a chunk already added into the middle core
   for (int64_t c0 = first / c->R; st == PSTT2_OK && c0 < (first + count) / c->R; c0 += ncmax) {
@@ -2068,12 +2057,14 @@ pstt2_status tt_reconstruct(const tt_cores* cores, void* x_out_dev, pstt2_dtype 
   for (int k = 0; k < cores->d; ++k) N *= cores->n[k];
   if (first < 0 || count < 0 || first + count > N) return fail(nullptr, PSTT2_EINVAL, "range outside the tensor");
   if (!x_out_dev && count > 0) return fail(nullptr, PSTT2_EINVAL, "null output");
-  // returns only after its stream is idle, so it shares tt_error's arena (where
-  // that cannot grow, the stream-ordered allocator serves the exact sizes)
-  Arena* ar = error_arena();
-  if (ar && arena_begin(ar, (hipStream_t)hip_stream) != hipSuccess) ar = nullptr;
-  ArenaScope scope(ar);
-  hipError_t e = tt_reconstruct_run(cores, x_out_dev, dtype, first, count, (hipStream_t)hip_stream);
+  // The call waits for its stream, and its workspace is kept where the pool's calls would
+  // be seen: 25 of 50 us for small trains, 150 of 330 at 0.3 GB.  Past 1 GiB the call takes
+  // milliseconds and the block goes back.
+  hipStream_t s = (hipStream_t)hip_stream;
+  constexpr int64_t kKeep = 1LL << 30;
+  std::optional<KeptScope> scope;
+  if (8 * tt_reconstruct_doubles(cores) <= kKeep) scope.emplace(nullptr, s);
+  const hipError_t e = tt_reconstruct_run(cores, x_out_dev, dtype, first, count, s);
   if (e != hipSuccess) return hfail(nullptr, e, "tt_reconstruct");
   return PSTT2_OK;
 }

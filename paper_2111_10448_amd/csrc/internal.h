@@ -43,6 +43,10 @@ struct Arena {
   char* base = nullptr;
   size_t cap = 0, off = 0, need = 0;
   std::vector<void*> spill;
+  // kept arenas (KeptScope) only
+  bool kept = false, any_stream = false;
+  int dev = 0;
+  hipStream_t stream = nullptr;
 };
 // the arena ws_alloc / ws_free use on this host thread (nullptr: none)
 Arena*& current_arena();
@@ -54,6 +58,19 @@ struct ArenaScope {
 // start a pass: release the last pass's overflow, regrow to what it needed, rewind
 hipError_t arena_begin(Arena* a, hipStream_t s);
 void arena_release(Arena* a, hipStream_t s);
+// A workspace kept between calls as a cache: while no call is in its scope it does not
+// count as live, and an allocation that finds the device full frees it (workspace.hip).
+// With own: that arena, for calls that may leave work queued on s, its one stream.
+// Without: one of the device's, for calls that wait for s before they return.
+struct KeptScope {
+  Arena* a;
+  Arena* prev;
+  hipStream_t s;
+  KeptScope(Arena* own, hipStream_t s);
+  void leave();    // later ws_alloc calls go elsewhere; what it gave stays until its end
+  ~KeptScope();    // nothing of it is freed by ws_free
+};
+void kept_drop(Arena* own, hipStream_t s);   // before own goes
 hipError_t ws_alloc(void** p, size_t bytes, hipStream_t s);
 void ws_free(void* p, hipStream_t s);
 

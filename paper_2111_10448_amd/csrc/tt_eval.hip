@@ -574,6 +574,11 @@ static void launch_rec_r(int RK, T* out, int64_t first, int64_t count, int64_t R
   }
 }
 
+int64_t tt_reconstruct_doubles(const tt_cores* c) {
+  const ErrPlan p = err_plan(c);
+  return p.n_iface + p.n_rp;
+}
+
 hipError_t tt_reconstruct_run(const tt_cores* c, void* out, int dtype, int64_t first, int64_t count, hipStream_t s) {
   const int d = c->d;
   const int split = (d + 1) / 2;

@@ -8,6 +8,15 @@
 // stream-ordered allocator and remembered; the next arena_begin releases them
 // and regrows the buffer to the size the last pass needed, so from the second
 // pass on every request fits.
+//
+// A KeptScope's arena is a cache like the one the stream-ordered allocator has of its
+// own freed memory: outside a scope its block counts neither as live nor against the
+// budget, what did not fit into it is freed at the scope's end, it grows to the need and
+// no further, and an allocation that the device refuses frees every idle one and tries
+// again.  The stream-ordered allocator alone does not do for requests of 4 GiB: in some
+// sequences it serves each from the device anew (80 ms of the host in a two-pass step on
+// 960^3 Gaussian bumps, 9.5 with the block kept).
+#include <algorithm>
 #include <atomic>
 #include <cstdlib>
 #include <mutex>
@@ -65,13 +74,65 @@ void book_release(void* p) {
   b.bytes -= (int64_t)it->second;
   b.live.erase(it);
 }
+// p stays allocated, but no longer counts as live; and back, unless the budget is short
+void book_park(void* p) {
+  MemBook& b = book();
+  std::lock_guard<std::mutex> g(b.mu);
+  auto it = b.live.find(p);
+  if (it == b.live.end()) return;
+  b.bytes -= (int64_t)it->second;
+  it->second = 0;
+}
+bool book_unpark(void* p, size_t bytes) {
+  if (!book_reserve(bytes)) return false;
+  book_commit(p, bytes);
+  return true;
+}
 std::atomic<int64_t> g_fault_after{-1};
+
+// Kept arenas that no call is using.
+struct Idle {
+  std::mutex mu;
+  std::vector<Arena*> list;
+};
+Idle& idle() {
+  static Idle* i = new Idle();   // never destroyed: scopes may end during exit
+  return *i;
+}
+
+// Free every idle kept block of the current device, each after the work queued on its
+// own stream (on s where its last call waited for that); false: there was none.
+bool give_back(hipStream_t s) {
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess) return false;
+  Idle& l = idle();
+  std::lock_guard<std::mutex> g(l.mu);
+  bool any = false;
+  for (Arena* a : l.list) {
+    if (a->dev != dev || !a->base) continue;
+    if (!a->any_stream) {   // a wait would break a capture that the caller runs on it
+      hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+      if (hipStreamIsCapturing(a->stream, &st) != hipSuccess || st != hipStreamCaptureStatusNone) continue;
+    }
+    any = true;
+    arena_release(a, a->any_stream ? s : a->stream);
+    if (!a->any_stream) (void)hipStreamSynchronize(a->stream);
+  }
+  if (any) {
+    (void)hipStreamSynchronize(s);
+    hipMemPool_t pool = nullptr;   // what the pool holds freed goes back to the device
+    if (hipDeviceGetDefaultMemPool(&pool, dev) == hipSuccess && pool) (void)hipMemPoolTrimTo(pool, 0);
+    (void)hipGetLastError();
+  }
+  return any;
+}
 }  // namespace
 
 hipError_t dev_malloc_raw(void** p, size_t bytes) {
   *p = nullptr;
   if (!book_reserve(bytes)) return hipErrorOutOfMemory;
-  const hipError_t e = hipMalloc(p, bytes);
+  hipError_t e = hipMalloc(p, bytes);
+  if (e == hipErrorOutOfMemory && give_back(nullptr)) e = hipMalloc(p, bytes);
   if (e != hipSuccess) {
     (void)hipGetLastError();   // HIP keeps it for the next launch check otherwise; callers may do without
     *p = nullptr;
@@ -85,7 +146,8 @@ hipError_t dev_malloc_raw(void** p, size_t bytes) {
 hipError_t dev_malloc_async(void** p, size_t bytes, hipStream_t s) {
   *p = nullptr;
   if (!book_reserve(bytes)) return hipErrorOutOfMemory;
-  const hipError_t e = hipMallocAsync(p, bytes, s);
+  hipError_t e = hipMallocAsync(p, bytes, s);
+  if (e == hipErrorOutOfMemory && give_back(s)) e = hipMallocAsync(p, bytes, s);
   if (e != hipSuccess) {
     (void)hipGetLastError();
     *p = nullptr;
@@ -152,7 +214,7 @@ hipError_t arena_begin(Arena* a, hipStream_t s) {
     if (a->base) dev_free_async(a->base, s);
     a->base = nullptr;
     a->cap = 0;
-    const size_t want = round_up(a->need + a->need / 4);
+    const size_t want = round_up(a->kept ? a->need : a->need + a->need / 4);
     hipError_t e = dev_malloc_async((void**)&a->base, want, s);
     if (e != hipSuccess) {
       a->base = nullptr;
@@ -172,6 +234,56 @@ void arena_release(Arena* a, hipStream_t s) {
   if (a->base) dev_free_async(a->base, s);
   a->base = nullptr;
   a->cap = a->off = a->need = 0;
+}
+
+KeptScope::KeptScope(Arena* own, hipStream_t stream) : a(own), prev(current_arena()), s(stream) {
+  int dev = 0;
+  (void)hipGetDevice(&dev);
+  {
+    Idle& l = idle();
+    std::lock_guard<std::mutex> g(l.mu);
+    for (auto it = l.list.rbegin(); it != l.list.rend(); ++it)
+      if (own ? *it == own : (*it)->any_stream && (*it)->dev == dev) {
+        a = *it;
+        l.list.erase(std::next(it).base());
+        break;
+      }
+  }
+  if (!a) {
+    a = new Arena();
+    a->any_stream = true;
+  }
+  a->kept = true;
+  a->dev = dev;
+  a->stream = s;
+  if (a->base && !book_unpark(a->base, a->cap)) {   // the budget has no room for the block: exact sizes
+    dev_free_async(a->base, s);
+    a->base = nullptr;
+    a->cap = 0;
+  }
+  (void)arena_begin(a, s);
+  current_arena() = a;
+}
+
+void KeptScope::leave() { current_arena() = prev; }
+
+KeptScope::~KeptScope() {
+  leave();
+  for (void* p : a->spill) dev_free_async(p, s);
+  a->spill.clear();
+  if (a->base) book_park(a->base);
+  Idle& l = idle();
+  std::lock_guard<std::mutex> g(l.mu);
+  l.list.push_back(a);
+}
+
+void kept_drop(Arena* own, hipStream_t s) {
+  {
+    Idle& l = idle();
+    std::lock_guard<std::mutex> g(l.mu);
+    l.list.erase(std::remove(l.list.begin(), l.list.end(), own), l.list.end());
+  }
+  arena_release(own, s);
 }
 
 hipError_t ws_alloc(void** p, size_t bytes, hipStream_t s) {
