@@ -1748,15 +1748,33 @@ pstt2_status pstt2_parallel_ttsvd(int32_t d, const int64_t* n, const double* x_d
     hipError_t e_ = (call);                                        \
     if (e_ != hipSuccess) return bail(hfail(nullptr, e_, #call)); \
   } while (0)
+  // The leading columns' workspace is up to a second W.  The steps that use it save time
+  // only: without room for it, or for anything that is needed beside it, the sweeps do
+  // without.  (call: allocates before it queues anything.)
+  auto yield = [&](auto&& call) -> hipError_t {
+    hipError_t e = call();
+    if (e == hipErrorOutOfMemory && lead) {
+      dev_free_async(lead, s);
+      lead = nullptr;
+      e = call();
+    }
+    return e;
+  };
+  auto take = [&](double** p, int64_t doubles) {
+    return yield([&] { return dev_malloc_async((void**)p, sizeof(double) * doubles, s); });
+  };
   SVDCK(dev_malloc_async((void**)&W, sizeof(double) * wmax, s));
   SVDCK(dev_malloc_async((void**)&J, sizeof(double) * spmax * spmax, s));
   SVDCK(dev_malloc_async((void**)&sig, sizeof(double) * spmax, s));
   SVDCK(dev_malloc_async((void**)&xmax, sizeof(double) * svd_max_parts(), s));
   SVDCK(dev_malloc_async((void**)&ortho, sizeof(double) * PSTT2_MAX_ELL * PSTT2_MAX_ELL, s));
   if (gmax > 0) SVDCK(dev_malloc_async((void**)&gws, sizeof(double) * gmax, s));
-  if (lmax > 0) SVDCK(dev_malloc_async((void**)&lead, sizeof(double) * lmax, s));
   SVDCK(dev_malloc_async((void**)&idx, sizeof(int) * spmax, s));
   SVDCK(dev_malloc_async((void**)&cnt, sizeof(int), s));
+  if (lmax > 0) {
+    const hipError_t e_ = take(&lead, lmax);
+    if (e_ != hipErrorOutOfMemory) SVDCK(e_);
+  }
   SVDCK(svd_absmax(x_dev, N, xmax, s));
   // the last core is formed with its split's SVD; the others from U by equation "core"
   const int nd = (int)n[d - 1];
@@ -1827,17 +1845,22 @@ pstt2_status pstt2_parallel_ttsvd(int32_t d, const int64_t* n, const double* x_d
       }
       return tau < 0.0 || below <= above;
     };
-    if (sh > kSvdLead) {
+    if (sh > kSvdLead && lead) {
       // power steps towards the kept columns while the rule cuts all but the leading
       // ones; without a gap there, or if they do not settle, the sweeps below go on
       // from the turned W and J.  20 x 17 x 19 x 21 at rank 6: 383 rounds of block
       // pairs, 6.6 ms, before.
-      SVDCK(svd_lead_init(W, L, J, sp, lead, s));
-      for (int step = 0; step < 2; ++step) {
-        SVDCK(svd_lead_products(W, L, sp, lead, s));
-        SVDCK(svd_lead_turn(W, L, J, sp, lead, s));
+      bool room = true;   // the products may need some more
+      auto product = [&](hipError_t e) {
+        room = e != hipErrorOutOfMemory;
+        return room ? e : hipSuccess;
+      };
+      SVDCK(product(svd_lead_init(W, L, J, sp, lead, s)));
+      for (int step = 0; step < 2 && room; ++step) {
+        SVDCK(product(svd_lead_products(W, L, sp, lead, s)));
+        if (room) SVDCK(svd_lead_turn(W, L, J, sp, lead, s));
       }
-      for (int step = 0; step < 8 && !converged; ++step) {
+      for (int step = 0; step < 8 && room && !converged; ++step) {
         for (int sweep = 0; sweep < 2; ++sweep) SVDCK(svd_sweep(W, L, J, sp, kSvdLead, tol, -1.0, small, gws, cnt, s));
         pstt2_status st = read_norms(nullptr);
         if (st != PSTT2_OK) return st;
@@ -1846,7 +1869,8 @@ pstt2_status pstt2_parallel_ttsvd(int32_t d, const int64_t* n, const double* x_d
         for (int j = kSvdLead; j < sh && led; ++j) led = sv[j] * sv[j] <= tau;
         if (!led) break;
         int rot = 0;
-        SVDCK(svd_lead_products(W, L, sp, lead, s));
+        SVDCK(product(svd_lead_products(W, L, sp, lead, s)));
+        if (!room) break;
         SVDCK(svd_lead_check(sig, sh, sp, lead, tol, tau, small, cnt, s));
         SVDCK(hipMemcpyAsync(&rot, cnt, sizeof(int), hipMemcpyDeviceToHost, s));
         SVDCK(hipStreamSynchronize(s));
@@ -1888,14 +1912,14 @@ pstt2_status pstt2_parallel_ttsvd(int32_t d, const int64_t* n, const double* x_d
     rk = std::min(rk, PSTT2_MAX_ELL);
     r[k] = rk;
     SVDCK(hipMemcpyAsync(idx, order.data(), sizeof(int) * rk, hipMemcpyHostToDevice, s));
-    SVDCK(dev_malloc_async((void**)&U[k], sizeof(double) * R * rk, s));
+    SVDCK(take(&U[k], R * rk));
     if (R <= C) SVDCK(svd_gather(J, sp, R, idx, nullptr, rk, U[k], s));   // U = J
     else SVDCK(svd_gather(W, R, R, idx, sig, rk, U[k], s));              // U = W' / sigma
-    SVDCK(adj_gemm(true, false, rk, rk, R, 1.0, U[k], R, U[k], R, 0.0, ortho, rk, s));
+    SVDCK(yield([&] { return adj_gemm(true, false, rk, rk, R, 1.0, U[k], R, U[k], R, 0.0, ortho, rk, s); }));
     if (k == d - 1) {
       // G_d = U^T X_{d-1}: W'^T where W' = X_{d-1}^T U, with the correction of U
       // applied to it; else a tall product with the corrected U
-      SVDCK(dev_malloc_async((void**)&glast, sizeof(double) * rk * nd, s));
+      SVDCK(take(&glast, (int64_t)rk * nd));
       U[0] = glast;   // released with the rest
       if (R <= C) {
         SVDCK(svd_last_core(W, C, idx, xmax, rk, nd, glast, s));
@@ -1904,7 +1928,7 @@ pstt2_status pstt2_parallel_ttsvd(int32_t d, const int64_t* n, const double* x_d
     }
     SVDCK(svd_polish(ortho, rk, R > C, R, R, 1, U[k], s));
     if (k == d - 1 && R > C) {
-      SVDCK(adj_gemm(true, false, rk, nd, R, 1.0, U[k], R, x_dev, R, 0.0, glast, rk, s));
+      SVDCK(yield([&] { return adj_gemm(true, false, rk, nd, R, 1.0, U[k], R, x_dev, R, 0.0, glast, rk, s); }));
       // The product's error is a rounding of the largest row in every row (5e-16 of
       // sigma_1), Sigma J^T's is that of the rotations (2e-15 to 5e-14 of the row itself):
       // rows of 1/64 of the largest and less come from J (rows of 1e-11 of the largest:
@@ -1918,7 +1942,7 @@ pstt2_status pstt2_parallel_ttsvd(int32_t d, const int64_t* n, const double* x_d
   }
   int64_t tot = 0;
   for (int k = 0; k < d; ++k) tot += (int64_t)r[k] * n[k] * r[k + 1];
-  SVDCK(dev_malloc_async((void**)&base, sizeof(double) * tot, s));
+  SVDCK(take(&base, tot));
   tc.d = d;
   tc.owned = 1;
   tc.stream = (void*)s;
@@ -1932,7 +1956,9 @@ pstt2_status pstt2_parallel_ttsvd(int32_t d, const int64_t* n, const double* x_d
   // G_1 = U_1; G_k = U_{k-1}^T reshape(U_k, R_{k-1}, n_k r_k) (equation "core"); G_d = Sigma V^T
   SVDCK(hipMemcpyAsync(tc.core[0], U[1], sizeof(double) * n[0] * r[1], hipMemcpyDeviceToDevice, s));
   for (int k = 2; k <= d - 1; ++k)
-    SVDCK(core_left(U[k - 1], Rk[k - 1], r[k - 1], U[k], (int)n[k - 1], r[k], tc.core[k - 1], s));
+    SVDCK(yield([&] {
+      return core_left(U[k - 1], Rk[k - 1], r[k - 1], U[k], (int)n[k - 1], r[k], tc.core[k - 1], s);
+    }));
   SVDCK(hipMemcpyAsync(tc.core[d - 1], glast, sizeof(double) * r[d - 1] * nd, hipMemcpyDeviceToDevice, s));
 #undef SVDCK
   cleanup();
