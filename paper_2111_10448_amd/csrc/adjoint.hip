@@ -420,7 +420,8 @@ struct AdjOutArgs {
   const double* om_tab;  // C x L4
   const double* Tbt;     // C x ell
   const double* Rt;      // r x C   (fused loss only)
-  int gi, gj;            // row blocks, column shares
+  int gi, gj;            // row blocks of the launch, column shares
+  int64_t row0;          // first row of the launch
 };
 
 constexpr int AO_ROWS = 128, AO_COLS = 64;
@@ -431,7 +432,7 @@ __global__ __launch_bounds__(256, 2) void k_adj_out(const AdjOutArgs A, const T*
   __shared__ double Co[4 * KS][LD];   // column operands of a tile, [inner index][column]
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, l16 = lane & 15, g4 = lane >> 4;
   const int64_t gi = blockIdx.x % A.gi, gj = blockIdx.x / A.gi;
-  const int64_t row0 = gi * AO_ROWS + 32 * w;
+  const int64_t row0 = A.row0 + gi * AO_ROWS + 32 * w;
   const int ks = A.n1 + A.n2 + A.n3;
   int64_t row[2];
   double ro[KS][2];   // row operands, zero past a term's length and past the matrix
@@ -669,15 +670,19 @@ hipError_t adj_out(int dtype, const SketchArgs& g, int prec, const double* Yb, c
     if (e != hipSuccess) return e;
   }
   A.psi = psi;
-  A.gi = (int)((g.R + AO_ROWS - 1) / AO_ROWS);
-  const int64_t ntile = (g.C + AO_COLS - 1) / AO_COLS;
-  A.gj = (int)std::max<int64_t>(1, std::min<int64_t>(ntile, (2048 + A.gi - 1) / A.gi));
+  const int64_t blocks = (g.R + AO_ROWS - 1) / AO_ROWS, ntile = (g.C + AO_COLS - 1) / AO_COLS;
+  constexpr int64_t kMaxBlocks = 1 << 22;   // a launch has less than 2^32 threads
   const int ks = A.n1 + A.n2 + A.n3;
-  if (ks <= 6) launch_adj_out<6>(dtype, fused, acc, A, x, gx, s);
-  else if (ks <= 12) launch_adj_out<12>(dtype, fused, acc, A, x, gx, s);
-  else if (ks <= 18) launch_adj_out<18>(dtype, fused, acc, A, x, gx, s);
-  else launch_adj_out<24>(dtype, fused, acc, A, x, gx, s);
-  e = hipGetLastError();
+  for (int64_t b0 = 0; b0 < blocks && e == hipSuccess; b0 += kMaxBlocks) {
+    A.row0 = b0 * AO_ROWS;
+    A.gi = (int)std::min(blocks - b0, kMaxBlocks);
+    A.gj = (int)std::max<int64_t>(1, std::min<int64_t>(ntile, (2048 + A.gi - 1) / A.gi));
+    if (ks <= 6) launch_adj_out<6>(dtype, fused, acc, A, x, gx, s);
+    else if (ks <= 12) launch_adj_out<12>(dtype, fused, acc, A, x, gx, s);
+    else if (ks <= 18) launch_adj_out<18>(dtype, fused, acc, A, x, gx, s);
+    else launch_adj_out<24>(dtype, fused, acc, A, x, gx, s);
+    e = hipGetLastError();
+  }
   ws_free(psi, s);
   return e;
 }

@@ -21,6 +21,10 @@ __device__ __forceinline__ double at(const double* A, int64_t lda, bool t, int64
   return t ? A[k + lda * i] : A[i + lda * k];
 }
 
+// Workgroups of a launch at most: one of 2^32 threads is refused, one of more wraps
+// around.  Larger grids go in several launches, blk0 the first workgroup of each.
+constexpr int64_t kMaxGrid = 1 << 23;
+
 // ---- C = alpha op(A) op(B) + beta C, short contractions ----
 // A wave forms one 16 x 16 tile of C^T (rows of C on the lanes of a store, so it
 // covers 16 consecutive rows), eight inner entries in flight.  SPLIT: the four
@@ -32,11 +36,12 @@ __device__ __forceinline__ double at(const double* A, int64_t lda, bool t, int64
 template <bool SPLIT>
 __global__ __launch_bounds__(256) void k_gemm_m(bool ta, bool tb, int64_t M, int64_t N, int64_t K, double alpha,
                                                 const double* __restrict__ A, int64_t lda, const double* __restrict__ B,
-                                                int64_t ldb, double beta, double* __restrict__ C, int64_t ldc) {
+                                                int64_t ldb, double beta, double* __restrict__ C, int64_t ldc,
+                                                int64_t blk0) {
   __shared__ double red[SPLIT ? 4 : 1][SPLIT ? 256 : 1];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, l16 = lane & 15, g4 = lane >> 4;
   const int64_t mt = (M + 15) / 16, ntile = mt * ((N + 15) / 16);
-  const int64_t tile = SPLIT ? (int64_t)blockIdx.x : blockIdx.x * (int64_t)4 + w;
+  const int64_t tile = SPLIT ? blk0 + blockIdx.x : (blk0 + blockIdx.x) * 4 + w;
   if (!SPLIT && tile >= ntile) return;
   const int64_t i0 = tile % mt * 16, j0 = tile / mt * 16;
   const int64_t i = i0 + l16 < M ? i0 + l16 : M - 1, j = j0 + l16 < N ? j0 + l16 : N - 1;
@@ -122,14 +127,15 @@ struct TnArgs {
   int nbatch, nb;        // products, slices
   int64_t rows;          // rows per slice (a multiple of 32)
   double* part;
+  int64_t blk0;
 };
 
 template <int MT, int NT, bool PAIR>
 __global__ __launch_bounds__(256) void k_tn(const TnArgs P) {
   __shared__ double red[4][MT * NT * 256];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, l16 = lane & 15, g4 = lane >> 4;
-  const int bi = (int)(blockIdx.x % P.nbatch);
-  const int64_t g = blockIdx.x / P.nbatch;
+  const int bi = (int)((P.blk0 + blockIdx.x) % P.nbatch);
+  const int64_t g = (P.blk0 + blockIdx.x) / P.nbatch;
   const int64_t s0 = g * P.rows, s1 = s0 + P.rows < P.K ? s0 + P.rows : P.K;
   // columns past the last one read it again; their results are dropped
   const double *pa[MT], *pb[NT];
@@ -226,12 +232,16 @@ __global__ __launch_bounds__(256) void k_tn_sum(const TnArgs P) {
 }
 
 template <bool PAIR>
-void launch_tn(const TnArgs& P, hipStream_t s) {
-  const dim3 g((unsigned)((int64_t)P.nb * P.nbatch)), b(256);
-  if (P.M <= 16 && P.N <= 16) hipLaunchKernelGGL((k_tn<1, 1, PAIR>), g, b, 0, s, P);
-  else if (P.M <= 16) hipLaunchKernelGGL((k_tn<1, 2, PAIR>), g, b, 0, s, P);
-  else if (P.N <= 16) hipLaunchKernelGGL((k_tn<2, 1, PAIR>), g, b, 0, s, P);
-  else hipLaunchKernelGGL((k_tn<2, 2, PAIR>), g, b, 0, s, P);
+void launch_tn(TnArgs P, hipStream_t s) {
+  const int64_t blocks = (int64_t)P.nb * P.nbatch;
+  const dim3 b(256);
+  for (P.blk0 = 0; P.blk0 < blocks; P.blk0 += kMaxGrid) {
+    const dim3 g((unsigned)std::min(blocks - P.blk0, kMaxGrid));
+    if (P.M <= 16 && P.N <= 16) hipLaunchKernelGGL((k_tn<1, 1, PAIR>), g, b, 0, s, P);
+    else if (P.M <= 16) hipLaunchKernelGGL((k_tn<1, 2, PAIR>), g, b, 0, s, P);
+    else if (P.N <= 16) hipLaunchKernelGGL((k_tn<2, 1, PAIR>), g, b, 0, s, P);
+    else hipLaunchKernelGGL((k_tn<2, 2, PAIR>), g, b, 0, s, P);
+  }
 }
 
 hipError_t run_tn(TnArgs P, hipStream_t s) {
@@ -272,25 +282,30 @@ hipError_t adj_gemm(bool ta, bool tb, int64_t M, int64_t N, int64_t K, double al
                     const double* B, int64_t ldb, double beta, double* C, int64_t ldc, hipStream_t s) {
   if (M <= 0 || N <= 0) return hipSuccess;
   if (ta && !tb && M <= 32 && N <= 32 && K >= 256)
-    return run_tn(TnArgs{(int)M, (int)N, K, A, lda, 1, 0, B, ldb, 1, 0, alpha, beta, C, ldc, 0, 1, 0, 0, nullptr}, s);
+    return run_tn(TnArgs{(int)M, (int)N, K, A, lda, 1, 0, B, ldb, 1, 0, alpha, beta, C, ldc, 0, 1, 0, 0, nullptr, 0}, s);
   const int64_t tiles = (M + 15) / 16 * ((N + 15) / 16);
   // long contractions with few outputs spread over one wavefront per entry
   if (K >= 256 && M * N <= 65536)
     hipLaunchKernelGGL(k_gemm_w, dim3((unsigned)std::max<int64_t>(1, std::min<int64_t>((M * N + 3) / 4, 16384))),
                        dim3(256), 0, s, ta, tb, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc);
-  else if (K >= 32)
-    hipLaunchKernelGGL(k_gemm_m<true>, dim3((unsigned)tiles), dim3(256), 0, s, ta, tb, M, N, K, alpha, A, lda, B, ldb,
-                       beta, C, ldc);
-  else
-    hipLaunchKernelGGL(k_gemm_m<false>, dim3((unsigned)((tiles + 3) / 4)), dim3(256), 0, s, ta, tb, M, N, K, alpha, A,
-                       lda, B, ldb, beta, C, ldc);
+  else {
+    const bool split = K >= 32;
+    const int64_t blocks = split ? tiles : (tiles + 3) / 4;
+    for (int64_t b0 = 0; b0 < blocks; b0 += kMaxGrid) {
+      const dim3 g((unsigned)std::min(blocks - b0, kMaxGrid));
+      if (split)
+        hipLaunchKernelGGL(k_gemm_m<true>, g, dim3(256), 0, s, ta, tb, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, b0);
+      else
+        hipLaunchKernelGGL(k_gemm_m<false>, g, dim3(256), 0, s, ta, tb, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, b0);
+    }
+  }
   return hipGetLastError();
 }
 
 hipError_t adj_gemm_tn_batch(int64_t M, int64_t N, int64_t K, int nbatch, const double* A, int64_t lda, int64_t ra,
                              int64_t sa, const double* B, int64_t ldb, int64_t sb, double* C, int64_t ldc, int64_t sc,
                              hipStream_t s) {
-  return run_tn(TnArgs{(int)M, (int)N, K, A, lda, ra, sa, B, ldb, 1, sb, 1.0, 0.0, C, ldc, sc, nbatch, 0, 0, nullptr},
+  return run_tn(TnArgs{(int)M, (int)N, K, A, lda, ra, sa, B, ldb, 1, sb, 1.0, 0.0, C, ldc, sc, nbatch, 0, 0, nullptr, 0},
                 s);
 }
 

@@ -104,9 +104,9 @@ struct GaussErr {
 
 template <bool ERR, typename T>
 __global__ __launch_bounds__(256, 2) void k_gauss_tiles(const GaussTabs g, int64_t c0, int64_t nc, T* __restrict__ W,
-                                                        const GaussErr er, int gi_count, int gj_count) {
+                                                        const GaussErr er, int64_t gi0, int gi_count, int gj_count) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, l16 = lane & 15, g4 = lane >> 4;
-  const int64_t gi = blockIdx.x % gi_count, gj = blockIdx.x / gi_count;
+  const int64_t gi = gi0 + blockIdx.x % gi_count, gj = blockIdx.x / gi_count;
   const int64_t row0 = gi * kGaussRows + 64 * w;
   const int64_t ntile = (nc + kGaussTile - 1) / kGaussTile;
   const int nt = g.nterms;
@@ -239,18 +239,33 @@ __global__ __launch_bounds__(256, 2) void k_gauss_tiles(const GaussTabs g, int64
     }
     __syncthreads();
     if (threadIdx.x == 0) {
-      er.part[2 * (int64_t)blockIdx.x] = red[0][0] + red[0][1] + red[0][2] + red[0][3];
-      er.part[2 * (int64_t)blockIdx.x + 1] = red[1][0] + red[1][1] + red[1][2] + red[1][3];
+      double* part = er.part + 2 * (gi + (g.R + kGaussRows - 1) / kGaussRows * gj);
+      part[0] = red[0][0] + red[0][1] + red[0][2] + red[0][3];
+      part[1] = red[1][0] + red[1][1] + red[1][2] + red[1][3];
     }
   }
 }
 
 // Row blocks and column shares: about 10000 workgroups, so that the last of the
 // (two per compute unit) rounds they run in is a small part of the whole.
-void gauss_grid(const GaussTabs& g, int64_t nc, int* gi, int* gj) {
-  *gi = (int)((g.R + kGaussRows - 1) / kGaussRows);
+void gauss_grid(const GaussTabs& g, int64_t nc, int64_t* gi, int* gj) {
+  *gi = (g.R + kGaussRows - 1) / kGaussRows;
   const int64_t ntile = (nc + kGaussTile - 1) / kGaussTile;
   *gj = (int)std::max<int64_t>(1, std::min<int64_t>(ntile, (10240 + *gi - 1) / *gi));
+}
+
+template <bool ERR, typename T>
+hipError_t launch_tiles(const GaussTabs& g, int64_t c0, int64_t nc, T* W, const GaussErr& er, hipStream_t s) {
+  constexpr int64_t kMaxBlocks = 1 << 22;   // a launch has less than 2^32 threads
+  int64_t gi = 1;
+  int gj = 1;
+  gauss_grid(g, nc, &gi, &gj);
+  for (int64_t b0 = 0; b0 < gi; b0 += kMaxBlocks) {
+    const int n = (int)std::min(gi - b0, kMaxBlocks);
+    hipLaunchKernelGGL((k_gauss_tiles<ERR, T>), dim3((unsigned)((int64_t)n * gj)), dim3(256), 0, s, g, c0, nc, W, er, b0,
+                       n, gj);
+  }
+  return hipGetLastError();
 }
 
 // ---- sketches of the Gaussian bumps without their entries ----
@@ -462,15 +477,9 @@ int64_t gauss_chunk_cols(const GaussTabs& g, int elem_bytes) {
 hipError_t gauss_columns(const GaussTabs& g, int64_t c0, int64_t nc, int dtype, void* W, hipStream_t s) {
   if (nc <= 0) return hipSuccess;
   if (fault_take()) return hipErrorLaunchFailure;
-  int gi = 1, gj = 1;
-  gauss_grid(g, nc, &gi, &gj);
-  const dim3 grid((unsigned)((int64_t)gi * gj)), b(256);
   const GaussErr none = {};
-  if (dtype == PSTT2_F64)
-    hipLaunchKernelGGL((k_gauss_tiles<false, double>), grid, b, 0, s, g, c0, nc, (double*)W, none, gi, gj);
-  else
-    hipLaunchKernelGGL((k_gauss_tiles<false, float>), grid, b, 0, s, g, c0, nc, (float*)W, none, gi, gj);
-  return hipGetLastError();
+  if (dtype == PSTT2_F64) return launch_tiles<false>(g, c0, nc, (double*)W, none, s);
+  return launch_tiles<false>(g, c0, nc, (float*)W, none, s);
 }
 
 hipError_t gauss_moments(const GaussTabs& g, const SketchArgs& a, const int64_t* n, double gamma, int64_t c0,
@@ -500,20 +509,16 @@ hipError_t gauss_sketch_t(const GaussTabs& g, const double* mom, int ell, int64_
 }
 
 int64_t gauss_error_parts(const GaussTabs& g) {
-  int gi = 1, gj = 1;
+  int64_t gi = 1;
+  int gj = 1;
   gauss_grid(g, g.C, &gi, &gj);
-  return (int64_t)gi * gj;
+  return gi * gj;
 }
 
 hipError_t gauss_error(const GaussTabs& g, const double* L, const double* Rp, int r, int RK, double* part,
                        hipStream_t s) {
   if (fault_take()) return hipErrorLaunchFailure;
-  int gi = 1, gj = 1;
-  gauss_grid(g, g.C, &gi, &gj);
-  const GaussErr er{L, Rp, r, RK, part};
-  hipLaunchKernelGGL((k_gauss_tiles<true, double>), dim3((unsigned)((int64_t)gi * gj)), dim3(256), 0, s, g, (int64_t)0,
-                     g.C, (double*)nullptr, er, gi, gj);
-  return hipGetLastError();
+  return launch_tiles<true>(g, 0, g.C, (double*)nullptr, GaussErr{L, Rp, r, RK, part}, s);
 }
 
 hipError_t hilbert_columns(const double* rec, const int32_t* row_t, const int32_t* col_t, int64_t R, int64_t c0,

@@ -500,10 +500,11 @@ hipError_t tt_error_run_gauss(const tt_cores* c, const double* centers_host, int
 template <typename T, int RK, int V, bool VEC>
 __global__ __launch_bounds__(256) void k_reconstruct(T* __restrict__ out, int64_t first, int64_t count, int64_t R,
                                                      int64_t c0, int64_t ncol, int r, const double* __restrict__ L,
-                                                     const double* __restrict__ Rp, int gi_count, int gj_count) {
+                                                     const double* __restrict__ Rp, int64_t gi0, int gi_count,
+                                                     int gj_count) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int gi = blockIdx.x % gi_count, gj = blockIdx.x / gi_count;
-  const int64_t row0 = ((int64_t)gi * 4 + w) * (64 * V) + (VEC ? V * lane : lane);
+  const int64_t row0 = ((gi0 + gi) * 4 + w) * (64 * V) + (VEC ? V * lane : lane);
   constexpr int ST = VEC ? 1 : 64;
   double l[V][RK];
 #pragma unroll
@@ -549,16 +550,20 @@ static void launch_rec(T* out, int64_t first, int64_t count, int64_t R, int r, c
   constexpr int V = sizeof(T) == 4 && RK <= 16 ? 4 : 2;
   const bool vec = R % V == 0 && first % V == 0 && count % V == 0 && (uintptr_t)out % (V * sizeof(T)) == 0;
   const int64_t c0 = first / R, ncol = (first + count + R - 1) / R - c0;
-  const int64_t gi = (R + 256 * V - 1) / (256 * V);
-  // about 4096 workgroups (a lane's V RK loads of L serve its share of the columns)
-  const int64_t gj = std::max<int64_t>(1, std::min<int64_t>(ncol, (4096 + gi - 1) / gi));
-  const dim3 g((unsigned)(gi * gj)), b(256);
-  if (vec)
-    hipLaunchKernelGGL((k_reconstruct<T, RK, V, true>), g, b, 0, s, out, first, count, R, c0, ncol, r, L, Rp, (int)gi,
-                       (int)gj);
-  else
-    hipLaunchKernelGGL((k_reconstruct<T, RK, V, false>), g, b, 0, s, out, first, count, R, c0, ncol, r, L, Rp,
-                       (int)gi, (int)gj);
+  const int64_t blocks = (R + 256 * V - 1) / (256 * V);
+  constexpr int64_t kMaxBlocks = 1 << 22;   // a launch has less than 2^32 threads
+  for (int64_t b0 = 0; b0 < blocks; b0 += kMaxBlocks) {
+    const int gi = (int)std::min(blocks - b0, kMaxBlocks);
+    // about 4096 workgroups (a lane's V RK loads of L serve its share of the columns)
+    const int gj = (int)std::max<int64_t>(1, std::min<int64_t>(ncol, (4096 + gi - 1) / gi));
+    const dim3 g((unsigned)gi * gj), b(256);
+    if (vec)
+      hipLaunchKernelGGL((k_reconstruct<T, RK, V, true>), g, b, 0, s, out, first, count, R, c0, ncol, r, L, Rp, b0, gi,
+                         gj);
+    else
+      hipLaunchKernelGGL((k_reconstruct<T, RK, V, false>), g, b, 0, s, out, first, count, R, c0, ncol, r, L, Rp, b0,
+                         gi, gj);
+  }
 }
 
 template <typename T>

@@ -410,15 +410,17 @@ __global__ void k_svd_omega(double* __restrict__ Om, int s) {
 // M <- M H for the rows of W (L x s) and of J (s x s); a workgroup takes 16 rows, its
 // waves share the columns.
 __global__ __launch_bounds__(kBS) void k_svd_turn(double* __restrict__ W, int64_t L, double* __restrict__ J, int s,
-                                                  const double* __restrict__ V, const double* __restrict__ T) {
+                                                  const double* __restrict__ V, const double* __restrict__ T,
+                                                  int64_t tile0) {
   constexpr int P = kSvdLead, NW = kBS / 64;
   static_assert(P == 16, "one tile");
   __shared__ double part[NW][P][17], MT[P][17], Ts[P][P];
   const int t = threadIdx.x, lane = t & 63, w = t >> 6, l16 = lane & 15, g4 = lane >> 4;
   const int64_t ntw = (L + 15) / 16;
-  const bool inw = blockIdx.x < ntw;
+  const int64_t tile = tile0 + blockIdx.x;
+  const bool inw = tile < ntw;
   double* M = inw ? W : J;
-  const int64_t ld = inw ? L : s, row = 16 * (inw ? blockIdx.x : blockIdx.x - ntw) + l16;
+  const int64_t ld = inw ? L : s, row = 16 * (inw ? tile : tile - ntw) + l16;
   const bool ok = row < ld;
   auto vx = [&](int j, int c) -> double {   // V with its unit diagonal
     const double v = j < s ? V[(int64_t)c * s + j] : 0.0;
@@ -640,8 +642,10 @@ hipError_t svd_lead_turn(double* W, int64_t L, double* J, int sp, double* lead, 
   double *V = lead + (int64_t)sp * kSvdLead, *T = V + (int64_t)sp * kSvdLead;
   hipError_t e = qr_reflectors(lead, sp, V, T, T + kSvdLead * kSvdLead, s);
   if (e != hipSuccess) return e;
-  const unsigned g = (unsigned)((L + 15) / 16 + (sp + 15) / 16);
-  hipLaunchKernelGGL(k_svd_turn, dim3(g), dim3(kBS), 0, s, W, L, J, sp, V, T);
+  const int64_t tiles = (L + 15) / 16 + (sp + 15) / 16;
+  constexpr int64_t kMaxGrid = 1 << 23;   // workgroups of a launch: 2^32 threads wrap around
+  for (int64_t t0 = 0; t0 < tiles; t0 += kMaxGrid)
+    hipLaunchKernelGGL(k_svd_turn, dim3((unsigned)std::min(tiles - t0, kMaxGrid)), dim3(kBS), 0, s, W, L, J, sp, V, T, t0);
   return hipGetLastError();
 }
 
