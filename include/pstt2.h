@@ -440,7 +440,8 @@ pstt2_status pstt2_memory_stats(int64_t* live_bytes, int64_t* peak_bytes, int64_
 
 /* Testing hook for the failure paths: after this call the next `count` kernel
  * launches of the library's streaming stages (sketch, partial reduction,
- * partial column, tensor-function columns, two-pass middle core) go ahead and
+ * partial column, a tensor function's tables, columns, moments and sketches,
+ * two-pass middle core) go ahead and
  * the one after them is reported as a failed launch (PSTT2_EDEVICE) without
  * running; then the hook disarms.  count < 0 disarms it.  Host-side only: no
  * kernel is altered.  Process-wide.  Never fails. */

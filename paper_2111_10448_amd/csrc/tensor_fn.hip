@@ -494,6 +494,7 @@ hipError_t gauss_moments(const GaussTabs& g, const SketchArgs& a, const int64_t*
 
 hipError_t gauss_sketch_y(const GaussTabs& g, const double* mom, int ell, bool store, double* Y, int* flag,
                           hipStream_t s) {
+  if (fault_take()) return hipErrorLaunchFailure;
   const dim3 grid((unsigned)((g.R + 255) / 256)), b(256);
   const double* m = mom + 32 * (int64_t)g.nterms;
   if (ell <= 16) hipLaunchKernelGGL(k_gauss_y<1>, grid, b, 0, s, g, m, ell, store, Y, flag);
@@ -503,6 +504,7 @@ hipError_t gauss_sketch_y(const GaussTabs& g, const double* mom, int ell, bool s
 
 hipError_t gauss_sketch_t(const GaussTabs& g, const double* mom, int ell, int64_t c0, int64_t nc, double* Tt, int* flag,
                           hipStream_t s) {
+  if (fault_take()) return hipErrorLaunchFailure;
   const dim3 grid((unsigned)std::max<int64_t>(1, std::min<int64_t>((nc + 255) / 256, 4096)), (unsigned)ell);
   hipLaunchKernelGGL(k_gauss_t, grid, dim3(256), 0, s, g, mom, c0, nc, Tt, flag);
   return hipGetLastError();
