@@ -35,6 +35,7 @@
 #include <cmath>
 
 #include "internal.h"
+#include "philox.h"
 
 namespace pstt2 {
 
@@ -396,14 +397,16 @@ __global__ __launch_bounds__(kJT) void k_jacobi_blocks(double* __restrict__ W, i
 // mixes them (90 x 24, column norms 1 .. 1e-23 increasing: singular values of 1e-9 to
 // 1e-11 of the largest off by 1e-9 to 2e-6, in order 1e-15, as by the sweeps alone).
 
-// Omega (s x kSvdLead): mixed bits of the index, in [-1, 1)
+// Omega (s x kSvdLead), uniform in [-1, 1): entries 4 p .. 4 p + 3 from the Philox block of
+// counter p (key 0)
 __global__ void k_svd_omega(double* __restrict__ Om, int s) {
-  for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < s * kSvdLead; t += gridDim.x * blockDim.x) {
-    uint32_t h = (uint32_t)t * 2654435761u + 12345u;
-    h = (h ^ (h >> 15)) * 2246822519u;
-    h = (h ^ (h >> 13)) * 3266489917u;
-    h ^= h >> 16;
-    Om[t] = (double)(int32_t)h * 0x1p-31;
+  static_assert(kSvdLead % 4 == 0, "whole blocks");
+  for (int p = blockIdx.x * blockDim.x + threadIdx.x; 4 * p < s * kSvdLead; p += gridDim.x * blockDim.x) {
+    const uint32_t ctr[4] = {(uint32_t)p, 0u, 0u, 0u};
+    uint32_t x[4];
+    philox4x32_10(ctr, 0u, 0u, x);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) Om[4 * p + i] = (double)(int32_t)x[i] * 0x1p-31;
   }
 }
 
@@ -658,7 +661,7 @@ hipError_t svd_lead_products(const double* W, int64_t L, int sp, double* lead, h
 hipError_t svd_lead_init(double* W, int64_t L, double* J, int sp, double* lead, hipStream_t s) {
   double* Z = lead + (int64_t)kSvdLead * (2 * (int64_t)sp + 2 * kSvdLead);
   double* Om = lead + (int64_t)sp * kSvdLead;   // where the reflectors go
-  hipLaunchKernelGGL(k_svd_omega, dim3(grid_of((int64_t)sp * kSvdLead)), dim3(256), 0, s, Om, sp);
+  hipLaunchKernelGGL(k_svd_omega, dim3(grid_of((int64_t)sp * kSvdLead / 4)), dim3(256), 0, s, Om, sp);
   hipError_t e = adj_gemm(false, false, L, kSvdLead, sp, 1.0, W, L, Om, sp, 0.0, Z, L, s);
   if (e == hipSuccess) e = adj_gemm(true, false, sp, kSvdLead, L, 1.0, W, L, Z, L, 0.0, lead, sp, s);
   if (e == hipSuccess) e = svd_lead_turn(W, L, J, sp, lead, s);
