@@ -55,13 +55,12 @@ struct PsiCursor {
   }
   // true when the caller must recompute its psi_hi values for this row
   __device__ __forceinline__ bool refresh(const SketchArgs& A) {
-    if (row >= A.R || A.psi_tab || h == hc) return false;
+    if (row >= A.R || h == hc) return false;
     hc = h;
     return true;
   }
   __device__ __forceinline__ double at(const SketchArgs& A, int a, double hi) const {
     if (row >= A.R || a >= A.ell) return 0.0;
-    if (A.psi_tab) return A.psi_tab[row * A.L4 + a];
     return A.fac[A.psi_off[0] + i1 * A.ell + a] * hi;
   }
 };

@@ -162,7 +162,6 @@ __device__ __forceinline__ int acc_row(int g4, int v) {
 // Sixteen bytes at the alignment of one entry: global loads take any (R not a multiple
 // of the vector; only whole vectors inside a column are loaded so).
 typedef double ud2 __attribute__((ext_vector_type(2), aligned(8)));
-typedef float uf4 __attribute__((ext_vector_type(4), aligned(4)));
 
 struct ChunkInfo {
   const char* ptr;   // column 0 of the chunk's segment
@@ -217,8 +216,9 @@ constexpr int NWS = 4;
 
 // Two waves to a SIMD are meant: where the registers allow three (split BF16, ell <= 16),
 // a schedule that aims at them issues its loads later (0.275 against 0.269 ms a launch at
-// 12^8 in 64 slabs, ell = 16).
-template <int PREC, int LP, bool ALIGNED, bool SEG1>
+// 12^8 in 64 slabs, ell = 16).  The other instances come out the same either way.
+// STAGE: the prologue with psi_stage; without it there is only the rolled one.
+template <int PREC, int LP, bool ALIGNED, bool SEG1, bool STAGE = true>
 __global__ __attribute__((amdgpu_flat_work_group_size(NWS * 64, NWS * 64), amdgpu_waves_per_eu(2, 2)))
 void k_sketch(const SketchArgs A) {
   using E = Eng<PREC>;
@@ -297,9 +297,7 @@ void k_sketch(const SketchArgs A) {
     static_assert(psi_stage_size(NWS * RW, LP) * sizeof(double) <= sizeof(Xl), "the table fits in the X tiles");
     const int64_t first = (int64_t)gi * (NWS * RW);
     double* table = (double*)&Xl[0][0];
-    if (A.psi_tab) {
-      fill(PsiTable<NT>(A));
-    } else if (psi_stage(A, first, NWS * RW, table)) {
+    if (STAGE && psi_stage(A, first, NWS * RW, table)) {
       fill(PsiStaged<NT>(A, table, first));
       __syncthreads();   // the X tiles take its place
     } else {   // rolled: the arrays move up, the new row last
@@ -398,16 +396,8 @@ void k_sketch(const SketchArgs A) {
           xr[slot][i][2] = v.z;
           xr[slot][i][3] = v.w;
         } else {
-          if (colok && row + VEC <= A.R) {
-            const uf4 v = *(const uf4*)(col + row);
-            xr[slot][i][0] = v.x;
-            xr[slot][i][1] = v.y;
-            xr[slot][i][2] = v.z;
-            xr[slot][i][3] = v.w;
-          } else {
 #pragma unroll
-            for (int v = 0; v < VEC; ++v) xr[slot][i][v] = (colok && row + v < A.R) ? col[row + v] : (elem)0;
-          }
+          for (int v = 0; v < VEC; ++v) xr[slot][i][v] = (colok && row + v < A.R) ? col[row + v] : (elem)0;
         }
       } else if constexpr (ALIGNED) {
         const bool ok = colok && row < A.R;
@@ -812,8 +802,7 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void k_sketch16(const Ske
     static_assert(psi_stage_size(NW * 64, LP) * sizeof(double) <= sizeof(Xl), "the table fits in the X tiles");
     const int64_t first = (int64_t)gi * (NW * 64);
     double* table = (double*)&Xl[0][0];
-    if (A.psi_tab) fill(PsiTable<NT>(A));
-    else if (psi_stage(A, first, NW * 64, table)) fill(PsiStaged<NT>(A, table, first));
+    if (psi_stage(A, first, NW * 64, table)) fill(PsiStaged<NT>(A, table, first));
     else fill(PsiDirect<NT>());
   }
   __syncthreads();   // the slot counters are zero; the X tiles take the table's place
@@ -1496,10 +1485,20 @@ static hipError_t launch_t(const SketchArgs& a, bool aligned, hipStream_t s) {
   if (aligned) {
     if (seg1) hipLaunchKernelGGL((k_sketch<PREC, LP, true, true>), grid, block, 0, s, a);
     else hipLaunchKernelGGL((k_sketch<PREC, LP, true, false>), grid, block, 0, s, a);
-  } else {
-    if (seg1) hipLaunchKernelGGL((k_sketch<PREC, LP, false, true>), grid, block, 0, s, a);
-    else hipLaunchKernelGGL((k_sketch<PREC, LP, false, false>), grid, block, 0, s, a);
+    return hipGetLastError();
   }
+  if constexpr (PREC == P_F32 && LP == 32) {
+    // The staged prologue saves a workgroup 10 us and more, but the compiler's loop
+    // behind it costs 4% here (31^6, ell = 32, 465 chunks a workgroup: 1.66 against
+    // 1.59 ms): without it from 96 chunks on, and where it would not be taken.
+    if (a.n[0] < kPsiStageMode || a.nchunks >= 96 * (int64_t)a.gj_count) {
+      if (seg1) hipLaunchKernelGGL((k_sketch<PREC, LP, false, true, false>), grid, block, 0, s, a);
+      else hipLaunchKernelGGL((k_sketch<PREC, LP, false, false, false>), grid, block, 0, s, a);
+      return hipGetLastError();
+    }
+  }
+  if (seg1) hipLaunchKernelGGL((k_sketch<PREC, LP, false, true>), grid, block, 0, s, a);
+  else hipLaunchKernelGGL((k_sketch<PREC, LP, false, false>), grid, block, 0, s, a);
   return hipGetLastError();
 }
 

@@ -1,0 +1,36 @@
+"""Rates of the streaming sketch relative to each other, from its own launch events: a
+size or shape that is next to another may not fall off it.  Minimum of several launches
+of both in one process; the bounds lie half way between what the kernels do and what
+they did when a variant had fallen off."""
+import numpy as np
+import pytest
+
+from gpu_common import say
+
+pytestmark = pytest.mark.gpu
+
+
+def _ps_per_entry(n, ell, dtype, prec, reps=5):
+    import torch
+    import paper_2111_10448_amd as P
+    x = torch.randn(int(np.prod(n)), dtype=torch.float64 if dtype == "f64" else torch.float32, device="cuda")
+    ctx = P.PSTT2(n, ell, dtype=dtype, prec=prec, ranks=[2] * (len(n) - 1), seed=1)
+    ctx.profile(True)
+    best = None
+    for _ in range(reps):
+        ctx.reset()
+        ctx.sketch(x)
+        ms, launches = ctx.profile_read()
+        assert launches == 1
+        best = ms if best is None else min(best, ms)
+    ctx.close()
+    return best * 1e9 / x.numel()
+
+
+@pytest.mark.parametrize("prec,bound", [("f32", 1.55), ("bf16x3", 1.45)])
+def test_odd_rows(prec, bound):
+    """Columns of an odd length against even ones, 3.5 GB and 4.3 GB, FP32 data: loads of
+    one entry cost 1.35 (FP32) and 1.2 (split BF16) here; vectors at an entry's alignment 1.8 and 1.7."""
+    odd, even = (_ps_per_entry(n, 32, "f32", prec) for n in ((31,) * 6, (32,) * 6))
+    say(f"[gpu] {prec}: odd rows {odd:.3f} ps an entry, even {even:.3f}, {odd / even:.2f}")
+    assert odd / even < bound
