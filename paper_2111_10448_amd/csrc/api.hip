@@ -613,7 +613,7 @@ pstt2_status pstt2_create(const pstt2_desc* desc, void* hip_stream, pstt2_ctx** 
   const double one = 1.0;
   if ((e = hipMemcpy(c->one, &one, sizeof(double), hipMemcpyHostToDevice)) != hipSuccess) return bail(e, "hipMemcpy");
   int rows_per_block = 0, threads = 0, wg_per_cu = 1;
-  sketch_geometry(c->prec, c->ell, &rows_per_block, &threads, &wg_per_cu);
+  sketch_geometry(c->prec, c->dtype, c->ell, &rows_per_block, &threads, &wg_per_cu);
   c->gi = (int)((c->R + rows_per_block - 1) / rows_per_block);
   c->gj_max = std::max(1, c->ncu * wg_per_cu / c->gi);
   const size_t psz = c->prec == PSTT2_P_F64 ? 8 : 4;
@@ -621,7 +621,7 @@ pstt2_status pstt2_create(const pstt2_desc* desc, void* hip_stream, pstt2_ctx** 
   const int64_t trows = omega16_planes(c->prec) ? c->lp : c->ell;   // see SketchArgs::tlp
   c->tpart_bytes = (int64_t)psz * (c->gi * trows * c->C + kTPartPad);
   if ((e = dev_malloc(&c->tpart, c->tpart_bytes)) != hipSuccess) return bail(e, "hipMalloc(tpart)");
-  c->L4 = (c->ell + 3) / 4 * 4;
+  c->L4 = sketch_columns(c->prec, c->dtype, c->ell);
   if ((e = dev_malloc(&c->om_tab, sizeof(double) * c->C * c->L4)) != hipSuccess) return bail(e, "hipMalloc(omega)");
   if ((e = build_omega_table(base_args(c), c->L4, c->om_tab, c->stream)) != hipSuccess)
     return bail(e, "omega table");
@@ -1390,7 +1390,7 @@ pstt2_status pstt2_vjp(pstt2_ctx* c, const tt_cores* cores, const void* x_dev, c
   //      kernel streams X itself and two r_m x r_m Gram matrices supply the rest,
   //      so no tensor-sized cotangent is ever formed. ----
   const void* src = gbar_dev ? gbar_dev : x_dev;
-  const int L4r = (rm + 3) / 4 * 4;
+  const int L4r = sketch_columns(PSTT2_P_F64, c->dtype, rm);
   double* psiT = take(c->R * L4r);
   double* omT = take(c->C * L4r);
   VJPCK(adj_table(Lm, c->R, rm, 1, c->R, L4r, psiT, s));
@@ -1401,7 +1401,7 @@ pstt2_status pstt2_vjp(pstt2_ctx* c, const tt_cores* cores, const void* x_dev, c
   a.om_tab = omT;
   a.psi_tab = psiT;
   int rpb = 0, thr = 0, wpc = 1;
-  sketch_geometry(PSTT2_P_F64, rm, &rpb, &thr, &wpc);
+  sketch_geometry(PSTT2_P_F64, c->dtype, rm, &rpb, &thr, &wpc);
   a.gi_count = (int)((c->R + rpb - 1) / rpb);
   a.nchunks = (c->C + 15) / 16;
   a.gj_count = (int)std::max<int64_t>(1, std::min<int64_t>(a.nchunks, std::max(1, c->ncu * wpc / a.gi_count)));

@@ -111,7 +111,7 @@ struct SketchArgs {
   int32_t x32;       // FP64 kernel: the segments hold FP32 entries (widened as loaded)
   int64_t C;         // columns of X_m (for the tpart stride)
   const double* om_tab;  // Omega_m(col, c) table, C x L4, FP64
-  int32_t L4;            // its row stride: ell rounded up to a multiple of 4
+  int32_t L4;            // its row stride: ell rounded up (sketch_columns)
   const double* psi_tab; // optional Psi(row, a) table, R x L4 (else products of the factors)
   const uint16_t* om16;  // 16-bit precisions: Omega_m rounded per plane, [plane][c < LP][col]
   Seg seg[kMaxSeg];
@@ -201,11 +201,20 @@ int sketch_chunk_cols(int prec);
 // om16[(q LP + c) C + col] = plane q of Omega_m(col, c) rounded as the kernel uses it.
 hipError_t build_omega16_table(const double* om_tab, int64_t C, int L4, int ell, int LP, int prec, uint16_t* om16,
                                hipStream_t s);
+// Columns the sketch kernel of this arithmetic forms for ell of them: multiples of 4, but
+// for FP64 no 28, and no 24 on FP64 data and formulas.  Psi's 4-wide groups cost twice
+// the registers of a 16-wide tile's columns, and these two spill: at 32^6 20 columns take
+// 2.03 ms, 24 3.67, 28 8.11 and 32 2.82 (64^5 Hilbert: 2.07, 3.17, 6.50, 2.78; FP32 data,
+// half the loads: 1.86, 2.27, 7.48, 2.60).
+inline int sketch_columns(int prec, int dtype, int ell) {
+  const int c = (ell + 3) / 4 * 4;
+  return prec == PSTT2_P_F64 && (c == 28 || (c == 24 && dtype == PSTT2_F64)) ? 32 : c;
+}
 // Build the Omega_m table (C x L4, FP64) from the factors.
 hipError_t build_omega_table(const SketchArgs& a, int L4, double* tab, hipStream_t s);
 // Per-precision launch geometry: rows of X_m per workgroup, threads per
 // workgroup, workgroups resident per CU.
-void sketch_geometry(int prec, int ell, int* rows_per_block, int* threads, int* wg_per_cu);
+void sketch_geometry(int prec, int dtype, int ell, int* rows_per_block, int* threads, int* wg_per_cu);
 // Sum the tile partials of one launch into the FP64 accumulators (fixed order).
 hipError_t launch_reduce(int prec, const SketchArgs& a, double* Y, double* Tt, int* flag, hipStream_t s);
 // FP64 contribution of up to kMaxSeg pieces of columns (seg[e]: first entry,

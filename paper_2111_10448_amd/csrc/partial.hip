@@ -257,7 +257,7 @@ static RowBlocks touched_blocks(const SketchArgs& a) {
 
 hipError_t launch_partial_cols(int dtype, const SketchArgs& a, double* Y, double* Tt, double* ws, int64_t ws_doubles,
                                bool* added, hipStream_t s) {
-  if (a.nseg < 1 || a.nseg > kMaxSeg || a.ell < 1 || a.L4 != (a.ell + 3) / 4 * 4) return hipErrorInvalidValue;
+  if (a.nseg < 1 || a.nseg > kMaxSeg || a.ell < 1 || a.L4 < a.ell || a.L4 % 4 != 0 || a.L4 > 32) return hipErrorInvalidValue;
   const RowBlocks rb = touched_blocks(a);
   const int64_t per = (int64_t)a.nseg * a.L4;
   const int nb = (int)std::min<int64_t>({rb.tot, (int64_t)PC_MAXBLK, ws_doubles / per});

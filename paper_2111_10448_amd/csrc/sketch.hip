@@ -1061,13 +1061,13 @@ static hipError_t launch_16(const SketchArgs& a, bool aligned, hipStream_t s) {
 // Output layouts: 16x16x4 element v of lane l at (4v + l/16, l%16); 4x4x4
 // block b = (l/4)%4 at (l/16, l%4) of that block.
 // ---------------------------------------------------------------------------
-// FP64 workgroups: for ell (rounded to 4) <= 28, 4 waves (256 rows) and two
+// FP64 workgroups: for ell (rounded to 4) <= 24, 4 waves (256 rows) and two
 // workgroups per CU, so one workgroup's matrix-core work overlaps the other's
 // barrier and load phases (measured 8% faster at ell = 20 than one 8-wave
 // workgroup).  For ell = 32 two such workgroups no longer fit in LDS, and one
 // 8-wave workgroup (two waves per SIMD) beats one 4-wave workgroup by 7%.
-constexpr int nwf_for(int L4) { return L4 > 28 ? 8 : 4; }
-constexpr int f64_wg_per_cu(int L4) { return L4 > 28 ? 1 : 2; }
+constexpr int nwf_for(int L4) { return L4 > 24 ? 8 : 4; }
+constexpr int f64_wg_per_cu(int L4) { return L4 > 24 ? 1 : 2; }
 
 // FN: the tensor is the Hilbert tensor, evaluated from the index tables in
 // place of the loads of X (one launch segment, no memory behind it).
@@ -1418,10 +1418,8 @@ static hipError_t launch_f64(const SketchArgs& a, bool aligned, hipStream_t s) {
   if (a.ydirect && (a.gj_count != 1 || !a.yflag)) return hipErrorInvalidValue;
   if (a.ystore && !a.ydirect) return hipErrorInvalidValue;
   const bool seg1 = a.nseg == 1 && a.seg[0].chunk0 == 0;
-  if (a.fn) {
-    if (!seg1 || a.fn != 1 || !a.fn_rec || !a.fn_row || !a.fn_col || a.x32) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((k_sketch_f64<L4, true, true, true>), grid, block, 0, s, a);
-  } else if (a.x32) {
+  if (a.x32) {
+    if (a.fn) return hipErrorInvalidValue;
     if (aligned) {
       if (seg1) hipLaunchKernelGGL((k_sketch_f64<L4, true, true, false, true>), grid, block, 0, s, a);
       else hipLaunchKernelGGL((k_sketch_f64<L4, true, false, false, true>), grid, block, 0, s, a);
@@ -1429,14 +1427,23 @@ static hipError_t launch_f64(const SketchArgs& a, bool aligned, hipStream_t s) {
       if (seg1) hipLaunchKernelGGL((k_sketch_f64<L4, false, true, false, true>), grid, block, 0, s, a);
       else hipLaunchKernelGGL((k_sketch_f64<L4, false, false, false, true>), grid, block, 0, s, a);
     }
-  } else if (aligned) {
-    if (seg1) hipLaunchKernelGGL((k_sketch_f64<L4, true, true, false>), grid, block, 0, s, a);
-    else hipLaunchKernelGGL((k_sketch_f64<L4, true, false, false>), grid, block, 0, s, a);
-  } else {
-    if (seg1) hipLaunchKernelGGL((k_sketch_f64<L4, false, true, false>), grid, block, 0, s, a);
-    else hipLaunchKernelGGL((k_sketch_f64<L4, false, false, false>), grid, block, 0, s, a);
+    return hipGetLastError();
   }
-  return hipGetLastError();
+  if constexpr (L4 == 24) {
+    return hipErrorInvalidValue;   // FP64 data and formulas: see sketch_columns
+  } else {
+    if (a.fn) {
+      if (!seg1 || a.fn != 1 || !a.fn_rec || !a.fn_row || !a.fn_col) return hipErrorInvalidValue;
+      hipLaunchKernelGGL((k_sketch_f64<L4, true, true, true>), grid, block, 0, s, a);
+    } else if (aligned) {
+      if (seg1) hipLaunchKernelGGL((k_sketch_f64<L4, true, true, false>), grid, block, 0, s, a);
+      else hipLaunchKernelGGL((k_sketch_f64<L4, true, false, false>), grid, block, 0, s, a);
+    } else {
+      if (seg1) hipLaunchKernelGGL((k_sketch_f64<L4, false, true, false>), grid, block, 0, s, a);
+      else hipLaunchKernelGGL((k_sketch_f64<L4, false, false, false>), grid, block, 0, s, a);
+    }
+    return hipGetLastError();
+  }
 }
 
 // Table of the right DRM of the middle unfolding, Omega_m(col, c), FP64, C x L4
@@ -1460,8 +1467,8 @@ hipError_t build_omega_table(const SketchArgs& a, int L4, double* tab, hipStream
 
 int sketch_chunk_cols(int prec) { return omega16_planes(prec) ? KC16 : KC; }
 
-void sketch_geometry(int prec, int ell, int* rows_per_block, int* threads, int* wg_per_cu) {
-  const int L4 = (ell + 3) / 4 * 4;
+void sketch_geometry(int prec, int dtype, int ell, int* rows_per_block, int* threads, int* wg_per_cu) {
+  const int L4 = sketch_columns(prec, dtype, ell);
   if (omega16_planes(prec)) {
     *rows_per_block = kNW16 * 64;
     *threads = kNW16 * 64;
@@ -1510,14 +1517,14 @@ hipError_t launch_sketch(int prec, int lp, const SketchArgs& a, hipStream_t s) {
   bool aligned = ((a.R * esz) % 16) == 0;
   for (int i = 0; i < a.nseg; ++i) aligned = aligned && (((uintptr_t)a.seg[i].ptr) % 16 == 0);
   if (prec == P_F64) {
-    switch ((a.ell + 3) / 4 * 4) {
+    if (a.L4 != sketch_columns(prec, a.x32 ? PSTT2_F32 : PSTT2_F64, a.ell)) return hipErrorInvalidValue;
+    switch (a.L4) {
       case 4: return launch_f64<4>(a, aligned, s);
       case 8: return launch_f64<8>(a, aligned, s);
       case 12: return launch_f64<12>(a, aligned, s);
       case 16: return launch_f64<16>(a, aligned, s);
       case 20: return launch_f64<20>(a, aligned, s);
-      case 24: return launch_f64<24>(a, aligned, s);
-      case 28: return launch_f64<28>(a, aligned, s);
+      case 24: return launch_f64<24>(a, aligned, s);   // FP32 data only
       case 32: return launch_f64<32>(a, aligned, s);
       default: return hipErrorInvalidValue;
     }
