@@ -47,6 +47,7 @@ struct IfaceLevel {
 
 template <int RP>
 __global__ __launch_bounds__(256) void k_ifaces(const IfaceLevel A) {
+  constexpr int LO = RP > 16 ? RP - 8 : RP - 4;   // the ranks of these slots are above it
   if (blockIdx.x < A.gl) {
     const int64_t Rk = A.Rp * A.nl;
     const int rp = A.rpl;
@@ -61,8 +62,8 @@ __global__ __launch_bounds__(256) void k_ifaces(const IfaceLevel A) {
         double s = 0.0;
 #pragma unroll
         for (int a = 0; a < RP; ++a) {
-          const double gv = g[a < rp ? a : 0];   // a finite product with lp = 0 past rp
-          s += lp[a] * (a < rp ? gv : 0.0);
+          const double gv = g[a < LO || a < rp ? a : 0];   // a finite product with lp = 0 past rp
+          s += lp[a] * (a < LO || a < rp ? gv : 0.0);
         }
         A.L[rr + Rk * b] = s;
       }
@@ -554,8 +555,11 @@ static void launch_rec(T* out, int64_t first, int64_t count, int64_t R, int r, c
   constexpr int64_t kMaxBlocks = 1 << 22;   // a launch has less than 2^32 threads
   for (int64_t b0 = 0; b0 < blocks; b0 += kMaxBlocks) {
     const int gi = (int)std::min(blocks - b0, kMaxBlocks);
-    // about 4096 workgroups (a lane's V RK loads of L serve its share of the columns)
-    const int gj = (int)std::max<int64_t>(1, std::min<int64_t>(ncol, (4096 + gi - 1) / gi));
+    // About 4096 workgroups, but shares of eight columns (a lane's V RK loads of L serve its
+    // share) while 512 remain: 40^4 FP32 at rank 16 took 97 us with shares of one column,
+    // 48 of three.
+    const auto shares = [&](int64_t wgs) { return std::min<int64_t>(ncol, (wgs + gi - 1) / gi); };
+    const int gj = (int)std::max(shares(512), std::min(shares(4096), ncol / 8));
     const dim3 g((unsigned)gi * gj), b(256);
     if (vec)
       hipLaunchKernelGGL((k_reconstruct<T, RK, V, true>), g, b, 0, s, out, first, count, R, c0, ncol, r, L, Rp, b0, gi,
