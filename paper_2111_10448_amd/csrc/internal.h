@@ -143,7 +143,7 @@ inline int64_t hilbert_rec_len(const int64_t* n, int d) {
 // split X_m: X(row, col) = sum_j e1(i_1, j) ahi(row / n_1, j) bc(col, j), the
 // per-mode factors multiplied out over modes 1, 2..m and m+1..d.  Tables are
 // j-major: e1[j * n1 + i_1], ahi[j * rhi + row / n_1], bc[j * bstride + col]
-// with bstride = C + kGaussPad and zero padding after column C - 1.
+// with bstride = C + kGaussPad (spare columns: nothing reads past column C - 1).
 constexpr int kGaussPad = 32;
 struct GaussTabs {
   const double* centers;   // nterms x d

@@ -1304,7 +1304,8 @@ __global__ void k_two_sided_htab(const TwoSidedBatch B) {
 // vector instructions around the tiles (a row's place in the first mode and H is
 // carried from slice to slice, not divided out again) and the tiles' rate.
 // 1.86 M rows, ell = 20: 162 -> 85 us with both; 32 columns always and a division a
-// slice before.
+// slice before.  24 and 28 columns would take two and three groups of four, 8 and 15 of
+// the small instructions in place of three tiles; these were not tried.
 constexpr int TS_FTAB = 1024;
 
 template <bool FTAB, int NQ, bool TAIL>

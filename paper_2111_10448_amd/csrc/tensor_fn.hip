@@ -73,10 +73,6 @@ __global__ void k_gauss_table(const Modes M, int q0, int q1, int64_t cnt, int64_
   }
 }
 
-__global__ void k_fill(double* __restrict__ p, int64_t n, double v) {
-  for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < n; t += (int64_t)gridDim.x * blockDim.x) p[t] = v;
-}
-
 typedef double d4 __attribute__((ext_vector_type(4)));
 constexpr int kGaussRows = 256;   // rows of X_m per workgroup of k_gauss_tiles
 constexpr int kGaussTile = 64;    // columns per step
@@ -459,7 +455,6 @@ hipError_t gauss_tables(const int64_t* n, int d, int m, const double* centers_ho
                      nterms, gamma, e1);
   hipLaunchKernelGGL(k_gauss_table, dim3(grid1(g.rhi * nterms)), dim3(256), 0, s, M, 1, m, g.rhi, g.rhi, ctr, d,
                      nterms, gamma, ahi);
-  hipLaunchKernelGGL(k_fill, dim3(grid1(g.bstride * nterms)), dim3(256), 0, s, bc, g.bstride * nterms, 0.0);
   hipLaunchKernelGGL(k_gauss_table, dim3(grid1(C * nterms)), dim3(256), 0, s, M, m, d, C, g.bstride, ctr, d, nterms,
                      gamma, bc);
   e = hipGetLastError();
