@@ -29,7 +29,7 @@ def build(verbose: bool = False) -> str:
     os.makedirs(objdir, exist_ok=True)
     flags = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}",
              "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-             "-I", os.path.join(ROOT, "include"), "-Wall", "-Wno-unused-function",
+             "-I", os.path.join(ROOT, "include"), "-Wall", "-Werror=uninitialized", "-Wno-unused-function",
              "-Wno-unused-variable", "-Wno-unused-but-set-variable", "-Wno-unused-result", "-Wno-unused-value"]
     objs = []
     procs = []

@@ -1772,8 +1772,8 @@ pstt2_status pstt2_parallel_ttsvd(int32_t d, const int64_t* n, const double* x_d
   SVDCK(dev_malloc_async((void**)&idx, sizeof(int) * spmax, s));
   SVDCK(dev_malloc_async((void**)&cnt, sizeof(int), s));
   if (lmax > 0) {
-    const hipError_t e_ = take(&lead, lmax);
-    if (e_ != hipErrorOutOfMemory) SVDCK(e_);
+    const hipError_t lead_e = take(&lead, lmax);
+    if (lead_e != hipErrorOutOfMemory) SVDCK(lead_e);
   }
   SVDCK(svd_absmax(x_dev, N, xmax, s));
   // the last core is formed with its split's SVD; the others from U by equation "core"
