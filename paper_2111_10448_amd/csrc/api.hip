@@ -62,8 +62,8 @@ struct pstt2_ctx {
   std::vector<uint16_t*> iom16;   // independent scheme: 16-bit tables of the right splits k < m
   int L4 = 4;
   // independent DRM scheme: per-split factor offsets, Omega_m tables of the
-  // right splits k < m, the extra sketches of X_m, and sinks for pass groups
-  // with only one side
+  // right splits k < m, the extra sketches of X_m, and the sink for pass groups
+  // with no left side
   bool indep = false;
   bool pstt = false;   // one-sided Algorithm PSTT: the pass sketches split d-1
   int64_t ipsi_off[PSTT2_MAX_D + 1][PSTT2_MAX_D] = {};  // [split k][mode q-1]
@@ -71,7 +71,6 @@ struct pstt2_ctx {
   std::vector<double*> iom_tab;   // [k], k < m
   std::vector<double*> iY;        // [k], k < m: X_m Omega_m^(k), R x ell
   std::vector<double*> iT;        // [k], m < k < d: (Psi_m^(k)T X_m)^T, C x ell
-  double* sinkY = nullptr;
   double* sinkT = nullptr;
   bool profile = false;
   std::vector<std::pair<hipEvent_t, hipEvent_t>> ev_used, ev_pool;
@@ -233,10 +232,10 @@ struct Piece {
 
 // Stream a list of slabs: partial columns and whole columns, each batched.
 // Pass groups.  Nested scheme: one group (Y_R and T_m).  Independent scheme:
-// group g forms the right sketch of split g + 1 (if g + 1 <= m) and the left
-// sketch of split m + g (if m + g <= d - 1), each with its own factors; the
-// absent side of a group goes to a sink.
-int pass_groups(const pstt2_ctx* c) { return c->indep ? std::max(c->m, c->d - c->m) : 1; }
+// group g < m forms the right sketch of split g + 1 and the left sketch of split
+// m + g (if m + g <= d - 1; m >= d - m), each with its own factors; an absent
+// left side goes to a sink.
+int pass_groups(const pstt2_ctx* c) { return c->indep ? c->m : 1; }
 
 SketchArgs group_args(const pstt2_ctx* c, int g, double** Ydst, double** Tdst) {
   SketchArgs a = base_args(c);
@@ -247,14 +246,10 @@ SketchArgs group_args(const pstt2_ctx* c, int g, double** Ydst, double** Tdst) {
   }
   const int m = c->m, d = c->d;
   const int kr = g + 1, kl = m + g;
-  if (kr <= m) {
-    for (int q = 0; q < PSTT2_MAX_D; ++q) a.omega_off[q] = c->iom_off[kr][q];
-    a.om_tab = kr == m ? c->om_tab : c->iom_tab[kr];
-    a.om16 = kr == m ? c->om16 : c->iom16[kr];
-    *Ydst = kr == m ? c->Y : c->iY[kr];
-  } else {
-    *Ydst = c->sinkY;
-  }
+  for (int q = 0; q < PSTT2_MAX_D; ++q) a.omega_off[q] = c->iom_off[kr][q];
+  a.om_tab = kr == m ? c->om_tab : c->iom_tab[kr];
+  a.om16 = kr == m ? c->om16 : c->iom16[kr];
+  *Ydst = kr == m ? c->Y : c->iY[kr];
   if (kl <= d - 1) {
     for (int q = 0; q < PSTT2_MAX_D; ++q) a.psi_off[q] = c->ipsi_off[kl][q];
     *Tdst = kl == m ? c->Tt : c->iT[kl];
@@ -653,7 +648,6 @@ pstt2_status pstt2_create(const pstt2_desc* desc, void* hip_stream, pstt2_ctx** 
     }
     for (int k = c->m + 1; k <= d - 1; ++k)
       if ((e = dev_malloc(&c->iT[k], sizeof(double) * c->C * c->ell)) != hipSuccess) return bail(e, "hipMalloc(T)");
-    if ((e = dev_malloc(&c->sinkY, sizeof(double) * c->R * c->ell)) != hipSuccess) return bail(e, "hipMalloc(sink)");
     if ((e = dev_malloc(&c->sinkT, sizeof(double) * c->C * c->ell)) != hipSuccess) return bail(e, "hipMalloc(sink)");
   }
   c->S.assign(d + 1, nullptr);
@@ -684,6 +678,9 @@ pstt2_status pstt2_reset(pstt2_ctx* c) {
     if (y) HIPCK(c, hipMemsetAsync(y, 0, sizeof(double) * c->R * c->ell, c->stream));
   for (double* t : c->iT)
     if (t) HIPCK(c, hipMemsetAsync(t, 0, sizeof(double) * c->C * c->ell, c->stream));
+  // The sink too: it is added into like the sketches, and a non-finite value there
+  // (left by fresh memory or by a refused X) raises the same flag.
+  if (c->sinkT) HIPCK(c, hipMemsetAsync(c->sinkT, 0, sizeof(double) * c->C * c->ell, c->stream));
   c->cover.clear();
   c->covered = 0;
   c->poisoned = false;
@@ -745,7 +742,6 @@ void pstt2_destroy(pstt2_ctx* c) {
   for (double* p : c->iom_tab) dev_free(p);
   for (double* p : c->iY) dev_free(p);
   for (double* p : c->iT) dev_free(p);
-  dev_free(c->sinkY);
   dev_free(c->sinkT);
   dev_free(c->fn_rec);
   dev_free(c->fn_row);
