@@ -1949,7 +1949,8 @@ pstt2_status pstt2_parallel_ttsvd(int32_t d, const int64_t* n, const double* x_d
     o += (int64_t)r[k] * n[k] * r[k + 1];
   }
   for (int k = 0; k <= d; ++k) tc.r[k] = r[k];
-  // G_1 = U_1; G_k = U_{k-1}^T reshape(U_k, R_{k-1}, n_k r_k) (equation "core"); G_d = Sigma V^T
+  // G_1 = U_1; G_k = U_{k-1}^T reshape(U_k, R_{k-1}, n_k r_k) (equation "core");
+  // G_d = Sigma V^T was formed with its split's SVD
   SVDCK(hipMemcpyAsync(tc.core[0], U[1], sizeof(double) * n[0] * r[1], hipMemcpyDeviceToDevice, s));
   for (int k = 2; k <= d - 1; ++k)
     SVDCK(yield([&] {
